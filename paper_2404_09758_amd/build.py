@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -17,7 +18,7 @@ SOURCES = [os.path.join(CSRC, "dr_kernels.hip"), os.path.join(CSRC, "dr_api.hip"
            os.path.join(CSRC, "dr_probe.hip")]
 OUT = os.path.join(HERE, "libdr.so")
 
-HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off", "-fPIC", "-shared",
+HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off", "-fPIC",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 
@@ -25,10 +26,19 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off"
 def build_lib(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = OUT + ".tmp"
-    cmd = [hipcc] + HIPCC_FLAGS + ["-o", tmp] + SOURCES
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+    with tempfile.TemporaryDirectory() as work:
+        # one compiler run per source, side by side
+        objs = [os.path.join(work, os.path.basename(src) + ".o") for src in SOURCES]
+        cmds = [[hipcc] + HIPCC_FLAGS + ["-c", "-o", obj, src] for src, obj in zip(SOURCES, objs)]
+        if verbose:
+            for cmd in cmds:
+                print(" ".join(cmd), flush=True)
+        procs = [subprocess.Popen(cmd) for cmd in cmds]
+        codes = [p.wait() for p in procs]
+        for cmd, code in zip(cmds, codes):
+            if code:
+                raise subprocess.CalledProcessError(code, cmd)
+        subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-o", tmp] + objs)
     os.replace(tmp, OUT)
     return OUT
 

@@ -75,12 +75,45 @@ __device__ __forceinline__ void tri_positions(const DScene& sc, const float* __r
     }
 }
 
-// Setup and binning of triangle t in one view from its perturbed corners p.
-__device__ __forceinline__ void setup_tri_at(const DView& vw, const float* p, int t,
-                                             TriR* __restrict__ recR, TriS* __restrict__ recS,
-                                             unsigned* __restrict__ counts,
-                                             unsigned* __restrict__ bins, int tile_px, int cap,
-                                             unsigned* __restrict__ spn, unsigned long long* __restrict__ spill) {
+// Inclusive prefix sum over the 64 lanes of a wave with DPP moves: shifts
+// by 1, 2, 4 and 8 within each row of 16 lanes (lanes shifted in from
+// outside the row add 0), then row 0's total to row 1 and row 2's to row 3
+// (row_bcast:15), then row 1's running total to rows 2 and 3 (row_bcast:31).
+// Must be called by every lane of the wave.
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);     // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);     // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);     // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);     // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);     // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);     // row_bcast:31
+    return v;
+}
+
+// Largest value over the wave's 64 lanes, the same moves with max (lanes
+// shifted in from outside hold the least int); every lane must call it.
+__device__ __forceinline__ int wave_max(int v) {
+    const int lo = (int)0x80000000;
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x111, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x142, 0xa, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Tiles a triangle's pixel box touches: [x0, x1] x [y0, y1], empty when
+// x0 > x1.
+struct TileRect {
+    int x0, x1, y0, y1;
+};
+
+// Raster record of triangle t in one view from its perturbed corners p;
+// returns the tiles its box touches (tile size 1 << lg pixels).
+__device__ __forceinline__ TileRect setup_tri_at(const DView& vw, const float* p, int t, TriR* __restrict__ recR,
+                                                 TriS* __restrict__ recS, int lg) {
+    const TileRect none = {1, 0, 1, 0};
     Vtx v[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) v[k] = xform(vw, p[3 * k + 0], p[3 * k + 1], p[3 * k + 2]);
@@ -98,7 +131,7 @@ __device__ __forceinline__ void setup_tri_at(const DView& vw, const float* p, in
     }
     if (!ok) {
         recR[t] = r;                 // flags 0: culled
-        return;
+        return none;
     }
     bool sw = area2 < 0;
     if (sw) {
@@ -129,96 +162,201 @@ __device__ __forceinline__ void setup_tri_at(const DView& vw, const float* p, in
     // pixels whose centre 256 x + 128 lies in [min, max]
     int bx0 = max((xmin + 127) >> 8, 0), bx1 = min((xmax - 128) >> 8, vw.W - 1);
     int by0 = max((ymin + 127) >> 8, 0), by1 = min((ymax - 128) >> 8, vw.H - 1);
-    if (bx0 > bx1 || by0 > by1) {               // no pixel centre in the bbox
-        bx0 = 1; bx1 = 0; by0 = 1; by1 = 0;
-    }
 #pragma unroll
     for (int k = 0; k < 9; ++k) sh.p[k] = p[k];
     recR[t] = r;
     recS[t] = sh;
-    if (bx0 > bx1) return;
-    // Bin entries, one per tile the bbox touches.  Neighbouring triangles
-    // share tiles, so the wave's lanes bidding for one tile are grouped
-    // first (ballots only), then each group's leader adds the group's size
-    // to the tile's counter -- all leaders at once -- and each lane takes its
-    // rank in its group: same-address atomics no longer queue at one L2
-    // channel.  Only the order of a bin's entries depends on this.
-    int tx0 = bx0 / tile_px, tx1 = bx1 / tile_px, ty0 = by0 / tile_px, ty1 = by1 / tile_px;
-    int ntx = tx1 - tx0 + 1;
-    int n = ntx * (ty1 - ty0 + 1);
-    int lane = threadIdx.x & 63;
-    unsigned long long below = (1ull << lane) - 1ull;
-    for (int i = 0;; ++i) {
-        bool has = i < n;
-        unsigned long long pend = __ballot(has);
-        if (pend == 0ull) break;
-        int tile = -1;
-        if (has) tile = (ty0 + i / ntx) * vw.tiles_x + tx0 + i % ntx;
-        int my_leader = lane;
-        unsigned rank = 0u, group = 0u;
-        while (pend) {
-            int leader = __ffsll(pend) - 1;
-            int lt = __shfl(tile, leader);
-            bool mine = has && tile == lt;
-            unsigned long long m = __ballot(mine);
-            if (mine) {
-                my_leader = leader;
-                rank = (unsigned)__popcll(m & below);
-            }
-            if (lane == leader) group = (unsigned)__popcll(m);
-            pend &= ~m;
+    if (bx0 > bx1 || by0 > by1) return none;    // no pixel centre in the bbox
+    return {bx0 >> lg, bx1 >> lg, by0 >> lg, by1 >> lg};
+}
+
+// Binning of a block's 256 triangles (one per thread) in one view.
+//
+// A bin entry takes its place from the tile's counter.  Neighbouring
+// triangles share tiles, so the block first counts its entries per tile in
+// LDS, over the rectangle of tiles that its triangles touch, then adds each
+// tile's total to the tile's counter with one global atomic (all tiles at
+// once), and gives the entries their places by counting up from the returned
+// bases.  Whatever the triangles' sizes, a block waits for one round of
+// global atomics; a rectangle of more than BIN_SLOTS tiles takes one atomic
+// per entry instead.  Threads walk their own triangle's tiles while none
+// touches more than BIN_OWN of them; past that the block shares all entries
+// evenly (prefix sums and a binary search for the owner), since a thread
+// with hundreds of tiles would leave the others waiting.
+//
+// Bound by the latency of the chain index -> vertices -> counter -> entry
+// where few blocks run, by the record writes where many do.  Measured against
+// one counter round per tile of a wave's largest triangle: 2 renders of 20480
+// triangles at 512 px 15.7 -> 8.6 us, 256 renders of a 10240-triangle soup
+// 368 -> 133 us, 64 renders of 46080 triangles at 1024 px 130 -> 100 us, one
+// render of 2420 triangles over 8 px tiles 222 -> 9 us.
+#define SETUP_TB 256
+#define BIN_SLOTS 4096
+#define BIN_OWN 16
+
+struct BinShared {
+    unsigned tab[BIN_SLOTS];         // entries per tile of the block's rectangle, then places
+    int red[SETUP_TB / 64][8];       // per-wave rectangle, largest and total entry count
+    int incl[SETUP_TB];              // inclusive prefix sums of the entry counts (shared walk)
+    int4 rect[SETUP_TB];
+};
+
+// The bins of one (item, sign): counters, entries and the spill list.
+struct BinOut {
+    unsigned* counts;
+    unsigned* bins;
+    int cap;
+    unsigned* spn;
+    unsigned long long* spill;
+};
+
+// Entry k of a tile's bin.  Entries past the capacity go to the render's
+// spill list (the first of a tile also counts the tile as overflowing).
+__device__ __forceinline__ void bin_put(const BinOut& o, int tile, unsigned k, unsigned t) {
+    if (k < (unsigned)o.cap) {
+        o.bins[(long long)tile * o.cap + k] = t;
+        return;
+    }
+    if (!o.spill) return;
+    const unsigned long long ms = __ballot(true);               // the lanes that spill together
+    const int first = __ffsll((long long)ms) - 1;
+    const unsigned below = __builtin_amdgcn_mbcnt_hi((unsigned)(ms >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((unsigned)ms, 0u));
+    unsigned j0 = 0u;
+    if (below == 0u) j0 = atomicAdd(&o.spn[0], (unsigned)__popcll(ms));
+    const unsigned j = __shfl(j0, first) + below;
+    if (j < SPILL_CAP) o.spill[j] = ((unsigned long long)(unsigned)tile << 32) | t;
+    if (k == (unsigned)o.cap) atomicAdd(&o.spn[1], 1u);
+}
+
+// r: the tiles of this thread's triangle t (x0 > x1: none); t0: the block's
+// first triangle.  Called by every thread of the block.
+__device__ __forceinline__ void bin_block(BinShared& S, const TileRect& r, int tiles_x, int t0, const BinOut& o) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool has = r.x0 <= r.x1;
+    const int ntx = has ? r.x1 - r.x0 + 1 : 0;
+    const int n = has ? ntx * (r.y1 - r.y0 + 1) : 0;
+    const int big = 0x7fffffff;
+    const int wx0 = -wave_max(has ? -r.x0 : -big), wx1 = wave_max(has ? r.x1 : -1);
+    const int wy0 = -wave_max(has ? -r.y0 : -big), wy1 = wave_max(has ? r.y1 : -1);
+    const int wn = wave_max(n);
+    if (lane == 0) {
+        int* q = S.red[wave];
+        q[0] = wx0; q[1] = wx1; q[2] = wy0; q[3] = wy1; q[4] = wn;
+    }
+    __syncthreads();
+    int x0 = big, x1 = -1, y0 = big, y1 = -1, nmax = 0;
+#pragma unroll
+    for (int w = 0; w < SETUP_TB / 64; ++w) {
+        x0 = min(x0, S.red[w][0]); x1 = max(x1, S.red[w][1]);
+        y0 = min(y0, S.red[w][2]); y1 = max(y1, S.red[w][3]);
+        nmax = max(nmax, S.red[w][4]);
+    }
+    if (nmax == 0) return;                                      // (uniform)
+    const int rw = x1 - x0 + 1;
+    const long long area = (long long)rw * (y1 - y0 + 1);
+    const bool local = area <= BIN_SLOTS;
+    const bool own = nmax <= BIN_OWN;
+    if (local)
+        for (int j = tid; j < (int)area; j += SETUP_TB) S.tab[j] = 0u;
+    if (!own) {
+        // inclusive prefix sums of the entry counts over the block
+        const int incl = wave_inclusive_sum(n);
+        if (lane == 63) S.red[wave][5] = incl;
+        S.rect[tid] = make_int4(r.x0, r.y0, ntx, 0);
+        __syncthreads();
+        int off = 0;
+        for (int w = 0; w < wave; ++w) off += S.red[w][5];
+        S.incl[tid] = off + incl;
+    }
+    __syncthreads();
+    const int P = own ? 0 : S.incl[SETUP_TB - 1];
+    // entry p of the block: its owner by binary search, its tile by its
+    // place in the owner's rectangle
+    auto entry = [&](int p, int& tx, int& ty) -> int {
+        int lo = 0, hi = SETUP_TB - 1;                          // first owner whose sum exceeds p
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int mid = (lo + hi) >> 1;
+            if (S.incl[mid] > p) hi = mid;
+            else lo = mid + 1;
         }
-        unsigned base = 0u;
-        if (has && my_leader == lane) base = atomicAdd(&counts[tile], group);
-        base = __shfl(base, my_leader);
-        const unsigned k = base + rank;
-        if (has && k < (unsigned)cap) bins[(long long)tile * cap + k] = (unsigned)t;
-        // entries past the capacity go to the render's spill list (the
-        // first of a tile also counts the tile as overflowing)
-        const bool sp = has && k >= (unsigned)cap && spill != nullptr;
-        const unsigned long long ms = __ballot(sp);
-        if (ms) {
-            const int first = __ffsll((long long)ms) - 1;
-            unsigned j0 = 0u;
-            if (lane == first) j0 = atomicAdd(&spn[0], (unsigned)__popcll(ms));
-            j0 = __shfl(j0, first);
-            if (sp) {
-                const unsigned j = j0 + __builtin_amdgcn_mbcnt_hi((unsigned)(ms >> 32),
-                                                                  __builtin_amdgcn_mbcnt_lo((unsigned)ms, 0u));
-                if (j < SPILL_CAP) spill[j] = ((unsigned long long)(unsigned)tile << 32) | (unsigned)t;
-                if (k == (unsigned)cap) atomicAdd(&spn[1], 1u);
+        const int4 q = S.rect[lo];
+        const int i = p - (lo > 0 ? S.incl[lo - 1] : 0);
+        const int iy = i / q.z;
+        tx = q.x + (i - iy * q.z);
+        ty = q.y + iy;
+        return lo;
+    };
+    if (local) {
+        if (own) {
+            for (int ty = r.y0; ty <= r.y1; ++ty)
+                for (int tx = r.x0; tx <= r.x1; ++tx) atomicAdd(&S.tab[(ty - y0) * rw + (tx - x0)], 1u);
+        } else {
+            for (int p = tid; p < P; p += SETUP_TB) {
+                int tx, ty;
+                (void)entry(p, tx, ty);
+                atomicAdd(&S.tab[(ty - y0) * rw + (tx - x0)], 1u);
             }
+        }
+        __syncthreads();
+        const float inv = 1.0f / (float)rw;
+        for (int j = tid; j < (int)area; j += SETUP_TB) {
+            const unsigned c = S.tab[j];
+            if (c == 0u) continue;
+            const int jy = (int)(((float)j + 0.5f) * inv);      // j / rw (exact: j < 4096)
+            S.tab[j] = atomicAdd(&o.counts[(y0 + jy) * tiles_x + x0 + (j - jy * rw)], c);
+        }
+        __syncthreads();
+    }
+    if (own) {
+        for (int ty = r.y0; ty <= r.y1; ++ty)
+            for (int tx = r.x0; tx <= r.x1; ++tx) {
+                const int tile = ty * tiles_x + tx;
+                const unsigned k = local ? atomicAdd(&S.tab[(ty - y0) * rw + (tx - x0)], 1u)
+                                         : atomicAdd(&o.counts[tile], 1u);
+                bin_put(o, tile, k, (unsigned)(t0 + tid));
+            }
+    } else {
+        for (int p = tid; p < P; p += SETUP_TB) {
+            int tx, ty;
+            const int w = entry(p, tx, ty);
+            const int tile = ty * tiles_x + tx;
+            const unsigned k = local ? atomicAdd(&S.tab[(ty - y0) * rw + (tx - x0)], 1u)
+                                     : atomicAdd(&o.counts[tile], 1u);
+            bin_put(o, tile, k, (unsigned)(t0 + w));
         }
     }
 }
 
-__device__ __forceinline__ void setup_tri(const DScene& sc, const DView& vw, const float* __restrict__ theta,
-                                          const uint32_t* __restrict__ pb, float e0, float sgn, int t,
-                                          TriR* __restrict__ recR, TriS* __restrict__ recS,
-                                          unsigned* __restrict__ counts,
-                                          unsigned* __restrict__ bins, int tile_px, int cap,
-                                          unsigned* __restrict__ spn, unsigned long long* __restrict__ spill,
-                                          const float* __restrict__ fpos) {
-    float p[9];
-    tri_positions(sc, theta, pb, e0, sgn, t, fpos, p);
-    setup_tri_at(vw, p, t, recR, recS, counts, bins, tile_px, cap, spn, spill);
+// Setup and binning of the block's triangles t0 + threadIdx.x in one view.
+__device__ __forceinline__ void setup_block(BinShared& S, const DScene& sc, const DView& vw,
+                                            const float* __restrict__ theta, const uint32_t* __restrict__ pb, float e0,
+                                            float sgn, int t0, TriR* __restrict__ recR, TriS* __restrict__ recS, int lg,
+                                            const BinOut& o, const float* __restrict__ fpos) {
+    const int t = t0 + (int)threadIdx.x;
+    TileRect r = {1, 0, 1, 0};
+    if (t < sc.n_tris) {
+        float p[9];
+        tri_positions(sc, theta, pb, e0, sgn, t, fpos, p);
+        r = setup_tri_at(vw, p, t, recR, recS, lg);
+    }
+    bin_block(S, r, vw.tiles_x, t0, o);
 }
 
-__global__ void __launch_bounds__(256) k_setup_bin(SetupArgs a) {
+__global__ void __launch_bounds__(SETUP_TB) k_setup_bin(SetupArgs a) {
+    __shared__ BinShared S;
     const DScene& sc = a.sc;
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= sc.n_tris) return;
     int slot = blockIdx.y;                       // (local item, sign)
     int li = slot / a.nsign, s = slot % a.nsign;
     int item = a.item0 + li;
     int pair = item / a.n_views, view = item % a.n_views;
     const uint32_t* pb = a.pert.bits ? a.pert.bits + (long long)pair * sc.words : nullptr;
     const float* fpos = a.fpos ? a.fpos + ((long long)pair * a.nsign + s) * 3 * sc.n_verts : nullptr;
-    setup_tri(sc, a.views.v[view], a.theta, pb, a.pert.eps[0], a.sgn[s], t, a.recR + (long long)slot * sc.n_tris,
-              a.recS + (long long)slot * sc.n_tris,
-              a.counts + (long long)slot * a.max_tiles, a.bins + (long long)slot * a.max_tiles * a.cap, a.tile,
-              a.cap, a.spn ? a.spn + 2ll * slot : nullptr, a.spill ? a.spill + (long long)slot * SPILL_CAP : nullptr,
-              fpos);
+    const BinOut o = {a.counts + (long long)slot * a.max_tiles, a.bins + (long long)slot * a.max_tiles * a.cap, a.cap,
+                      a.spn ? a.spn + 2ll * slot : nullptr, a.spill ? a.spill + (long long)slot * SPILL_CAP : nullptr};
+    setup_block(S, sc, a.views.v[view], a.theta, pb, a.pert.eps[0], a.sgn[s], (int)blockIdx.x * SETUP_TB,
+                a.recR + (long long)slot * sc.n_tris, a.recS + (long long)slot * sc.n_tris, 31 - __clz(a.tile), o, fpos);
 }
 
 // Tessellated vertex positions of a subdivision surface for every (pair,
@@ -317,21 +455,6 @@ __device__ __forceinline__ void raster_tri(const TriR& r, unsigned t, int px0, i
             raster_px<TILE, DEEP>(r, t, x0 + dx, y0 + dy, px0, py0, key, L);
         }
     }
-}
-
-// Inclusive prefix sum over the 64 lanes of a wave with DPP moves: shifts
-// by 1, 2, 4 and 8 within each row of 16 lanes (lanes shifted in from
-// outside the row add 0), then row 0's total to row 1 and row 2's to row 3
-// (row_bcast:15), then row 1's running total to rows 2 and 3 (row_bcast:31).
-// Must be called by every lane of the wave.
-__device__ __forceinline__ int wave_inclusive_sum(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);     // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);     // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);     // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);     // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);     // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);     // row_bcast:31
-    return v;
 }
 
 // Per-wave LDS staging of a batch of small triangles for the packed raster
@@ -1647,9 +1770,16 @@ __global__ void __launch_bounds__(256) k_signs_b(BatchArgs b) {
                 S.bits + (long long)pair * S.sc.words);
 }
 
+// The bins of sign s of batch item I in a view of `tiles` tiles.
+__device__ __forceinline__ BinOut item_bins(const BatchArgs& b, const BItem& I, int s, int tiles) {
+    return {b.counts + I.cnt_off + (long long)s * tiles, b.bins + I.bin_off + (long long)s * tiles * I.cap, I.cap,
+            b.spn + 2 * (I.sp_off + s), b.spill + (I.sp_off + s) * SPILL_CAP};
+}
+
 // Setup of every (item, sign, triangle): each (item, sign) starts on a
 // block boundary.
-__global__ void __launch_bounds__(256) k_setup_b(BatchArgs b) {
+__global__ void __launch_bounds__(SETUP_TB) k_setup_b(BatchArgs b) {
+    __shared__ BinShared SB;
     long long blk = b.unit0 + blockIdx.x;
     int it = last_le((const char*)&b.items[0].setup_blk0, sizeof(BItem), b.n_items, blk);
     it = __builtin_amdgcn_readfirstlane(it);
@@ -1659,22 +1789,19 @@ __global__ void __launch_bounds__(256) k_setup_b(BatchArgs b) {
     long long per_sign = ((long long)sc.n_tris + 255) >> 8;
     long long local = blk - I.setup_blk0;
     int s = (int)(local / per_sign);
-    int t = (int)((local % per_sign) * 256 + threadIdx.x);
-    if (t >= sc.n_tris) return;
+    const int t0 = (int)(local - s * per_sign) * SETUP_TB;
     const DView& vw = b.views[I.view];
-    int tiles = vw.tiles_x * vw.tiles_y;
-    setup_tri(sc, vw, S.theta, S.bits + (long long)I.pair * sc.words, S.eps[0], s == 0 ? 1.0f : -1.0f, t,
-              b.recR + I.rec_off + (long long)s * sc.n_tris, b.recS + I.rec_off + (long long)s * sc.n_tris,
-              b.counts + I.cnt_off + (long long)s * tiles,
-              b.bins + I.bin_off + (long long)s * tiles * I.cap, b.tile, I.cap, b.spn + 2 * (I.sp_off + s),
-              b.spill + (I.sp_off + s) * SPILL_CAP, nullptr);
+    setup_block(SB, sc, vw, S.theta, S.bits + (long long)I.pair * sc.words, S.eps[0], s == 0 ? 1.0f : -1.0f, t0,
+                b.recR + I.rec_off + (long long)s * sc.n_tris, b.recS + I.rec_off + (long long)s * sc.n_tris,
+                31 - __clz(b.tile), item_bins(b, I, s, vw.tiles_x * vw.tiles_y), nullptr);
 }
 
 // Setup of a one-scene batch: a thread takes one (pair, sign, triangle)
 // and sets the triangle up in every view, so the perturbed corners (index,
 // parameter and sign reads) are formed once for all the views.  Items are
 // numbered (pair, view).
-__global__ void __launch_bounds__(256) k_setup_b1(BatchArgs b, BatchOne one) {
+__global__ void __launch_bounds__(SETUP_TB) k_setup_b1(BatchArgs b, BatchOne one) {
+    __shared__ BinShared SB;
     const DScene& sc = one.sc;
     const BScene& S = b.scenes[0];
     const long long per_sign = ((long long)sc.n_tris + 255) >> 8;
@@ -1682,18 +1809,21 @@ __global__ void __launch_bounds__(256) k_setup_b1(BatchArgs b, BatchOne one) {
     const int pair = (int)(blk / (2 * per_sign));
     const long long rem = blk - (long long)pair * 2 * per_sign;
     const int s = (int)(rem / per_sign);
-    const int t = (int)((rem - s * per_sign) * 256 + threadIdx.x);
-    if (t >= sc.n_tris) return;
+    const int t0 = (int)(rem - s * per_sign) * SETUP_TB;
+    const int t = t0 + (int)threadIdx.x;
+    const int lg = 31 - __clz(b.tile);
     float p[9];
-    tri_positions(sc, S.theta, S.bits + (long long)pair * sc.words, S.eps[0], s == 0 ? 1.0f : -1.0f, t, nullptr, p);
+    if (t < sc.n_tris)
+        tri_positions(sc, S.theta, S.bits + (long long)pair * sc.words, S.eps[0], s == 0 ? 1.0f : -1.0f, t, nullptr, p);
     for (int v = 0; v < one.n_views; ++v) {
         const BItem& I = b.items[pair * one.n_views + v];
         const DView& vw = one.views[v];
-        const int tiles = vw.tiles_x * vw.tiles_y;
-        setup_tri_at(vw, p, t, b.recR + I.rec_off + (long long)s * sc.n_tris,
-                     b.recS + I.rec_off + (long long)s * sc.n_tris, b.counts + I.cnt_off + (long long)s * tiles,
-                     b.bins + I.bin_off + (long long)s * tiles * I.cap, b.tile, I.cap, b.spn + 2 * (I.sp_off + s),
-                     b.spill + (I.sp_off + s) * SPILL_CAP);
+        TileRect r = {1, 0, 1, 0};
+        if (t < sc.n_tris)
+            r = setup_tri_at(vw, p, t, b.recR + I.rec_off + (long long)s * sc.n_tris,
+                             b.recS + I.rec_off + (long long)s * sc.n_tris, lg);
+        if (v > 0) __syncthreads();              // the view before is done with the shared tables
+        bin_block(SB, r, vw.tiles_x, t0, item_bins(b, I, s, vw.tiles_x * vw.tiles_y));
     }
 }
 
