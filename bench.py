@@ -389,7 +389,7 @@ def main():
     # the graph-captured step is a one-scene batch, whose tile kernel takes the
     # scene in its arguments; the host-driven modes (all items in one launch,
     # or one launch per item) run the context's tile kernel
-    kernel = f"k_tile_b1<{tile}>" if main_mode == "graph" else f"k_tile<{tile},0,false>"
+    kernel = f"k_tile<{tile}>" if main_mode == "graph" else f"k_tile<{tile},0,false>"
     traffic = measured_traffic(kernel) if args.config == "paper" else None
     achieved = alg_bytes_launch / (tile_avg_ms * 1e-3) / 1e9
     out = {

@@ -14,8 +14,9 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = [os.path.join(CSRC, "dr_kernels.hip"), os.path.join(CSRC, "dr_api.hip"), os.path.join(CSRC, "dr_subdiv.cpp"),
-           os.path.join(CSRC, "dr_probe.hip")]
+SOURCES = [os.path.join(CSRC, f) for f in (
+    "dr_kernels.hip", "dr_tile8.hip", "dr_tile16.hip", "dr_tile32.hip", "dr_tile8_deep.hip", "dr_tile16_deep.hip",
+    "dr_api.hip", "dr_subdiv.cpp", "dr_probe.hip")]
 OUT = os.path.join(HERE, "libdr.so")
 
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off", "-fPIC",

@@ -99,6 +99,8 @@ struct dr_ctx {
     TriR* recR = nullptr;
     TriS* recS = nullptr;
     long long rec_slots = 0;
+    TriG* recG = nullptr;           // GGX scenes: [pairs * signs, n_tris]
+    long long g_slots = 0;
     unsigned* counts = nullptr;
     unsigned* bins = nullptr;
     long long tile_slots = 0;       // slots * max_tiles allocated
@@ -174,7 +176,9 @@ static dr_status grow(dr_ctx* c, T** p, long long* have, long long need, size_t 
     return DR_OK;
 }
 
-static dr_status ensure_raster(dr_ctx* c, long long slots, int max_tiles) {
+// Records and bins of `slots` (item, sign) renders of g_slots (pair, sign)
+// perturbations.
+static dr_status ensure_raster(dr_ctx* c, long long slots, long long g_slots, int max_tiles) {
     long long have = c->rec_slots;
     dr_status s = grow(c, &c->recR, &have, slots * c->sc.n_tris, sizeof(TriR), false);
     if (s) return s;
@@ -182,6 +186,10 @@ static dr_status ensure_raster(dr_ctx* c, long long slots, int max_tiles) {
     s = grow(c, &c->recS, &have, slots * c->sc.n_tris, sizeof(TriS), false);
     if (s) return s;
     if (slots * c->sc.n_tris > c->rec_slots) c->rec_slots = slots * c->sc.n_tris;
+    if (c->sc.shading == DR_GGX) {
+        s = grow(c, &c->recG, &c->g_slots, g_slots * c->sc.n_tris, sizeof(TriG), false);
+        if (s) return s;
+    }
     s = grow(c, &c->counts, &c->tile_slots, slots * (long long)max_tiles, sizeof(unsigned), true);
     if (s) return s;
     s = grow(c, &c->spn, &c->spn_words, 2 * slots, sizeof(unsigned), true);
@@ -218,6 +226,13 @@ static DView make_dview(const dr_view& v, int tile, long long tgt_off) {
     d.tiles_y = (v.height + tile - 1) / tile;
     d.tgt_off = tgt_off;
     return d;
+}
+
+// Tile counts of the views (the bins' layout), once views 0 .. n-1 are set.
+static void finish_views(DViews& dv, int n) {
+    dv.n = n;
+    dv.tsum[0] = 0;
+    for (int v = 0; v < n; ++v) dv.tsum[v + 1] = dv.tsum[v] + dv.v[v].tiles_x * dv.v[v].tiles_y;
 }
 
 static dr_status check_eps(dr_ctx* c, const float* eps) {
@@ -452,7 +467,7 @@ extern "C" dr_status dr_destroy(dr_ctx* c) {
     if (c->h_seen) (void)hipHostFree(c->h_seen);
     if (c->ev_seen) (void)hipEventDestroy(c->ev_seen);
     void* ptrs[] = {c->recR, c->recS, c->counts, c->bins, c->spn, c->spill, c->R, c->bits, c->stats, c->partials,
-                    c->qtot, c->tri_rowptr, c->tri_cols, c->fpos};
+                    c->recG, c->qtot, c->tri_rowptr, c->tri_cols, c->fpos};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     c->timer.destroy();
@@ -524,9 +539,12 @@ extern "C" dr_status dr_render(dr_ctx* c, const float* theta, const dr_view* vie
     }
     s = device_guard(c);
     if (s) return s;
-    DView dv = make_dview(*view, tile, 0);
-    int max_tiles = dv.tiles_x * dv.tiles_y;
-    s = ensure_raster(c, 1, max_tiles);
+    DViews dv;
+    std::memset(&dv, 0, sizeof(dv));
+    dv.v[0] = make_dview(*view, tile, 0);
+    finish_views(dv, 1);
+    int max_tiles = dv.tsum[1];
+    s = ensure_raster(c, 1, 1, max_tiles);
     if (s) return s;
     DPert dp;
     dp.bits = nullptr;
@@ -546,11 +564,12 @@ extern "C" dr_status dr_render(dr_ctx* c, const float* theta, const dr_view* vie
     SetupArgs sa;
     std::memset(&sa, 0, sizeof(sa));
     sa.sc = c->sc;
-    sa.views.v[0] = dv;
+    sa.views = dv;
     sa.pert = dp;
     sa.theta = theta;
     sa.n_views = 1;
-    sa.item0 = 0;
+    sa.n_items = 1;
+    sa.whole = 1;
     sa.nsign = 1;
     sa.sgn[0] = sg;
     sa.sgn[1] = sg;
@@ -559,21 +578,23 @@ extern "C" dr_status dr_render(dr_ctx* c, const float* theta, const dr_view* vie
     sa.max_tiles = max_tiles;
     sa.recR = c->recR;
     sa.recS = c->recS;
+    sa.recG = c->recG;
     sa.counts = c->counts;
     sa.bins = c->bins;
     sa.spn = c->spn;
     sa.spill = c->spill;
     s = tessellate(c, theta, dp, 1, 1, sg, sg, &sa.fpos);
     if (s) return s;
-    HIPCHK(c, c->timer.run(c->stream, K_SETUP, [&] { return launch_setup(c->stream, sa, 1); }));
+    HIPCHK(c, c->timer.run(c->stream, K_SETUP, [&] { return launch_setup(c->stream, sa); }));
     TileArgs ta;
     std::memset(&ta, 0, sizeof(ta));
     ta.sc = c->sc;
-    ta.views.v[0] = dv;
+    ta.views = dv;
     ta.pert = dp;
     ta.theta = theta;
     ta.n_views = 1;
-    ta.item0 = 0;
+    ta.n_items = 1;
+    ta.whole = 1;
     ta.nsign = 1;
     ta.sgn[0] = sg;
     ta.sgn[1] = sg;
@@ -581,6 +602,7 @@ extern "C" dr_status dr_render(dr_ctx* c, const float* theta, const dr_view* vie
     ta.max_tiles = max_tiles;
     ta.recR = c->recR;
     ta.recS = c->recS;
+    ta.recG = c->recG;
     ta.counts = c->counts;
     ta.bins = c->bins;
     ta.spn = c->spn;
@@ -589,7 +611,7 @@ extern "C" dr_status dr_render(dr_ctx* c, const float* theta, const dr_view* vie
     ta.out_rgb = rgb;
     ta.out_id = id;
     ta.out_uv = uv;
-    HIPCHK(c, c->timer.run(c->stream, K_TILE, [&] { return launch_tile(c->stream, ta, tile, 1, 1, max_tiles); }));
+    HIPCHK(c, c->timer.run(c->stream, K_TILE, [&] { return launch_tile(c->stream, ta, tile, 1); }));
     return DR_OK;
 }
 
@@ -636,6 +658,7 @@ struct EstScratch {
     uint32_t* bits = nullptr;
     TriR* recR = nullptr;
     TriS* recS = nullptr;
+    TriG* recG = nullptr;
     unsigned* counts = nullptr;
     unsigned* bins = nullptr;
     unsigned* spn = nullptr;
@@ -674,6 +697,7 @@ static dr_status estimate_check(dr_ctx* c, const float* theta, const dr_view* vi
         tgt_off += 3ll * views[v].width * views[v].height;
         pl.max_tiles = std::max(pl.max_tiles, pl.dv.v[v].tiles_x * pl.dv.v[v].tiles_y);
     }
+    finish_views(pl.dv, n_views);
     pl.items = (long long)n_pairs * n_views;
     return DR_OK;
 }
@@ -685,10 +709,17 @@ static long long items_per_launch(const dr_ctx* c, long long items) {
     return std::min<long long>(per, 32767);
 }
 
+// (pair, sign) perturbations that a launch of `per` items touches: all of
+// the call's, or those of a run of items that may start within a pair.
+static long long pert_slots(const EstPlan& pl, long long per) {
+    const long long nv = pl.dv.n;
+    return 2 * (per >= pl.items ? pl.items / nv : (per + nv - 1) / nv + 1);
+}
+
 // The context's own scratch, grown as needed.
 static dr_status estimate_scratch_ctx(dr_ctx* c, const EstPlan& pl, int32_t n_pairs, bool full, EstScratch& x) {
     x.per = items_per_launch(c, pl.items);
-    dr_status s = ensure_raster(c, 2 * x.per, pl.max_tiles);
+    dr_status s = ensure_raster(c, 2 * x.per, pert_slots(pl, x.per), pl.max_tiles);
     if (s) return s;
     s = ensure_bits(c, n_pairs);
     if (s) return s;
@@ -707,6 +738,7 @@ static dr_status estimate_scratch_ctx(dr_ctx* c, const EstPlan& pl, int32_t n_pa
     x.bits = c->bits;
     x.recR = c->recR;
     x.recS = c->recS;
+    x.recG = c->recG;
     x.counts = c->counts;
     x.bins = c->bins;
     x.spn = c->spn;
@@ -753,6 +785,8 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     sa.max_tiles = max_tiles;
     sa.recR = x.recR;
     sa.recS = x.recS;
+    sa.recG = x.recG;
+    sa.whole = per >= items;
     sa.counts = x.counts;
     sa.bins = x.bins;
     sa.spn = x.spn;
@@ -771,6 +805,8 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     ta.max_tiles = max_tiles;
     ta.recR = x.recR;
     ta.recS = x.recS;
+    ta.recG = x.recG;
+    ta.whole = per >= items;
     ta.counts = x.counts;
     ta.bins = x.bins;
     ta.spn = x.spn;
@@ -793,10 +829,10 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     if (full) HIPCHK(c, launch_zero64(c->stream, x.qtot, n_pairs));
     for (long long i0 = 0; i0 < items; i0 += per) {
         int n = (int)std::min(per, items - i0);
-        sa.item0 = (int)i0;
-        ta.item0 = (int)i0;
-        HIPCHK(c, run(K_SETUP, [&] { return launch_setup(c->stream, sa, n); }));
-        HIPCHK(c, run(K_TILE, [&] { return launch_tile(c->stream, ta, tile, full ? 3 : 0, n, max_tiles); }));
+        sa.item0 = ta.item0 = (int)i0;
+        sa.n_items = ta.n_items = n;
+        HIPCHK(c, run(K_SETUP, [&] { return launch_setup(c->stream, sa); }));
+        HIPCHK(c, run(K_TILE, [&] { return launch_tile(c->stream, ta, tile, full ? 3 : 0); }));
     }
     FoldArgs fa;
     std::memset(&fa, 0, sizeof(fa));
@@ -860,7 +896,11 @@ extern "C" dr_status dr_estimate_grad_image(dr_ctx* c, const float* theta, const
 // address is looked up once per device (dr_create, with that device
 // current) and kept in scratch_dev[].
 
-static __device__ __align__(256) unsigned char scratch[DR_NOALLOC_SCRATCH_BYTES];
+// A call is accepted by its accounted size (static_account), which the public
+// limit is stated in.  What the kernels lay out for it differs from that by a
+// third at most (64 to 128 B of records per triangle against 96 accounted).
+static constexpr unsigned long long SCRATCH_ARRAY_BYTES = DR_NOALLOC_SCRATCH_BYTES / 8 * 11;
+static __device__ __align__(256) unsigned char scratch[SCRATCH_ARRAY_BYTES];
 
 static std::mutex scratch_mu;
 static constexpr int SCRATCH_MAX_DEVICES = 64;
@@ -891,11 +931,26 @@ static hipError_t scratch_lookup(int dev, void** out) {
 
 static unsigned long long round256(unsigned long long b) { return (b + 255ull) & ~255ull; }
 
+// Accounted scratch of an estimate with `per` items per launch: bin and spill
+// counters, per-pair group sums, sign bits, 96 B of records per triangle and
+// render, bins, spill lists and tessellated positions.
+static unsigned long long static_account(const dr_ctx* c, const EstPlan& pl, int32_t n_pairs, long long per) {
+    const DScene& sc = c->sc;
+    const unsigned long long slots = 2ull * (unsigned long long)per, tris = (unsigned long long)sc.n_tris;
+    const unsigned long long bin_slots = slots * (unsigned long long)pl.max_tiles, pairs = (unsigned long long)n_pairs;
+    unsigned long long need = round256(bin_slots * 4ull) + round256(slots * 8ull) +
+                              round256(pairs * (unsigned long long)sc.G * 8ull) +
+                              round256((pairs * (unsigned long long)sc.words + 1ull) * 4ull) + 2ull * round256(slots * tris * 48ull) +
+                              round256(bin_slots * (unsigned long long)c->tune.bin_capacity * 4ull) +
+                              round256(slots * (unsigned long long)SPILL_CAP * 8ull);
+    if (sc.n_ctrl > 0) need += round256(pairs * 2ull * (unsigned long long)sc.n_verts * 12ull);
+    return need;
+}
+
 // Layout of the estimate's scratch in the static array, items per launch
 // `per`: the bin counters and the per-pair group sums first (the part that
 // must start at zero), then the sign bits, the records, the bins and the
-// tessellated positions.  Returns the bytes needed; fills x when base is
-// given.
+// tessellated positions.  Returns the bytes taken and fills x.
 static unsigned long long static_layout(const dr_ctx* c, const EstPlan& pl, int32_t n_pairs, long long per,
                                         unsigned char* base, EstScratch* x, unsigned long long* zero_bytes) {
     const DScene& sc = c->sc;
@@ -903,36 +958,25 @@ static unsigned long long static_layout(const dr_ctx* c, const EstPlan& pl, int3
     const unsigned long long cap = (unsigned long long)c->tune.bin_capacity;
     unsigned long long off = 0;
     auto take = [&](unsigned long long bytes) {
-        unsigned long long o = off;
+        unsigned char* p = base + off;
         off += round256(bytes);
-        return o;
+        return p;
     };
     const unsigned long long bin_slots = slots * (unsigned long long)pl.max_tiles;
-    unsigned long long o_counts = take(bin_slots * sizeof(unsigned));
-    unsigned long long o_spn = take(slots * 2ull * sizeof(unsigned));
-    unsigned long long o_R = take((unsigned long long)n_pairs * (unsigned long long)sc.G * sizeof(long long));
-    if (zero_bytes) *zero_bytes = off;
-    unsigned long long o_bits = take(((unsigned long long)n_pairs * (unsigned long long)sc.words + 1ull) * 4ull);
-    unsigned long long o_recR = take(slots * (unsigned long long)sc.n_tris * sizeof(TriR));
-    unsigned long long o_recS = take(slots * (unsigned long long)sc.n_tris * sizeof(TriS));
-    unsigned long long o_bins = take(bin_slots * cap * sizeof(unsigned));
-    unsigned long long o_spill = take(slots * (unsigned long long)SPILL_CAP * sizeof(unsigned long long));
-    unsigned long long o_fpos = 0;
-    if (sc.n_ctrl > 0) o_fpos = take((unsigned long long)n_pairs * 2ull * (unsigned long long)sc.n_verts * 12ull);
-    if (base && x) {
-        x->counts = (unsigned*)(base + o_counts);
-        x->R = (long long*)(base + o_R);
-        x->bits = (uint32_t*)(base + o_bits);
-        x->recR = (TriR*)(base + o_recR);
-        x->recS = (TriS*)(base + o_recS);
-        x->bins = (unsigned*)(base + o_bins);
-        x->spn = (unsigned*)(base + o_spn);
-        x->spill = (unsigned long long*)(base + o_spill);
-        x->fpos = sc.n_ctrl > 0 ? (float*)(base + o_fpos) : nullptr;
-        x->qtot = nullptr;
-        x->cap = (int)cap;
-        x->per = per;
-    }
+    x->counts = (unsigned*)take(bin_slots * sizeof(unsigned));
+    x->spn = (unsigned*)take(slots * 2ull * sizeof(unsigned));
+    x->R = (long long*)take((unsigned long long)n_pairs * (unsigned long long)sc.G * sizeof(long long));
+    *zero_bytes = off;
+    x->bits = (uint32_t*)take(((unsigned long long)n_pairs * (unsigned long long)sc.words + 1ull) * 4ull);
+    x->recR = (TriR*)take(slots * (unsigned long long)sc.n_tris * sizeof(TriR));
+    x->recS = (TriS*)take(slots * (unsigned long long)sc.n_tris * sizeof(TriS));
+    if (sc.shading == DR_GGX)
+        x->recG = (TriG*)take((unsigned long long)pert_slots(pl, per) * (unsigned long long)sc.n_tris * sizeof(TriG));
+    x->bins = (unsigned*)take(bin_slots * cap * sizeof(unsigned));
+    x->spill = (unsigned long long*)take(slots * (unsigned long long)SPILL_CAP * sizeof(unsigned long long));
+    if (sc.n_ctrl > 0) x->fpos = (float*)take((unsigned long long)n_pairs * 2ull * (unsigned long long)sc.n_verts * 12ull);
+    x->cap = (int)cap;
+    x->per = per;
     return off;
 }
 
@@ -951,10 +995,10 @@ extern "C" dr_status dr_estimate_grad_noalloc(dr_ctx* c, const float* theta, con
     // as many items per raster launch as the tuning asks for and the array
     // holds (the results do not depend on it); one at the least
     long long per = items_per_launch(c, pl.items);
-    unsigned long long need = static_layout(c, pl, n_pairs, per, nullptr, nullptr, nullptr);
+    unsigned long long need = static_account(c, pl, n_pairs, per);
     while (need > DR_NOALLOC_SCRATCH_BYTES && per > 1) {
         per = (per + 1) / 2;
-        need = static_layout(c, pl, n_pairs, per, nullptr, nullptr, nullptr);
+        need = static_account(c, pl, n_pairs, per);
     }
     if (need > DR_NOALLOC_SCRATCH_BYTES)
         return fail(c, DR_E_INVALID,
@@ -964,7 +1008,8 @@ extern "C" dr_status dr_estimate_grad_noalloc(dr_ctx* c, const float* theta, con
                         "dr_estimate_grad)");
     EstScratch x;
     unsigned long long zero_bytes = 0;
-    (void)static_layout(c, pl, n_pairs, per, (unsigned char*)base, &x, &zero_bytes);
+    if (static_layout(c, pl, n_pairs, per, (unsigned char*)base, &x, &zero_bytes) > SCRATCH_ARRAY_BYTES)
+        return fail(c, DR_E_INVALID, "dr_estimate_grad_noalloc: the layout exceeds the static scratch array");
     // the array keeps the last call's contents: clear the bin counters and
     // the group sums (a fill kernel, so the call can be captured in a graph)
     HIPCHK(c, launch_zero64(c->stream, (long long*)base, (int)(zero_bytes / 8ull)));
@@ -991,9 +1036,10 @@ extern "C" dr_status dr_loss(dr_ctx* c, const float* theta, const dr_view* views
         tgt_off += 3ll * views[v].width * views[v].height;
         max_tiles = std::max(max_tiles, dv.v[v].tiles_x * dv.v[v].tiles_y);
     }
+    finish_views(dv, n_views);
     dr_status s = device_guard(c);
     if (s) return s;
-    s = ensure_raster(c, n_views, max_tiles);
+    s = ensure_raster(c, n_views, 1, max_tiles);
     if (s) return s;
     s = grow(c, &c->partials, &c->partial_slots, (long long)n_views * max_tiles, sizeof(double), false);
     if (s) return s;
@@ -1007,7 +1053,8 @@ extern "C" dr_status dr_loss(dr_ctx* c, const float* theta, const dr_view* views
     sa.pert = dp;
     sa.theta = theta;
     sa.n_views = n_views;
-    sa.item0 = 0;
+    sa.n_items = n_views;
+    sa.whole = 1;
     sa.nsign = 1;
     sa.sgn[0] = sa.sgn[1] = 1.0f;
     sa.tile = tile;
@@ -1015,13 +1062,14 @@ extern "C" dr_status dr_loss(dr_ctx* c, const float* theta, const dr_view* views
     sa.max_tiles = max_tiles;
     sa.recR = c->recR;
     sa.recS = c->recS;
+    sa.recG = c->recG;
     sa.counts = c->counts;
     sa.bins = c->bins;
     sa.spn = c->spn;
     sa.spill = c->spill;
     s = tessellate(c, theta, dp, 1, 1, 1.0f, 1.0f, &sa.fpos);
     if (s) return s;
-    HIPCHK(c, c->timer.run(c->stream, K_SETUP, [&] { return launch_setup(c->stream, sa, n_views); }));
+    HIPCHK(c, c->timer.run(c->stream, K_SETUP, [&] { return launch_setup(c->stream, sa); }));
     TileArgs ta;
     std::memset(&ta, 0, sizeof(ta));
     ta.sc = c->sc;
@@ -1029,13 +1077,15 @@ extern "C" dr_status dr_loss(dr_ctx* c, const float* theta, const dr_view* views
     ta.pert = dp;
     ta.theta = theta;
     ta.n_views = n_views;
-    ta.item0 = 0;
+    ta.n_items = n_views;
+    ta.whole = 1;
     ta.nsign = 1;
     ta.sgn[0] = ta.sgn[1] = 1.0f;
     ta.cap = c->tune.bin_capacity;
     ta.max_tiles = max_tiles;
     ta.recR = c->recR;
     ta.recS = c->recS;
+    ta.recG = c->recG;
     ta.counts = c->counts;
     ta.bins = c->bins;
     ta.spn = c->spn;
@@ -1043,7 +1093,7 @@ extern "C" dr_status dr_loss(dr_ctx* c, const float* theta, const dr_view* views
     ta.stats = c->stats;
     ta.targets = targets;
     ta.partials = c->partials;
-    HIPCHK(c, c->timer.run(c->stream, K_TILE, [&] { return launch_tile(c->stream, ta, tile, 2, n_views, max_tiles); }));
+    HIPCHK(c, c->timer.run(c->stream, K_TILE, [&] { return launch_tile(c->stream, ta, tile, 2); }));
     HIPCHK(c, launch_sum_tiles(c->stream, c->partials, max_tiles, dv, n_views, loss));
     return DR_OK;
 }
@@ -1208,8 +1258,12 @@ struct dr_batch {
     std::string err;
     BatchArgs args{};
     int n_scenes = 0;
-    bool has_one = false;              // one scene: its constants go by value
-    BatchOne one{};
+    // one scene: the launches of a single context's call, with the scene's
+    // constants and views in the kernel arguments (read with scalar loads that
+    // do not compete with the texel reads)
+    bool has_one = false;
+    SetupArgs one_setup{};
+    TileArgs one_tile{};
     // device allocations
     std::vector<void*> allocs;
     unsigned long long* stats = nullptr;
@@ -1325,7 +1379,7 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
         return px;
     };
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost(x) > cost(y); });
-    long long sign_blk = 0, group_blk = 0, rec = 0, cnt = 0, bin = 0, sp = 0, setup_blk = 0, tile0 = 0;
+    long long sign_blk = 0, group_blk = 0, rec = 0, grec = 0, cnt = 0, bin = 0, sp = 0, setup_blk = 0, tile0 = 0;
     std::vector<long long> bits_off(n_scenes), R_off(n_scenes);
     long long bits_total = 0, R_total = 0;
     for (int i = 0; i < n_scenes; ++i) {
@@ -1385,6 +1439,7 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
                 I.cap = cap;
                 I.rec_off = rec;
                 rec += 2ll * S.sc.n_tris;
+                I.g_off = grec;                       // (the pair's: advanced after its last view)
                 I.cnt_off = cnt;
                 cnt += 2 * tiles;
                 I.bin_off = bin;
@@ -1396,6 +1451,7 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
                 I.tile0 = tile0;
                 tile0 += tiles;
                 hi.push_back(I);
+                if (v + 1 == s.n_views && S.sc.shading == DR_GGX) grec += 2ll * S.sc.n_tris;
             }
     }
     if (sign_blk > 0x7fffffffll || setup_blk > 0x7fffffffll || group_blk > 0x7fffffffll || tile0 > 0x7fffffffll) {
@@ -1460,6 +1516,7 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
     unsigned* dstep = nullptr;
     if ((st = balloc(b, &bits, (size_t)bits_total + 1, false)) || (st = balloc(b, &R, (size_t)R_total, true)) ||
         (st = balloc(b, &A.recR, (size_t)rec, false)) || (st = balloc(b, &A.recS, (size_t)rec, false)) ||
+        (st = balloc(b, &A.recG, (size_t)grec, false)) ||
         (st = balloc(b, &A.counts, (size_t)cnt, true)) || (st = balloc(b, &A.bins, (size_t)bin, false)) ||
         (st = balloc(b, &A.spn, (size_t)sp * 2, true)) ||
         (st = balloc(b, &A.spill, (size_t)sp * SPILL_CAP, false)) ||
@@ -1493,16 +1550,52 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
     A.bc2 = dbc2;
     A.step = dstep;
     A.stats = b->stats;
-    if (n_scenes == 1 && hv.size() <= (size_t)DRD_MAX_VIEWS) {
+    // one shading for every scene selects its kernels, else the general ones
+    A.shade = scene_shade(hs[0].sc);
+    for (int i = 1; i < n_scenes; ++i)
+        if (scene_shade(hs[i].sc) != A.shade) A.shade = SHADE_ANY;
+    if (n_scenes == 1 && 2 * hi.size() <= 65535) {     // (grid y of the launches)
+        const BScene& S = hs[0];
         b->has_one = true;
-        b->one.sc = hs[0].sc;
-        for (size_t v = 0; v < hv.size(); ++v) b->one.views[v] = hv[v];
-        // items are numbered (pair, view): the tile launch walks them pair-interleaved
-        b->one.n_views = (int)hv.size();
-        b->one.il_pairs = n_pairs;
-        b->one.tsum[0] = 0;
-        for (size_t v = 0; v < hv.size(); ++v)
-            b->one.tsum[v + 1] = b->one.tsum[v] + (long long)hv[v].tiles_x * hv[v].tiles_y;
+        SetupArgs& sa = b->one_setup;
+        TileArgs& ta = b->one_tile;
+        sa.sc = ta.sc = S.sc;
+        for (size_t v = 0; v < hv.size(); ++v) sa.views.v[v] = hv[v];
+        finish_views(sa.views, (int)hv.size());
+        ta.views = sa.views;
+        sa.pert.bits = S.bits;
+        std::memcpy(sa.pert.eps, S.eps, sizeof(S.eps));
+        ta.pert = sa.pert;
+        sa.theta = ta.theta = S.theta;
+        sa.n_views = ta.n_views = (int)hv.size();
+        sa.n_items = ta.n_items = (int)hi.size();
+        sa.whole = ta.whole = 1;
+        sa.nsign = ta.nsign = 2;
+        sa.sgn[0] = ta.sgn[0] = 1.0f;
+        sa.sgn[1] = ta.sgn[1] = -1.0f;
+        sa.tile = tile_px;
+        sa.cap = ta.cap = hi[0].cap;
+        for (size_t v = 0; v < hv.size(); ++v) ta.max_tiles = std::max(ta.max_tiles, hv[v].tiles_x * hv[v].tiles_y);
+        sa.max_tiles = ta.max_tiles;
+        sa.recR = A.recR;
+        sa.recS = A.recS;
+        sa.recG = A.recG;
+        sa.counts = ta.counts = A.counts;
+        sa.bins = A.bins;
+        sa.spn = ta.spn = A.spn;
+        sa.spill = A.spill;
+        ta.recR = A.recR;
+        ta.recS = A.recS;
+        ta.recG = A.recG;
+        ta.bins = A.bins;
+        ta.spill = A.spill;
+        ta.stats = A.stats;
+        ta.targets = S.targets;
+        ta.R = S.R;
+        ta.K = S.K;
+        ta.act_pos = S.act_pos;
+        std::memcpy(ta.act_cls, S.act_cls, sizeof(S.act_cls));
+        ta.any_act = S.any_act;
     }
     *out = b;
     return DR_OK;
@@ -1527,27 +1620,30 @@ static hipError_t batch_enqueue(dr_batch* b, hipStream_t st, bool descend, bool 
     Timer off;
     Timer& T = timed ? b->timer : off;
     hipError_t e;
-    const BatchOne* one = b->has_one ? &b->one : nullptr;
     if ((e = T.run(st, K_SIGNS, [&] { return launch_batch_signs(st, A); })) != hipSuccess) return e;
     const size_t G = b->groups.size();
     if (!timed && G > 1) {
         if ((e = hipEventRecord(b->ev_signs, st)) != hipSuccess) return e;
         if ((e = hipStreamWaitEvent(b->astream, b->ev_signs, 0)) != hipSuccess) return e;
         for (size_t g = 1; g < G; ++g) {
-            if ((e = launch_batch_setup(b->astream, A, one, b->groups[g].blk0, b->groups[g].nblk)) != hipSuccess) return e;
+            if ((e = launch_batch_setup(b->astream, A, b->groups[g].blk0, b->groups[g].nblk)) != hipSuccess) return e;
             if ((e = hipEventRecord(b->ev_setup[g], b->astream)) != hipSuccess) return e;
         }
-        if ((e = launch_batch_setup(st, A, one, b->groups[0].blk0, b->groups[0].nblk)) != hipSuccess) return e;
+        if ((e = launch_batch_setup(st, A, b->groups[0].blk0, b->groups[0].nblk)) != hipSuccess) return e;
         for (size_t g = 0; g < G; ++g) {
             if (g > 0 && (e = hipStreamWaitEvent(st, b->ev_setup[g], 0)) != hipSuccess) return e;
-            if ((e = launch_batch_tile(st, A, one, b->groups[g].w0, b->groups[g].nw)) != hipSuccess) return e;
+            if ((e = launch_batch_tile(st, A, b->groups[g].w0, b->groups[g].nw)) != hipSuccess) return e;
         }
     } else {
         for (size_t g = 0; g < G; ++g) {
             const auto& gr = b->groups[g];
-            if ((e = T.run(st, K_SETUP, [&] { return launch_batch_setup(st, A, one, gr.blk0, gr.nblk); })) != hipSuccess)
+            if ((e = T.run(st, K_SETUP, [&] {
+                     return b->has_one ? launch_setup(st, b->one_setup) : launch_batch_setup(st, A, gr.blk0, gr.nblk);
+                 })) != hipSuccess)
                 return e;
-            if ((e = T.run(st, K_TILE, [&] { return launch_batch_tile(st, A, one, gr.w0, gr.nw); })) != hipSuccess)
+            if ((e = T.run(st, K_TILE, [&] {
+                     return b->has_one ? launch_tile(st, b->one_tile, A.tile, 0) : launch_batch_tile(st, A, gr.w0, gr.nw);
+                 })) != hipSuccess)
                 return e;
         }
     }

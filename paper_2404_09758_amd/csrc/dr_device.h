@@ -60,6 +60,8 @@ struct DView {
 
 struct DViews {
     DView v[DRD_MAX_VIEWS];
+    int n;
+    int tsum[DRD_MAX_VIEWS + 1];         // tiles of the views before v
 };
 
 // Perturbation of one launch: per-block eps and the sign bits of the pairs.
@@ -80,25 +82,30 @@ struct __align__(16) TriR {
     int pad;
 };
 
-// Shading half (48 B): 1/w in normalised order and the perturbed world
-// positions in the original corner order.
+// Shading half (16 B): 1/w in normalised order and, for Lambert shading, the
+// face's shade (ambient + diffuse n.l), which is the same for all its pixels.
 struct __align__(16) TriS {
     float iw[3];
-    float p[9];
+    float sh;
 };
 
-// Per-face shading frame: the unit face normal and (GGX) the tangent frame
-// of the face's UV map, formed per shaded pixel from the shading record
-// (measured as fast as storing it per triangle, and 64 B per triangle and
-// render less to write).
-struct TriF {
+// GGX shading: what a face's pixels share in every view of one perturbation
+// (64 B): the perturbed world positions in the original corner order, the
+// unit face normal and the unit tangent of the face's UV map.  Formed once
+// per triangle and perturbation by the setup instead of once per pixel (two
+// of a pixel's five normalisations), and kept once for all views, so the
+// setup writes less than with positions in every view's record (paper step:
+// 236 MB against 283 MB).
+struct __align__(16) TriG {
+    float p[9];
     float nf[3];
     float T[3];
-    float B[3];
+    float pad;
 };
 
 static_assert(sizeof(TriR) == 48, "TriR layout");
-static_assert(sizeof(TriS) == 48, "TriS layout");
+static_assert(sizeof(TriS) == 16, "TriS layout");
+static_assert(sizeof(TriG) == 64, "TriG layout");
 
 #define TRI_VALID 1u
 #define TRI_SWAPPED 16u
@@ -271,10 +278,15 @@ __device__ __forceinline__ T gload(const T* p) {
 // 64-bit word at a 4-byte aligned address (one load of two sign words)
 typedef unsigned long long __attribute__((aligned(4))) drd_u64_a4;
 
-template <int C>
+//
+// COMPACT: the texture has at most 2^24 texels, so a texel's byte offset is
+// one 24-bit product and fits in 32 bits; the loads then take the texture's
+// uniform base and a 32-bit offset instead of a 64-bit address per lane.
+template <int C, bool COMPACT>
 __device__ __forceinline__ void sample_texels(const DRD_GLOBAL float* th, const DRD_GLOBAL uint32_t* pb,
                                               long long base, int W, float e, float sgn, const Foot& f,
                                               float* out) {
+    typedef float __attribute__((ext_vector_type(C == 1 ? 2 : C), aligned(4))) texel_t;
     const DRD_GLOBAL float* tt = th + base;
     const bool pert = pb != nullptr && e != 0.0f;
     const DRD_GLOBAL uint32_t* pw = pb + (base >> 5);
@@ -292,24 +304,35 @@ __device__ __forceinline__ void sample_texels(const DRD_GLOBAL float* th, const 
     for (int row = 0; row < 2; ++row) {
         int yy = row ? f.yb : f.ya;
         float wy = row ? f.fy : 1.0f - f.fy;
-        // texel offsets within the texture: W, H <= 32768 and C <= 4 keep
-        // them below 2^32
+        // texel indices within the texture: W, H <= 32768 keep them below 2^30
         unsigned o[2];
         const unsigned ro = __umul24((unsigned)yy, (unsigned)W);      // W, H <= 32768: exact
         o[0] = (ro + (unsigned)f.xa) * C;
         o[1] = (ro + (unsigned)f.xb) * C;
         float x[2][C];
-        if (C == 1 && f.xb == f.xa + 1) {
-            // the row's two single-channel texels are adjacent: one 8 B read
-            typedef float __attribute__((ext_vector_type(2), aligned(4))) f2a4;
-            f2a4 v = *(const DRD_GLOBAL f2a4*)(tt + o[0]);
-            x[0][0] = v.x;
-            x[1][0] = v.y;
-        } else {
+        const bool adj = f.xb == f.xa + 1;
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+        for (int k = 0; k < 2; ++k) {
+            const DRD_GLOBAL float* a;
+            if constexpr (COMPACT) {
+                a = (const DRD_GLOBAL float*)((const DRD_GLOBAL char*)tt + (o[k] << 2));
+            } else {
+                a = tt + (unsigned long long)o[k];
+            }
+            if constexpr (C == 1) {
+                // the row's two single-channel texels are adjacent: one 8 B read
+                if (k == 0 && adj) {
+                    texel_t v = *(const DRD_GLOBAL texel_t*)a;
+                    x[0][0] = v.x;
+                    x[1][0] = v.y;
+                } else if (k == 0 || !adj) {
+                    x[k][0] = a[0];
+                }
+            } else {
+                texel_t v = *(const DRD_GLOBAL texel_t*)a;
 #pragma unroll
-                for (int c = 0; c < C; ++c) x[k][c] = tt[(unsigned long long)o[k] + c];
+                for (int c = 0; c < C; ++c) x[k][c] = v[c];
+            }
         }
         if (pert) {
             // parameter base + o has its sign at bit (base + o) mod 32 of
@@ -320,13 +343,13 @@ __device__ __forceinline__ void sample_texels(const DRD_GLOBAL float* th, const 
             // end, so the read past a pair's last word stays in bounds (its
             // bits belong to no parameter of the texel).
             unsigned r = (o[0] & 31u) + bb;
-            unsigned long long w = *(const DRD_GLOBAL drd_u64_a4*)(pw + (o[0] >> 5) + (r >> 5));
+            unsigned long long w = *(const DRD_GLOBAL drd_u64_a4*)(pw + ((o[0] >> 5) + (r >> 5)));
             unsigned win[2];
             win[0] = __builtin_amdgcn_alignbit((unsigned)(w >> 32), (unsigned)w, r & 31u);
             win[1] = win[0] >> C;
-            if (f.xb != f.xa + 1) {
+            if (!adj) {
                 unsigned rb = (o[1] & 31u) + bb;
-                unsigned long long wb = *(const DRD_GLOBAL drd_u64_a4*)(pw + (o[1] >> 5) + (rb >> 5));
+                unsigned long long wb = *(const DRD_GLOBAL drd_u64_a4*)(pw + ((o[1] >> 5) + (rb >> 5)));
                 win[1] = __builtin_amdgcn_alignbit((unsigned)(wb >> 32), (unsigned)wb, rb & 31u);
             }
 #pragma unroll
@@ -347,20 +370,14 @@ __device__ __forceinline__ void sample_texels(const DRD_GLOBAL float* th, const 
     for (int c = 0; c < C; ++c) out[c] = acc[c];
 }
 
-// Bilinear sample of texture t of the perturbed scene (theta + sgn s eps)
-// over a precomputed footprint.  out has room for 4 channels; channels at
-// and beyond the texture's count keep their values.
+// Bilinear sample of texture t (C channels) of the perturbed scene
+// (theta + sgn s eps) over a precomputed footprint.
+template <int C, bool COMPACT>
 __device__ __forceinline__ void sample_tex(const DScene& sc, const float* __restrict__ th,
                                            const uint32_t* __restrict__ pb, float e, float sgn, int t,
                                            const Foot& f, float* out) {
-    int W = sc.tex_w[t], C = sc.tex_c[t];
-    long long base = sc.tex_off[t];
-    const DRD_GLOBAL float* gth = (const DRD_GLOBAL float*)th;
-    const DRD_GLOBAL uint32_t* gpb = (const DRD_GLOBAL uint32_t*)pb;
-    if (C == 3) sample_texels<3>(gth, gpb, base, W, e, sgn, f, out);
-    else if (C == 1) sample_texels<1>(gth, gpb, base, W, e, sgn, f, out);
-    else if (C == 4) sample_texels<4>(gth, gpb, base, W, e, sgn, f, out);
-    else sample_texels<2>(gth, gpb, base, W, e, sgn, f, out);
+    sample_texels<C, COMPACT>((const DRD_GLOBAL float*)th, (const DRD_GLOBAL uint32_t*)pb, sc.tex_off[t], sc.tex_w[t],
+                              e, sgn, f, out);
 }
 
 // Correctly rounded square root and reciprocal for operands in a normal
@@ -427,10 +444,7 @@ __device__ __forceinline__ void cross3(const float* a, const float* b, float* o)
     o[2] = a[0] * b[1] - a[1] * b[0];
 }
 
-// Face frame of a triangle from its perturbed corners p (original order)
-// and corner UVs: the unit face normal and, for GGX, the tangent frame.
-// A triangle's corner UVs (original corner order), read once per shaded
-// pixel and render for both the face frame and the attributes.
+// A triangle's corner UVs (original corner order).
 struct CornerUV {
     float c[6];
 };
@@ -439,19 +453,22 @@ __device__ __forceinline__ CornerUV load_cuv(const DScene& sc, unsigned t) {
     return gload((const CornerUV*)(sc.cuv + 6 * (long long)t));
 }
 
-__device__ __forceinline__ void face_frame(int shading, const float* p, const CornerUV& cu, TriF& F) {
-    const float* cuv = cu.c;
-    float e1v[3], e2v[3], nf[3];
+// Unit face normal of a triangle with perturbed corners p (original order).
+__device__ __forceinline__ void face_normal(const float* p, float* nf) {
+    float e1v[3], e2v[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) { e1v[c] = p[3 + c] - p[c]; e2v[c] = p[6 + c] - p[c]; }
     cross3(e1v, e2v, nf);
     nrm3(nf);
+}
+
+// Unit tangent of the face's UV map (the bitangent is nf x T).
+__device__ __forceinline__ void face_tangent(const float* p, const float* cuv, const float* nf, float* T) {
+    float e1v[3], e2v[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) { F.nf[c] = nf[c]; F.T[c] = 0.0f; F.B[c] = 0.0f; }
-    if (shading != 2) return;
+    for (int c = 0; c < 3; ++c) { e1v[c] = p[3 + c] - p[c]; e2v[c] = p[6 + c] - p[c]; }
     float du1 = cuv[2] - cuv[0], dv1 = cuv[3] - cuv[1], du2 = cuv[4] - cuv[0], dv2 = cuv[5] - cuv[1];
     float rr = du1 * dv2 - du2 * dv1;
-    float T[3], B[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) T[c] = e1v[c] * dv2 - e2v[c] * dv1;
     if (rr < 0.0f) { T[0] = -T[0]; T[1] = -T[1]; T[2] = -T[2]; }
@@ -459,9 +476,6 @@ __device__ __forceinline__ void face_frame(int shading, const float* p, const Co
 #pragma unroll
     for (int c = 0; c < 3; ++c) T[c] = T[c] - nf[c] * nt;
     nrm3(T);
-    cross3(nf, T, B);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) { F.T[c] = T[c]; F.B[c] = B[c]; }
 }
 
 // Perspective-correct attributes of pixel (px,py) on triangle t: the
@@ -502,40 +516,47 @@ __device__ __forceinline__ Attr frag_attr(const DScene& sc, const TriR& r, const
 
 // Colour, opacity and UV of pixel (px,py) (subpixel sample coordinates)
 // covered by triangle t: perspective-correct attributes, then unlit /
-// Lambert / GGX.  foot0 receives the bilinear footprint of texel class 0 at
-// the pixel; opacity the albedo's fourth channel clamped to [0, 1] (1 for a
-// three-channel albedo).
+// Lambert / GGX.  opacity: the albedo's fourth channel clamped to [0, 1]
+// (DEEP only).
+//
+// SHADE is the scene's shading, fixed at compile time, for scenes whose
+// textures are compact (sample_texels); SHADE_ANY reads the shading from the
+// scene and takes textures of any size.  DEEP: the albedo has four channels.
+// G: the face's GGX record (read for GGX only).
+#define SHADE_ANY 3
+
+template <int SHADE, bool DEEP>
 __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, const float* __restrict__ th,
                                             const uint32_t* __restrict__ pb, const float* eps, float sgn,
-                                            const TriR& r, const TriS& s, const TriF& fr, const CornerUV& cu,
-                                            int px, int py,
-                                            float* rgb, float* uvo, Foot& foot0, float& opacity) {
+                                            const TriR& r, const TriS& s, const TriG* __restrict__ G,
+                                            const CornerUV& cu, int px, int py, float* rgb, float* uvo,
+                                            float& opacity) {
+    constexpr bool COMPACT = SHADE != SHADE_ANY;
+    const int shading = SHADE != SHADE_ANY ? SHADE : sc.shading;
     Attr a = frag_attr(sc, r, s, cu, px, py);
     float pc0 = a.pc0, pc1 = a.pc1, pc2 = a.pc2, iS = a.iS, u = a.u, v = a.v;
     bool sw = (r.flags & TRI_SWAPPED) != 0u;
-    int o1 = sw ? 2 : 1, o2 = sw ? 1 : 2;
     uvo[0] = u;
     uvo[1] = v;
     float alb[4] = {0.0f, 0.0f, 0.0f, 1.0f};
+    Foot foot0;
     if (sc.n_tex > 0) {
         foot0 = footprint(u, v, sc.cls_w[0], sc.cls_h[0]);
-        sample_tex(sc, th, pb, eps[1], sgn, 0, foot0, alb);
+        sample_tex<DEEP ? 4 : 3, COMPACT>(sc, th, pb, eps[1], sgn, 0, foot0, alb);
     }
-    float al = alb[3];
-    if (!(al > 0.0f)) al = 0.0f;
-    if (al > 1.0f) al = 1.0f;
-    opacity = al;
-    if (sc.shading == 0) {
+    if constexpr (DEEP) {
+        float al = alb[3];
+        if (!(al > 0.0f)) al = 0.0f;
+        if (al > 1.0f) al = 1.0f;
+        opacity = al;
+    }
+    if (shading == 0) {
         rgb[0] = alb[0]; rgb[1] = alb[1]; rgb[2] = alb[2];
         return;
     }
-    const float* nf = fr.nf;
-    if (sc.shading == 1) {
-        float ndl = dot3(nf, sc.light);
-        if (!(ndl > 0.0f)) ndl = 0.0f;
-        float sh = sc.ambient + sc.diffuse * ndl;
+    if (shading == 1) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) rgb[c] = alb[c] * (sh * sc.light_rgb[c]);
+        for (int c = 0; c < 3; ++c) rgb[c] = alb[c] * (s.sh * sc.light_rgb[c]);
         return;
     }
     // GGX with a tangent-space normal map in the face's UV frame
@@ -543,25 +564,27 @@ __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, c
     if (sc.n_tex > 1) {
         int c1 = sc.tex_cls[1];
         Foot f1 = (c1 == 0) ? foot0 : footprint(u, v, sc.cls_w[c1], sc.cls_h[c1]);
-        sample_tex(sc, th, pb, eps[2], sgn, 1, f1, nm);
+        sample_tex<3, COMPACT>(sc, th, pb, eps[2], sgn, 1, f1, nm);
     }
     float tn[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) tn[c] = 2.0f * nm[c] - 1.0f;
-    float n[3];
+    const TriG g = gload(G);
+    float n[3], B[3];
+    cross3(g.nf, g.T, B);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) n[c] = (fr.T[c] * tn[0] + fr.B[c] * tn[1]) + nf[c] * tn[2];
+    for (int c = 0; c < 3; ++c) n[c] = (g.T[c] * tn[0] + B[c] * tn[1]) + g.nf[c] * tn[2];
     nrm3(n);
     float rough4[4] = {0.5f, 0.0f, 0.0f, 0.0f};
     if (sc.n_tex > 2) {
         int c2 = sc.tex_cls[2];
         Foot f2 = (c2 == 0) ? foot0 : footprint(u, v, sc.cls_w[c2], sc.cls_h[c2]);
-        sample_tex(sc, th, pb, eps[3], sgn, 2, f2, rough4);
+        sample_tex<1, COMPACT>(sc, th, pb, eps[3], sgn, 2, f2, rough4);
     }
     float P[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        float q0 = s.p[c], q1 = s.p[3 * o1 + c], q2 = s.p[3 * o2 + c];
+        float q0 = g.p[c], q1 = sw ? g.p[6 + c] : g.p[3 + c], q2 = sw ? g.p[3 + c] : g.p[6 + c];
         P[c] = ((pc0 * q0 + pc1 * q1) + pc2 * q2) * iS;
     }
     float V[3] = {vw.cam[0] - P[0], vw.cam[1] - P[1], vw.cam[2] - P[2]};

@@ -19,6 +19,16 @@
 #define SPILL_CAP 8192
 
 // ------------------------------------------------------- single scene --
+//
+// Bin counters (and bins) of a launch: the whole of a call's items packed in
+// (pair, view) order, or max_tiles per slot for a part of them.
+__host__ __device__ inline long long bin_base(int whole, const DViews& views, int n_views, int nsign, int max_tiles,
+                                              int li, int s) {
+    if (!whole) return ((long long)li * nsign + s) * max_tiles;
+    const int pair = li / n_views, v = li - pair * n_views;
+    const int tiles = views.tsum[v + 1] - views.tsum[v];
+    return ((long long)pair * views.tsum[n_views] + views.tsum[v]) * nsign + (long long)s * tiles;
+}
 
 struct SetupArgs {
     DScene sc;
@@ -27,13 +37,17 @@ struct SetupArgs {
     const float* theta;
     int n_views;            // views per pair (item -> pair = item / n_views)
     int item0;              // first item of this launch
+    int n_items;            // items of this launch
+    int whole;              // the launch covers every (pair, view) of the call
+    int vpb;                // views that a block sets its triangles up in
     int nsign;              // 1 (render, loss) or 2 (+ and -)
     float sgn[2];
     int tile;               // tile size in pixels
     int cap;                // bin capacity
     int max_tiles;          // tile slots per (item, sign)
-    TriR* recR;
+    TriR* recR;             // [slots, n_tris]; slot = item of the launch * nsign + sign
     TriS* recS;
+    TriG* recG;             // GGX: [pairs of the launch * nsign, n_tris]
     unsigned* counts;
     unsigned* bins;
     unsigned* spn;                   // [slots, 2] spill counters, or null (no spill lists)
@@ -48,12 +62,16 @@ struct TileArgs {
     const float* theta;
     int n_views;
     int item0;
+    int n_items;
+    int whole;
+    int interleave;                  // grid of tile units in (view, tile, pair) order (launch_tile)
     int nsign;
     float sgn[2];
     int cap;
     int max_tiles;
     const TriR* recR;
     const TriS* recS;
+    const TriG* recG;
     unsigned* counts;
     const unsigned* bins;
     unsigned* spn;
@@ -143,6 +161,7 @@ struct BItem {
     int scene, pair, view;       // view: index in the batch view table
     int cap;                     // bin capacity
     long long rec_off;           // records of sign 0 (sign 1 at + n_tris)
+    long long g_off;             // GGX records of the item's pair, sign 0 (sign 1 at + n_tris)
     long long cnt_off;           // bin counters of sign 0 (sign 1 at + tiles)
     long long bin_off;           // bin entries of sign 0 (sign 1 at + tiles * cap)
     long long sp_off;            // spill list of sign 0 (sign 1 at + 1)
@@ -162,6 +181,7 @@ struct BatchArgs {
     long long sign_blocks, setup_blocks, group_blocks, total_tiles;
     TriR* recR;
     TriS* recS;
+    TriG* recG;
     unsigned* counts;
     unsigned* bins;
     unsigned* spn;               // [2 items, 2] spill counters
@@ -172,16 +192,26 @@ struct BatchArgs {
     const float* bc2;
     int n_bc;
     int tile;
+    int shade;                   // shading of every scene when all are alike and compact, else SHADE_ANY
     int q_zero;                  // every scene's Q is known to be zero (the fused step skips reading it)
     long long unit0;             // setup and tile launches: the first block / tile unit of the launch
 };
 
 hipError_t launch_signs(hipStream_t st, unsigned long long seed, unsigned step, unsigned pair0, unsigned scene,
                         long long d, int words, int n_pairs, uint32_t* bits);
-hipError_t launch_setup(hipStream_t st, const SetupArgs& a, int n_items);
+hipError_t launch_setup(hipStream_t st, SetupArgs a);
 hipError_t launch_subdiv(hipStream_t st, const DScene& sc, const DPert& pert, const float* theta, int n_pairs,
                          int nsign, float sgn0, float sgn1, float* fpos);
-hipError_t launch_tile(hipStream_t st, const TileArgs& a, int tile, int mode, int n_items, int max_tiles);
+// Shading that the kernels may be specialised for (SHADE_ANY otherwise).
+int scene_shade(const DScene& sc);
+// One tile size's kernels (a source file each); launch_tile picks by size.
+template <int TILE>
+hipError_t launch_batch_tile_t(hipStream_t st, const BatchArgs& b, unsigned grid);
+template <int TILE>
+hipError_t launch_tile_t(hipStream_t st, const TileArgs& a, int mode, dim3 grid);
+template <int TILE>
+hipError_t launch_tile_deep_t(hipStream_t st, const TileArgs& a, int mode, dim3 grid);
+hipError_t launch_tile(hipStream_t st, TileArgs a, int tile, int mode);
 hipError_t launch_sum_tiles(hipStream_t st, const double* partials, int max_tiles, const DViews& views,
                             int n_views, double* out);
 hipError_t launch_check_tri(hipStream_t st, const int* tri, long long n, int n_verts, unsigned long long* bad);
@@ -192,27 +222,9 @@ hipError_t launch_step(hipStream_t st, const StepArgs& a);
 
 hipError_t launch_batch_signs(hipStream_t st, const BatchArgs& b);
 // setup blocks [blk0, blk0 + nblk) of the batch's setup grid
-struct BatchOne;
-// setup blocks [blk0, blk0 + nblk); one: the batch's scene when it has one
-hipError_t launch_batch_setup(hipStream_t st, const BatchArgs& b, const BatchOne* one, long long blk0,
-                              long long nblk);
-// A one-scene batch's scene constants and views, passed to the tile launch
-// by value.
-struct BatchOne {
-    DScene sc;
-    DView views[DRD_MAX_VIEWS];
-    int n_views;
-    // Tile units in pair-interleaved order: the launch walks (view, tile,
-    // pair) while the units are numbered (pair, view, tile); tsum[v] is the
-    // number of tiles of views 0 .. v-1.  il_pairs = 1 keeps unit order.
-    int il_pairs;
-    long long tsum[DRD_MAX_VIEWS + 1];
-};
-
-// one: non-null for a one-scene batch (the batch's view table is then the
-// scene's views).
+hipError_t launch_batch_setup(hipStream_t st, const BatchArgs& b, long long blk0, long long nblk);
 // tile units [w0, w0 + n) of the batch
-hipError_t launch_batch_tile(hipStream_t st, const BatchArgs& b, const BatchOne* one, long long w0, long long n);
+hipError_t launch_batch_tile(hipStream_t st, const BatchArgs& b, long long w0, long long n);
 hipError_t launch_batch_fold(hipStream_t st, const BatchArgs& b);
 hipError_t launch_batch_step(hipStream_t st, const BatchArgs& b);
 // fold and step in one launch (at most 8 pairs)

@@ -1,0 +1,5 @@
+// dr_tile16.hip -- the opaque tile kernels of 16-pixel tiles.
+#include "dr_tile.h"
+
+template hipError_t launch_tile_t<16>(hipStream_t, const TileArgs&, int, dim3);
+template hipError_t launch_batch_tile_t<16>(hipStream_t, const BatchArgs&, unsigned);

@@ -1,0 +1,5 @@
+// dr_tile8.hip -- the opaque tile kernels of 8-pixel tiles.
+#include "dr_tile.h"
+
+template hipError_t launch_tile_t<8>(hipStream_t, const TileArgs&, int, dim3);
+template hipError_t launch_batch_tile_t<8>(hipStream_t, const BatchArgs&, unsigned);

@@ -1,0 +1,46 @@
+// dr_wave.h -- wave-wide and search helpers shared by the kernels.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+// Inclusive prefix sum over the 64 lanes of a wave with DPP moves: shifts
+// by 1, 2, 4 and 8 within each row of 16 lanes (lanes shifted in from
+// outside the row add 0), then row 0's total to row 1 and row 2's to row 3
+// (row_bcast:15), then row 1's running total to rows 2 and 3 (row_bcast:31).
+// Must be called by every lane of the wave.
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);     // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);     // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);     // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);     // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);     // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);     // row_bcast:31
+    return v;
+}
+
+// Largest value over the wave's 64 lanes, the same moves with max (lanes
+// shifted in from outside hold the least int); every lane must call it.
+__device__ __forceinline__ int wave_max(int v) {
+    const int lo = (int)0x80000000;
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x111, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x142, 0xa, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(lo, v, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Index of the last entry of a non-decreasing sequence (stride in bytes
+// between entries, starting at `first`) that is <= x; n >= 1 entries.
+__device__ __forceinline__ int last_le(const char* first, int stride, int n, long long x) {
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        int mid = (lo + hi + 1) >> 1;
+        long long v = *(const long long*)(first + (long long)mid * stride);
+        if (v <= x) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
