@@ -109,7 +109,7 @@ static_assert(sizeof(TriG) == 64, "TriG layout");
 
 #define TRI_VALID 1u
 #define TRI_SWAPPED 16u
-#define TRI_SMALL 32u          // bbox spans < 2^15 subpixels: 32-bit edge functions are exact
+#define TRI_SMALL 32u          // bbox spans < 32000 subpixels: 32-bit edge functions are exact
 
 // ---------------------------------------------------------------- signs --
 
@@ -184,18 +184,6 @@ __device__ __forceinline__ bool inside(const TriR& r, int px, int py, long long&
     e0 = edge_at(r.X[1], r.Y[1], r.X[2], r.Y[2], px, py);
     e1 = edge_at(r.X[2], r.Y[2], r.X[0], r.Y[0], px, py);
     e2 = edge_at(r.X[0], r.Y[0], r.X[1], r.Y[1], px, py);
-    bool ok0 = (e0 > 0) || (e0 == 0 && (r.flags & 2u));
-    bool ok1 = (e1 > 0) || (e1 == 0 && (r.flags & 4u));
-    bool ok2 = (e2 > 0) || (e2 == 0 && (r.flags & 8u));
-    return ok0 && ok1 && ok2;
-}
-
-// The same coverage test for triangles flagged TRI_SMALL: every product is
-// below 2^30 in magnitude, so 24-bit multiplies give the exact values.
-__device__ __forceinline__ bool inside_small(const TriR& r, int px, int py) {
-    int e0 = __mul24(r.X[2] - r.X[1], py - r.Y[1]) - __mul24(r.Y[2] - r.Y[1], px - r.X[1]);
-    int e1 = __mul24(r.X[0] - r.X[2], py - r.Y[2]) - __mul24(r.Y[0] - r.Y[2], px - r.X[2]);
-    int e2 = __mul24(r.X[1] - r.X[0], py - r.Y[0]) - __mul24(r.Y[1] - r.Y[0], px - r.X[0]);
     bool ok0 = (e0 > 0) || (e0 == 0 && (r.flags & 2u));
     bool ok1 = (e1 > 0) || (e1 == 0 && (r.flags & 4u));
     bool ok2 = (e2 > 0) || (e2 == 0 && (r.flags & 8u));

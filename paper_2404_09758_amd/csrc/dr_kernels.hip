@@ -155,7 +155,7 @@ __device__ __forceinline__ TileRect setup_tri_at(const DView& vw, const float* p
     r.ia = 1.0f / fa;
     int xmin = min(r.X[0], min(r.X[1], r.X[2])), xmax = max(r.X[0], max(r.X[1], r.X[2]));
     int ymin = min(r.Y[0], min(r.Y[1], r.Y[2])), ymax = max(r.Y[0], max(r.Y[1], r.Y[2]));
-    if (xmax - xmin < 32768 && ymax - ymin < 32768) r.flags |= TRI_SMALL;
+    if (xmax - xmin < 32000 && ymax - ymin < 32000) r.flags |= TRI_SMALL;
     // pixels whose centre 256 x + 128 lies in [min, max]
     int bx0 = max((xmin + 127) >> 8, 0), bx1 = min((xmax - 128) >> 8, vw.W - 1);
     int by0 = max((ymin + 127) >> 8, 0), by1 = min((ymax - 128) >> 8, vw.H - 1);

@@ -40,31 +40,21 @@ __device__ __forceinline__ void insert_key(unsigned long long* key, int li, unsi
     }
 }
 
-// Coverage, depth and the depth|id resolve of triangle t at pixel (x, y) of
-// the tile.
+// Keys per row of a tile: three more than its pixels for opaque tiles, since
+// a raster slot that starts at the row's last pixel runs past it.
 template <int TILE, bool DEEP>
-__device__ __forceinline__ void raster_px(const TriR& r, unsigned t, int x, int y, int px0, int py0,
-                                          unsigned long long* key, int L) {
-    int px = 256 * x + 128, py = 256 * y + 128;
-    bool cov;
-    if (r.flags & TRI_SMALL) {
-        cov = inside_small(r, px, py);
-    } else {
-        long long e0, e1, e2;
-        cov = inside(r, px, py, e0, e1, e2);
-    }
-    if (!cov) return;
-    float z = depth_at(r, px, py);
-    insert_key<DEEP>(key, (y - py0) * TILE + (x - px0), ((unsigned long long)__float_as_uint(z) << 32) | t, L);
-}
+struct KeyRow {
+    static constexpr int N = DEEP ? TILE : TILE + 4;
+};
 
-// (cx1, cy1): the tile's last pixel inside the view.
+// Rasterise triangle t over its box in the tile, one lane per covered pixel:
+// triangles too large for the staged raster.  (cx1, cy1): the tile's last
+// pixel inside the view.
 template <int TILE, bool DEEP>
 __device__ __forceinline__ void raster_tri(const TriR& r, unsigned t, int px0, int py0, int cx1, int cy1,
                                            int lane, unsigned long long* key, int L) {
     int x0, x1, y0, y1;
     tri_box(r, px0, py0, cx1, cy1, x0, x1, y0, y1);
-    if (x0 > x1 || y0 > y1) return;
     int bw = x1 - x0 + 1;
     int n = bw * (y1 - y0 + 1);
     unsigned m = ((1u << 20) + (unsigned)bw - 1u) / (unsigned)bw;     // exact for bw <= 32, idx < 1024
@@ -72,28 +62,29 @@ __device__ __forceinline__ void raster_tri(const TriR& r, unsigned t, int px0, i
         int idx = base + lane;
         if (idx < n) {
             int dy = (int)(((unsigned)idx * m) >> 20);
-            int dx = idx - dy * bw;
-            raster_px<TILE, DEEP>(r, t, x0 + dx, y0 + dy, px0, py0, key, L);
+            int x = x0 + idx - dy * bw, y = y0 + dy;
+            int px = 256 * x + 128, py = 256 * y + 128;
+            long long e0, e1, e2;
+            if (!inside(r, px, py, e0, e1, e2)) continue;
+            float z = depth_at(r, px, py);
+            insert_key<DEEP>(key, (y - py0) * KeyRow<TILE, DEEP>::N + (x - px0),
+                             ((unsigned long long)__float_as_uint(z) << 32) | t, L);
         }
     }
 }
 
 // Per-wave LDS staging of a batch of small triangles for the packed raster
-// (80 B each): edge k as an integer plane over the triangle's clipped
-// bounding box, e_k(dx, dy) = a_k dx + b_k dy + c_k at pixel (x0 + dx,
-// y0 + dy), the depth plane's offsets and the key index of the box corner.
+// (48 B each, three 16-byte reads): edge k over the triangle's clipped
+// bounding box is e_k(dx, dy) = 256 dX_k dy - 256 dY_k dx + c_k at pixel
+// (x0 + dx, y0 + dy).  16-bit fields hold differences of snapped corners,
+// which a TRI_SMALL triangle keeps within +-2^15.
 struct __align__(16) PTri {
-    int b[3];            // 256 dX_k: change of edge k per pixel row
-    int a[3];            // -256 dY_k: change of edge k per pixel column
-    int c[3];            // edge k at the corner pixel, plus 1 on a top-left edge
-    int dz[2];           // corner pixel centre minus vertex 0, in subpixels
-    float z0, zx, zy;
+    int c[3];            // edge k at the box's corner pixel, plus 1 on a top-left edge
     unsigned t;
-    int off0;            // key index of the corner pixel
-    int bw;              // box width
-    unsigned m;          // ceil(2^20 / slots per row), slots of two pixels
-    int pex;             // the triangle's first slot in the packed sequence
-    int pad;
+    int d[3];            // dX_k (low half), dY_k (high half)
+    unsigned pk;         // bits 0..4 box width - 1, 5..15 key index of the corner pixel, 16.. first slot
+    float z0, zx, zy;    // depth plane
+    int dz;              // corner pixel centre minus vertex 0, in subpixels: x low, y high
 };
 
 struct RasterStage {
@@ -112,31 +103,44 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-static_assert(sizeof(PTri) == 80, "PTri layout");
+static_assert(sizeof(PTri) == 48, "PTri layout");
 
-// Packed raster of a batch whose triangles are all TRI_SMALL, through the
-// wave's LDS stage.  Each triangle's clipped box is cut into slots of
-// RASTER_SLOT horizontally adjacent pixels (a row of w pixels gives
-// ceil(w / RASTER_SLOT) slots), the batch's slots are laid end to end, and
-// each pass gives one slot to every lane: one read of the staged record, one
-// index computation and one pass marking then serve all the slot's pixels.  The non-empty triangles are stored
-// by rank; each pass marks the slots where a triangle begins, and a lane's
-// triangle is then the number of triangles begun up to its slot (a ballot
-// and a lane-masked bit count) -- one LDS read of the staged record instead
-// of a binary search and a shuffle per field.  Edge values are exact: for a
-// TRI_SMALL triangle both products of an edge function are below 2^30 in
-// magnitude at every pixel of the box, so the edge value (and its value
-// plus 1) fits in 32 bits and the wrapped 32-bit sums a dx + b dy + c equal
-// it, as do the slot's further pixels' values, each its left neighbour's
-// plus a; e > 0 || (e == 0 && top-left) is e + [top-left] > 0.
-// Slots of 4 pixels: measured on the paper-scale step against 2, 3, 6 and 8
-// (2 -> 4: tile kernel -2 % at the start of an optimisation run, -9 % after
-// 50 Adam steps, when the triangles have grown; 6 and 8 within 2 % of 4).
+// Packed raster of a batch of TRI_SMALL triangles (one per lane; bh = 0:
+// none), through the wave's LDS stage.  Each triangle's clipped box is cut
+// into slots of RASTER_SLOT horizontally adjacent pixels (a row of w pixels
+// gives ceil(w / RASTER_SLOT) slots), the batch's slots are laid end to end,
+// and each pass gives one slot to every lane: one read of the staged record,
+// one index computation and one pass marking then serve all the slot's
+// pixels.  The non-empty triangles are stored by rank; each pass marks the
+// slots where a triangle begins, and a lane's triangle is then the number of
+// triangles begun up to its slot (a ballot and a lane-masked bit count) --
+// one LDS read of the staged record instead of a binary search and a shuffle
+// per field.  Edge values are exact: a TRI_SMALL triangle spans less than
+// 32000 subpixels, so at every pixel of the box and up to three to its right
+// both products of an edge function stay below 2^30 + 2^25 in magnitude and
+// the edge value (plus 1) fits in 32 bits; the wrapped 32-bit sums equal it,
+// as do the slot's further pixels' values, each its left neighbour's minus
+// 256 dY.  e > 0 || (e == 0 && top-left) is e + [top-left] > 0.  A slot's
+// pixels beyond the box are not covered, unless the box was clipped at the
+// tile's or the view's edge: those keys fall on the row's spare columns, or
+// on pixels that are not in the view and are not read (opaque; deep tiles
+// test the box).
+// Bound by vector issue.  The record's 48 B (80 B before) set the block's LDS
+// (25.6 -> 18.5 KB for 16-pixel tiles, 6 -> 8 waves per SIMD) and a pass's LDS
+// reads; with the raster compiled in once for bins, spill lists and scans
+// (52 -> 34 KB of code) the GGX paper step went 1739 -> 1578 us, the
+// full-image soup 1325 -> 1160 us.  Slots of 4 pixels: measured on the paper-scale step
+// against 2, 3, 6 and 8 (2 -> 4: tile kernel -2 % at the start of an
+// optimisation run, -9 % after 50 Adam steps, when the triangles have grown;
+// 6 and 8 within 2 % of 4).
 #define RASTER_SLOT 4
+#define PK_SLOT 16               // first bit of PTri::pk's first slot
 template <int TILE, bool DEEP>
 __device__ __forceinline__ void raster_staged(RasterStage* st, const TriR& r, unsigned t, int x0, int y0, int bw,
                                               int bh, int px0, int py0, int lane, unsigned long long* key, int L) {
     constexpr int SL = RASTER_SLOT;                     // pixels per slot
+    constexpr int KS = KeyRow<TILE, DEEP>::N;
+    static_assert(TILE * KS <= 2048 && 64 * TILE * (TILE / SL) <= 65536 && SL == 4, "PTri::pk fields");
     const int sw = (bw + SL - 1) / SL;                  // slots per row
     const int c = sw * bh;                              // slots of this lane's triangle (0: none)
     const int P = wave_inclusive_sum(c);
@@ -151,19 +155,13 @@ __device__ __forceinline__ void raster_staged(RasterStage* st, const TriR& r, un
         for (int k = 0; k < 3; ++k) {
             int ia = (k + 1) % 3, ib = (k + 2) % 3;
             int dX = r.X[ib] - r.X[ia], dY = r.Y[ib] - r.Y[ia];
-            q.b[k] = 256 * dX;
-            q.a[k] = -256 * dY;
+            q.d[k] = (dX & 0xFFFF) | (dY << 16);
             q.c[k] = (__mul24(dX, cy - r.Y[ia]) - __mul24(dY, cx - r.X[ia])) + (int)((r.flags >> (k + 1)) & 1u);
         }
-        q.dz[0] = cx - r.X[0];
-        q.dz[1] = cy - r.Y[0];
+        q.dz = ((cx - r.X[0]) & 0xFFFF) | ((cy - r.Y[0]) << 16);
         q.z0 = r.z0; q.zx = r.zx; q.zy = r.zy;
         q.t = t;
-        q.off0 = (y0 - py0) * TILE + (x0 - px0);
-        q.bw = bw;
-        q.m = ((1u << 20) + (unsigned)sw - 1u) / (unsigned)sw;     // exact for sw <= 32, idx < 1024
-        q.pex = pex;
-        q.pad = 0;
+        q.pk = (unsigned)(bw - 1) | ((unsigned)((y0 - py0) * KS + (x0 - px0)) << 5) | ((unsigned)pex << PK_SLOT);
         st->tri[rank] = q;
     }
     wave_sync();
@@ -180,110 +178,78 @@ __device__ __forceinline__ void raster_staged(RasterStage* st, const TriR& r, un
         base += __popcll(M);
         int sl = s0 + lane;
         if (sl < N) {
-            PTri q = st->tri[rr];
-            int idx = sl - q.pex;
-            int dy = (int)(((unsigned)idx * q.m) >> 20);
-            int qsw = (q.bw + SL - 1) / SL;
-            int dx = SL * (idx - dy * qsw);
-            int e0 = (__mul24(q.a[0], dx) + __mul24(q.b[0], dy)) + q.c[0];
-            int e1 = (__mul24(q.a[1], dx) + __mul24(q.b[1], dy)) + q.c[1];
-            int e2 = (__mul24(q.a[2], dx) + __mul24(q.b[2], dy)) + q.c[2];
-            const float zrow = (float)(256 * dy + q.dz[1]);
+            const PTri q = st->tri[rr];
+            const int idx = sl - (int)(q.pk >> PK_SLOT);
+            const unsigned w4 = q.pk & 0x1Cu;           // 4 (slots per row - 1)
+            int dy;                                     // idx / slots per row
+            if constexpr (TILE <= 16) {
+                // idx < 64, at most 4 slots: idx * ceil(128 / slots) >> 7
+                dy = (int)(__umul24((unsigned)idx, (0x202B4080u >> (2u * w4)) & 0xFFu) >> 7);
+            } else {
+                dy = (int)(((float)idx + 0.5f) * __builtin_amdgcn_rcpf((float)((w4 >> 2) + 1u)));
+            }
+            const int dx = 4 * idx - __mul24(dy, (int)w4 + 4);
+            int e[3], a[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const int dX = (int)(short)q.d[k], dY = q.d[k] >> 16;
+                a[k] = 256 * dY;
+                e[k] = (__mul24(dX, 256 * dy) + q.c[k]) - __mul24(dY, 256 * dx);
+            }
+            float xf = (float)(256 * dx + (int)(short)q.dz);
+            const float zrow = q.zy * (float)(256 * dy + (q.dz >> 16));
+            unsigned long long* kp = key;
+            const int off = (int)((q.pk >> 5) & ((1u << (PK_SLOT - 5)) - 1u)) + dy * KS + dx;
 #pragma unroll
             for (int k = 0; k < SL; ++k) {
-                if ((k == 0 || dx + k < q.bw) && min(e0, min(e1, e2)) > 0) {
-                    float z = (q.z0 + q.zx * (float)(256 * (dx + k) + q.dz[0])) + q.zy * zrow;
-                    if (!(z > 0.0f)) z = 0.0f;
-                    insert_key<DEEP>(key, q.off0 + dy * TILE + dx + k,
-                                     ((unsigned long long)__float_as_uint(z) << 32) | q.t, L);
+                const bool in = !DEEP || k == 0 || dx + k <= (int)(q.pk & 31u);
+                if (in && min(e[0], min(e[1], e[2])) > 0) {
+                    float z = (q.z0 + q.zx * xf) + zrow;
+                    z = fmaxf(z, 0.0f);                 // 0 for negative values and NaN
+                    insert_key<DEEP>(kp, off + k, ((unsigned long long)__float_as_uint(z) << 32) | q.t, L);
                 }
-                e0 += q.a[0];
-                e1 += q.a[1];
-                e2 += q.a[2];
+                e[0] -= a[0];
+                e[1] -= a[1];
+                e[2] -= a[2];
+                xf += 256.0f;                           // (exact)
             }
         }
         wave_sync();
     }
 }
 
-// Raster of up to 64 triangles held one per lane (mine: the triangle
-// index, valid for lanes below n).  A batch of TRI_SMALL triangles goes
-// through the wave's LDS stage (raster_staged) whenever there is one.
-// Otherwise, lane-packed when that takes fewer passes: the triangles' clipped bounding boxes are laid end to end (a
-// prefix sum of their pixel counts) and each pass gives one pixel of that
-// sequence to every lane, which finds its triangle by binary search over
-// the prefix sums and reads the triangle's data from its lane.  For small
-// triangles this replaces one pass per triangle, mostly idle lanes, with a
-// pass per 64 candidates; large triangles keep a pass per 64 pixels of each.
-// A packed pass costs more, so packing is taken when it saves a quarter of
-// the passes (measured against always and never packing on the mesh, the
-// 64-scene batch and the triangle soups).
+// Raster of up to 64 triangles held one per lane (mine: the triangle index,
+// valid for lanes below n): the small ones through the wave's stage, then
+// the large ones one at a time, their records read from the lanes that hold
+// them.
 template <int TILE, bool DEEP>
 __device__ __forceinline__ void raster_batch(const TriR* __restrict__ R, unsigned mine, unsigned n, int px0,
                                              int py0, int cx1, int cy1, int lane, unsigned long long* key, int L,
                                              RasterStage* stage) {
     TriR r{};
-    int x0 = 0, y0 = 0, bw = 1, bh = 0, c = 0;
+    int x0 = 0, y0 = 0, bw = 1, bh = 0;
+    bool large = false;
     if ((unsigned)lane < n) {
         r = gload(&R[mine]);
         int x1, y1;
         tri_box(r, px0, py0, cx1, cy1, x0, x1, y0, y1);
         if (x0 <= x1 && y0 <= y1) {
+            large = !(r.flags & TRI_SMALL);
             bw = x1 - x0 + 1;
-            bh = y1 - y0 + 1;
-            c = bw * bh;
+            bh = large ? 0 : y1 - y0 + 1;
         }
     }
-    // Packed, never more passes than one triangle at a time: the staged
-    // form is taken whenever it applies.
-    if (stage != nullptr && __ballot(c > 0 && !(r.flags & TRI_SMALL)) == 0ull) {
-        raster_staged<TILE, DEEP>(stage, r, mine, x0, y0, bw, bh, px0, py0, lane, key, L);
-        return;
-    }
-    int P = wave_inclusive_sum(c);                      // prefix sums of the pixel counts
-    int N = __builtin_amdgcn_readlane(P, 63);
-    int T = wave_inclusive_sum((c + 63) >> 6);          // passes of the per-triangle loop
-    int passes_tri = __builtin_amdgcn_readlane(T, 63);
-    int passes_packed = (N + 63) >> 6;
-    if (4 * passes_packed >= 3 * passes_tri) {
-        // one triangle at a time, its record read from the lane that holds it
+    raster_staged<TILE, DEEP>(stage, r, mine, x0, y0, bw, bh, px0, py0, lane, key, L);
+    unsigned long long big = __ballot(large);
+    while (big) {
+        const int j = __ffsll((long long)big) - 1;
+        big &= big - 1ull;
         const int* mw = reinterpret_cast<const int*>(&r);
-        for (unsigned j = 0; j < n; ++j) {
-            TriR q;
-            int* qw = reinterpret_cast<int*>(&q);
-#pragma unroll
-            for (int k = 0; k < (int)(sizeof(TriR) / 4); ++k) qw[k] = __builtin_amdgcn_readlane(mw[k], j);
-            raster_tri<TILE, DEEP>(q, __builtin_amdgcn_readlane(mine, j), px0, py0, cx1, cy1, lane, key, L);
-        }
-        return;
-    }
-    int Pex = P - c;
-    unsigned m = ((1u << 20) + (unsigned)bw - 1u) / (unsigned)bw;
-    for (int s0 = 0; s0 < N; s0 += 64) {
-        int sl = s0 + lane;
-        int lo = 0, hi = 63;                            // first lane whose prefix exceeds sl
-#pragma unroll
-        for (int step = 0; step < 6; ++step) {
-            int mid = (lo + hi) >> 1;
-            int pm = __shfl(P, mid);
-            if (pm > sl) hi = mid;
-            else lo = mid + 1;
-        }
-        int j = lo;
         TriR q;
-        q.X[0] = __shfl(r.X[0], j); q.X[1] = __shfl(r.X[1], j); q.X[2] = __shfl(r.X[2], j);
-        q.Y[0] = __shfl(r.Y[0], j); q.Y[1] = __shfl(r.Y[1], j); q.Y[2] = __shfl(r.Y[2], j);
-        q.z0 = __shfl(r.z0, j); q.zx = __shfl(r.zx, j); q.zy = __shfl(r.zy, j);
-        q.flags = (unsigned)__shfl((int)r.flags, j);
-        int qx0 = __shfl(x0, j), qy0 = __shfl(y0, j), qbw = __shfl(bw, j), qpex = __shfl(Pex, j);
-        unsigned qm = (unsigned)__shfl((int)m, j);
-        unsigned qt = (unsigned)__shfl((int)mine, j);
-        if (sl < N) {
-            int idx = sl - qpex;
-            int dy = (int)(((unsigned)idx * qm) >> 20);
-            int dx = idx - dy * qbw;
-            raster_px<TILE, DEEP>(q, qt, qx0 + dx, qy0 + dy, px0, py0, key, L);
-        }
+        int* qw = reinterpret_cast<int*>(&q);
+#pragma unroll
+        for (int k = 0; k < (int)(sizeof(TriR) / 4); ++k) qw[k] = __builtin_amdgcn_readlane(mw[k], j);
+        raster_tri<TILE, DEEP>(q, __builtin_amdgcn_readlane(mine, j), px0, py0, cx1, cy1, lane, key, L);
     }
 }
 
@@ -302,114 +268,15 @@ __device__ __forceinline__ void note_bin(unsigned long long* stats, unsigned c, 
     note_max_bin(stats, c);
 }
 
-// A wave's batch of bin entries holding at least this many triangles goes
-// through raster_batch (lane-packed when that saves passes); smaller batches
-// take one triangle per pass.
-#ifndef PACK_MIN_TRIS
-#define PACK_MIN_TRIS 8u
-#endif
-
-// Rasterise the cnt triangles of a tile's bin.  Wave w takes entries
-// w, w + nw, w + 2 nw, ...; it fetches 64 of them at once (one per lane),
-// so only the record load remains per triangle.
-// One wave's batch of n <= 64 triangles, triangle `mine` held by lane < n.
-template <int TILE, bool DEEP>
-__device__ __forceinline__ void raster_group(const TriR* __restrict__ R, unsigned mine, unsigned n, int px0,
-                                             int py0, int cx1, int cy1, int lane, unsigned long long* key, int L,
-                                             RasterStage* stage) {
-    if (n >= PACK_MIN_TRIS) {
-        raster_batch<TILE, DEEP>(R, mine, n, px0, py0, cx1, cy1, lane, key, L, stage);
-        return;
-    }
-    for (unsigned j = 0; j < n; ++j) {
-        unsigned t = __builtin_amdgcn_readlane(mine, j);
-        TriR r = gload(&R[t]);
-        raster_tri<TILE, DEEP>(r, t, px0, py0, cx1, cy1, lane, key, L);
-    }
-}
-
-template <int TILE, bool DEEP>
-__device__ __forceinline__ void raster_bin(const unsigned* __restrict__ list, unsigned cnt,
-                                           const TriR* __restrict__ R, int wave, int nw, int lane, int px0,
-                                           int py0, int cx1, int cy1, unsigned long long* key, int L,
-                                           RasterStage* stage) {
-    for (unsigned base = (unsigned)wave; base < cnt; base += 64u * (unsigned)nw) {
-        unsigned k = base + (unsigned)lane * (unsigned)nw;
-        unsigned mine = k < cnt ? gload(&list[k]) : 0u;
-        unsigned n = (cnt - base + (unsigned)nw - 1u) / (unsigned)nw;
-        if (n > 64u) n = 64u;
-        raster_group<TILE, DEEP>(R, mine, n, px0, py0, cx1, cy1, lane, key, L, stage);
-    }
-}
-
-// A tile whose bin overflowed while its render's spill list was full (or
-// absent): every valid triangle of the render whose pixel box meets the
-// tile, found 64 at a time (one record's flags and box
-// per lane), packed to the low lanes and rasterised as one batch.  The cost
-// is one coalesced pass over the render's records per overflowing tile,
-// not one dependent record read per triangle.
-template <int TILE, bool DEEP>
-__device__ __forceinline__ void raster_scan(const TriR* __restrict__ R, int n_tris, int wave, int nw, int lane,
-                                            int px0, int py0, int cx1, int cy1, unsigned long long* key, int L,
-                                            RasterStage* stage) {
-    for (int t0 = wave * 64; t0 < n_tris; t0 += 64 * nw) {
-        int t = t0 + lane;
-        bool hit = false;
-        if (t < n_tris) {
-            const TriR* q = &R[t];
-            TriR b;                                          // corners and flags (the first 28 B)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                b.X[k] = gload(&q->X[k]);
-                b.Y[k] = gload(&q->Y[k]);
-            }
-            unsigned fl = gload(&q->flags);
-            int x0 = 1, x1 = 0, y0 = 1, y1 = 0;
-            if (fl & TRI_VALID) tri_box(b, px0, py0, cx1, cy1, x0, x1, y0, y1);
-            hit = x0 <= x1 && y0 <= y1;
-        }
-        unsigned long long m = __ballot(hit);
-        if (m == 0ull) continue;
-        int n = __popcll(m);
-        int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-        // a permutation of the lanes: the hits to the front, in lane order
-        int dst = hit ? below : n + (lane - below);
-        unsigned mine = (unsigned)__builtin_amdgcn_ds_permute(dst * 4, t);
-        raster_group<TILE, DEEP>(R, mine, (unsigned)n, px0, py0, cx1, cy1, lane, key, L, stage);
-    }
-}
-
-// The spill entries of an overflowing bin: the render's spill list read 64
-// entries at a time, the triangles that name this tile packed to the low
-// lanes and rasterised as one batch.
-template <int TILE, bool DEEP>
-__device__ __forceinline__ void raster_spill(const TriR* __restrict__ R, const unsigned long long* __restrict__ spill,
-                                             unsigned ns, int tile, int wave, int nw, int lane, int px0, int py0,
-                                             int cx1, int cy1, unsigned long long* key, int L, RasterStage* stage) {
-    for (unsigned j0 = (unsigned)wave * 64u; j0 < ns; j0 += 64u * (unsigned)nw) {
-        const unsigned j = j0 + (unsigned)lane;
-        bool hit = false;
-        unsigned t = 0u;
-        if (j < ns) {
-            const unsigned long long e = gload(&spill[j]);
-            hit = (unsigned)(e >> 32) == (unsigned)tile;
-            t = (unsigned)e;
-        }
-        unsigned long long m = __ballot(hit);
-        if (m == 0ull) continue;
-        int n = __popcll(m);
-        int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-        int dst = hit ? below : n + (lane - below);
-        unsigned mine = (unsigned)__builtin_amdgcn_ds_permute(dst * 4, (int)t);
-        raster_group<TILE, DEEP>(R, mine, (unsigned)n, px0, py0, cx1, cy1, lane, key, L, stage);
-    }
-}
-
-// Every triangle of one render that may cover the tile: its bin of cnt
-// entries; for a bin past its capacity the full bin and the tile's entries
-// of the render's spill list, or, when that list ran out of room (or there
-// is none), every triangle of the render.  `note`: this wave counts a
-// full scan in the statistics.
+// Every triangle of one render that may cover the tile, in batches of up to
+// 64 per wave (wave `wave` of nw): the tile's bin of cnt entries; for a bin
+// past its capacity the full bin and then the tile's entries of the render's
+// spill list, or, when that list ran out of room, every valid triangle of the
+// render whose pixel box meets the tile.  The spill list and the render are
+// read 64 entries at a time, the hits packed to the low lanes, so the cost is
+// a coalesced pass, not one dependent read per entry.  One loop serves the
+// three sources, so the raster is compiled in once.  `note`: this wave counts
+// a full scan in the statistics.
 template <int TILE, bool DEEP>
 __device__ __forceinline__ void raster_render(const TriR* __restrict__ R, const unsigned* __restrict__ bin,
                                               unsigned cnt, unsigned cap, const unsigned* spn,
@@ -417,17 +284,66 @@ __device__ __forceinline__ void raster_render(const TriR* __restrict__ R, const 
                                               int wave, int nw, int lane, int px0, int py0, int cx1, int cy1,
                                               unsigned long long* key, int L, RasterStage* stage,
                                               unsigned long long* stats, bool note) {
-    if (cnt <= cap) {
-        raster_bin<TILE, DEEP>(bin, cnt, R, wave, nw, lane, px0, py0, cx1, cy1, key, L, stage);
-        return;
+    enum { BIN, SPILL, SCAN };
+    int src = BIN, next = BIN;
+    unsigned limit = cnt, ns = 0u;
+    if (cnt > cap) {
+        limit = cap;
+        ns = gload(&spn[0]);
+        next = SPILL;
+        if (ns > SPILL_CAP) {
+            src = next = SCAN;
+            limit = (unsigned)n_tris;
+            if (note && lane == 0) atomicAdd(&stats[ST_FULL_SCANS], 1ull);
+        }
     }
-    const unsigned ns = spn ? gload(&spn[0]) : 0xFFFFFFFFu;
-    if (ns <= SPILL_CAP) {
-        raster_bin<TILE, DEEP>(bin, cap, R, wave, nw, lane, px0, py0, cx1, cy1, key, L, stage);
-        raster_spill<TILE, DEEP>(R, spill, ns, tile, wave, nw, lane, px0, py0, cx1, cy1, key, L, stage);
-    } else {
-        if (note && lane == 0) atomicAdd(&stats[ST_FULL_SCANS], 1ull);
-        raster_scan<TILE, DEEP>(R, n_tris, wave, nw, lane, px0, py0, cx1, cy1, key, L, stage);
+    unsigned base = src == BIN ? (unsigned)wave : 64u * (unsigned)wave;
+    for (;; base += 64u * (unsigned)nw) {
+        if (base >= limit) {
+            if (src == next) break;
+            src = next;                                  // the bin is done: the spill list
+            limit = ns;
+            base = 64u * (unsigned)wave;
+            if (base >= limit) break;
+        }
+        unsigned mine = 0u, n;
+        if (src == BIN) {
+            // entries wave, wave + nw, wave + 2 nw, ...
+            const unsigned k = base + (unsigned)lane * (unsigned)nw;
+            if (k < limit) mine = gload(&bin[k]);
+            n = min((limit - base + (unsigned)nw - 1u) / (unsigned)nw, 64u);
+        } else {
+            const unsigned j = base + (unsigned)lane;
+            bool hit = false;
+            unsigned t = j;
+            if (j < limit) {
+                if (src == SPILL) {
+                    const unsigned long long e = gload(&spill[j]);
+                    hit = (unsigned)(e >> 32) == (unsigned)tile;
+                    t = (unsigned)e;
+                } else {
+                    const TriR* q = &R[j];
+                    TriR b;                              // corners and flags (the first 28 B)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        b.X[k] = gload(&q->X[k]);
+                        b.Y[k] = gload(&q->Y[k]);
+                    }
+                    int x0 = 1, x1 = 0, y0 = 1, y1 = 0;
+                    if (gload(&q->flags) & TRI_VALID) tri_box(b, px0, py0, cx1, cy1, x0, x1, y0, y1);
+                    hit = x0 <= x1 && y0 <= y1;
+                }
+            }
+            const unsigned long long m = __ballot(hit);
+            if (m == 0ull) continue;
+            n = (unsigned)__popcll(m);
+            const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+            // a permutation of the lanes: the hits to the front, in lane order
+            const int dst = hit ? below : (int)n + (lane - below);
+            mine = (unsigned)__builtin_amdgcn_ds_permute(dst * 4, (int)t);
+        }
+        raster_batch<TILE, DEEP>(R, mine, n, px0, py0, cx1, cy1, lane, key, L, stage);
     }
 }
 
@@ -546,12 +462,11 @@ __device__ __forceinline__ void ctrl_union_add(GroupTable<LOG2T>& tb, long long*
     }
 }
 
-// Opaque tile kernels of 8- and 16-pixel tiles are asked for 6 resident
-// waves per SIMD (at most 80 VGPRs), which they meet without spilling
-// (measured per paper-scale step: 3.35 ms at 5 waves, 3.04 ms at 6; 7 and
-// 8 waves spill).  Larger tiles and deep buffers are held to fewer waves by
-// their LDS anyway.
-#define TILE_MIN_WAVES 6
+// Opaque tile kernels of 8- and 16-pixel tiles are asked for 8 resident
+// waves per SIMD (at most 64 VGPRs): 16-pixel tiles hold 18.7 KB of LDS, so
+// eight blocks of four waves share a CU's 160 KB.  Larger tiles and deep
+// buffers are held to fewer waves by their LDS anyway.
+#define TILE_MIN_WAVES 8
 
 template <int TILE>
 struct TileCfg {
@@ -604,7 +519,8 @@ struct TileShared {
     static constexpr int TB = NPIX / PPT;
     static constexpr int NS = (MODE == 0 || MODE == 3) ? 2 : 1;
     static constexpr int LOG2T = MODE == 0 ? TileCfg<TILE>::LOG2T : 1;
-    unsigned long long key[NS][NPIX];
+    static constexpr int KS = KeyRow<TILE, false>::N;
+    unsigned long long key[NS][TILE * KS];
     // the raster's per-wave stages, then (estimate) the group table
     union {
         RasterStage stage[TB / 64];
@@ -634,7 +550,7 @@ __device__ __forceinline__ void tile_body(const TileJob& J, TileShared<TILE, MOD
         // background in both, so the tile adds nothing (its bins are empty)
         if ((J.counts[0][J.tile] | J.counts[NS - 1][J.tile]) == 0u) return;
     }
-    for (int j = tid; j < NS * NPIX; j += TB) (&S.key[0][0])[j] = ~0ull;
+    for (int j = tid; j < NS * TILE * SH::KS; j += TB) (&S.key[0][0])[j] = ~0ull;
     __syncthreads();
 
     // Both signs' bins: with two signs and several waves, half of the
@@ -689,7 +605,7 @@ __device__ __forceinline__ void tile_body(const TileJob& J, TileShared<TILE, MOD
         float rgb[NS][3], uv[NS][2];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            unsigned long long k = inpix ? S.key[s][local] : ~0ull;
+            unsigned long long k = inpix ? S.key[s][ly * SH::KS + lx] : ~0ull;
             id[s] = (k == ~0ull) ? DRD_BG : (unsigned)(k & 0xFFFFFFFFull);
             rgb[s][0] = 0.0f; rgb[s][1] = 0.0f; rgb[s][2] = 0.0f;
             uv[s][0] = 0.0f; uv[s][1] = 0.0f;

@@ -8,6 +8,7 @@ import torch
 import oracle
 from paper_2404_09758_amd import api, batch
 from paper_2404_09758_amd import scenes as S
+from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -68,3 +69,60 @@ def test_binning_edges_bit_exact(n, sizes, tile, cap):
             bt.estimate()
             assert np.array_equal(host(bt.K[0]).view(np.uint32), Ko)
             assert np.array_equal(host(bt.Q[0]), Qo)
+
+
+def raster_edges_scene(w, h, layers=0, seed=0):
+    """Triangles given in pixels under the identity projection: spans of
+    31999, 32000 and 32001 subpixels (the bound of the 32-bit edge functions),
+    boxes of 1 to 20 pixels that end at and one pixel either side of tile
+    edges and of the view's right edge, and a large one behind them all."""
+    rng = np.random.default_rng(70 + seed)
+    px = []
+    for span in (31999, 32000, 32001):
+        s = span / 256.0
+        x, y = rng.uniform(-20, w - 60), rng.uniform(-20, h - 60)
+        px.append([(x, y), (x + s, y + 0.3 * s), (x + 0.4 * s, y + s)])
+        px.append([(x, y + s), (x + s, y), (x + s - 3.0, y + 4.0)])          # a long thin one
+    for width in range(1, 21):
+        for edge in (32, 64, w, w + 2):
+            for d in (-1, 0, 1):
+                x1, y0 = edge + d, rng.uniform(0, h)
+                px.append([(x1 - width, y0), (x1, y0 + rng.uniform(-2, 9)), (x1 - width * rng.random(), y0 + width)])
+    px.append([(-w, -h), (3 * w, -h), (-w, 3 * h)])
+    px = np.asarray(px, np.float64)
+    n = len(px)
+    z = np.concatenate([rng.uniform(-0.8, 0.5, n - 1), [0.9]])
+    pos = np.empty((n, 3, 3))
+    pos[:, :, 0] = 2 * px[:, :, 0] / w - 1
+    pos[:, :, 1] = 1 - 2 * px[:, :, 1] / h
+    pos[:, :, 2] = z[:, None] + rng.uniform(-0.05, 0.05, (n, 3))
+    c = 4 if layers else 3
+    tex = [rng.uniform(0.05, 0.95, (20, 28, c)).astype(np.float32)]
+    ttex = [rng.uniform(0.05, 0.95, (20, 28, c)).astype(np.float32)]
+    tri = np.arange(3 * n, dtype=np.int32).reshape(n, 3)
+    pos = pos.reshape(-1, 3).astype(np.float32)
+    eps = [1.5 / w, 1.0 / 255.0]
+    return S.Scene("edges", tri, rng.uniform(0, 1, (n, 3, 2)).astype(np.float32), pos, tex, pos, ttex,
+                   [H.ndc_view(w, h)], shading=S.SHADING_UNLIT, eps=eps, lr=list(eps), n_pairs=1, layers=layers)
+
+
+# Raster: slots that run past the tile's and the view's right edge, triangles
+# at the bound of the staged raster, large ones mixed with small ones.
+@pytest.mark.parametrize("tile,cap,layers", [(8, 256, 0), (16, 256, 0), (32, 256, 0), (16, 3, 0), (8, 256, 2),
+                                             (16, 256, 3)])
+def test_raster_edges_bit_exact(tile, cap, layers):
+    print(f"[kernels] raster tile {tile} cap {cap} layers {layers}", flush=True)
+    sc = raster_edges_scene(187, 153, layers)
+    o = oracle.Oracle(sc)
+    v = sc.views[0]
+    ctx = api.Context(sc, DEV, tuning=(tile, cap, 0))
+    th = torch.tensor(sc.flat_params(), device=DEV)
+    rgb, ids, uv = ctx.render(th, v)
+    ro, io, uo = o.render(sc.flat_params(), v)
+    assert np.array_equal(host(ids).view(np.uint32), io)
+    assert np.array_equal(host(rgb), ro) and np.array_equal(host(uv), uo)
+    tg = [o.render(sc.flat_params(True), v)[0]]
+    Qo, Ko, _, _ = o.estimate(sc.flat_params(), sc.views, tg, 11, 2, 2, sc.eps)
+    Q, K = ctx.estimate_grad(th, sc.views, torch.tensor(tg[0], device=DEV).reshape(-1), 11, 2, 2, sc.eps)
+    assert np.array_equal(host(K).view(np.uint32), Ko)
+    assert np.array_equal(host(Q), Qo)
