@@ -272,7 +272,7 @@ typedef unsigned long long __attribute__((aligned(4))) drd_u64_a4;
 // uniform base and a 32-bit offset instead of a 64-bit address per lane.
 template <int C, bool COMPACT>
 __device__ __forceinline__ void sample_texels(const DRD_GLOBAL float* th, const DRD_GLOBAL uint32_t* pb,
-                                              long long base, int W, float e, float sgn, const Foot& f,
+                                              long long base, int W, float e, unsigned flip, const Foot& f,
                                               float* out) {
     typedef float __attribute__((ext_vector_type(C == 1 ? 2 : C), aligned(4))) texel_t;
     const DRD_GLOBAL float* tt = th + base;
@@ -280,10 +280,9 @@ __device__ __forceinline__ void sample_texels(const DRD_GLOBAL float* th, const 
     const DRD_GLOBAL uint32_t* pw = pb + (base >> 5);
     unsigned bb = (unsigned)(base & 31);
     // s_i (sgn e) is e (>= 0) with its sign bit set to the sign bit s_i
-    // holds -- complemented for the minus render: the IEEE value of
+    // holds -- complemented (flip) for the minus render: the IEEE value of
     // +-e exactly, so x + it is the same operation as pval's
     const unsigned eb = __float_as_uint(e);
-    const unsigned flip = (sgn > 0.0f) ? 0u : 0xFFFFFFFFu;
     float wx[2] = {1.0f - f.fx, f.fx};
     float acc[C];
     // row by row (ya, then yb), two texels each: the weighted sum keeps its
@@ -362,10 +361,10 @@ __device__ __forceinline__ void sample_texels(const DRD_GLOBAL float* th, const 
 // (theta + sgn s eps) over a precomputed footprint.
 template <int C, bool COMPACT>
 __device__ __forceinline__ void sample_tex(const DScene& sc, const float* __restrict__ th,
-                                           const uint32_t* __restrict__ pb, float e, float sgn, int t,
+                                           const uint32_t* __restrict__ pb, float e, unsigned flip, int t,
                                            const Foot& f, float* out) {
     sample_texels<C, COMPACT>((const DRD_GLOBAL float*)th, (const DRD_GLOBAL uint32_t*)pb, sc.tex_off[t], sc.tex_w[t],
-                              e, sgn, f, out);
+                              e, flip, f, out);
 }
 
 // Correctly rounded square root and reciprocal for operands in a normal
@@ -515,7 +514,7 @@ __device__ __forceinline__ Attr frag_attr(const DScene& sc, const TriR& r, const
 
 template <int SHADE, bool DEEP>
 __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, const float* __restrict__ th,
-                                            const uint32_t* __restrict__ pb, const float* eps, float sgn,
+                                            const uint32_t* __restrict__ pb, const float* eps, unsigned flip,
                                             const TriR& r, const TriS& s, const TriG* __restrict__ G,
                                             const CornerUV& cu, int px, int py, float* rgb, float* uvo,
                                             float& opacity) {
@@ -530,7 +529,7 @@ __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, c
     Foot foot0;
     if (sc.n_tex > 0) {
         foot0 = footprint(u, v, sc.cls_w[0], sc.cls_h[0]);
-        sample_tex<DEEP ? 4 : 3, COMPACT>(sc, th, pb, eps[1], sgn, 0, foot0, alb);
+        sample_tex<DEEP ? 4 : 3, COMPACT>(sc, th, pb, eps[1], flip, 0, foot0, alb);
     }
     if constexpr (DEEP) {
         float al = alb[3];
@@ -552,7 +551,7 @@ __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, c
     if (sc.n_tex > 1) {
         int c1 = sc.tex_cls[1];
         Foot f1 = (c1 == 0) ? foot0 : footprint(u, v, sc.cls_w[c1], sc.cls_h[c1]);
-        sample_tex<3, COMPACT>(sc, th, pb, eps[2], sgn, 1, f1, nm);
+        sample_tex<3, COMPACT>(sc, th, pb, eps[2], flip, 1, f1, nm);
     }
     float tn[3];
 #pragma unroll
@@ -567,7 +566,7 @@ __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, c
     if (sc.n_tex > 2) {
         int c2 = sc.tex_cls[2];
         Foot f2 = (c2 == 0) ? foot0 : footprint(u, v, sc.cls_w[c2], sc.cls_h[c2]);
-        sample_tex<1, COMPACT>(sc, th, pb, eps[3], sgn, 2, f2, rough4);
+        sample_tex<1, COMPACT>(sc, th, pb, eps[3], flip, 2, f2, rough4);
     }
     float P[3];
 #pragma unroll

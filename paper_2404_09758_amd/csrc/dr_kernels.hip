@@ -769,7 +769,7 @@ int scene_shade(const DScene& sc) {
 hipError_t launch_tile(hipStream_t st, TileArgs a, int tile, int mode) {
     // the interleaved order needs the call's units in one grid dimension
     const long long units = (long long)(a.n_items / a.n_views) * a.views.tsum[a.n_views];
-    a.interleave = a.whole && units * 256 < (1ll << 32);
+    a.interleave = a.whole && units * 512 < (1ll << 32);
     dim3 grid((unsigned)a.max_tiles, (unsigned)a.n_items);
     if (a.interleave) grid = dim3((unsigned)units);
     if (a.sc.layers > 0) {
@@ -838,12 +838,15 @@ hipError_t launch_batch_setup(hipStream_t st, const BatchArgs& b, long long blk0
 }
 
 hipError_t launch_batch_tile(hipStream_t st, const BatchArgs& b, long long w0, long long n) {
-    if (n <= 0) return hipSuccess;
     BatchArgs a = b;
-    a.unit0 = w0;
-    if (a.tile == 8) return launch_batch_tile_t<8>(st, a, (unsigned)n);
-    if (a.tile == 16) return launch_batch_tile_t<16>(st, a, (unsigned)n);
-    return launch_batch_tile_t<32>(st, a, (unsigned)n);
+    const long long most = 1ll << 22;               // a grid dimension holds 2^32 threads
+    for (a.unit0 = w0; a.unit0 < w0 + n; a.unit0 += most) {
+        const unsigned grid = (unsigned)(w0 + n - a.unit0 < most ? w0 + n - a.unit0 : most);
+        hipError_t e = a.tile == 8 ? launch_batch_tile_t<8>(st, a, grid)
+                     : a.tile == 16 ? launch_batch_tile_t<16>(st, a, grid) : launch_batch_tile_t<32>(st, a, grid);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_batch_fold(hipStream_t st, const BatchArgs& b) {

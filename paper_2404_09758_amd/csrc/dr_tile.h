@@ -40,319 +40,398 @@ __device__ __forceinline__ void insert_key(unsigned long long* key, int li, unsi
     }
 }
 
-// Keys per row of a tile: three more than its pixels for opaque tiles, since
-// a raster slot that starts at the row's last pixel runs past it.
+// Work split of one tile.  Opaque: a thread takes a pixel (four of a 32-pixel
+// tile's) and shades both its signs, so the two chains of dependent reads
+// overlap.  Deep: a thread takes one side of a pixel, lanes l and l + 32 of a
+// wave holding the + and - side; half the layers per thread.
+template <int TILE, int MODE, bool DEEP>
+struct TileCfg {
+    static constexpr int NS = (MODE == 0 || MODE == 3) ? 2 : 1;
+    static constexpr int NPIX = TILE * TILE;
+    static constexpr int TB = DEEP ? NS * NPIX : (NPIX > 256 ? 256 : NPIX);
+    static constexpr int NW = TB / 64;
+    static constexpr int LOG2T = MODE != 0 ? 1 : (TILE == 8 ? 9 : (TILE == 16 ? 10 : 11));
+    // triangles rasterised at a time
+    static constexpr int NE = TILE == 32 ? 128 : (TB < 192 ? TB : 192);
+};
+
+// Keys per row of a tile: spare ones after its pixels for opaque tiles, since
+// a raster slot that starts at the row's last pixel runs three past it.
 template <int TILE, bool DEEP>
 struct KeyRow {
     static constexpr int N = DEEP ? TILE : TILE + 4;
 };
 
-// Rasterise triangle t over its box in the tile, one lane per covered pixel:
-// triangles too large for the staged raster.  (cx1, cy1): the tile's last
-// pixel inside the view.
-template <int TILE, bool DEEP>
-__device__ __forceinline__ void raster_tri(const TriR& r, unsigned t, int px0, int py0, int cx1, int cy1,
-                                           int lane, unsigned long long* key, int L) {
-    int x0, x1, y0, y1;
-    tri_box(r, px0, py0, cx1, cy1, x0, x1, y0, y1);
-    int bw = x1 - x0 + 1;
-    int n = bw * (y1 - y0 + 1);
-    unsigned m = ((1u << 20) + (unsigned)bw - 1u) / (unsigned)bw;     // exact for bw <= 32, idx < 1024
-    for (int base = 0; base < n; base += 64) {
-        int idx = base + lane;
-        if (idx < n) {
-            int dy = (int)(((unsigned)idx * m) >> 20);
-            int x = x0 + idx - dy * bw, y = y0 + dy;
-            int px = 256 * x + 128, py = 256 * y + 128;
-            long long e0, e1, e2;
-            if (!inside(r, px, py, e0, e1, e2)) continue;
-            float z = depth_at(r, px, py);
-            insert_key<DEEP>(key, (y - py0) * KeyRow<TILE, DEEP>::N + (x - px0),
-                             ((unsigned long long)__float_as_uint(z) << 32) | t, L);
-        }
-    }
-}
-
-// Per-wave LDS staging of a batch of small triangles for the packed raster
-// (48 B each, three 16-byte reads): edge k over the triangle's clipped
-// bounding box is e_k(dx, dy) = 256 dX_k dy - 256 dY_k dx + c_k at pixel
-// (x0 + dx, y0 + dy).  16-bit fields hold differences of snapped corners,
-// which a TRI_SMALL triangle keeps within +-2^15.
+// LDS staging of a batch of small triangles for the raster (48 B each, three
+// 16-byte reads): edge k over the triangle's clipped bounding box is
+// e_k(dx, dy) = 256 dX_k dy - 256 dY_k dx + c_k at pixel (x0 + dx, y0 + dy).
+// 16-bit fields hold differences of snapped corners, which a TRI_SMALL
+// triangle keeps within +-2^15.
 struct __align__(16) PTri {
     int c[3];            // edge k at the box's corner pixel, plus 1 on a top-left edge
     unsigned t;
     int d[3];            // dX_k (low half), dY_k (high half)
-    unsigned pk;         // bits 0..4 box width - 1, 5..15 key index of the corner pixel, 16.. first slot
+    unsigned pk;         // box width - 1, key index of the corner pixel, first slot (PK_*)
     float z0, zx, zy;    // depth plane
     int dz;              // corner pixel centre minus vertex 0, in subpixels: x low, y high
 };
-
-struct RasterStage {
-    PTri tri[64];
-    int mark[64];
-};
-
-// Lanes of one wave exchange data through the wave's stage: a release fence
-// before the wave barrier and an acquire fence after it make each lane's LDS
-// stores visible to the other lanes' later loads (the barrier itself
-// declares no memory effects, so without the fences the compiler could
-// forward a lane's own store to its load past the other lanes' writes).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+#define PK_KEY 5                 // bits 0..4: box width - 1
+#define PK_SLOT 17               // bits 5..16: key index; from 17: the triangle's first slot
 
 static_assert(sizeof(PTri) == 48, "PTri layout");
 
-// Packed raster of a batch of TRI_SMALL triangles (one per lane; bh = 0:
-// none), through the wave's LDS stage.  Each triangle's clipped box is cut
-// into slots of RASTER_SLOT horizontally adjacent pixels (a row of w pixels
-// gives ceil(w / RASTER_SLOT) slots), the batch's slots are laid end to end,
-// and each pass gives one slot to every lane: one read of the staged record,
-// one index computation and one pass marking then serve all the slot's
-// pixels.  The non-empty triangles are stored by rank; each pass marks the
-// slots where a triangle begins, and a lane's triangle is then the number of
-// triangles begun up to its slot (a ballot and a lane-masked bit count) --
-// one LDS read of the staged record instead of a binary search and a shuffle
-// per field.  Edge values are exact: a TRI_SMALL triangle spans less than
-// 32000 subpixels, so at every pixel of the box and up to three to its right
-// both products of an edge function stay below 2^30 + 2^25 in magnitude and
-// the edge value (plus 1) fits in 32 bits; the wrapped 32-bit sums equal it,
-// as do the slot's further pixels' values, each its left neighbour's minus
-// 256 dY.  e > 0 || (e == 0 && top-left) is e + [top-left] > 0.  A slot's
-// pixels beyond the box are not covered, unless the box was clipped at the
-// tile's or the view's edge: those keys fall on the row's spare columns, or
-// on pixels that are not in the view and are not read (opaque; deep tiles
-// test the box).
-// Bound by vector issue.  The record's 48 B (80 B before) set the block's LDS
-// (25.6 -> 18.5 KB for 16-pixel tiles, 6 -> 8 waves per SIMD) and a pass's LDS
-// reads; with the raster compiled in once for bins, spill lists and scans
-// (52 -> 34 KB of code) the GGX paper step went 1739 -> 1578 us, the
-// full-image soup 1325 -> 1160 us.  Slots of 4 pixels: measured on the paper-scale step
-// against 2, 3, 6 and 8 (2 -> 4: tile kernel -2 % at the start of an
-// optimisation run, -9 % after 50 Adam steps, when the triangles have grown;
-// 6 and 8 within 2 % of 4).
+template <int TILE, int NE, int NW>
+struct RasterShared {
+    union {
+        PTri tri[NE];
+        unsigned hit[NE];        // overflowing bins: triangles found (bit 31: sign), until they are staged
+    };
+    // bit i: a triangle begins at slot i of the batch
+    unsigned long long begin[NE * TILE * (TILE / 4) / 64];
+    unsigned wtot[NW];           // slots and triangles staged by each wave
+    unsigned big[NE];            // large triangles of the batch (bit 31: sign)
+    unsigned nbig;               // their number
+    unsigned nhit;
+};
+
+// Where one tile's triangles come from: counters, bins, records and spill
+// lists of the two signs (sign 1's follow sign 0's at a fixed distance).
+struct RasterJob {
+    const TriR* rec;             // [NS, n_tris]
+    int n_tris;
+    const unsigned* counts;      // of the tile; sign 1's tstride further
+    const unsigned* bins;        // of the tile; sign 1's tstride * cap further
+    long long tstride;
+    int cap;
+    const unsigned* spn;         // [NS, 2]
+    const unsigned long long* spill;   // [NS, SPILL_CAP]
+    int tile;
+    int px0, py0, cx1, cy1;      // the tile's pixels that lie in the view
+    unsigned long long* stats;
+};
+
+// Rasterise the tile's triangles of both signs into key[] (sign 1's keys
+// TILE * KeyRow further).
+//
+// Batches of up to NE triangles, the bins of both signs laid end to end, go
+// through LDS: each thread stages one triangle; its clipped box is cut into
+// slots of RASTER_SLOT horizontally adjacent pixels (a row of w pixels gives
+// ceil(w / RASTER_SLOT) slots), the batch's slots are laid end to end over
+// the block, and each wave takes an even share of them, one slot per lane and
+// pass: one read of the staged record and one index computation serve all the
+// slot's pixels.  The triangle of a slot is the number of triangles begun up
+// to it: a bit per slot marks the beginnings, so a pass reads its 64 bits
+// (the same for all lanes) and counts the ones up to each lane.  Edge values
+// are exact: a TRI_SMALL triangle spans less than 32000 subpixels, so at every
+// pixel of the box and up to three to its right both products of an edge
+// function stay below 2^30 + 2^25 in magnitude and the edge value (plus 1)
+// fits in 32 bits; the wrapped 32-bit sums equal it, as do the slot's further
+// pixels' values, each its left neighbour's minus 256 dY.
+// e > 0 || (e == 0 && top-left) is e + [top-left] > 0.  A slot's pixels beyond
+// the box are not covered, unless the box was clipped at the tile's or the
+// view's edge: those keys fall on the row's spare columns, or on pixels that
+// are not in the view and are not read (opaque; deep tiles test the box).
+// Large triangles of a batch follow one at a time, 64 pixels per wave.
+//
+// Entries of a bin past its capacity are in the render's spill list, or, when
+// that list ran out of room, anywhere in the render: the waves look through
+// either 64 entries at a time and gather the tile's into batches.
+//
+// Bound by vector issue, in small launches by the latency of its chain.
+// Staging by the block instead of by each wave for its own share of one
+// sign's bin: every triangle is staged by a full wave and the passes are even
+// over the waves whatever the bins hold.  Slots of 4 pixels: measured on the
+// paper-scale step against 2, 3, 6 and 8 (2 -> 4: tile kernel -2 % at the
+// start of an optimisation run, -9 % after 50 Adam steps, when the triangles
+// have grown; 6 and 8 within 2 % of 4).
 #define RASTER_SLOT 4
-#define PK_SLOT 16               // first bit of PTri::pk's first slot
-template <int TILE, bool DEEP>
-__device__ __forceinline__ void raster_staged(RasterStage* st, const TriR& r, unsigned t, int x0, int y0, int bw,
-                                              int bh, int px0, int py0, int lane, unsigned long long* key, int L) {
-    constexpr int SL = RASTER_SLOT;                     // pixels per slot
-    constexpr int KS = KeyRow<TILE, DEEP>::N;
-    static_assert(TILE * KS <= 2048 && 64 * TILE * (TILE / SL) <= 65536 && SL == 4, "PTri::pk fields");
-    const int sw = (bw + SL - 1) / SL;                  // slots per row
-    const int c = sw * bh;                              // slots of this lane's triangle (0: none)
-    const int P = wave_inclusive_sum(c);
-    const int N = __builtin_amdgcn_readlane(P, 63);
-    const int pex = P - c;
-    unsigned long long nz = __ballot(c > 0);
-    if (c > 0) {
-        int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(nz >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)nz, 0u));
-        PTri q;
-        int cx = 256 * x0 + 128, cy = 256 * y0 + 128;
+
+template <int TILE, bool DEEP, int NS, int TB, int NE>
+__device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TILE, NE, TB / 64>& S,
+                                            unsigned long long* key, int L) {
+    constexpr int SL = RASTER_SLOT, KS = KeyRow<TILE, DEEP>::N, NW = TB / 64;
+    constexpr int MW = NE * TILE * (TILE / SL) / 64;     // words of begin[]
+    constexpr int GATHER = NE / 64 < 3 ? NE / 64 : 3;    // a wave's hits of one look fit an empty list
+    static_assert(SL == 4 && NS * TILE * KS <= (1 << (PK_SLOT - PK_KEY)), "PTri::pk key index");
+    static_assert(64 * MW <= (1 << (32 - PK_SLOT)), "PTri::pk first slot");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned cap = (unsigned)J.cap;
+    unsigned cnt[NS], nb[NS];                            // entries of each sign; those read from its bin
+    bool over = false;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            int ia = (k + 1) % 3, ib = (k + 2) % 3;
-            int dX = r.X[ib] - r.X[ia], dY = r.Y[ib] - r.Y[ia];
-            q.d[k] = (dX & 0xFFFF) | (dY << 16);
-            q.c[k] = (__mul24(dX, cy - r.Y[ia]) - __mul24(dY, cx - r.X[ia])) + (int)((r.flags >> (k + 1)) & 1u);
-        }
-        q.dz = ((cx - r.X[0]) & 0xFFFF) | ((cy - r.Y[0]) << 16);
-        q.z0 = r.z0; q.zx = r.zx; q.zy = r.zy;
-        q.t = t;
-        q.pk = (unsigned)(bw - 1) | ((unsigned)((y0 - py0) * KS + (x0 - px0)) << 5) | ((unsigned)pex << PK_SLOT);
-        st->tri[rank] = q;
-    }
-    wave_sync();
-    int base = 0;                                       // triangles begun before this pass
-    for (int s0 = 0; s0 < N; s0 += 64) {
-        st->mark[lane] = 0;
-        wave_sync();
-        if (c > 0 && pex >= s0 && pex < s0 + 64) st->mark[pex - s0] = 1;
-        wave_sync();
-        int f = st->mark[lane];
-        unsigned long long M = __ballot(f != 0);
-        int rr = base + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(M >> 32),
-                                                       __builtin_amdgcn_mbcnt_lo((unsigned)M, 0u)) + f - 1;
-        base += __popcll(M);
-        int sl = s0 + lane;
-        if (sl < N) {
-            const PTri q = st->tri[rr];
-            const int idx = sl - (int)(q.pk >> PK_SLOT);
-            const unsigned w4 = q.pk & 0x1Cu;           // 4 (slots per row - 1)
-            int dy;                                     // idx / slots per row
-            if constexpr (TILE <= 16) {
-                // idx < 64, at most 4 slots: idx * ceil(128 / slots) >> 7
-                dy = (int)(__umul24((unsigned)idx, (0x202B4080u >> (2u * w4)) & 0xFFu) >> 7);
-            } else {
-                dy = (int)(((float)idx + 0.5f) * __builtin_amdgcn_rcpf((float)((w4 >> 2) + 1u)));
+    for (int s = 0; s < NS; ++s) {
+        cnt[s] = gload(&J.counts[s * J.tstride]);
+        nb[s] = cnt[s];
+        if (cnt[s] > cap) {
+            over = true;
+            nb[s] = gload(&J.spn[2 * s]) > SPILL_CAP ? 0u : cap;
+            if (tid == 0) {
+                atomicAdd(&J.stats[ST_OVERFLOWS], 1ull);
+                if (nb[s] == 0u) atomicAdd(&J.stats[ST_FULL_SCANS], 1ull);
             }
-            const int dx = 4 * idx - __mul24(dy, (int)w4 + 4);
-            int e[3], a[3];
+        }
+    }
+    if (tid == 0) {
+        const unsigned mx = NS == 2 ? max(cnt[0], cnt[NS - 1]) : cnt[0];
+        // the value only grows, so a workgroup that reads one at least as
+        // large (possibly stale) may skip the atomic: almost all do
+        if ((unsigned long long)mx > J.stats[ST_MAX_BIN]) atomicMax(&J.stats[ST_MAX_BIN], (unsigned long long)mx);
+        S.nhit = 0u;
+    }
+    const unsigned total = nb[0] + (NS == 2 ? nb[NS - 1] : 0u);
+    unsigned pos = 0u;                                   // bin entries done (both signs end to end)
+    int gs = -1;                                         // sign whose overflow is gathered (-1: bins)
+    unsigned gpos = 0u, glimit = 0u;                     // this wave's place in it
+    for (;;) {
+        // ---- this thread's triangle of the batch
+        bool has = false;
+        unsigned t = 0u;
+        int s = 0;
+        if (gs < 0 && pos >= total) {
+            if (!over) break;
+            gs = 0;
+            gpos = glimit = 0u;
+            if (cnt[0] > cap) {
+                glimit = nb[0] == 0u ? (unsigned)J.n_tris : gload(&J.spn[0]);
+                gpos = 64u * GATHER * (unsigned)wave;
+            }
+        }
+        if (gs < 0) {
+            const unsigned e = pos + (unsigned)tid;
+            has = tid < NE && e < total;
+            if (has) {
+                s = (NS == 2 && e >= nb[0]) ? 1 : 0;
+                const unsigned k = s ? e - nb[0] : e;
+                t = gload(&J.bins[s * J.tstride * (long long)cap + k]);
+            }
+            pos += NE;
+        } else {
+            __syncthreads();
+            const bool scan = nb[NS == 2 && gs ? NS - 1 : 0] == 0u;
+            const TriR* R = J.rec + (long long)gs * J.n_tris;
+            while (gpos < glimit) {
+                // GATHER times 64 entries, their reads all in flight together
+                bool hit[GATHER];
+                unsigned tj[GATHER];
+                if (!scan) {
+                    unsigned long long e[GATHER];
+#pragma unroll
+                    for (int i = 0; i < GATHER; ++i)
+                        e[i] = gload(&J.spill[(long long)gs * SPILL_CAP + min(gpos + 64u * i + (unsigned)lane, glimit - 1u)]);
+#pragma unroll
+                    for (int i = 0; i < GATHER; ++i) {
+                        hit[i] = gpos + 64u * i + (unsigned)lane < glimit && (unsigned)(e[i] >> 32) == (unsigned)J.tile;
+                        tj[i] = (unsigned)e[i];
+                    }
+                } else {
+                    struct __align__(16) Corners { int X[3], Y[3]; unsigned flags, pad; };      // (TriR's first 32 B)
+                    Corners q[GATHER];
+#pragma unroll
+                    for (int i = 0; i < GATHER; ++i) {
+                        tj[i] = min(gpos + 64u * i + (unsigned)lane, glimit - 1u);
+                        q[i] = gload((const Corners*)&R[tj[i]]);
+                    }
+#pragma unroll
+                    for (int i = 0; i < GATHER; ++i) {
+                        TriR b;
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) { b.X[k] = q[i].X[k]; b.Y[k] = q[i].Y[k]; }
+                        int x0, x1, y0, y1;
+                        tri_box(b, J.px0, J.py0, J.cx1, J.cy1, x0, x1, y0, y1);
+                        hit[i] = gpos + 64u * i + (unsigned)lane < glimit && (q[i].flags & TRI_VALID) && x0 <= x1 && y0 <= y1;
+                    }
+                }
+                unsigned n = 0u, place[GATHER];          // all of the wave's hits, in order
+#pragma unroll
+                for (int i = 0; i < GATHER; ++i) {
+                    const unsigned long long m = __ballot(hit[i]);
+                    place[i] = n + lanes_below(m);
+                    n += (unsigned)__popcll(m);
+                }
+                if (n > 0u) {
+                    // room for all of them, or this wave waits for the next batch
+                    unsigned at = 0xFFFFFFFFu;
+                    if (lane == 0) {
+                        unsigned old = S.nhit;
+                        while (old + n <= (unsigned)NE) {
+                            const unsigned seen = atomicCAS(&S.nhit, old, old + n);
+                            if (seen == old) {
+                                at = old;
+                                break;
+                            }
+                            old = seen;
+                        }
+                    }
+                    at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
+                    if (at == 0xFFFFFFFFu) break;
+#pragma unroll
+                    for (int i = 0; i < GATHER; ++i)
+                        if (hit[i]) S.hit[at + place[i]] = tj[i] | ((unsigned)gs << 31);
+                }
+                gpos += 64u * GATHER * NW;
+            }
+            __syncthreads();
+            const unsigned nh = S.nhit;
+            if (nh == 0u) {                              // this sign's are all done
+                if (++gs == NS) break;
+                gpos = glimit = 0u;
+                if (NS == 2 && cnt[NS - 1] > cap) {
+                    glimit = nb[NS - 1] == 0u ? (unsigned)J.n_tris : gload(&J.spn[2]);
+                    gpos = 64u * GATHER * (unsigned)wave;
+                }
+                continue;
+            }
+            has = (unsigned)tid < nh;
+            if (has) {
+                t = S.hit[tid] & 0x7FFFFFFFu;
+                s = (int)(S.hit[tid] >> 31);
+            }
+        }
+        // ---- stage it
+        TriR r{};
+        int x0 = 0, y0 = 0, bw = 1, bh = 0;
+        bool large = false;
+        if (has) {
+            r = gload(&J.rec[(long long)s * J.n_tris + t]);
+            int x1, y1;
+            tri_box(r, J.px0, J.py0, J.cx1, J.cy1, x0, x1, y0, y1);
+            if (x0 <= x1 && y0 <= y1) {
+                large = !(r.flags & TRI_SMALL);
+                bw = x1 - x0 + 1;
+                bh = large ? 0 : y1 - y0 + 1;
+            }
+        }
+        const int c = ((bw + SL - 1) / SL) * bh;         // slots
+        const unsigned mine = ((unsigned)c << 9) | (c > 0 ? 1u : 0u);
+        const unsigned incl = (unsigned)wave_inclusive_sum((int)mine);
+        if (lane == 63) S.wtot[wave] = incl;
+        for (int j = tid; j < MW; j += TB) S.begin[j] = 0ull;
+        if (tid == 0) S.nbig = 0u;                       // (read by all before the last barrier)
+        __syncthreads();
+        unsigned before = 0u, all = 0u;
+#pragma unroll
+        for (int w = 0; w < (NE + 63) / 64; ++w) {
+            const unsigned v = S.wtot[w];
+            all += v;
+            if (w < wave) before += v;
+        }
+        const int N = (int)(all >> 9);
+        if (c > 0) {
+            const unsigned ex = before + incl - mine;
+            const unsigned pex = ex >> 9;
+            PTri q;
+            const int cx = 256 * x0 + 128, cy = 256 * y0 + 128;
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const int dX = (int)(short)q.d[k], dY = q.d[k] >> 16;
-                a[k] = 256 * dY;
-                e[k] = (__mul24(dX, 256 * dy) + q.c[k]) - __mul24(dY, 256 * dx);
+                const int ia = (k + 1) % 3, ib = (k + 2) % 3;
+                const int dX = r.X[ib] - r.X[ia], dY = r.Y[ib] - r.Y[ia];
+                q.d[k] = (dX & 0xFFFF) | (dY << 16);
+                q.c[k] = (__mul24(dX, cy - r.Y[ia]) - __mul24(dY, cx - r.X[ia])) + (int)((r.flags >> (k + 1)) & 1u);
             }
-            float xf = (float)(256 * dx + (int)(short)q.dz);
-            const float zrow = q.zy * (float)(256 * dy + (q.dz >> 16));
-            unsigned long long* kp = key;
-            const int off = (int)((q.pk >> 5) & ((1u << (PK_SLOT - 5)) - 1u)) + dy * KS + dx;
-#pragma unroll
-            for (int k = 0; k < SL; ++k) {
-                const bool in = !DEEP || k == 0 || dx + k <= (int)(q.pk & 31u);
-                if (in && min(e[0], min(e[1], e[2])) > 0) {
-                    float z = (q.z0 + q.zx * xf) + zrow;
-                    z = fmaxf(z, 0.0f);                 // 0 for negative values and NaN
-                    insert_key<DEEP>(kp, off + k, ((unsigned long long)__float_as_uint(z) << 32) | q.t, L);
-                }
-                e[0] -= a[0];
-                e[1] -= a[1];
-                e[2] -= a[2];
-                xf += 256.0f;                           // (exact)
-            }
+            q.dz = ((cx - r.X[0]) & 0xFFFF) | ((cy - r.Y[0]) << 16);
+            q.z0 = r.z0; q.zx = r.zx; q.zy = r.zy;
+            q.t = t;
+            q.pk = (unsigned)(bw - 1) | ((unsigned)((s * TILE + y0 - J.py0) * KS + (x0 - J.px0)) << PK_KEY) |
+                   (pex << PK_SLOT);
+            S.tri[ex & 511u] = q;
+            atomicOr(reinterpret_cast<unsigned*>(S.begin) + (pex >> 5), 1u << (pex & 31u));
         }
-        wave_sync();
-    }
-}
-
-// Raster of up to 64 triangles held one per lane (mine: the triangle index,
-// valid for lanes below n): the small ones through the wave's stage, then
-// the large ones one at a time, their records read from the lanes that hold
-// them.
-template <int TILE, bool DEEP>
-__device__ __forceinline__ void raster_batch(const TriR* __restrict__ R, unsigned mine, unsigned n, int px0,
-                                             int py0, int cx1, int cy1, int lane, unsigned long long* key, int L,
-                                             RasterStage* stage) {
-    TriR r{};
-    int x0 = 0, y0 = 0, bw = 1, bh = 0;
-    bool large = false;
-    if ((unsigned)lane < n) {
-        r = gload(&R[mine]);
-        int x1, y1;
-        tri_box(r, px0, py0, cx1, cy1, x0, x1, y0, y1);
-        if (x0 <= x1 && y0 <= y1) {
-            large = !(r.flags & TRI_SMALL);
-            bw = x1 - x0 + 1;
-            bh = large ? 0 : y1 - y0 + 1;
+        const unsigned long long lm = __ballot(large);
+        if (lm) {
+            unsigned at = 0u;
+            if (lane == 0) at = atomicAdd(&S.nbig, (unsigned)__popcll(lm));
+            at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
+            if (large) S.big[at + lanes_below(lm)] = t | ((unsigned)s << 31);
         }
-    }
-    raster_staged<TILE, DEEP>(stage, r, mine, x0, y0, bw, bh, px0, py0, lane, key, L);
-    unsigned long long big = __ballot(large);
-    while (big) {
-        const int j = __ffsll((long long)big) - 1;
-        big &= big - 1ull;
-        const int* mw = reinterpret_cast<const int*>(&r);
-        TriR q;
-        int* qw = reinterpret_cast<int*>(&q);
-#pragma unroll
-        for (int k = 0; k < (int)(sizeof(TriR) / 4); ++k) qw[k] = __builtin_amdgcn_readlane(mw[k], j);
-        raster_tri<TILE, DEEP>(q, __builtin_amdgcn_readlane(mine, j), px0, py0, cx1, cy1, lane, key, L);
-    }
-}
-
-// Record the largest bin occupancy.  The value only grows, so a workgroup
-// that reads a value at least as large (possibly a stale one) may skip the
-// atomic: almost all do, and the single counter no longer serialises a
-// launch of a hundred thousand workgroups on one L2 channel.
-__device__ __forceinline__ void note_max_bin(unsigned long long* stats, unsigned c) {
-    unsigned long long seen = stats[ST_MAX_BIN];
-    if ((unsigned long long)c > seen) atomicMax(&stats[ST_MAX_BIN], (unsigned long long)c);
-}
-
-// A bin of c entries, capacity cap: its overflow and occupancy statistics.
-__device__ __forceinline__ void note_bin(unsigned long long* stats, unsigned c, unsigned cap) {
-    if (c > cap) atomicAdd(&stats[ST_OVERFLOWS], 1ull);
-    note_max_bin(stats, c);
-}
-
-// Every triangle of one render that may cover the tile, in batches of up to
-// 64 per wave (wave `wave` of nw): the tile's bin of cnt entries; for a bin
-// past its capacity the full bin and then the tile's entries of the render's
-// spill list, or, when that list ran out of room, every valid triangle of the
-// render whose pixel box meets the tile.  The spill list and the render are
-// read 64 entries at a time, the hits packed to the low lanes, so the cost is
-// a coalesced pass, not one dependent read per entry.  One loop serves the
-// three sources, so the raster is compiled in once.  `note`: this wave counts
-// a full scan in the statistics.
-template <int TILE, bool DEEP>
-__device__ __forceinline__ void raster_render(const TriR* __restrict__ R, const unsigned* __restrict__ bin,
-                                              unsigned cnt, unsigned cap, const unsigned* spn,
-                                              const unsigned long long* __restrict__ spill, int n_tris, int tile,
-                                              int wave, int nw, int lane, int px0, int py0, int cx1, int cy1,
-                                              unsigned long long* key, int L, RasterStage* stage,
-                                              unsigned long long* stats, bool note) {
-    enum { BIN, SPILL, SCAN };
-    int src = BIN, next = BIN;
-    unsigned limit = cnt, ns = 0u;
-    if (cnt > cap) {
-        limit = cap;
-        ns = gload(&spn[0]);
-        next = SPILL;
-        if (ns > SPILL_CAP) {
-            src = next = SCAN;
-            limit = (unsigned)n_tris;
-            if (note && lane == 0) atomicAdd(&stats[ST_FULL_SCANS], 1ull);
+        if (tid == 0) S.nhit = 0u;
+        __syncthreads();
+        // ---- its slots, an even share of the passes per wave
+        const int nwin = (N + 63) >> 6;
+        const int w0 = wave * nwin / NW, w1 = (wave + 1) * nwin / NW;
+        int base = 0;                                    // triangles begun before window w0
+        if (w0 > 0 && w0 < w1) {
+            for (int j = lane; j < w0; j += 64) base += __popcll(S.begin[j]);
+            base = __builtin_amdgcn_readlane(wave_inclusive_sum(base), 63);
         }
-    }
-    unsigned base = src == BIN ? (unsigned)wave : 64u * (unsigned)wave;
-    for (;; base += 64u * (unsigned)nw) {
-        if (base >= limit) {
-            if (src == next) break;
-            src = next;                                  // the bin is done: the spill list
-            limit = ns;
-            base = 64u * (unsigned)wave;
-            if (base >= limit) break;
-        }
-        unsigned mine = 0u, n;
-        if (src == BIN) {
-            // entries wave, wave + nw, wave + 2 nw, ...
-            const unsigned k = base + (unsigned)lane * (unsigned)nw;
-            if (k < limit) mine = gload(&bin[k]);
-            n = min((limit - base + (unsigned)nw - 1u) / (unsigned)nw, 64u);
-        } else {
-            const unsigned j = base + (unsigned)lane;
-            bool hit = false;
-            unsigned t = j;
-            if (j < limit) {
-                if (src == SPILL) {
-                    const unsigned long long e = gload(&spill[j]);
-                    hit = (unsigned)(e >> 32) == (unsigned)tile;
-                    t = (unsigned)e;
+        for (int w = w0; w < w1; ++w) {
+            const unsigned long long Mv = S.begin[w];    // (the same for all lanes)
+            const unsigned mlo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)Mv);
+            const unsigned mhi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(Mv >> 32));
+            const unsigned long long M = ((unsigned long long)mhi << 32) | mlo;
+            // begun at or before the lane's slot, less one
+            const int rr = base + (int)(mlo & 1u) - 1 + (int)lanes_below(M >> 1);
+            base += __popcll(M);
+            const int sl = 64 * w + lane;
+            if (sl < N) {
+                const PTri q = S.tri[rr];
+                const int idx = sl - (int)(q.pk >> PK_SLOT);
+                const unsigned w4 = q.pk & 0x1Cu;        // 4 (slots per row - 1)
+                int dy;                                  // idx / slots per row
+                if constexpr (TILE <= 16) {
+                    // idx < 64, at most 4 slots: idx * ceil(128 / slots) >> 7
+                    dy = (int)(__umul24((unsigned)idx, (0x202B4080u >> (2u * w4)) & 0xFFu) >> 7);
                 } else {
-                    const TriR* q = &R[j];
-                    TriR b;                              // corners and flags (the first 28 B)
+                    dy = (int)(((float)idx + 0.5f) * __builtin_amdgcn_rcpf((float)((w4 >> 2) + 1u)));
+                }
+                const int dx = 4 * idx - __mul24(dy, (int)w4 + 4);
+                int e[3], a[3];
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        b.X[k] = gload(&q->X[k]);
-                        b.Y[k] = gload(&q->Y[k]);
+                for (int k = 0; k < 3; ++k) {
+                    const int dX = (int)(short)q.d[k], dY = q.d[k] >> 16;
+                    a[k] = 256 * dY;
+                    e[k] = (__mul24(dX, 256 * dy) + q.c[k]) - __mul24(dY, 256 * dx);
+                }
+                float xf = (float)(256 * dx + (int)(short)q.dz);
+                const float zrow = q.zy * (float)(256 * dy + (q.dz >> 16));
+                const int off = (int)((q.pk >> PK_KEY) & ((1u << (PK_SLOT - PK_KEY)) - 1u)) + dy * KS + dx;
+#pragma unroll
+                for (int k = 0; k < SL; ++k) {
+                    const bool in = !DEEP || k == 0 || dx + k <= (int)(q.pk & 31u);
+                    if (in && min(e[0], min(e[1], e[2])) > 0) {
+                        float z = (q.z0 + q.zx * xf) + zrow;
+                        z = fmaxf(z, 0.0f);              // 0 for negative values and NaN
+                        insert_key<DEEP>(key, off + k, ((unsigned long long)__float_as_uint(z) << 32) | q.t, L);
                     }
-                    int x0 = 1, x1 = 0, y0 = 1, y1 = 0;
-                    if (gload(&q->flags) & TRI_VALID) tri_box(b, px0, py0, cx1, cy1, x0, x1, y0, y1);
-                    hit = x0 <= x1 && y0 <= y1;
+                    e[0] -= a[0];
+                    e[1] -= a[1];
+                    e[2] -= a[2];
+                    xf += 256.0f;                        // (exact)
                 }
             }
-            const unsigned long long m = __ballot(hit);
-            if (m == 0ull) continue;
-            n = (unsigned)__popcll(m);
-            const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                                             __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-            // a permutation of the lanes: the hits to the front, in lane order
-            const int dst = hit ? below : (int)n + (lane - below);
-            mine = (unsigned)__builtin_amdgcn_ds_permute(dst * 4, (int)t);
         }
-        raster_batch<TILE, DEEP>(R, mine, n, px0, py0, cx1, cy1, lane, key, L, stage);
+        // ---- its large triangles, 64 pixels of a box per wave and pass
+        const unsigned nbig = S.nbig;
+        for (unsigned i = 0; i < nbig; ++i) {
+            const unsigned ts = (unsigned)__builtin_amdgcn_readfirstlane((int)S.big[i]);
+            const unsigned tt = ts & 0x7FFFFFFFu;
+            const int sb = (int)(ts >> 31);
+            const TriR b = gload(&J.rec[(long long)sb * J.n_tris + tt]);
+            int bx0, bx1, by0, by1;
+            tri_box(b, J.px0, J.py0, J.cx1, J.cy1, bx0, bx1, by0, by1);
+            const int w = bx1 - bx0 + 1, n = w * (by1 - by0 + 1);
+            const unsigned m = ((1u << 20) + (unsigned)w - 1u) / (unsigned)w;     // exact for w <= 32, idx < 1024
+            for (int idx = tid; idx < n; idx += TB) {
+                const int dy = (int)(((unsigned)idx * m) >> 20);
+                const int x = bx0 + idx - dy * w, y = by0 + dy;
+                const int px = 256 * x + 128, py = 256 * y + 128;
+                long long e0, e1, e2;
+                if (!inside(b, px, py, e0, e1, e2)) continue;
+                const float z = depth_at(b, px, py);
+                insert_key<DEEP>(key, (sb * TILE + y - J.py0) * KS + (x - J.px0),
+                                 ((unsigned long long)__float_as_uint(z) << 32) | tt, L);
+            }
+        }
+        __syncthreads();
     }
 }
 
-// After the tile's raster: leave its bin empty for the next use, and the
-// last overflowing tile of the render empties the render's spill list.
-__device__ __forceinline__ void release_bin(unsigned* counts, int tile, unsigned cap, unsigned* spn) {
-    const unsigned c = counts[tile];
-    counts[tile] = 0u;
-    if (c > cap && spn != nullptr && atomicSub(&spn[1], 1u) == 1u) spn[0] = 0u;
+// After the tile's raster: leave its bin (counter *count) empty for the next
+// use, and the last overflowing tile of the render empties the render's spill
+// list.
+__device__ __forceinline__ void release_bin(unsigned* count, unsigned cap, unsigned* spn) {
+    const unsigned c = *count;
+    *count = 0u;
+    if (c > cap && atomicSub(&spn[1], 1u) == 1u) spn[0] = 0u;
 }
 
 // ------------------------------------------------ tile-local aggregation --
@@ -368,7 +447,8 @@ __device__ __forceinline__ void release_bin(unsigned* counts, int tile, unsigned
 
 // A slot packs the group's sum and count into one 64-bit word,
 // sum * 2^12 + count, so one LDS atomic adds both: a tile has at most 1024
-// pixels, so the count stays below 2^12, and |sum| <= 1024 * 2^37 keeps the
+// pixels, so the count stays below 2^12 (a subdivision surface's control
+// vertex is counted once per pixel too), and |sum| <= 1024 * 2^37 keeps the
 // packed word within int64.
 #define PACK_SHIFT 12
 #define PACK_MASK ((1ull << PACK_SHIFT) - 1ull)
@@ -415,6 +495,17 @@ __device__ __forceinline__ void table_add(GroupTable<LOG2T>& tb, long long* __re
     global_add(Rp, K, g, q, c);      // crowded table: go straight to memory
 }
 
+// Adds (q, 1) to N groups (HASH_EMPTY: none), one after another: requesting
+// all their slots at once was 2 to 5 % slower (more of them are then found
+// empty and compare-and-swap on the same words).
+template <int LOG2T, int N>
+__device__ __forceinline__ void table_add_all(GroupTable<LOG2T>& tb, long long* __restrict__ Rp,
+                                              unsigned* __restrict__ K, const unsigned (&g)[N], long long q) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (g[i] != HASH_EMPTY) table_add<LOG2T>(tb, Rp, K, g[i], q, 1u);
+}
+
 // Subdivision surface: pixels whose + and - renders show the same
 // tessellated triangle are combined per wave -- lanes with equal triangle
 // ids are summed with a butterfly -- and the wave's lanes then share the
@@ -442,37 +533,28 @@ __device__ __forceinline__ void wave_ctrl(GroupTable<LOG2T>& tb, long long* __re
     }
 }
 
-// The union of two tessellated triangles' control vertices (both lists
-// ascending), each once, for one pixel.
+// The control vertices of tessellated triangle t, each once for one pixel,
+// without those of triangle tp (both lists ascending; DRD_BG: empty).
 template <int LOG2T>
-__device__ __forceinline__ void ctrl_union_add(GroupTable<LOG2T>& tb, long long* __restrict__ Rp,
-                                               unsigned* __restrict__ K, const DScene& sc, unsigned t0,
-                                               unsigned t1, long long q) {
-    int a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-    if (t0 != DRD_BG) { a0 = sc.tri_rowptr[t0]; a1 = sc.tri_rowptr[t0 + 1]; }
-    if (t1 != DRD_BG) { b0 = sc.tri_rowptr[t1]; b1 = sc.tri_rowptr[t1 + 1]; }
-    int i = a0, j = b0;
-    while (i < a1 || j < b1) {
-        int ga = i < a1 ? sc.tri_cols[i] : 0x7FFFFFFF;
-        int gb = j < b1 ? sc.tri_cols[j] : 0x7FFFFFFF;
-        int g = ga < gb ? ga : gb;
-        if (ga == g) ++i;
-        if (gb == g) ++j;
+__device__ __forceinline__ void ctrl_add(GroupTable<LOG2T>& tb, long long* __restrict__ Rp,
+                                         unsigned* __restrict__ K, const DScene& sc, unsigned t, unsigned tp,
+                                         long long q) {
+    if (t == DRD_BG) return;
+    const int b1 = sc.tri_rowptr[t + 1];
+    int i = 0, a1 = 0;
+    if (tp != DRD_BG) { i = sc.tri_rowptr[tp]; a1 = sc.tri_rowptr[tp + 1]; }
+    for (int j = sc.tri_rowptr[t]; j < b1; ++j) {
+        const int g = sc.tri_cols[j];
+        while (i < a1 && sc.tri_cols[i] < g) ++i;
+        if (i < a1 && sc.tri_cols[i] == g) continue;
         table_add<LOG2T>(tb, Rp, K, (unsigned)g, q, 1u);
     }
 }
 
 // Opaque tile kernels of 8- and 16-pixel tiles are asked for 8 resident
-// waves per SIMD (at most 64 VGPRs): 16-pixel tiles hold 18.7 KB of LDS, so
-// eight blocks of four waves share a CU's 160 KB.  Larger tiles and deep
-// buffers are held to fewer waves by their LDS anyway.
+// waves per SIMD (at most 64 VGPRs): 16-pixel tiles hold 20 KB of LDS in
+// blocks of eight waves.  Larger tiles are held to fewer waves by their LDS.
 #define TILE_MIN_WAVES 8
-
-template <int TILE>
-struct TileCfg {
-    static constexpr int LOG2T = TILE == 8 ? 9 : (TILE == 16 ? 10 : 11);
-};
-
 
 // Everything the tile body needs, resolved by the kernel's prologue.
 struct TileJob {
@@ -481,17 +563,12 @@ struct TileJob {
     const float* theta;
     const uint32_t* pb;                  // sign bits of the pair (null: unperturbed)
     const float* eps;                    // per block
-    float sgn[2];
-    const TriR* recR[2];                 // records of each sign (index = triangle)
-    const TriS* recS[2];
-    const TriG* recG[2];                 // GGX records of each sign
-    unsigned* counts[2];                 // bin counters of each sign (index = tile)
-    const unsigned* bins[2];             // bin entries of each sign (tile * cap + k)
-    unsigned* spn[2];                    // spill counters of each sign, or null
-    const unsigned long long* spill[2];  // spill lists of each sign
-    int cap;
-    int tile;
-    unsigned long long* stats;
+    unsigned flip;                       // one-sign modes: sign 0 is the minus render (all ones) or the plus one
+    RasterJob ras;                       // (its tile's pixels are set by the body)
+    unsigned* counts;                    // bin counter of the tile; sign 1's ras.tstride further
+    unsigned* spn;
+    const TriS* recS;                    // [NS, n_tris]
+    const TriG* recG;
     // estimate
     const float* targets;                // this view's target image (image form: dL/dI)
     int img;                             // image form of the per-pixel difference
@@ -509,127 +586,197 @@ struct TileJob {
     long long* qtot;
 };
 
+// The two sides' values of a pixel, known to both of its lanes: x of the
+// lane below 32 (+) and of the lane above (-).
+__device__ __forceinline__ void both_sides(unsigned x, unsigned& p, unsigned& m) {
+    auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    p = r[0];
+    m = r[1];
+}
+
+__device__ __forceinline__ void both_sides(float x, float& p, float& m) {
+    unsigned a, b;
+    both_sides(__float_as_uint(x), a, b);
+    p = __uint_as_float(a);
+    m = __uint_as_float(b);
+}
+
+// A footprint's texel columns and rows, two 16-bit halves each (texture
+// sides are at most 2^15, so all ones matches no coordinate).  Nearest mode:
+// both the nearest texel's.
+__device__ __forceinline__ void foot_coords(const DScene& sc, int c, float u, float v, unsigned& X, unsigned& Y) {
+    const Foot f = footprint(u, v, sc.cls_w[c], sc.cls_h[c]);
+    int xa = f.xa, xb = f.xb, ya = f.ya, yb = f.yb;
+    if (sc.tex_mode == 1) {
+        xa = xb = (f.fx >= 0.5f) ? f.xb : f.xa;
+        ya = yb = (f.fy >= 0.5f) ? f.yb : f.ya;
+    }
+    X = (unsigned)xa | ((unsigned)xb << 16);
+    Y = (unsigned)ya | ((unsigned)yb << 16);
+}
+
+// Which of a footprint's texels another footprint holds too, as bits
+// 2 row + column.
+__device__ __forceinline__ unsigned foot_shared(unsigned X, unsigned Y, unsigned Xo, unsigned Yo) {
+    const unsigned oxa = Xo & 0xFFFFu, oxb = Xo >> 16, oya = Yo & 0xFFFFu, oyb = Yo >> 16;
+    const unsigned xa = X & 0xFFFFu, xb = X >> 16, ya = Y & 0xFFFFu, yb = Y >> 16;
+    const unsigned cols = ((xa == oxa || xa == oxb) ? 1u : 0u) | ((xb == oxa || xb == oxb) ? 2u : 0u);
+    return ((ya == oya || ya == oyb) ? cols : 0u) | ((yb == oya || yb == oyb) ? cols << 2 : 0u);
+}
+
+// Groups of a footprint's texels that are neither repeated in it nor among
+// `shared` (HASH_EMPTY in the others' place).
+__device__ __forceinline__ void foot_groups(const DScene& sc, int c, unsigned X, unsigned Y, unsigned shared,
+                                            unsigned* g) {
+    const unsigned xa = X & 0xFFFFu, xb = X >> 16, ya = Y & 0xFFFFu, yb = Y >> 16;
+    if (xa == xb) shared |= 0xAu;
+    if (ya == yb) shared |= 0xCu;
+    const unsigned base = (unsigned)sc.cls_goff[c], W = (unsigned)sc.cls_w[c];
+    const unsigned ra = base + __umul24(ya, W), rb = base + __umul24(yb, W);
+    g[0] = (shared & 1u) ? HASH_EMPTY : ra + xa;
+    g[1] = (shared & 2u) ? HASH_EMPTY : ra + xb;
+    g[2] = (shared & 4u) ? HASH_EMPTY : rb + xa;
+    g[3] = (shared & 8u) ? HASH_EMPTY : rb + xb;
+}
+
+template <int LOG2T, int TB>
+__device__ __forceinline__ void table_clear(GroupTable<LOG2T>& tb, int tid) {
+    for (int j = tid; j < (1 << LOG2T); j += TB) {
+        tb.key[j] = HASH_EMPTY;
+        tb.sum[j] = 0ull;
+    }
+}
+
+// The table's groups to the global accumulators.  Occupied slots are first
+// gathered into a dense list, so the atomics go out in full waves.
+template <int LOG2T, int TB>
+__device__ __forceinline__ void table_flush(GroupTable<LOG2T>& tb, unsigned* list, unsigned* n_list, const TileJob& J,
+                                            int tid) {
+    const int lane = tid & 63;
+    for (int j = tid; j < (1 << LOG2T); j += TB) {
+        const bool occ = tb.key[j] != HASH_EMPTY;
+        const unsigned long long m = __ballot(occ);
+        unsigned base = 0;
+        if (lane == 0 && m) base = atomicAdd(n_list, (unsigned)__popcll(m));
+        base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+        if (occ) list[base + lanes_below(m)] = (unsigned)j;
+    }
+    __syncthreads();
+    const unsigned n = *n_list;
+    for (unsigned i = (unsigned)tid; i < n; i += TB) {
+        const unsigned j = list[i];
+        long long q;
+        unsigned c;
+        unpack_sc(tb.sum[j], q, c);
+        global_add(J.Rp, J.K, (long long)tb.key[j], q, c);
+    }
+}
+
+// Sums over the block in a fixed tree order (double: loss) or any order
+// (int64: full-image totals).
+template <int TB, typename T>
+__device__ __forceinline__ T block_sum(T* red, T v, int tid) {
+    red[tid] = v;
+    __syncthreads();
+    for (int w = TB / 2; w > 0; w >>= 1) {
+        if (tid < w) red[tid] = red[tid] + red[tid + w];
+        __syncthreads();
+    }
+    return red[0];
+}
+
+// The loss difference's fixed-point code of a pixel from its two sides'
+// colours; `note`: this lane reports its saturation.
+__device__ __forceinline__ long long pixel_code(const TileJob& J, const float* P, const float* M, long long pix,
+                                                bool note) {
+    int flag;
+    const long long q = quantize(pixel_delta(P, M, J.targets + 3 * pix, J.img), flag);
+    if (flag && note) atomicAdd(&J.ras.stats[flag == 1 ? ST_SATURATIONS : ST_NONFINITE], 1ull);
+    return q;
+}
+
 // MODE: 0 estimate (both signs, scatter), 1 render (write rgb/id/uv),
 // 2 loss (per-tile sum of the per-pixel L2 error f_{w,h}), 3 full-image
 // estimate (both signs, per-tile sum of the fixed-point differences).
 template <int TILE, int MODE>
 struct TileShared {
-    static constexpr int NPIX = TILE * TILE;
-    static constexpr int PPT = NPIX > 256 ? NPIX / 256 : 1;
-    static constexpr int TB = NPIX / PPT;
-    static constexpr int NS = (MODE == 0 || MODE == 3) ? 2 : 1;
-    static constexpr int LOG2T = MODE == 0 ? TileCfg<TILE>::LOG2T : 1;
+    using C = TileCfg<TILE, MODE, false>;
     static constexpr int KS = KeyRow<TILE, false>::N;
-    unsigned long long key[NS][TILE * KS];
-    // the raster's per-wave stages, then (estimate) the group table
+    unsigned long long key[C::NS * TILE * KS];
+    // the raster's stage, then (estimate) the group table, or the sums
     union {
-        RasterStage stage[TB / 64];
-        GroupTable<LOG2T> table;
+        RasterShared<TILE, C::NE, C::NW> ras;
+        struct {
+            GroupTable<C::LOG2T> table;
+            unsigned list[TILE == 8 ? 1 << C::LOG2T : 1];
+        } g;
+        double red[C::TB];
+        long long qred[C::TB];
     } u;
-    double red[MODE == 2 ? TB : 1];
-    long long qred[MODE == 3 ? TB : 1];
     unsigned nfl;                        // occupied table slots (flush)
 };
 
 template <int TILE, int MODE, int SHADE>
-__device__ __forceinline__ void tile_body(const TileJob& J, TileShared<TILE, MODE>& S) {
-    using SH = TileShared<TILE, MODE>;
-    constexpr int NPIX = SH::NPIX, PPT = SH::PPT, TB = SH::TB, NS = SH::NS;
-    constexpr int NW = TB / 64;
-    constexpr int LOG2T = SH::LOG2T;
-    constexpr int TSIZE = 1 << LOG2T;
+__device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S) {
+    using C = TileCfg<TILE, MODE, false>;
+    constexpr int TB = C::TB, NS = C::NS, KS = TileShared<TILE, MODE>::KS, LOG2T = C::LOG2T;
     const DScene& sc = *J.sc;
     const DView& vw = *J.vw;
-    int tx = J.tile % vw.tiles_x, ty = J.tile / vw.tiles_x;
-    int px0 = tx * TILE, py0 = ty * TILE;
-    const int cx1 = min(px0 + TILE - 1, vw.W - 1), cy1 = min(py0 + TILE - 1, vw.H - 1);   // last pixel in view
-    int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    RasterJob& R = J.ras;
+    const int tx = R.tile % vw.tiles_x, ty = R.tile / vw.tiles_x;
+    const int px0 = tx * TILE, py0 = ty * TILE;
+    R.px0 = px0;
+    R.py0 = py0;
+    R.cx1 = min(px0 + TILE - 1, vw.W - 1);
+    R.cy1 = min(py0 + TILE - 1, vw.H - 1);
+    const int tid = threadIdx.x;
 
-    if constexpr (MODE == 0 || MODE == 3) {
+    if constexpr (NS == 2) {
         // no triangle of either render touches the tile: every pixel is
         // background in both, so the tile adds nothing (its bins are empty)
-        if ((J.counts[0][J.tile] | J.counts[NS - 1][J.tile]) == 0u) return;
+        if ((gload(&J.counts[0]) | gload(&J.counts[R.tstride])) == 0u) return;
     }
-    for (int j = tid; j < NS * TILE * SH::KS; j += TB) (&S.key[0][0])[j] = ~0ull;
-    __syncthreads();
-
-    // Both signs' bins: with two signs and several waves, half of the
-    // waves take each sign, so the two chains of dependent reads (bin
-    // counter, entries, records) run at once; one wave takes both in turn.
-    {
-        constexpr int SPLIT = (NS == 2 && NW >= 2) ? 2 : 1;
-        constexpr int NWS = NW / SPLIT;                  // waves per sign
-        const int s_lo = SPLIT == 2 ? wave / NWS : 0;
-        const int s_hi = SPLIT == 2 ? s_lo + 1 : NS;
-        const int wv = wave - s_lo * NWS;
-        for (int s = s_lo; s < s_hi; ++s) {
-            // the sign picked by selects: a run-time index into J's arrays
-            // would move J to private memory
-            const bool s1 = NS == 2 && s == 1;
-            const TriR* __restrict__ R = s1 ? J.recR[NS - 1] : J.recR[0];
-            const unsigned* bins = s1 ? J.bins[NS - 1] : J.bins[0];
-            unsigned* counts = s1 ? J.counts[NS - 1] : J.counts[0];
-            const unsigned* spn = s1 ? J.spn[NS - 1] : J.spn[0];
-            const unsigned long long* spill = s1 ? J.spill[NS - 1] : J.spill[0];
-            unsigned long long* key = s1 ? S.key[NS - 1] : S.key[0];
-            unsigned cnt = counts[J.tile];
-            if (wv == 0 && lane == 0) note_bin(J.stats, cnt, (unsigned)J.cap);
-            raster_render<TILE, false>(R, bins + (long long)J.tile * J.cap, cnt, (unsigned)J.cap, spn, spill,
-                                       sc.n_tris, J.tile, wv, NWS, lane, px0, py0, cx1, cy1, key, 1,
-                                       &S.u.stage[wave], J.stats, wv == 0);
-        }
-    }
-    __syncthreads();
-    if (tid < NS) {                              // leave the bins empty for the next use
-        const bool s1 = NS == 2 && tid == 1;
-        release_bin(s1 ? J.counts[NS - 1] : J.counts[0], J.tile, (unsigned)J.cap, s1 ? J.spn[NS - 1] : J.spn[0]);
-    }
-    if constexpr (MODE == 0) {
-        // the stages are done with: the group table takes their place
-        if (tid == 0) S.nfl = 0u;
-        for (int j = tid; j < TSIZE; j += TB) {
-            S.u.table.key[j] = HASH_EMPTY;
-            S.u.table.sum[j] = 0ull;
-        }
-    }
+    for (int j = tid; j < NS * TILE * KS; j += TB) S.key[j] = ~0ull;
+    if (tid == 0) S.nfl = 0u;
+    raster_tile<TILE, false, NS, TB, C::NE>(R, S.u.ras, S.key, 1);
+    __syncthreads();                             // (a tile without triangles has only cleared its keys)
+    if (tid < NS) release_bin(&J.counts[tid * R.tstride], (unsigned)R.cap, J.spn + 2 * tid);
+    if constexpr (MODE == 0) table_clear<LOG2T, TB>(S.u.g.table, tid);
 
     double loss_acc = 0.0;
     long long qsum = 0;
-    for (int j = 0; j < PPT; ++j) {
-        int local = tid + j * TB;
-        int lx = local % TILE, ly = local / TILE;
-        int x = px0 + lx, y = py0 + ly;
-        bool inpix = x < vw.W && y < vw.H;
-        int px = 256 * x + 128, py = 256 * y + 128;
+    for (int local = tid; local < C::NPIX; local += TB) {
+        const int lx = local % TILE, ly = local / TILE;
+        const int x = px0 + lx, y = py0 + ly;
+        const bool inpix = x < vw.W && y < vw.H;
+        const int px = 256 * x + 128, py = 256 * y + 128;
         unsigned id[NS];
         float rgb[NS][3], uv[NS][2];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            unsigned long long k = inpix ? S.key[s][ly * SH::KS + lx] : ~0ull;
-            id[s] = (k == ~0ull) ? DRD_BG : (unsigned)(k & 0xFFFFFFFFull);
+            const unsigned long long k = inpix ? S.key[(s * TILE + ly) * KS + lx] : ~0ull;
+            id[s] = (k == ~0ull) ? DRD_BG : (unsigned)k;
             rgb[s][0] = 0.0f; rgb[s][1] = 0.0f; rgb[s][2] = 0.0f;
             uv[s][0] = 0.0f; uv[s][1] = 0.0f;
             if (id[s] != DRD_BG) {
-                TriR r = gload(&J.recR[s][id[s]]);
-                TriS sh = gload(&J.recS[s][id[s]]);
-                CornerUV cu = load_cuv(sc, id[s]);
+                const TriR* rec = R.rec + (long long)s * sc.n_tris;
+                const TriS* recS = J.recS + (long long)s * sc.n_tris;
+                const TriG* recG = J.recG + (long long)s * sc.n_tris;
+                const TriR r = gload(&rec[id[s]]);
+                const TriS sh = gload(&recS[id[s]]);
+                const CornerUV cu = load_cuv(sc, id[s]);
                 float alpha;
-                shade_pixel<SHADE, false>(sc, vw, J.theta, J.pb, J.eps, J.sgn[s], r, sh, J.recG[s] + id[s], cu, px, py,
-                                          rgb[s], uv[s], alpha);
+                const unsigned flip = NS == 2 ? (s ? 0xFFFFFFFFu : 0u) : J.flip;
+                shade_pixel<SHADE, false>(sc, vw, J.theta, J.pb, J.eps, flip, r, sh, recG + id[s], cu, px, py, rgb[s],
+                                          uv[s], alpha);
             }
         }
-        long long pix = (long long)y * vw.W + x;
+        const long long pix = (long long)y * vw.W + x;
         if constexpr (MODE == 2) {
             if (inpix) {
                 const float* tg = J.targets + 3 * pix;
                 float dr = rgb[0][0] - tg[0], dg = rgb[0][1] - tg[1], db = rgb[0][2] - tg[2];
                 loss_acc += (double)((dr * dr + dg * dg) + db * db);
-            }
-        } else if constexpr (MODE == 3) {
-            if (inpix && (id[0] != DRD_BG || id[1] != DRD_BG)) {
-                int flag;
-                qsum += quantize(pixel_delta(rgb[0], rgb[1], J.targets + 3 * pix, J.img), flag);
-                if (flag) atomicAdd(&J.stats[flag == 1 ? ST_SATURATIONS : ST_NONFINITE], 1ull);
             }
         } else if constexpr (MODE == 1) {
             if (!inpix) continue;
@@ -645,138 +792,64 @@ __device__ __forceinline__ void tile_body(const TileJob& J, TileShared<TILE, MOD
             }
         } else {
             // an empty contribution set (background in both renders) adds nothing
-            bool act = inpix && (id[0] != DRD_BG || id[1] != DRD_BG) && J.any_act;
+            const bool act = inpix && (id[0] != DRD_BG || id[NS - 1] != DRD_BG) && (MODE == 3 || J.any_act);
             long long q = 0;
-            if (act) {
-                int flag;
-                q = quantize(pixel_delta(rgb[0], rgb[1], J.targets + 3 * pix, J.img), flag);
-                if (flag) atomicAdd(&J.stats[flag == 1 ? ST_SATURATIONS : ST_NONFINITE], 1ull);
-            }
-            if (j == 0) __syncthreads();         // the group table is cleared
-            if (J.act_pos && sc.n_ctrl > 0) {
-                bool same = act && id[0] == id[1];
-                wave_ctrl<LOG2T>(S.u.table, J.Rp, J.K, sc, same, id[0], q);
-                if (act && !same) ctrl_union_add<LOG2T>(S.u.table, J.Rp, J.K, sc, id[0], id[1], q);
-            } else if (J.act_pos && act) {
-                // the union of the two renders' triangles' vertices, each once
-                int v0[3] = {-1, -1, -1};
-                if (id[0] != DRD_BG) {
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        v0[k] = gload(&sc.tri[3 * (long long)id[0] + k]);
-                        table_add<LOG2T>(S.u.table, J.Rp, J.K, (unsigned)v0[k], q, 1u);
+            if (act) q = pixel_code(J, rgb[0], rgb[NS - 1], pix, true);
+            if constexpr (MODE == 3) {
+                qsum += q;
+            } else {
+                if (local == tid) __syncthreads();           // the group table is cleared
+                GroupTable<LOG2T>& tb = S.u.g.table;
+                // the + side's groups, and those of the - side that it does not hold
+                if (J.act_pos && sc.n_ctrl > 0) {
+                    wave_ctrl<LOG2T>(tb, J.Rp, J.K, sc, act && id[0] == id[1], id[0], q);
+                    if (act && id[0] != id[1]) {
+                        ctrl_add<LOG2T>(tb, J.Rp, J.K, sc, id[0], DRD_BG, q);
+                        ctrl_add<LOG2T>(tb, J.Rp, J.K, sc, id[1], id[0], q);
                     }
+                } else if (J.act_pos && act) {
+                    struct Tri3 { unsigned v[3]; };
+                    Tri3 a = {{HASH_EMPTY, HASH_EMPTY, HASH_EMPTY}}, b = a;
+                    if (id[0] != DRD_BG) a = gload((const Tri3*)(sc.tri + 3 * (long long)id[0]));
+                    if (id[1] != DRD_BG && id[1] != id[0]) b = gload((const Tri3*)(sc.tri + 3 * (long long)id[1]));
+                    unsigned g[6];
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        g[i] = a.v[i];
+                        g[3 + i] = (b.v[i] == a.v[0] || b.v[i] == a.v[1] || b.v[i] == a.v[2]) ? HASH_EMPTY : b.v[i];
+                    }
+                    table_add_all<LOG2T>(tb, J.Rp, J.K, g, q);
                 }
-                if (id[1] != DRD_BG && id[1] != id[0]) {
+                if (act) {
+                    for (int c = 0; c < sc.n_cls; ++c) {
+                        if (!J.act_cls[c]) continue;
+                        unsigned X[2] = {0xFFFFFFFFu, 0xFFFFFFFFu}, Y[2] = {0xFFFFFFFFu, 0xFFFFFFFFu}, g[8];
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        int g = gload(&sc.tri[3 * (long long)id[1] + k]);
-                        bool dup = (g == v0[0]) || (g == v0[1]) || (g == v0[2]);
-                        if (!dup) table_add<LOG2T>(S.u.table, J.Rp, J.K, (unsigned)g, q, 1u);
+                        for (int s = 0; s < 2; ++s)
+                            if (id[s] != DRD_BG) foot_coords(sc, c, uv[s][0], uv[s][1], X[s], Y[s]);
+                        foot_groups(sc, c, X[0], Y[0], id[0] != DRD_BG ? 0u : 0xFu, g);
+                        foot_groups(sc, c, X[1], Y[1], id[1] != DRD_BG ? foot_shared(X[1], Y[1], X[0], Y[0]) : 0xFu, g + 4);
+                        table_add_all<LOG2T>(tb, J.Rp, J.K, g, q);
                     }
-                }
-            }
-            if (act) {
-                for (int c = 0; c < sc.n_cls; ++c) {
-                    if (!J.act_cls[c]) continue;
-                    int W = sc.cls_w[c], H = sc.cls_h[c];
-                    unsigned base = (unsigned)sc.cls_goff[c];
-                    unsigned gs[NS][4];
-#pragma unroll
-                    for (int s = 0; s < NS; ++s) {
-                        gs[s][0] = gs[s][1] = gs[s][2] = gs[s][3] = HASH_EMPTY;
-                        if (id[s] == DRD_BG) continue;
-                        Foot f = footprint(uv[s][0], uv[s][1], W, H);
-                        if (sc.tex_mode == 1) {
-                            int xn = (f.fx >= 0.5f) ? f.xb : f.xa;
-                            int yn = (f.fy >= 0.5f) ? f.yb : f.ya;
-                            gs[s][0] = base + (__umul24((unsigned)yn, (unsigned)W) + (unsigned)xn);
-                        } else {
-                            gs[s][0] = base + (__umul24((unsigned)f.ya, (unsigned)W) + (unsigned)f.xa);
-                            gs[s][1] = base + (__umul24((unsigned)f.ya, (unsigned)W) + (unsigned)f.xb);
-                            gs[s][2] = base + (__umul24((unsigned)f.yb, (unsigned)W) + (unsigned)f.xa);
-                            gs[s][3] = base + (__umul24((unsigned)f.yb, (unsigned)W) + (unsigned)f.xb);
-                        }
-                    }
-#pragma unroll
-                    for (int s = 0; s < NS; ++s)
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            unsigned g = gs[s][k];
-                            if (g == HASH_EMPTY) continue;
-                            bool dup = false;
-#pragma unroll
-                            for (int j2 = 0; j2 < 4; ++j2)
-                                if (j2 < k && gs[s][j2] == g) dup = true;
-                            if (s == 1) {
-#pragma unroll
-                                for (int j2 = 0; j2 < 4; ++j2)
-                                    if (gs[0][j2] == g) dup = true;
-                            }
-                            if (!dup) table_add<LOG2T>(S.u.table, J.Rp, J.K, g, q, 1u);
-                        }
                 }
             }
         }
     }
     if constexpr (MODE == 2) {
-        // fixed-order tree reduction of the tile's per-pixel errors
-        S.red[tid] = loss_acc;
-        __syncthreads();
-        for (int w = TB / 2; w > 0; w >>= 1) {
-            if (tid < w) S.red[tid] = S.red[tid] + S.red[tid + w];
-            __syncthreads();
-        }
-        if (tid == 0) *J.partial = S.red[0];
+        loss_acc = block_sum<TB>(S.u.red, loss_acc, tid);
+        if (tid == 0) *J.partial = loss_acc;
     }
     if constexpr (MODE == 3) {
-        // integer sums: the order of the additions does not matter
-        S.qred[tid] = qsum;
-        __syncthreads();
-        for (int w = TB / 2; w > 0; w >>= 1) {
-            if (tid < w) S.qred[tid] = S.qred[tid] + S.qred[tid + w];
-            __syncthreads();
-        }
-        if (tid == 0 && S.qred[0] != 0) atomicAdd((unsigned long long*)J.qtot, (unsigned long long)S.qred[0]);
+        qsum = block_sum<TB>(S.u.qred, qsum, tid);
+        if (tid == 0 && qsum != 0) atomicAdd((unsigned long long*)J.qtot, (unsigned long long)qsum);
     }
     if constexpr (MODE == 0) {
         __syncthreads();
-        if constexpr (TILE >= 16) {
-            // occupied slots first gathered into a dense list (in the key
-            // buffers, free by now and large enough from 16-pixel tiles
-            // on), so the global atomics go out in full waves
-            unsigned* list = reinterpret_cast<unsigned*>(&S.key[0][0]);
-            for (int j = tid; j < TSIZE; j += TB) {
-                bool occ = S.u.table.key[j] != HASH_EMPTY;
-                unsigned long long m = __ballot(occ);
-                unsigned base = 0;
-                if (lane == 0 && m) base = atomicAdd(&S.nfl, (unsigned)__popcll(m));
-                base = __shfl(base, 0);
-                if (occ) list[base + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = (unsigned)j;
-            }
-            __syncthreads();
-            unsigned n = S.nfl;
-            for (unsigned i = (unsigned)tid; i < n; i += TB) {
-                unsigned j = list[i];
-                long long q;
-                unsigned c;
-                unpack_sc(S.u.table.sum[j], q, c);
-                global_add(J.Rp, J.K, (long long)S.u.table.key[j], q, c);
-            }
-        } else {
-            for (int j = tid; j < TSIZE; j += TB) {
-                unsigned g = S.u.table.key[j];
-                if (g != HASH_EMPTY) {
-                    long long q;
-                    unsigned c;
-                    unpack_sc(S.u.table.sum[j], q, c);
-                    global_add(J.Rp, J.K, (long long)g, q, c);
-                }
-            }
-        }
+        // the list of occupied slots takes the keys' place where it fits
+        unsigned* list = TILE == 8 ? S.u.g.list : reinterpret_cast<unsigned*>(S.key);
+        table_flush<LOG2T, TB>(S.u.g.table, list, &S.nfl, J, tid);
     }
 }
-
 
 // ------------------------------------------------- semi-transparent tile --
 //
@@ -791,127 +864,96 @@ __device__ __forceinline__ void tile_body(const TileJob& J, TileShared<TILE, MOD
 
 template <int TILE, int MODE>
 struct DeepShared {
-    static constexpr int NPIX = TILE * TILE;
-    static constexpr int TB = NPIX;
-    static constexpr int NS = (MODE == 0 || MODE == 3) ? 2 : 1;
-    static constexpr int LOG2T = MODE == 0 ? TileCfg<TILE>::LOG2T : 1;
-    unsigned long long key[NS][NPIX * DRD_MAX_LAYERS];
-    // the raster's per-wave stages, then (estimate) the group table
+    using C = TileCfg<TILE, MODE, true>;
+    unsigned long long key[C::NS * C::NPIX * DRD_MAX_LAYERS];
+    float v[MODE == 0 ? C::NS * C::NPIX * DRD_MAX_LAYERS : 1];      // the fragments' texture coordinate v
+    // the raster's stage, then (estimate) the group table, or the sums
     union {
-        RasterStage stage[TB / 64 > 0 ? TB / 64 : 1];
-        GroupTable<LOG2T> table;
+        RasterShared<TILE, C::NE, C::NW> ras;
+        struct {
+            GroupTable<C::LOG2T> table;
+            unsigned list[1 << C::LOG2T];
+        } g;
+        double red[C::TB];
+        long long qred[C::TB];
     } u;
-    double red[MODE == 2 ? TB : 1];
-    long long qred[MODE == 3 ? TB : 1];
+    unsigned nfl;
 };
 
-// Texel groups of one fragment in class c: the bilinear footprint, or the
-// nearest texel (the other entries HASH_EMPTY).
-__device__ __forceinline__ void texel_groups(const DScene& sc, int c, float u, float v, unsigned* gs) {
-    int W = sc.cls_w[c], H = sc.cls_h[c];
-    unsigned base = (unsigned)sc.cls_goff[c];
-    Foot f = footprint(u, v, W, H);
-    if (sc.tex_mode == 1) {
-        int xn = (f.fx >= 0.5f) ? f.xb : f.xa;
-        int yn = (f.fy >= 0.5f) ? f.yb : f.ya;
-        gs[0] = base + (__umul24((unsigned)yn, (unsigned)W) + (unsigned)xn);
-        gs[1] = gs[2] = gs[3] = HASH_EMPTY;
-    } else {
-        gs[0] = base + (__umul24((unsigned)f.ya, (unsigned)W) + (unsigned)f.xa);
-        gs[1] = base + (__umul24((unsigned)f.ya, (unsigned)W) + (unsigned)f.xb);
-        gs[2] = base + (__umul24((unsigned)f.yb, (unsigned)W) + (unsigned)f.xa);
-        gs[3] = base + (__umul24((unsigned)f.yb, (unsigned)W) + (unsigned)f.xb);
-    }
-}
-
 template <int TILE, int MODE, int SHADE>
-__device__ __forceinline__ void tile_body_deep(const TileJob& J, DeepShared<TILE, MODE>& S) {
-    using SH = DeepShared<TILE, MODE>;
-    constexpr int NPIX = SH::NPIX, TB = SH::TB, NS = SH::NS;
-    constexpr int NW = TB / 64 > 0 ? TB / 64 : 1;
-    constexpr int LOG2T = SH::LOG2T;
-    constexpr int TSIZE = 1 << LOG2T;
+__device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE>& S) {
+    using C = TileCfg<TILE, MODE, true>;
+    constexpr int TB = C::TB, NS = C::NS, NPIX = C::NPIX, LOG2T = C::LOG2T;
     constexpr int LM = DRD_MAX_LAYERS;
-    constexpr int NE = NS * LM;                    // fragment entries per pixel
     const DScene& sc = *J.sc;
     const DView& vw = *J.vw;
     const int L = sc.layers;
-    int tx = J.tile % vw.tiles_x, ty = J.tile / vw.tiles_x;
-    int px0 = tx * TILE, py0 = ty * TILE;
-    const int cx1 = min(px0 + TILE - 1, vw.W - 1), cy1 = min(py0 + TILE - 1, vw.H - 1);   // last pixel in view
-    int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    RasterJob& R = J.ras;
+    const int tx = R.tile % vw.tiles_x, ty = R.tile / vw.tiles_x;
+    const int px0 = tx * TILE, py0 = ty * TILE;
+    R.px0 = px0;
+    R.py0 = py0;
+    R.cx1 = min(px0 + TILE - 1, vw.W - 1);
+    R.cy1 = min(py0 + TILE - 1, vw.H - 1);
+    const int tid = threadIdx.x, lane = tid & 63;
 
-    if constexpr (MODE == 0 || MODE == 3) {
+    if constexpr (NS == 2) {
         // no fragment in either render: the tile adds nothing
-        if ((J.counts[0][J.tile] | J.counts[NS - 1][J.tile]) == 0u) return;
+        if ((gload(&J.counts[0]) | gload(&J.counts[R.tstride])) == 0u) return;
     }
-    for (int j = tid; j < NS * NPIX * LM; j += TB) (&S.key[0][0])[j] = ~0ull;
+    for (int j = tid; j < NS * NPIX * LM; j += TB) S.key[j] = ~0ull;
+    if (tid == 0) S.nfl = 0u;
+    raster_tile<TILE, true, NS, TB, C::NE>(R, S.u.ras, S.key, L);
     __syncthreads();
+    if (tid < NS) release_bin(&J.counts[tid * R.tstride], (unsigned)R.cap, J.spn + 2 * tid);
+    if constexpr (MODE == 0) table_clear<LOG2T, TB>(S.u.g.table, tid);
 
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        unsigned cnt = J.counts[s][J.tile];
-        if (tid == 0) note_bin(J.stats, cnt, (unsigned)J.cap);
-        const TriR* __restrict__ R = J.recR[s];
-        raster_render<TILE, true>(R, J.bins[s] + (long long)J.tile * J.cap, cnt, (unsigned)J.cap, J.spn[s],
-                                  J.spill[s], sc.n_tris, J.tile, wave, NW, lane, px0, py0, cx1, cy1, S.key[s], L,
-                                  &S.u.stage[wave], J.stats, wave == 0);
-    }
-    __syncthreads();
-    if (tid == 0) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) release_bin(J.counts[s], J.tile, (unsigned)J.cap, J.spn[s]);
-    }
-    if constexpr (MODE == 0) {
-        // the stages are done with: the group table takes their place
-        for (int j = tid; j < TSIZE; j += TB) {
-            S.u.table.key[j] = HASH_EMPTY;
-            S.u.table.sum[j] = 0ull;
-        }
-    }
-
-    int local = tid;
-    int lx = local % TILE, ly = local / TILE;
-    int x = px0 + lx, y = py0 + ly;
-    bool inpix = x < vw.W && y < vw.H;
-    int px = 256 * x + 128, py = 256 * y + 128;
-    long long pix = (long long)y * vw.W + x;
+    const int side = NS == 2 ? lane >> 5 : 0;
+    const int local = NS == 2 ? (tid >> 6) * 32 + (lane & 31) : tid;
+    const int lx = local % TILE, ly = local / TILE;
+    const int x = px0 + lx, y = py0 + ly;
+    const bool inpix = x < vw.W && y < vw.H;
+    const int px = 256 * x + 128, py = 256 * y + 128;
+    const long long pix = (long long)y * vw.W + x;
+    unsigned long long* mine = &S.key[(side * NPIX + local) * LM];   // this side's fragments
+    float* mine_v = &S.v[MODE == 0 ? (side * NPIX + local) * LM : 0];
     // Lists fill from the front, so a list is empty when its first layer is.
-    // The loops over layers stay rolled (the fragments are re-read from the
-    // LDS list, their UVs recomputed where needed) so that nothing indexed
-    // by layer has to live in registers.
-    float rgb[NS][3];
+    // The loop over layers stays rolled: one copy of the shading.  For the
+    // scatter a fragment keeps its id and its texture coordinates (u over the
+    // key's depth, v beside).
+    float rgb[3] = {0.0f, 0.0f, 0.0f};
     bool any = false;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        rgb[s][0] = 0.0f; rgb[s][1] = 0.0f; rgb[s][2] = 0.0f;
-        float T = 1.0f;
-        for (int l = 0; l < L; ++l) {
-            unsigned long long k = inpix ? S.key[s][local * LM + l] : ~0ull;
-            unsigned id = (k == ~0ull) ? DRD_BG : (unsigned)(k & 0xFFFFFFFFull);
-            float uv[2] = {0.0f, 0.0f};
-            if (id != DRD_BG) {
-                any = true;
-                TriR r = gload(&J.recR[s][id]);
-                TriS sh = gload(&J.recS[s][id]);
-                CornerUV cu = load_cuv(sc, id);
-                float c[3], al;
-                shade_pixel<SHADE, true>(sc, vw, J.theta, J.pb, J.eps, J.sgn[s], r, sh, J.recG[s] + id, cu, px, py, c,
-                                         uv, al);
-                float wt = T * al;
-                rgb[s][0] = rgb[s][0] + wt * c[0];
-                rgb[s][1] = rgb[s][1] + wt * c[1];
-                rgb[s][2] = rgb[s][2] + wt * c[2];
-                T = T * (1.0f - al);
+    float T = 1.0f;
+    for (int l = 0; l < L; ++l) {
+        const unsigned long long k = inpix ? mine[l] : ~0ull;
+        const unsigned id = (k == ~0ull) ? DRD_BG : (unsigned)k;
+        float uv[2] = {0.0f, 0.0f};
+        if (id != DRD_BG) {
+            any = true;
+            const unsigned ti = id + (unsigned)side * (unsigned)sc.n_tris;
+            const TriR r = gload(&R.rec[ti]);
+            const TriS sh = gload(&J.recS[ti]);
+            const CornerUV cu = load_cuv(sc, id);
+            float c[3], al;
+            const unsigned flip = NS == 2 ? (unsigned)-side : J.flip;
+            shade_pixel<SHADE, true>(sc, vw, J.theta, J.pb, J.eps, flip, r, sh, J.recG + ti, cu, px, py, c, uv, al);
+            const float wt = T * al;
+            rgb[0] = rgb[0] + wt * c[0];
+            rgb[1] = rgb[1] + wt * c[1];
+            rgb[2] = rgb[2] + wt * c[2];
+            T = T * (1.0f - al);
+            if constexpr (MODE == 0) {
+                mine[l] = ((unsigned long long)__float_as_uint(uv[0]) << 32) | id;
+                mine_v[l] = uv[1];
             }
-            if constexpr (MODE == 1) {
-                if (inpix) {
-                    long long e = pix * L + l;
-                    if (J.out_id) J.out_id[e] = id;
-                    if (J.out_uv) {
-                        J.out_uv[2 * e + 0] = uv[0];
-                        J.out_uv[2 * e + 1] = uv[1];
-                    }
+        }
+        if constexpr (MODE == 1) {
+            if (inpix) {
+                const long long e = pix * L + l;
+                if (J.out_id) J.out_id[e] = id;
+                if (J.out_uv) {
+                    J.out_uv[2 * e + 0] = uv[0];
+                    J.out_uv[2 * e + 1] = uv[1];
                 }
             }
         }
@@ -919,9 +961,9 @@ __device__ __forceinline__ void tile_body_deep(const TileJob& J, DeepShared<TILE
 
     if constexpr (MODE == 1) {
         if (inpix && J.out_rgb) {
-            J.out_rgb[3 * pix + 0] = rgb[0][0];
-            J.out_rgb[3 * pix + 1] = rgb[0][1];
-            J.out_rgb[3 * pix + 2] = rgb[0][2];
+            J.out_rgb[3 * pix + 0] = rgb[0];
+            J.out_rgb[3 * pix + 1] = rgb[1];
+            J.out_rgb[3 * pix + 2] = rgb[2];
         }
         return;
     }
@@ -929,111 +971,104 @@ __device__ __forceinline__ void tile_body_deep(const TileJob& J, DeepShared<TILE
         double loss_acc = 0.0;
         if (inpix) {
             const float* tg = J.targets + 3 * pix;
-            float dr = rgb[0][0] - tg[0], dg = rgb[0][1] - tg[1], db = rgb[0][2] - tg[2];
+            float dr = rgb[0] - tg[0], dg = rgb[1] - tg[1], db = rgb[2] - tg[2];
             loss_acc = (double)((dr * dr + dg * dg) + db * db);
         }
-        S.red[tid] = loss_acc;
-        __syncthreads();
-        for (int w = TB / 2; w > 0; w >>= 1) {
-            if (tid < w) S.red[tid] = S.red[tid] + S.red[tid + w];
-            __syncthreads();
-        }
-        if (tid == 0) *J.partial = S.red[0];
+        loss_acc = block_sum<TB>(S.u.red, loss_acc, tid);
+        if (tid == 0) *J.partial = loss_acc;
         return;
     }
-    if constexpr (MODE == 3) {
-        long long qsum = 0;
-        if (inpix && any) {
-            int flag;
-            qsum = quantize(pixel_delta(rgb[0], rgb[1], J.targets + 3 * pix, J.img), flag);
-            if (flag) atomicAdd(&J.stats[flag == 1 ? ST_SATURATIONS : ST_NONFINITE], 1ull);
-        }
-        S.qred[tid] = qsum;
-        __syncthreads();
-        for (int w = TB / 2; w > 0; w >>= 1) {
-            if (tid < w) S.qred[tid] = S.qred[tid] + S.qred[tid + w];
+    if constexpr (MODE == 0 || MODE == 3) {
+        unsigned anyP, anyM;
+        float P[3], M[3];
+        both_sides(any ? 1u : 0u, anyP, anyM);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) both_sides(rgb[c], P[c], M[c]);
+        const bool act = inpix && (anyP | anyM) != 0u && (MODE == 3 || J.any_act);
+        long long q = 0;
+        if (act) q = pixel_code(J, P, M, pix, side == 0);
+        if constexpr (MODE == 3) {
+            q = block_sum<TB>(S.u.qred, side == 0 ? q : 0ll, tid);
+            if (tid == 0 && q != 0) atomicAdd((unsigned long long*)J.qtot, (unsigned long long)q);
+        } else {
+            __syncthreads();                         // the group table is cleared
+            GroupTable<LOG2T>& tb = S.u.g.table;
+            // Each side adds its own fragments' groups, each by the first
+            // fragment that holds it; the - side leaves out what the + side
+            // holds.  Empty layers have all ones for a vertex or coordinate.
+            if (J.act_pos) {
+                struct Tri3 { unsigned v[3]; };
+                Tri3 g[LM];
+#pragma unroll
+                for (int l = 0; l < LM; ++l) {
+                    g[l] = {{DRD_BG, DRD_BG, DRD_BG}};
+                    if (l < L && act && mine[l] != ~0ull)
+                        g[l] = gload((const Tri3*)(sc.tri + 3 * (long long)(unsigned)mine[l]));
+                }
+                bool dup[LM][3];
+#pragma unroll
+                for (int l = 0; l < LM; ++l)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        dup[l][i] = g[l].v[i] == DRD_BG;
+#pragma unroll
+                        for (int o = 0; o < l; ++o)
+                            dup[l][i] = dup[l][i] || g[l].v[i] == g[o].v[0] || g[l].v[i] == g[o].v[1] ||
+                                        g[l].v[i] == g[o].v[2];
+                    }
+#pragma unroll
+                for (int o = 0; o < LM; ++o) {
+                    if (o >= L) break;
+                    unsigned gp[3], gm;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) both_sides(g[o].v[i], gp[i], gm);
+#pragma unroll
+                    for (int l = 0; l < LM; ++l)
+#pragma unroll
+                        for (int i = 0; i < 3; ++i)
+                            dup[l][i] = dup[l][i] || (side && (g[l].v[i] == gp[0] || g[l].v[i] == gp[1] ||
+                                                               g[l].v[i] == gp[2]));
+                }
+#pragma unroll
+                for (int l = 0; l < LM; ++l) {
+                    if (l >= L) break;
+                    const unsigned gl[3] = {dup[l][0] ? HASH_EMPTY : g[l].v[0], dup[l][1] ? HASH_EMPTY : g[l].v[1],
+                                            dup[l][2] ? HASH_EMPTY : g[l].v[2]};
+                    table_add_all<LOG2T>(tb, J.Rp, J.K, gl, q);
+                }
+            }
+            for (int c = 0; c < sc.n_cls; ++c) {
+                if (!J.act_cls[c]) continue;
+                unsigned X[LM], Y[LM], shared[LM];
+#pragma unroll
+                for (int l = 0; l < LM; ++l) {
+                    X[l] = Y[l] = 0xFFFFFFFFu;
+                    if (l < L && act && mine[l] != ~0ull)
+                        foot_coords(sc, c, __uint_as_float((unsigned)(mine[l] >> 32)), mine_v[l], X[l], Y[l]);
+                    shared[l] = X[l] == 0xFFFFFFFFu ? 0xFu : 0u;
+                }
+#pragma unroll
+                for (int o = 0; o < LM; ++o) {
+                    if (o >= L) break;
+                    unsigned Xp, Yp, other;
+                    both_sides(X[o], Xp, other);
+                    both_sides(Y[o], Yp, other);
+#pragma unroll
+                    for (int l = 0; l < LM; ++l) {
+                        if (l > o) shared[l] |= foot_shared(X[l], Y[l], X[o], Y[o]);
+                        if (side) shared[l] |= foot_shared(X[l], Y[l], Xp, Yp);
+                    }
+                }
+#pragma unroll
+                for (int l = 0; l < LM; ++l) {
+                    if (shared[l] == 0xFu) continue;
+                    unsigned g[4];
+                    foot_groups(sc, c, X[l], Y[l], shared[l], g);
+                    table_add_all<LOG2T>(tb, J.Rp, J.K, g, q);
+                }
+            }
             __syncthreads();
-        }
-        if (tid == 0 && S.qred[0] != 0) atomicAdd((unsigned long long*)J.qtot, (unsigned long long)S.qred[0]);
-        return;
-    }
-    if constexpr (MODE == 0) {
-        __syncthreads();                             // the group table is cleared
-        bool act = inpix && any && J.any_act;
-        if (act) {
-            int flag;
-            long long q = quantize(pixel_delta(rgb[0], rgb[1], J.targets + 3 * pix, J.img), flag);
-            if (flag) atomicAdd(&J.stats[flag == 1 ? ST_SATURATIONS : ST_NONFINITE], 1ull);
-            // fragment e = s * L + l; each group is added by the first
-            // fragment that holds it
-            const int NF = NS * L;
-            for (int e = 0; e < NF; ++e) {
-                int s1 = e / L, l1 = e % L;
-                unsigned long long k1 = (&S.key[0][0])[(s1 * NPIX + local) * LM + l1];
-                if (k1 == ~0ull) continue;
-                unsigned id1 = (unsigned)(k1 & 0xFFFFFFFFull);
-                if (J.act_pos) {
-                    int v1[3];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) v1[k] = gload(&sc.tri[3 * (long long)id1 + k]);
-                    bool dup[3] = {false, false, false};
-                    for (int e2 = 0; e2 < e; ++e2) {
-                        unsigned long long k2 = (&S.key[0][0])[((e2 / L) * NPIX + local) * LM + e2 % L];
-                        if (k2 == ~0ull) continue;
-                        const int* t2 = sc.tri + 3 * (long long)(unsigned)(k2 & 0xFFFFFFFFull);
-                        int v2[3] = {gload(&t2[0]), gload(&t2[1]), gload(&t2[2])};
-#pragma unroll
-                        for (int k = 0; k < 3; ++k)
-                            dup[k] = dup[k] || v1[k] == v2[0] || v1[k] == v2[1] || v1[k] == v2[2];
-                    }
-#pragma unroll
-                    for (int k = 0; k < 3; ++k)
-                        if (!dup[k]) table_add<LOG2T>(S.u.table, J.Rp, J.K, (unsigned)v1[k], q, 1u);
-                }
-                if (J.any_act && sc.n_cls > 0) {
-                    Attr a1 = frag_attr(sc, (s1 ? J.recR[1] : J.recR[0])[id1], (s1 ? J.recS[1] : J.recS[0])[id1],
-                                        load_cuv(sc, id1), px, py);
-                    for (int c = 0; c < sc.n_cls; ++c) {
-                        if (!J.act_cls[c]) continue;
-                        unsigned gs[4];
-                        texel_groups(sc, c, a1.u, a1.v, gs);
-                        bool dup[4];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            dup[k] = gs[k] == HASH_EMPTY;
-#pragma unroll
-                            for (int k2 = 0; k2 < 4; ++k2)
-                                if (k2 < k && gs[k2] == gs[k]) dup[k] = true;
-                        }
-                        for (int e2 = 0; e2 < e; ++e2) {
-                            unsigned long long k2 = (&S.key[0][0])[((e2 / L) * NPIX + local) * LM + e2 % L];
-                            if (k2 == ~0ull) continue;
-                            unsigned id2 = (unsigned)(k2 & 0xFFFFFFFFull);
-                            Attr a2 = frag_attr(sc, (e2 >= L ? J.recR[1] : J.recR[0])[id2],
-                                                (e2 >= L ? J.recS[1] : J.recS[0])[id2], load_cuv(sc, id2), px, py);
-                            unsigned gs2[4];
-                            texel_groups(sc, c, a2.u, a2.v, gs2);
-#pragma unroll
-                            for (int k = 0; k < 4; ++k)
-                                dup[k] = dup[k] || gs[k] == gs2[0] || gs[k] == gs2[1] || gs[k] == gs2[2] ||
-                                         gs[k] == gs2[3];
-                        }
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            if (!dup[k]) table_add<LOG2T>(S.u.table, J.Rp, J.K, gs[k], q, 1u);
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        for (int j = tid; j < TSIZE; j += TB) {
-            unsigned g = S.u.table.key[j];
-            if (g != HASH_EMPTY) {
-                long long q;
-                unsigned c;
-                unpack_sc(S.u.table.sum[j], q, c);
-                global_add(J.Rp, J.K, (long long)g, q, c);
-            }
+            table_flush<LOG2T, TB>(tb, S.u.g.list, &S.nfl, J, tid);
         }
     }
 }
@@ -1051,11 +1086,11 @@ __device__ __forceinline__ void tile_body_deep(const TileJob& J, DeepShared<TILE
 // Measured at 1024 px, 46080 triangles, GGX, 32 items: 1989 -> 1586 us
 // (specialised and interleaved; the interleaved general kernel 1640 us).
 template <int TILE, int MODE, bool DEEP, int SHADE>
-__global__ void __launch_bounds__((TILE * TILE > 256) ? 256 : TILE * TILE, (DEEP || TILE > 16) ? 1 : TILE_MIN_WAVES)
+__global__ void __launch_bounds__((TileCfg<TILE, MODE, DEEP>::TB), (DEEP || TILE > 16) ? 1 : TILE_MIN_WAVES)
 k_tile(TileArgs a) {
     using SH = std::conditional_t<DEEP, DeepShared<TILE, MODE>, TileShared<TILE, MODE>>;
     __shared__ SH S;
-    constexpr int NS = SH::NS;
+    constexpr int NS = TileCfg<TILE, MODE, DEEP>::NS;
     const DScene& sc = a.sc;
     int li, pair, view, tile;
     if (a.interleave) {
@@ -1082,25 +1117,21 @@ k_tile(TileArgs a) {
     J.theta = a.theta;
     J.pb = a.pert.bits ? a.pert.bits + (long long)pair * sc.words : nullptr;
     J.eps = a.pert.eps;
-    J.sgn[0] = a.sgn[0];
-    J.sgn[1] = a.sgn[1];
-    const int gslot = (pair - a.item0 / a.n_views) * NS;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int s1 = s < NS ? s : 0;
-        const int slot = li * NS + s1;
-        const long long base = bin_base(a.whole, a.views, a.n_views, NS, a.max_tiles, li, s1);
-        J.recR[s] = a.recR + (long long)slot * sc.n_tris;
-        J.recS[s] = a.recS + (long long)slot * sc.n_tris;
-        J.recG[s] = a.recG + (long long)(gslot + s1) * sc.n_tris;
-        J.counts[s] = a.counts + base;
-        J.bins[s] = a.bins + base * a.cap;
-        J.spn[s] = a.spn + 2ll * slot;
-        J.spill[s] = a.spill + (long long)slot * SPILL_CAP;
-    }
-    J.cap = a.cap;
-    J.tile = tile;
-    J.stats = a.stats;
+    J.flip = a.sgn[0] > 0.0f ? 0u : 0xFFFFFFFFu;
+    const long long slot = (long long)li * NS;
+    const long long base = bin_base(a.whole, a.views, a.n_views, NS, a.max_tiles, li, 0) + tile;
+    J.ras.rec = a.recR + slot * sc.n_tris;
+    J.ras.n_tris = sc.n_tris;
+    J.ras.counts = J.counts = a.counts + base;
+    J.ras.bins = a.bins + base * a.cap;
+    J.ras.tstride = a.whole ? vw.tiles_x * vw.tiles_y : a.max_tiles;
+    J.ras.cap = a.cap;
+    J.ras.spn = J.spn = a.spn + 2 * slot;
+    J.ras.spill = a.spill + slot * SPILL_CAP;
+    J.ras.tile = tile;
+    J.ras.stats = a.stats;
+    J.recS = a.recS + slot * sc.n_tris;
+    J.recG = a.recG + (long long)(pair - a.item0 / a.n_views) * NS * sc.n_tris;
     J.targets = a.targets ? a.targets + vw.tgt_off : nullptr;
     J.img = a.img_grad;
     J.Rp = (MODE == 0) ? a.R + (long long)pair * sc.G : nullptr;
@@ -1121,7 +1152,7 @@ k_tile(TileArgs a) {
 // batch of several scenes: one workgroup per unit, units in the XCD-aware
 // order of xcd_tile(), items of the costliest scenes first.
 template <int TILE, int SHADE>
-__global__ void __launch_bounds__((TILE * TILE > 256) ? 256 : TILE * TILE, TILE > 16 ? 1 : TILE_MIN_WAVES)
+__global__ void __launch_bounds__((TileCfg<TILE, 0, false>::TB), TILE > 16 ? 1 : TILE_MIN_WAVES)
 k_tile_b(BatchArgs b) {
     __shared__ TileShared<TILE, 0> S;
     const long long w = b.unit0 + xcd_tile(blockIdx.x, gridDim.x);
@@ -1138,21 +1169,20 @@ k_tile_b(BatchArgs b) {
     J.theta = Sc.theta;
     J.pb = Sc.bits + (long long)I.pair * sc.words;
     J.eps = Sc.eps;
-    J.sgn[0] = 1.0f;
-    J.sgn[1] = -1.0f;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        J.recR[s] = b.recR + I.rec_off + (long long)s * sc.n_tris;
-        J.recS[s] = b.recS + I.rec_off + (long long)s * sc.n_tris;
-        J.recG[s] = b.recG + I.g_off + (long long)s * sc.n_tris;
-        J.counts[s] = b.counts + I.cnt_off + (long long)s * tiles;
-        J.bins[s] = b.bins + I.bin_off + (long long)s * tiles * I.cap;
-        J.spn[s] = b.spn + 2 * (I.sp_off + s);
-        J.spill[s] = b.spill + (I.sp_off + s) * SPILL_CAP;
-    }
-    J.cap = I.cap;
-    J.tile = (int)(w - I.tile0);
-    J.stats = b.stats;
+    J.flip = 0u;
+    const int tile = (int)(w - I.tile0);
+    J.ras.rec = b.recR + I.rec_off;
+    J.ras.n_tris = sc.n_tris;
+    J.ras.counts = J.counts = b.counts + I.cnt_off + tile;
+    J.ras.bins = b.bins + I.bin_off + (long long)tile * I.cap;
+    J.ras.tstride = tiles;
+    J.ras.cap = I.cap;
+    J.ras.spn = J.spn = b.spn + 2 * I.sp_off;
+    J.ras.spill = b.spill + I.sp_off * SPILL_CAP;
+    J.ras.tile = tile;
+    J.ras.stats = b.stats;
+    J.recS = b.recS + I.rec_off;
+    J.recG = b.recG + I.g_off;
     J.targets = Sc.targets + vw.tgt_off;
     J.img = 0;
     J.Rp = Sc.R + (long long)I.pair * sc.G;
@@ -1170,11 +1200,11 @@ k_tile_b(BatchArgs b) {
 
 template <int TILE, bool DEEP, int SHADE>
 static void launch_tile_mode(hipStream_t st, const TileArgs& a, int mode, dim3 grid) {
-    dim3 block((TILE * TILE > 256) ? 256 : TILE * TILE);
-    if (mode == 0) hipLaunchKernelGGL((k_tile<TILE, 0, DEEP, SHADE>), grid, block, 0, st, a);
-    else if (mode == 1) hipLaunchKernelGGL((k_tile<TILE, 1, DEEP, SHADE>), grid, block, 0, st, a);
-    else if (mode == 2) hipLaunchKernelGGL((k_tile<TILE, 2, DEEP, SHADE>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((k_tile<TILE, 3, DEEP, SHADE>), grid, block, 0, st, a);
+    const dim3 one(TileCfg<TILE, 1, DEEP>::TB), two(TileCfg<TILE, 0, DEEP>::TB);      // threads of one- and two-sign tiles
+    if (mode == 0) hipLaunchKernelGGL((k_tile<TILE, 0, DEEP, SHADE>), grid, two, 0, st, a);
+    else if (mode == 1) hipLaunchKernelGGL((k_tile<TILE, 1, DEEP, SHADE>), grid, one, 0, st, a);
+    else if (mode == 2) hipLaunchKernelGGL((k_tile<TILE, 2, DEEP, SHADE>), grid, one, 0, st, a);
+    else hipLaunchKernelGGL((k_tile<TILE, 3, DEEP, SHADE>), grid, two, 0, st, a);
 }
 
 template <int TILE, bool DEEP>
@@ -1199,7 +1229,7 @@ hipError_t launch_tile_deep_t(hipStream_t st, const TileArgs& a, int mode, dim3 
 
 template <int TILE>
 hipError_t launch_batch_tile_t(hipStream_t st, const BatchArgs& b, unsigned grid) {
-    dim3 block((TILE * TILE > 256) ? 256 : TILE * TILE);
+    const dim3 block(TileCfg<TILE, 0, false>::TB);
     if (b.shade == 0) hipLaunchKernelGGL((k_tile_b<TILE, 0>), dim3(grid), block, 0, st, b);
     else if (b.shade == 1) hipLaunchKernelGGL((k_tile_b<TILE, 1>), dim3(grid), block, 0, st, b);
     else if (b.shade == 2) hipLaunchKernelGGL((k_tile_b<TILE, 2>), dim3(grid), block, 0, st, b);

@@ -31,6 +31,11 @@ __device__ __forceinline__ int wave_max(int v) {
     return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Lanes below this one whose bit is set in m.
+__device__ __forceinline__ unsigned lanes_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
 // Index of the last entry of a non-decreasing sequence (stride in bytes
 // between entries, starting at `first`) that is <= x; n >= 1 entries.
 __device__ __forceinline__ int last_le(const char* first, int stride, int n, long long x) {
