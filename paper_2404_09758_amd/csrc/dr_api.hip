@@ -111,8 +111,8 @@ struct dr_ctx {
     long long spill_entries = 0;
     long long* R = nullptr;
     long long R_pairs = 0;
-    uint32_t* bits = nullptr;
-    long long bits_words = 0;
+    uint8_t* sg = nullptr;          // group sign bytes of the pairs
+    long long sg_bytes = 0;
     long long* qtot = nullptr;
     long long qtot_pairs = 0;
     double* partials = nullptr;
@@ -386,6 +386,7 @@ extern "C" dr_status dr_create(dr_ctx** out, const dr_scene* s, const dr_tuning*
         sc.tex_w[t] = sc.tex_h[t] = sc.tex_c[t] = 0;
         sc.tex_off[t] = 0;
         sc.tex_cls[t] = -1;
+        sc.tex_bit[t] = 0;
         sc.cls_w[t] = sc.cls_h[t] = 0;
         sc.cls_goff[t] = 0;
     }
@@ -406,6 +407,8 @@ extern "C" dr_status dr_create(dr_ctx** out, const dr_scene* s, const dr_tuning*
             goff += (long long)s->tex_w[t] * s->tex_h[t];
         }
         sc.tex_cls[t] = cls;
+        for (int k = 0; k < t; ++k)
+            if (sc.tex_cls[k] == cls) sc.tex_bit[t] += s->tex_c[k];
     }
     sc.shading = s->shading;
     sc.tex_mode = s->tex_mode;
@@ -418,7 +421,7 @@ extern "C" dr_status dr_create(dr_ctx** out, const dr_scene* s, const dr_tuning*
     sc.diffuse = s->diffuse;
     sc.d = off;
     sc.G = goff;
-    sc.words = (int)((off + 31) / 32);
+    sc.sg_stride = (goff + 64) & ~63ll;        // (at least a byte past the last group's)
     if (hipMalloc(&c->stats, ST_COUNT * sizeof(unsigned long long)) != hipSuccess ||
         hipMemset(c->stats, 0, ST_COUNT * sizeof(unsigned long long)) != hipSuccess) {
         (void)hipGetLastError();
@@ -466,7 +469,7 @@ extern "C" dr_status dr_destroy(dr_ctx* c) {
     (void)hipStreamSynchronize(c->stream);
     if (c->h_seen) (void)hipHostFree(c->h_seen);
     if (c->ev_seen) (void)hipEventDestroy(c->ev_seen);
-    void* ptrs[] = {c->recR, c->recS, c->counts, c->bins, c->spn, c->spill, c->R, c->bits, c->stats, c->partials,
+    void* ptrs[] = {c->recR, c->recS, c->counts, c->bins, c->spn, c->spill, c->R, c->sg, c->stats, c->partials,
                     c->recG, c->qtot, c->tri_rowptr, c->tri_cols, c->fpos};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -507,10 +510,9 @@ extern "C" int64_t dr_group_count(const dr_ctx* c) { return c ? c->sc.G : -1; }
 
 // -------------------------------------------------------------- signs --
 
-// Sign bits of `pairs` pairs, plus a spare word that the texture sampling
-// may read past the last pair's last word.
-static dr_status ensure_bits(dr_ctx* c, long long pairs) {
-    return grow(c, &c->bits, &c->bits_words, pairs * c->sc.words + 1, sizeof(uint32_t), false);
+// Group sign bytes of `pairs` pairs.
+static dr_status ensure_signs(dr_ctx* c, long long pairs) {
+    return grow(c, &c->sg, &c->sg_bytes, pairs * c->sc.sg_stride, 1, false);
 }
 
 extern "C" dr_status dr_signs(dr_ctx* c, uint64_t seed, uint32_t step, uint32_t pair, uint32_t scene,
@@ -519,7 +521,7 @@ extern "C" dr_status dr_signs(dr_ctx* c, uint64_t seed, uint32_t step, uint32_t 
     if (!bits) return fail(c, DR_E_INVALID, "bits is NULL");
     dr_status s = device_guard(c);
     if (s) return s;
-    HIPCHK(c, c->timer.run(c->stream, K_SIGNS, [&] { return launch_signs(c->stream, seed, step, pair, scene, c->sc.d, c->sc.words, 1, bits); }));
+    HIPCHK(c, c->timer.run(c->stream, K_SIGNS, [&] { return launch_signs(c->stream, seed, step, pair, scene, c->sc.d, bits); }));
     return DR_OK;
 }
 
@@ -547,17 +549,16 @@ extern "C" dr_status dr_render(dr_ctx* c, const float* theta, const dr_view* vie
     s = ensure_raster(c, 1, 1, max_tiles);
     if (s) return s;
     DPert dp;
-    dp.bits = nullptr;
+    dp.sg = nullptr;
     for (int b = 0; b <= DRD_MAX_TEX; ++b) dp.eps[b] = 0.0f;
     float sg = 1.0f;
     if (pert) {
-        s = ensure_bits(c, 1);
+        s = ensure_signs(c, 1);
         if (s) return s;
         HIPCHK(c, c->timer.run(c->stream, K_SIGNS, [&] {
-            return launch_signs(c->stream, pert->seed, pert->step, pert->pair, pert->scene_index, c->sc.d,
-                                c->sc.words, 1, c->bits);
+            return launch_group_signs(c->stream, c->sc, pert->seed, pert->step, pert->pair, pert->scene_index, 1, c->sg);
         }));
-        dp.bits = c->bits;
+        dp.sg = c->sg;
         for (int b = 0; b < 1 + c->sc.n_tex; ++b) dp.eps[b] = pert->eps[b];
         sg = (float)pert->sign;
     }
@@ -655,7 +656,7 @@ static dr_status note_bins(dr_ctx* c) {
 // per-pair group sums (or full-image totals) and tessellated positions go,
 // the bin capacity and the number of items per raster launch.
 struct EstScratch {
-    uint32_t* bits = nullptr;
+    uint8_t* sg = nullptr;
     TriR* recR = nullptr;
     TriS* recS = nullptr;
     TriG* recG = nullptr;
@@ -721,7 +722,7 @@ static dr_status estimate_scratch_ctx(dr_ctx* c, const EstPlan& pl, int32_t n_pa
     x.per = items_per_launch(c, pl.items);
     dr_status s = ensure_raster(c, 2 * x.per, pert_slots(pl, x.per), pl.max_tiles);
     if (s) return s;
-    s = ensure_bits(c, n_pairs);
+    s = ensure_signs(c, n_pairs);
     if (s) return s;
     if (full) {
         s = grow(c, &c->qtot, &c->qtot_pairs, n_pairs, sizeof(long long), false);
@@ -735,7 +736,7 @@ static dr_status estimate_scratch_ctx(dr_ctx* c, const EstPlan& pl, int32_t n_pa
                  false);
         if (s) return s;
     }
-    x.bits = c->bits;
+    x.sg = c->sg;
     x.recR = c->recR;
     x.recS = c->recS;
     x.recG = c->recG;
@@ -764,10 +765,10 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     const int max_tiles = pl.max_tiles;
     const long long items = pl.items, per = x.per;
     DPert dp;
-    dp.bits = x.bits;
+    dp.sg = x.sg;
     for (int b = 0; b <= DRD_MAX_TEX; ++b) dp.eps[b] = (b < 1 + c->sc.n_tex) ? eps[b] : 0.0f;
     HIPCHK(c, run(K_SIGNS, [&] {
-        return launch_signs(c->stream, seed, step, 0u, c->scene_index, c->sc.d, c->sc.words, n_pairs, x.bits);
+        return launch_group_signs(c->stream, c->sc, seed, step, 0u, c->scene_index, n_pairs, x.sg);
     }));
 
     SetupArgs sa;
@@ -838,7 +839,7 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     std::memset(&fa, 0, sizeof(fa));
     fa.sc = c->sc;
     fa.R = x.R;
-    fa.bits = x.bits;
+    fa.sg = x.sg;
     fa.n_pairs = n_pairs;
     for (int b = 0; b <= DRD_MAX_TEX; ++b) fa.eps[b] = dp.eps[b];
     fa.Q = (long long*)Q;
@@ -940,7 +941,7 @@ static unsigned long long static_account(const dr_ctx* c, const EstPlan& pl, int
     const unsigned long long bin_slots = slots * (unsigned long long)pl.max_tiles, pairs = (unsigned long long)n_pairs;
     unsigned long long need = round256(bin_slots * 4ull) + round256(slots * 8ull) +
                               round256(pairs * (unsigned long long)sc.G * 8ull) +
-                              round256((pairs * (unsigned long long)sc.words + 1ull) * 4ull) + 2ull * round256(slots * tris * 48ull) +
+                              round256((pairs * (unsigned long long)((sc.d + 31) / 32) + 1ull) * 4ull) + 2ull * round256(slots * tris * 48ull) +
                               round256(bin_slots * (unsigned long long)c->tune.bin_capacity * 4ull) +
                               round256(slots * (unsigned long long)SPILL_CAP * 8ull);
     if (sc.n_ctrl > 0) need += round256(pairs * 2ull * (unsigned long long)sc.n_verts * 12ull);
@@ -967,7 +968,7 @@ static unsigned long long static_layout(const dr_ctx* c, const EstPlan& pl, int3
     x->spn = (unsigned*)take(slots * 2ull * sizeof(unsigned));
     x->R = (long long*)take((unsigned long long)n_pairs * (unsigned long long)sc.G * sizeof(long long));
     *zero_bytes = off;
-    x->bits = (uint32_t*)take(((unsigned long long)n_pairs * (unsigned long long)sc.words + 1ull) * 4ull);
+    x->sg = (uint8_t*)take((unsigned long long)n_pairs * (unsigned long long)sc.sg_stride);
     x->recR = (TriR*)take(slots * (unsigned long long)sc.n_tris * sizeof(TriR));
     x->recS = (TriS*)take(slots * (unsigned long long)sc.n_tris * sizeof(TriS));
     if (sc.shading == DR_GGX)
@@ -1044,7 +1045,7 @@ extern "C" dr_status dr_loss(dr_ctx* c, const float* theta, const dr_view* views
     s = grow(c, &c->partials, &c->partial_slots, (long long)n_views * max_tiles, sizeof(double), false);
     if (s) return s;
     DPert dp;
-    dp.bits = nullptr;
+    dp.sg = nullptr;
     for (int b = 0; b <= DRD_MAX_TEX; ++b) dp.eps[b] = 0.0f;
     SetupArgs sa;
     std::memset(&sa, 0, sizeof(sa));
@@ -1380,8 +1381,8 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
     };
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost(x) > cost(y); });
     long long sign_blk = 0, group_blk = 0, rec = 0, grec = 0, cnt = 0, bin = 0, sp = 0, setup_blk = 0, tile0 = 0;
-    std::vector<long long> bits_off(n_scenes), R_off(n_scenes);
-    long long bits_total = 0, R_total = 0;
+    std::vector<long long> sg_off(n_scenes), R_off(n_scenes);
+    long long sg_total = 0, R_total = 0;
     for (int i = 0; i < n_scenes; ++i) {
         const dr_batch_scene& s = scenes[i];
         BScene& S = hs[i];
@@ -1412,13 +1413,13 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
             hv.push_back(make_dview(s.views[v], tile_px, tgt_off));
             tgt_off += 3ll * s.views[v].width * s.views[v].height;
         }
-        long long nblk = (S.sc.d + 255) >> 8;
         S.sign_blk0 = sign_blk;
-        sign_blk += (long long)n_pairs * ((nblk + 255) >> 8);
+        S.sign_nblk = group_sign_blocks(S.sc);
+        sign_blk += n_pairs * S.sign_nblk;
         S.group_blk0 = group_blk;
         group_blk += (S.sc.G + 255) >> 8;
-        bits_off[i] = bits_total;
-        bits_total += (long long)n_pairs * S.sc.words;
+        sg_off[i] = sg_total;
+        sg_total += n_pairs * S.sc.sg_stride;
         R_off[i] = R_total;
         R_total += (long long)n_pairs * S.sc.G;
     }
@@ -1507,14 +1508,14 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
 
     // device memory
     dr_status st = DR_OK;
-    uint32_t* bits = nullptr;
+    uint8_t* sg = nullptr;
     long long* R = nullptr;
     BScene* dsc = nullptr;
     DView* dvw = nullptr;
     BItem* dit = nullptr;
     float *dbc1 = nullptr, *dbc2 = nullptr;
     unsigned* dstep = nullptr;
-    if ((st = balloc(b, &bits, (size_t)bits_total + 1, false)) || (st = balloc(b, &R, (size_t)R_total, true)) ||
+    if ((st = balloc(b, &sg, (size_t)sg_total, false)) || (st = balloc(b, &R, (size_t)R_total, true)) ||
         (st = balloc(b, &A.recR, (size_t)rec, false)) || (st = balloc(b, &A.recS, (size_t)rec, false)) ||
         (st = balloc(b, &A.recG, (size_t)grec, false)) ||
         (st = balloc(b, &A.counts, (size_t)cnt, true)) || (st = balloc(b, &A.bins, (size_t)bin, false)) ||
@@ -1529,7 +1530,7 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
         return st;
     }
     for (int i = 0; i < n_scenes; ++i) {
-        hs[i].bits = bits + bits_off[i];
+        hs[i].sg = sg + sg_off[i];
         hs[i].R = R + R_off[i];
     }
     bool ok = hipMemcpy(dsc, hs.data(), hs.size() * sizeof(BScene), hipMemcpyHostToDevice) == hipSuccess &&
@@ -1563,7 +1564,7 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
         for (size_t v = 0; v < hv.size(); ++v) sa.views.v[v] = hv[v];
         finish_views(sa.views, (int)hv.size());
         ta.views = sa.views;
-        sa.pert.bits = S.bits;
+        sa.pert.sg = S.sg;
         std::memcpy(sa.pert.eps, S.eps, sizeof(S.eps));
         ta.pert = sa.pert;
         sa.theta = ta.theta = S.theta;

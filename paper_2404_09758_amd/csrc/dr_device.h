@@ -28,6 +28,7 @@ struct DScene {
     int tex_w[DRD_MAX_TEX], tex_h[DRD_MAX_TEX], tex_c[DRD_MAX_TEX];
     long long tex_off[DRD_MAX_TEX];      // first parameter of each texture
     int tex_cls[DRD_MAX_TEX];            // texel class of each texture
+    int tex_bit[DRD_MAX_TEX];            // first sign bit of the texture in its class's group bytes
     int n_cls;
     int cls_w[DRD_MAX_TEX], cls_h[DRD_MAX_TEX];
     long long cls_goff[DRD_MAX_TEX];     // first group of each class
@@ -46,7 +47,7 @@ struct DScene {
     const int* tri_cols;
     float light[3], light_rgb[3], ambient, diffuse;
     long long d, G;
-    int words;                           // ceil(d / 32) sign words per pair
+    long long sg_stride;                 // group sign bytes per pair (G and room to read on)
 };
 
 struct DView {
@@ -64,9 +65,13 @@ struct DViews {
     int tsum[DRD_MAX_VIEWS + 1];         // tiles of the views before v
 };
 
-// Perturbation of one launch: per-block eps and the sign bits of the pairs.
+// Perturbation of one launch: per-block eps and the signs of the pairs, a
+// byte per group: bit k is set where the group's k-th parameter has sign -1 (a
+// vertex's x, y, z; a texel's channels in every texture of its class, in
+// texture order: at most 8).  A texel's signs in all its textures thus come
+// with one byte, those of two adjacent texels with one 16-bit read.
 struct DPert {
-    const uint32_t* bits;                // [pairs, words] or null (no perturbation)
+    const uint8_t* sg;                   // [pairs, sg_stride] or null (no perturbation)
     float eps[1 + DRD_MAX_TEX];
 };
 
@@ -130,18 +135,21 @@ __device__ __forceinline__ void philox4x64_10(unsigned long long c0, unsigned lo
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
-// theta_i perturbed by sgn * s_i * eps (one fp32 add or subtract).
-__device__ __forceinline__ float pval(const float* __restrict__ th, long long i, float e,
-                                      const uint32_t* __restrict__ pb, float sgn) {
-    float x = th[i];
-    if (pb == nullptr || e == 0.0f) return x;
-    unsigned w = pb[i >> 5];
-    float se = ((w >> (unsigned)(i & 31)) & 1u) ? -e : e;
+// x perturbed by sgn * s * e (one fp32 add or subtract), s = -1 where `neg`.
+__device__ __forceinline__ float perturbed(float x, float e, bool neg, float sgn) {
+    float se = neg ? -e : e;
     return (sgn > 0.0f) ? (x + se) : (x - se);
 }
 
-__device__ __forceinline__ int sign_of(const uint32_t* __restrict__ pb, long long i) {
-    return ((pb[i >> 5] >> (unsigned)(i & 31)) & 1u) ? -1 : 1;
+// The perturbed coordinates of (control) vertex v.
+__device__ __forceinline__ void perturbed_vertex(const float* __restrict__ th, long long v, float e,
+                                                 const uint8_t* __restrict__ sg, float sgn, float* p) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) p[c] = th[3 * v + c];
+    if (sg == nullptr || e == 0.0f) return;
+    const unsigned b = sg[v];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) p[c] = perturbed(p[c], e, (b >> c) & 1u, sgn);
 }
 
 // ------------------------------------------------------------ geometry --
@@ -258,46 +266,55 @@ __device__ __forceinline__ T gload(const T* p) {
 #endif
 }
 
-// Bilinear sample of one texture with C channels per texel (C consecutive
-// parameters per texel), perturbed as by pval.  All four texels' values and
-// sign words are requested before any is used.  The perturbed value is
-// x + (s_i ? -es : es) with es = +-eps by the render's sign: x - y and
-// x + (-y) are the same IEEE operation, so this equals pval's result.
-// 64-bit word at a 4-byte aligned address (one load of two sign words)
-typedef unsigned long long __attribute__((aligned(4))) drd_u64_a4;
+// Signs of a footprint's four texels: sg is the class's first group byte.
+// w[row] holds the row's two bytes in its upper half, complemented (flip) for
+// the minus render.  The two texels of a row are adjacent unless the row
+// wraps.
+struct FootSigns {
+    unsigned w[2];
+};
 
+__device__ __forceinline__ FootSigns foot_signs(const DRD_GLOBAL uint8_t* sg, int W, unsigned flip, const Foot& f) {
+    typedef uint16_t __attribute__((aligned(1))) u16a1;
+    FootSigns s;
+#pragma unroll
+    for (int row = 0; row < 2; ++row) {
+        const unsigned o = __umul24((unsigned)(row ? f.yb : f.ya), (unsigned)W) + (unsigned)f.xa;      // < 2^30
+        unsigned w = *(const DRD_GLOBAL u16a1*)(sg + o);
+        if (f.xb != f.xa + 1) w = (w & 0xFFu) | ((unsigned)sg[o - (unsigned)f.xa + (unsigned)f.xb] << 8);
+        s.w[row] = (w << 16) ^ flip;
+    }
+    return s;
+}
+
+// Bilinear sample of texture t (C channels) of the perturbed scene
+// (theta + sgn s eps) over a precomputed footprint and its signs (null
+// perturbation: pert false).  The perturbed value is x + (s_i ? -es : es) with
+// es = +-eps by the render's sign: x - y and x + (-y) are the same IEEE
+// operation, so this equals perturbed()'s result.  The weighted sum keeps its
+// order ((w00 t00 + w10 t10) + w01 t01) + w11 t11.
 //
 // COMPACT: the texture has at most 2^24 texels, so a texel's byte offset is
 // one 24-bit product and fits in 32 bits; the loads then take the texture's
 // uniform base and a 32-bit offset instead of a 64-bit address per lane.
 template <int C, bool COMPACT>
-__device__ __forceinline__ void sample_texels(const DRD_GLOBAL float* th, const DRD_GLOBAL uint32_t* pb,
-                                              long long base, int W, float e, unsigned flip, const Foot& f,
-                                              float* out) {
+__device__ __forceinline__ void sample_tex(const DScene& sc, const float* __restrict__ th, bool pert, float e, int t,
+                                           const Foot& f, const FootSigns& sig, float* out) {
     typedef float __attribute__((ext_vector_type(C == 1 ? 2 : C), aligned(4))) texel_t;
-    const DRD_GLOBAL float* tt = th + base;
-    const bool pert = pb != nullptr && e != 0.0f;
-    const DRD_GLOBAL uint32_t* pw = pb + (base >> 5);
-    unsigned bb = (unsigned)(base & 31);
-    // s_i (sgn e) is e (>= 0) with its sign bit set to the sign bit s_i
-    // holds -- complemented (flip) for the minus render: the IEEE value of
-    // +-e exactly, so x + it is the same operation as pval's
+    const DRD_GLOBAL float* tt = (const DRD_GLOBAL float*)th + sc.tex_off[t];
     const unsigned eb = __float_as_uint(e);
-    float wx[2] = {1.0f - f.fx, f.fx};
+    const float wx[2] = {1.0f - f.fx, f.fx};
+    const bool adj = f.xb == f.xa + 1;
     float acc[C];
-    // row by row (ya, then yb), two texels each: the weighted sum keeps its
-    // order ((w00 t00 + w10 t10) + w01 t01) + w11 t11
 #pragma unroll
     for (int row = 0; row < 2; ++row) {
-        int yy = row ? f.yb : f.ya;
-        float wy = row ? f.fy : 1.0f - f.fy;
+        const float wy = row ? f.fy : 1.0f - f.fy;
         // texel indices within the texture: W, H <= 32768 keep them below 2^30
         unsigned o[2];
-        const unsigned ro = __umul24((unsigned)yy, (unsigned)W);      // W, H <= 32768: exact
+        const unsigned ro = __umul24((unsigned)(row ? f.yb : f.ya), (unsigned)sc.tex_w[t]);
         o[0] = (ro + (unsigned)f.xa) * C;
         o[1] = (ro + (unsigned)f.xb) * C;
         float x[2][C];
-        const bool adj = f.xb == f.xa + 1;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const DRD_GLOBAL float* a;
@@ -322,30 +339,14 @@ __device__ __forceinline__ void sample_texels(const DRD_GLOBAL float* th, const 
             }
         }
         if (pert) {
-            // parameter base + o has its sign at bit (base + o) mod 32 of
-            // word (base + o) / 32.  One 64-bit read at that word holds the
-            // texel's C bits and, when xb = xa + 1, the next texel's C bits
-            // right after them (at most bit 31 + 2 C < 64); a wrapped xb
-            // reads its own.  The sign buffers carry a spare word at the
-            // end, so the read past a pair's last word stays in bounds (its
-            // bits belong to no parameter of the texel).
-            unsigned r = (o[0] & 31u) + bb;
-            unsigned long long w = *(const DRD_GLOBAL drd_u64_a4*)(pw + ((o[0] >> 5) + (r >> 5)));
-            unsigned win[2];
-            win[0] = __builtin_amdgcn_alignbit((unsigned)(w >> 32), (unsigned)w, r & 31u);
-            win[1] = win[0] >> C;
-            if (!adj) {
-                unsigned rb = (o[1] & 31u) + bb;
-                unsigned long long wb = *(const DRD_GLOBAL drd_u64_a4*)(pw + ((o[1] >> 5) + (rb >> 5)));
-                win[1] = __builtin_amdgcn_alignbit((unsigned)(wb >> 32), (unsigned)wb, rb & 31u);
-            }
+            // the sign of texel k's channel c is bit 16 + 8 k + c of w: moved
+            // to the top, it is the sign bit of the offset
+            const unsigned w = sig.w[row] >> sc.tex_bit[t];
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const unsigned wk = win[k] ^ flip;
+            for (int k = 0; k < 2; ++k)
 #pragma unroll
                 for (int c = 0; c < C; ++c)
-                    x[k][c] = x[k][c] + __uint_as_float(((wk << (31 - c)) & 0x80000000u) | eb);
-            }
+                    x[k][c] = x[k][c] + __uint_as_float(((w << (15 - 8 * k - c)) & 0x80000000u) | eb);
         }
 #pragma unroll
         for (int c = 0; c < C; ++c) {
@@ -355,16 +356,6 @@ __device__ __forceinline__ void sample_texels(const DRD_GLOBAL float* th, const 
     }
 #pragma unroll
     for (int c = 0; c < C; ++c) out[c] = acc[c];
-}
-
-// Bilinear sample of texture t (C channels) of the perturbed scene
-// (theta + sgn s eps) over a precomputed footprint.
-template <int C, bool COMPACT>
-__device__ __forceinline__ void sample_tex(const DScene& sc, const float* __restrict__ th,
-                                           const uint32_t* __restrict__ pb, float e, unsigned flip, int t,
-                                           const Foot& f, float* out) {
-    sample_texels<C, COMPACT>((const DRD_GLOBAL float*)th, (const DRD_GLOBAL uint32_t*)pb, sc.tex_off[t], sc.tex_w[t],
-                              e, flip, f, out);
 }
 
 // Correctly rounded square root and reciprocal for operands in a normal
@@ -514,7 +505,7 @@ __device__ __forceinline__ Attr frag_attr(const DScene& sc, const TriR& r, const
 
 template <int SHADE, bool DEEP>
 __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, const float* __restrict__ th,
-                                            const uint32_t* __restrict__ pb, const float* eps, unsigned flip,
+                                            const uint8_t* __restrict__ sg, const float* eps, unsigned flip,
                                             const TriR& r, const TriS& s, const TriG* __restrict__ G,
                                             const CornerUV& cu, int px, int py, float* rgb, float* uvo,
                                             float& opacity) {
@@ -526,10 +517,15 @@ __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, c
     uvo[0] = u;
     uvo[1] = v;
     float alb[4] = {0.0f, 0.0f, 0.0f, 1.0f};
+    // footprint and signs of texel class 0; a texture of another class has its own
+    const bool pert = sg != nullptr;
+    const DRD_GLOBAL uint8_t* gsg = (const DRD_GLOBAL uint8_t*)sg;
     Foot foot0;
+    FootSigns sig0 = {{0u, 0u}};
     if (sc.n_tex > 0) {
         foot0 = footprint(u, v, sc.cls_w[0], sc.cls_h[0]);
-        sample_tex<DEEP ? 4 : 3, COMPACT>(sc, th, pb, eps[1], flip, 0, foot0, alb);
+        if (pert) sig0 = foot_signs(gsg + sc.cls_goff[0], sc.cls_w[0], flip, foot0);
+        sample_tex<DEEP ? 4 : 3, COMPACT>(sc, th, pert && eps[1] != 0.0f, eps[1], 0, foot0, sig0, alb);
     }
     if constexpr (DEEP) {
         float al = alb[3];
@@ -549,9 +545,14 @@ __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, c
     // GGX with a tangent-space normal map in the face's UV frame
     float nm[4] = {0.5f, 0.5f, 1.0f, 0.0f};
     if (sc.n_tex > 1) {
-        int c1 = sc.tex_cls[1];
-        Foot f1 = (c1 == 0) ? foot0 : footprint(u, v, sc.cls_w[c1], sc.cls_h[c1]);
-        sample_tex<3, COMPACT>(sc, th, pb, eps[2], flip, 1, f1, nm);
+        const int c1 = sc.tex_cls[1];
+        Foot f1 = foot0;
+        FootSigns s1 = sig0;
+        if (c1 != 0) {
+            f1 = footprint(u, v, sc.cls_w[c1], sc.cls_h[c1]);
+            if (pert) s1 = foot_signs(gsg + sc.cls_goff[c1], sc.cls_w[c1], flip, f1);
+        }
+        sample_tex<3, COMPACT>(sc, th, pert && eps[2] != 0.0f, eps[2], 1, f1, s1, nm);
     }
     float tn[3];
 #pragma unroll
@@ -564,9 +565,14 @@ __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, c
     nrm3(n);
     float rough4[4] = {0.5f, 0.0f, 0.0f, 0.0f};
     if (sc.n_tex > 2) {
-        int c2 = sc.tex_cls[2];
-        Foot f2 = (c2 == 0) ? foot0 : footprint(u, v, sc.cls_w[c2], sc.cls_h[c2]);
-        sample_tex<1, COMPACT>(sc, th, pb, eps[3], flip, 2, f2, rough4);
+        const int c2 = sc.tex_cls[2];
+        Foot f2 = foot0;
+        FootSigns s2 = sig0;
+        if (c2 != 0) {
+            f2 = footprint(u, v, sc.cls_w[c2], sc.cls_h[c2]);
+            if (pert) s2 = foot_signs(gsg + sc.cls_goff[c2], sc.cls_w[c2], flip, f2);
+        }
+        sample_tex<1, COMPACT>(sc, th, pert && eps[3] != 0.0f, eps[3], 2, f2, s2, rough4);
     }
     float P[3];
 #pragma unroll

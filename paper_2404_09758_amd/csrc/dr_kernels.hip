@@ -27,25 +27,114 @@
 
 // ---------------------------------------------------------------- signs --
 
-// Philox block `blk` of pair `pair`: 256 signs, written as 8 uint32 words.
-__device__ __forceinline__ void signs_block(unsigned long long seed, unsigned step, unsigned pair, unsigned scene,
-                                            long long blk, int words, uint32_t* __restrict__ out) {
+// Sign words of one pair: a Philox block holds 256 signs, 8 uint32 words.
+__global__ void k_signs(unsigned long long seed, unsigned step, unsigned pair, unsigned scene, long long d, int words,
+                        uint32_t* __restrict__ out) {
+    const long long blk = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (blk >= ((d + 255) >> 8)) return;
     unsigned long long r[4];
     philox4x64_10((unsigned long long)blk, (unsigned long long)pair, step, scene, seed, 0ull, r);
 #pragma unroll
     for (int w = 0; w < 8; ++w) {
-        long long word = blk * 8 + w;
+        const long long word = blk * 8 + w;
         if (word < words) out[word] = (w & 1) ? (uint32_t)(r[w >> 1] >> 32) : (uint32_t)r[w >> 1];
     }
 }
 
-__global__ void k_signs(unsigned long long seed, unsigned step, unsigned pair0, unsigned scene,
-                        long long d, int words, uint32_t* __restrict__ bits) {
-    long long blk = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    int p = blockIdx.y;
-    long long nblk = (d + 255) >> 8;
-    if (blk >= nblk) return;
-    signs_block(seed, step, pair0 + p, scene, blk, words, bits + (long long)p * words);
+// Group sign bytes (DPert): a block makes those of up to SIGN_CH groups that
+// lie in one segment (the vertices, or one texel class).  The signs are
+// numbered by parameter, and a group's parameters lie in up to three ranges of
+// them (one per texture of the class), so the block first forms the Philox
+// blocks that its ranges touch in LDS (a range starts and ends within a block,
+// so two of about a hundred are formed by a neighbour too) and then gathers
+// each group's bits.  Writing bytes per group instead of the words in
+// parameter order: the tile kernel reads a footprint's signs in all textures
+// with two 16-bit loads per side (six 64-bit ones before) and the fold a byte
+// per (pair, group) instead of a word per (pair, parameter).
+// Bound by the Philox rounds' 64-bit products.
+#define SIGN_CH 8192
+
+struct SignShared {
+    uint32_t bits[SIGN_CH / 4 + 64];             // at most 8 bits per group, a spare block per range
+};
+
+__host__ __device__ inline long long sign_chunks(long long n) { return (n + SIGN_CH - 1) / SIGN_CH; }
+
+__device__ __forceinline__ void group_signs_block(SignShared& S, const DScene& sc, unsigned long long seed,
+                                                  unsigned step, unsigned pair, unsigned scene, long long chunk,
+                                                  uint8_t* __restrict__ sg) {
+    // the segment: first group, its size, and its parameter ranges
+    long long goff = 0, size = sc.n_vg, first[DRD_MAX_TEX] = {0, 0, 0};
+    int C[DRD_MAX_TEX] = {3, 0, 0}, bit[DRD_MAX_TEX] = {0, 0, 0};
+    long long left = chunk - sign_chunks(sc.n_vg);
+    if (left >= 0) {
+        int c = 0;
+        while (c + 1 < sc.n_cls && left >= sign_chunks((long long)sc.cls_w[c] * sc.cls_h[c])) {
+            left -= sign_chunks((long long)sc.cls_w[c] * sc.cls_h[c]);
+            ++c;
+        }
+        chunk = left;
+        goff = sc.cls_goff[c];
+        size = (long long)sc.cls_w[c] * sc.cls_h[c];
+#pragma unroll
+        for (int t = 0; t < DRD_MAX_TEX; ++t) {
+            C[t] = (t < sc.n_tex && sc.tex_cls[t] == c) ? sc.tex_c[t] : 0;
+            first[t] = sc.tex_off[t];
+            bit[t] = sc.tex_bit[t];
+        }
+    }
+    const long long g0 = chunk * SIGN_CH;
+    const int n = (int)min((long long)SIGN_CH, size - g0), tid = threadIdx.x;
+    // Philox blocks of each range, end to end
+    long long blk0[DRD_MAX_TEX];
+    int at[DRD_MAX_TEX + 1];
+    at[0] = 0;
+#pragma unroll
+    for (int t = 0; t < DRD_MAX_TEX; ++t) {
+        const long long b0 = first[t] + g0 * C[t], b1 = b0 + (long long)n * C[t];
+        blk0[t] = b0 >> 8;
+        at[t + 1] = at[t] + (C[t] > 0 ? (int)(((b1 - 1) >> 8) - blk0[t]) + 1 : 0);
+    }
+    for (int i = tid; i < at[DRD_MAX_TEX]; i += (int)blockDim.x) {
+        long long blk = blk0[0] + i;
+#pragma unroll
+        for (int t = 1; t < DRD_MAX_TEX; ++t)
+            if (i >= at[t]) blk = blk0[t] + (i - at[t]);
+        unsigned long long r[4];
+        philox4x64_10((unsigned long long)blk, (unsigned long long)pair, step, scene, seed, 0ull, r);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            S.bits[8 * i + 2 * w] = (uint32_t)r[w];
+            S.bits[8 * i + 2 * w + 1] = (uint32_t)(r[w] >> 32);
+        }
+    }
+    __syncthreads();
+    // four groups at a time
+    typedef uint32_t __attribute__((aligned(1))) u32a1;
+    for (int q = 4 * tid; q < n; q += 4 * (int)blockDim.x) {
+        uint32_t out = 0u;
+#pragma unroll
+        for (int t = 0; t < DRD_MAX_TEX; ++t) {
+            if (C[t] == 0) continue;
+            // the range's bits of these groups: at most 16, within two words
+            const unsigned b = (unsigned)((first[t] + g0 * C[t]) & 255) + (unsigned)(q * C[t]);
+            const uint32_t* w = &S.bits[8 * at[t] + (b >> 5)];
+            const uint32_t x = __builtin_amdgcn_alignbit(w[1], w[0], b & 31u);
+            const uint32_t m = (1u << C[t]) - 1u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) out |= ((x >> (k * C[t])) & m) << (8 * k + bit[t]);
+        }
+        uint8_t* p = sg + goff + g0 + q;
+        if (q + 4 <= n) *(u32a1*)p = out;
+        else
+            for (int k = 0; k < n - q; ++k) p[k] = (uint8_t)(out >> (8 * k));
+    }
+}
+
+__global__ void __launch_bounds__(256) k_group_signs(DScene sc, unsigned long long seed, unsigned step, unsigned pair0,
+                                                     unsigned scene, uint8_t* __restrict__ sg) {
+    __shared__ SignShared S;
+    group_signs_block(S, sc, seed, step, pair0 + blockIdx.y, scene, blockIdx.x, sg + blockIdx.y * sc.sg_stride);
 }
 
 // ---------------------------------------------------------------- setup --
@@ -56,20 +145,17 @@ __global__ void k_signs(unsigned long long seed, unsigned step, unsigned pair0, 
 // subdivision surface, or null (positions are the perturbed parameters).
 // The perturbed world positions of triangle t's corners (original order).
 __device__ __forceinline__ void tri_positions(const DScene& sc, const float* __restrict__ theta,
-                                              const uint32_t* __restrict__ pb, float e0, float sgn, int t,
+                                              const uint8_t* __restrict__ sg, float e0, float sgn, int t,
                                               const float* __restrict__ fpos, float* p) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const int vid = sc.tri[3 * (long long)t + k];
-        long long base = 3 * (long long)vid;
+        const long long vid = sc.tri[3 * (long long)t + k];
         if (fpos) {
-            p[3 * k + 0] = fpos[base + 0];
-            p[3 * k + 1] = fpos[base + 1];
-            p[3 * k + 2] = fpos[base + 2];
+            p[3 * k + 0] = fpos[3 * vid + 0];
+            p[3 * k + 1] = fpos[3 * vid + 1];
+            p[3 * k + 2] = fpos[3 * vid + 2];
         } else {
-            p[3 * k + 0] = pval(theta, base + 0, e0, pb, sgn);
-            p[3 * k + 1] = pval(theta, base + 1, e0, pb, sgn);
-            p[3 * k + 2] = pval(theta, base + 2, e0, pb, sgn);
+            perturbed_vertex(theta, vid, e0, sg, sgn, p + 3 * k);
         }
     }
 }
@@ -350,9 +436,9 @@ __global__ void __launch_bounds__(SETUP_TB) k_setup(SetupArgs a) {
     const int lg = 31 - __clz(a.tile);
     float p[9], shade = 0.0f;
     if (t < sc.n_tris) {
-        const uint32_t* pb = a.pert.bits ? a.pert.bits + (long long)pair * sc.words : nullptr;
+        const uint8_t* sg = a.pert.sg ? a.pert.sg + pair * sc.sg_stride : nullptr;
         const float* fpos = a.fpos ? a.fpos + ((long long)pair * a.nsign + s) * 3 * sc.n_verts : nullptr;
-        tri_positions(sc, a.theta, pb, a.pert.eps[0], a.sgn[s], t, fpos, p);
+        tri_positions(sc, a.theta, sg, a.pert.eps[0], a.sgn[s], t, fpos, p);
         // the first view of the pair in this launch stores what all share
         const bool first = li == 0 || (a.item0 + li) - pair * a.n_views == 0;
         shade = face_shade(sc, p, t, first ? a.recG + (long long)((pair - pair0) * a.nsign + s) * sc.n_tris : nullptr);
@@ -378,16 +464,17 @@ __global__ void __launch_bounds__(256) k_subdiv(DScene sc, DPert pert, const flo
     if (j >= sc.n_verts) return;
     int slot = blockIdx.y;                       // (pair, sign)
     int pair = slot / nsign, s = slot % nsign;
-    const uint32_t* pb = pert.bits ? pert.bits + (long long)pair * sc.words : nullptr;
+    const uint8_t* sg = pert.sg ? pert.sg + pair * sc.sg_stride : nullptr;
     float sgn = s == 0 ? sgn0 : sgn1;
     float e0 = pert.eps[0];
     int k0 = sc.sub_rowptr[j], k1 = sc.sub_rowptr[j + 1];
     float acc[3] = {0.0f, 0.0f, 0.0f};
     for (int k = k0; k < k1; ++k) {
         float w = sc.sub_w[k];
-        long long base = 3 * (long long)sc.sub_cols[k];
+        float p[3];
+        perturbed_vertex(theta, sc.sub_cols[k], e0, sg, sgn, p);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) acc[c] = acc[c] + w * pval(theta, base + c, e0, pb, sgn);
+        for (int c = 0; c < 3; ++c) acc[c] = acc[c] + w * p[c];
     }
     float* out = fpos + ((long long)slot * sc.n_verts + j) * 3;
     out[0] = acc[0];
@@ -416,13 +503,13 @@ __global__ void __launch_bounds__(256) k_sum_tiles(const double* __restrict__ pa
 // -------------------------------------------------------------- fold --
 
 // Parameters of group g: a vertex's x, y, z, or a texel's channels in
-// every texture of its class.  Calls fn(param index, block).
+// every texture of its class.  Calls fn(param index, block, sign bit).
 template <typename Fn>
 __device__ __forceinline__ void for_params(const DScene& sc, long long g, Fn fn) {
     if (g < sc.n_vg) {
-        fn(3 * g + 0, 0);
-        fn(3 * g + 1, 0);
-        fn(3 * g + 2, 0);
+        fn(3 * g + 0, 0, 0);
+        fn(3 * g + 1, 0, 1);
+        fn(3 * g + 2, 0, 2);
         return;
     }
     for (int c = 0; c < sc.n_cls; ++c) {
@@ -432,35 +519,41 @@ __device__ __forceinline__ void for_params(const DScene& sc, long long g, Fn fn)
         for (int t = 0; t < sc.n_tex; ++t) {
             if (sc.tex_cls[t] != c) continue;
             int C = sc.tex_c[t];
-            for (int ch = 0; ch < C; ++ch) fn(sc.tex_off[t] + texel * C + ch, 1 + t);
+            for (int ch = 0; ch < C; ++ch) fn(sc.tex_off[t] + texel * C + ch, 1 + t, sc.tex_bit[t] + ch);
         }
     }
 }
 
+// v with sign -1 where bit k of b is set
+__device__ __forceinline__ long long signed_by(long long v, unsigned b, int k) {
+    const long long m = -(long long)((b >> k) & 1u);
+    return (v ^ m) - m;
+}
+
 // Q_i += sum_n s_i^(n) R_g^(n) for the parameters of group g, then R_g = 0.
-// Pairs are taken 8 at a time: the group's 8 sums are read once (not once
-// per parameter), a chunk that is all zero (the group was not seen by those
-// pairs) costs no sign reads, and only non-zero sums are cleared.
+// Pairs are taken 8 at a time: the group's 8 sums and sign bytes are read
+// once (not once per parameter), a chunk that is all zero (the group was not
+// seen by those pairs) changes nothing, and only non-zero sums are cleared.
 __device__ __forceinline__ void fold_group(const DScene& sc, long long g, long long* __restrict__ R,
-                                           const uint32_t* __restrict__ bits, int n_pairs, const float* eps,
+                                           const uint8_t* __restrict__ sg, int n_pairs, const float* eps,
                                            long long* __restrict__ Q) {
     for (int n0 = 0; n0 < n_pairs; n0 += 8) {
         long long r[8];
+        unsigned b[8];
         bool any = false;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            r[j] = (n0 + j < n_pairs) ? R[(long long)(n0 + j) * sc.G + g] : 0;
+            const bool in = n0 + j < n_pairs;
+            r[j] = in ? R[(long long)(n0 + j) * sc.G + g] : 0;
+            b[j] = in ? sg[(n0 + j) * sc.sg_stride + g] : 0u;
             any = any || r[j] != 0;
         }
         if (!any) continue;
-        for_params(sc, g, [&](long long i, int b) {
-            if (eps[b] == 0.0f) return;
+        for_params(sc, g, [&](long long i, int blk, int k) {
+            if (eps[blk] == 0.0f) return;
             long long acc = 0;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if (r[j] == 0) continue;
-                acc += (sign_of(bits + (long long)(n0 + j) * sc.words, i) > 0) ? r[j] : -r[j];
-            }
+            for (int j = 0; j < 8; ++j) acc += signed_by(r[j], b[j], k);
             if (acc != 0) Q[i] += acc;
         });
 #pragma unroll
@@ -477,26 +570,23 @@ __global__ void __launch_bounds__(256) k_broadcast(FoldArgs a) {
     const DScene& sc = a.sc;
     if (g >= sc.G) return;
     bool active = false;
-    if (g < sc.n_vg) {
-        active = a.eps[0] != 0.0f;
-    } else {
-        for (int c = 0; c < sc.n_cls; ++c) {
-            long long size = (long long)sc.cls_w[c] * sc.cls_h[c];
-            long long texel = g - sc.cls_goff[c];
-            if (texel >= 0 && texel < size)
-                for (int t = 0; t < sc.n_tex; ++t)
-                    if (sc.tex_cls[t] == c && a.eps[1 + t] != 0.0f) active = true;
-        }
-    }
+    for_params(sc, g, [&](long long, int b, int) { active = active || a.eps[b] != 0.0f; });
     if (!active) return;
-    for_params(sc, g, [&](long long i, int b) {
+    // a group has at most 8 parameters: all their sums in one walk over the pairs
+    long long acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int n = 0; n < a.n_pairs; ++n) {
+        const long long r = a.qtot[n];
+        const unsigned b = a.sg[n * sc.sg_stride + g];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[k] += signed_by(r, b, k);
+    }
+    for_params(sc, g, [&](long long i, int b, int k) {
         if (a.eps[b] == 0.0f) return;
-        long long acc = 0;
-        for (int n = 0; n < a.n_pairs; ++n) {
-            long long r = a.qtot[n];
-            acc += (sign_of(a.bits + (long long)n * sc.words, i) > 0) ? r : -r;
-        }
-        if (acc != 0) a.Q[i] += acc;
+        long long v = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (j == k) v = acc[j];
+        if (v != 0) a.Q[i] += v;
     });
     a.K[g] += (unsigned)(a.n_pairs * a.n_views);
 }
@@ -509,7 +599,7 @@ __global__ void k_zero64(long long* p, int n) {
 __global__ void __launch_bounds__(256) k_fold(FoldArgs a) {
     long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= a.sc.G) return;
-    fold_group(a.sc, g, a.R, a.bits, a.n_pairs, a.eps, a.Q);
+    fold_group(a.sc, g, a.R, a.sg, a.n_pairs, a.eps, a.Q);
 }
 
 // ------------------------------------------------------ step / decode --
@@ -522,7 +612,7 @@ __device__ __forceinline__ void step_group(const DScene& sc, long long g, const 
                                            unsigned long long* __restrict__ stats) {
     unsigned kc = K[g];
     double D = (oc.averaging == 0) ? (double)kc : (double)n_pairs;
-    for_params(sc, g, [&](long long i, int b) {
+    for_params(sc, g, [&](long long i, int b, int) {
         float e = eps[b];
         long long qv = Q[i];
         float gi = 0.0f;
@@ -578,21 +668,18 @@ __global__ void k_check_tri(const int* __restrict__ tri, long long n, int n_vert
 
 __global__ void k_batch_end(unsigned* step) { *step = *step + 1u; }
 
-// Signs of every (scene, pair): the blocks of a scene are contiguous and
-// each (scene, pair) starts on a block boundary.
+// Group sign bytes of every (scene, pair): the blocks of a scene are
+// contiguous, sign_nblk per pair.
 __global__ void __launch_bounds__(256) k_signs_b(BatchArgs b) {
-    long long blk = blockIdx.x;
+    __shared__ SignShared SH;
+    const long long blk = blockIdx.x;
     int si = last_le((const char*)&b.scenes[0].sign_blk0, sizeof(BScene), b.n_scenes, blk);
     si = __builtin_amdgcn_readfirstlane(si);
     const BScene& S = b.scenes[si];
-    long long nblk = (S.sc.d + 255) >> 8;
-    long long per_pair = (nblk + 255) >> 8;               // blocks per pair
-    long long local = blk - S.sign_blk0;
-    int pair = (int)(local / per_pair);
-    long long pblk = (local % per_pair) * 256 + threadIdx.x;
-    if (pblk >= nblk) return;
-    signs_block(b.seed, *b.step, (unsigned)pair, (unsigned)S.scene_index, pblk, S.sc.words,
-                S.bits + (long long)pair * S.sc.words);
+    const long long local = blk - S.sign_blk0;
+    const int pair = (int)(local / S.sign_nblk);
+    group_signs_block(SH, S.sc, b.seed, *b.step, (unsigned)pair, (unsigned)S.scene_index, local - pair * S.sign_nblk,
+                      S.sg + pair * S.sc.sg_stride);
 }
 
 // Setup of every (item, sign, triangle) of a batch of several scenes: each
@@ -614,7 +701,7 @@ __global__ void __launch_bounds__(SETUP_TB) k_setup_b(BatchArgs b) {
     TileRect r = {1, 0, 1, 0};
     if (t < sc.n_tris) {
         float p[9];
-        tri_positions(sc, S.theta, S.bits + (long long)I.pair * sc.words, S.eps[0], s == 0 ? 1.0f : -1.0f, t, nullptr, p);
+        tri_positions(sc, S.theta, S.sg + I.pair * sc.sg_stride, S.eps[0], s == 0 ? 1.0f : -1.0f, t, nullptr, p);
         // the items of a pair share its GGX records, stored by the first view's
         const float shade = face_shade(sc, p, t, I.view == S.view0 ? b.recG + I.g_off + (long long)s * sc.n_tris : nullptr);
         r = setup_tri_at(vw, p, t, b.recR + I.rec_off + (long long)s * sc.n_tris,
@@ -634,7 +721,7 @@ __global__ void __launch_bounds__(256) k_fold_b(BatchArgs b) {
     const BScene& S = b.scenes[si];
     long long g = (blk - S.group_blk0) * 256 + threadIdx.x;
     if (g >= S.sc.G) return;
-    fold_group(S.sc, g, S.R, S.bits, b.n_pairs, S.eps, S.Q);
+    fold_group(S.sc, g, S.R, S.sg, b.n_pairs, S.eps, S.Q);
 }
 
 __global__ void __launch_bounds__(256) k_step_b(BatchArgs b) {
@@ -659,31 +746,30 @@ __global__ void __launch_bounds__(256) k_step_b(BatchArgs b) {
 // left zero as the two kernels leave them.
 // q_zero: Q is known to be zero (not read).
 __device__ __forceinline__ void fold_step_group(const DScene& sc, long long g, long long* __restrict__ R,
-                                                const uint32_t* __restrict__ bits, int n_pairs, const float* eps,
+                                                const uint8_t* __restrict__ sg, int n_pairs, const float* eps,
                                                 const float* lr, const OptimConst& oc, float bc1, float bc2,
                                                 float* __restrict__ theta, float* __restrict__ m,
                                                 float* __restrict__ v, long long* __restrict__ Q,
                                                 unsigned* __restrict__ K, unsigned long long* __restrict__ stats,
                                                 int q_zero) {
     long long r[8];
+    unsigned sb[8];
     bool any = false;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         r[j] = (j < n_pairs) ? R[(long long)j * sc.G + g] : 0;
+        sb[j] = (j < n_pairs) ? sg[j * sc.sg_stride + g] : 0u;
         any = any || r[j] != 0;
     }
     unsigned kc = K[g];
     double D = (oc.averaging == 0) ? (double)kc : (double)n_pairs;
-    for_params(sc, g, [&](long long i, int b) {
+    for_params(sc, g, [&](long long i, int b, int k) {
         float e = eps[b];
         long long q0 = q_zero ? 0ll : Q[i];
         long long acc = 0;
         if (any && e != 0.0f) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if (r[j] == 0) continue;
-                acc += (sign_of(bits + (long long)j * sc.words, i) > 0) ? r[j] : -r[j];
-            }
+            for (int j = 0; j < 8; ++j) acc += signed_by(r[j], sb[j], k);
         }
         long long qv = q0 + acc;
         float gi = 0.0f;
@@ -725,17 +811,30 @@ __global__ void __launch_bounds__(256) k_fold_step_b(BatchArgs b) {
     unsigned t = *b.step;
     if (t < 1u) t = 1u;                      // Adam steps count from 1
     int ti = (int)min(t, (unsigned)b.n_bc) - 1;
-    fold_step_group(S.sc, g, S.R, S.bits, b.n_pairs, S.eps, S.lr, b.oc, b.bc1[ti], b.bc2[ti], (float*)S.theta,
+    fold_step_group(S.sc, g, S.R, S.sg, b.n_pairs, S.eps, S.lr, b.oc, b.bc1[ti], b.bc2[ti], (float*)S.theta,
                     S.m, S.v, S.Q, S.K, b.stats, b.q_zero);
 }
 
 // --------------------------------------------------------- launchers --
 
-hipError_t launch_signs(hipStream_t st, unsigned long long seed, unsigned step, unsigned pair0, unsigned scene,
-                        long long d, int words, int n_pairs, uint32_t* bits) {
-    long long nblk = (d + 255) >> 8;
-    dim3 grid((unsigned)((nblk + 255) / 256), (unsigned)n_pairs);
-    hipLaunchKernelGGL(k_signs, grid, dim3(256), 0, st, seed, step, pair0, scene, d, words, bits);
+hipError_t launch_signs(hipStream_t st, unsigned long long seed, unsigned step, unsigned pair, unsigned scene,
+                        long long d, uint32_t* bits) {
+    const long long nblk = (d + 255) >> 8;
+    hipLaunchKernelGGL(k_signs, dim3((unsigned)((nblk + 255) / 256)), dim3(256), 0, st, seed, step, pair, scene, d,
+                       (int)((d + 31) / 32), bits);
+    return hipGetLastError();
+}
+
+long long group_sign_blocks(const DScene& sc) {
+    long long n = sign_chunks(sc.n_vg);
+    for (int c = 0; c < sc.n_cls; ++c) n += sign_chunks((long long)sc.cls_w[c] * sc.cls_h[c]);
+    return n;
+}
+
+hipError_t launch_group_signs(hipStream_t st, const DScene& sc, unsigned long long seed, unsigned step, unsigned pair0,
+                              unsigned scene, int n_pairs, uint8_t* sg) {
+    dim3 grid((unsigned)group_sign_blocks(sc), (unsigned)n_pairs);
+    hipLaunchKernelGGL(k_group_signs, grid, dim3(256), 0, st, sc, seed, step, pair0, scene, sg);
     return hipGetLastError();
 }
 

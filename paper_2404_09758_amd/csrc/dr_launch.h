@@ -98,7 +98,7 @@ struct TileArgs {
 struct FoldArgs {
     DScene sc;
     long long* R;                // [pairs, G], zeroed on the way out
-    const uint32_t* bits;        // [pairs, words]
+    const uint8_t* sg;           // [pairs, sg_stride] group sign bytes
     int n_pairs;
     float eps[1 + DRD_MAX_TEX];
     long long* Q;
@@ -144,7 +144,7 @@ struct BScene {
     float* v;
     long long* Q;                // caller [d]
     unsigned* K;                 // caller [G]
-    uint32_t* bits;              // scratch [pairs, words]
+    uint8_t* sg;                 // scratch [pairs, sg_stride] group sign bytes
     long long* R;                // scratch [pairs, G]
     const float* targets;        // caller: the scene's views, concatenated
     float eps[1 + DRD_MAX_TEX];
@@ -154,6 +154,7 @@ struct BScene {
     int n_views, view0;          // views [view0, view0 + n_views) of the view table
     int scene_index;             // counter word 3 of the signs
     long long sign_blk0;         // first block of this scene in the signs launch
+    long long sign_nblk;         // blocks per pair
     long long group_blk0;        // first block of this scene in the fold / step launches
 };
 
@@ -197,8 +198,14 @@ struct BatchArgs {
     long long unit0;             // setup and tile launches: the first block / tile unit of the launch
 };
 
-hipError_t launch_signs(hipStream_t st, unsigned long long seed, unsigned step, unsigned pair0, unsigned scene,
-                        long long d, int words, int n_pairs, uint32_t* bits);
+// the sign words of one pair, in parameter order
+hipError_t launch_signs(hipStream_t st, unsigned long long seed, unsigned step, unsigned pair, unsigned scene,
+                        long long d, uint32_t* bits);
+// group sign bytes of pairs pair0 .. pair0 + n_pairs - 1
+hipError_t launch_group_signs(hipStream_t st, const DScene& sc, unsigned long long seed, unsigned step, unsigned pair0,
+                              unsigned scene, int n_pairs, uint8_t* sg);
+// blocks of one pair's group sign bytes
+long long group_sign_blocks(const DScene& sc);
 hipError_t launch_setup(hipStream_t st, SetupArgs a);
 hipError_t launch_subdiv(hipStream_t st, const DScene& sc, const DPert& pert, const float* theta, int n_pairs,
                          int nsign, float sgn0, float sgn1, float* fpos);

@@ -561,7 +561,7 @@ struct TileJob {
     const DScene* sc;
     const DView* vw;
     const float* theta;
-    const uint32_t* pb;                  // sign bits of the pair (null: unperturbed)
+    const uint8_t* sg;                   // group sign bytes of the pair (null: unperturbed)
     const float* eps;                    // per block
     unsigned flip;                       // one-sign modes: sign 0 is the minus render (all ones) or the plus one
     RasterJob ras;                       // (its tile's pixels are set by the body)
@@ -767,7 +767,7 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
                 const CornerUV cu = load_cuv(sc, id[s]);
                 float alpha;
                 const unsigned flip = NS == 2 ? (s ? 0xFFFFFFFFu : 0u) : J.flip;
-                shade_pixel<SHADE, false>(sc, vw, J.theta, J.pb, J.eps, flip, r, sh, recG + id[s], cu, px, py, rgb[s],
+                shade_pixel<SHADE, false>(sc, vw, J.theta, J.sg, J.eps, flip, r, sh, recG + id[s], cu, px, py, rgb[s],
                                           uv[s], alpha);
             }
         }
@@ -936,7 +936,7 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
             const CornerUV cu = load_cuv(sc, id);
             float c[3], al;
             const unsigned flip = NS == 2 ? (unsigned)-side : J.flip;
-            shade_pixel<SHADE, true>(sc, vw, J.theta, J.pb, J.eps, flip, r, sh, J.recG + ti, cu, px, py, c, uv, al);
+            shade_pixel<SHADE, true>(sc, vw, J.theta, J.sg, J.eps, flip, r, sh, J.recG + ti, cu, px, py, c, uv, al);
             const float wt = T * al;
             rgb[0] = rgb[0] + wt * c[0];
             rgb[1] = rgb[1] + wt * c[1];
@@ -1115,7 +1115,7 @@ k_tile(TileArgs a) {
     J.sc = &a.sc;
     J.vw = &vw;
     J.theta = a.theta;
-    J.pb = a.pert.bits ? a.pert.bits + (long long)pair * sc.words : nullptr;
+    J.sg = a.pert.sg ? a.pert.sg + pair * sc.sg_stride : nullptr;
     J.eps = a.pert.eps;
     J.flip = a.sgn[0] > 0.0f ? 0u : 0xFFFFFFFFu;
     const long long slot = (long long)li * NS;
@@ -1167,7 +1167,7 @@ k_tile_b(BatchArgs b) {
     J.sc = &sc;
     J.vw = &vw;
     J.theta = Sc.theta;
-    J.pb = Sc.bits + (long long)I.pair * sc.words;
+    J.sg = Sc.sg + I.pair * sc.sg_stride;
     J.eps = Sc.eps;
     J.flip = 0u;
     const int tile = (int)(w - I.tile0);
