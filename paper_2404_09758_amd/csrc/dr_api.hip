@@ -229,8 +229,9 @@ static DView make_dview(const dr_view& v, int tile, long long tgt_off) {
 }
 
 // Tile counts of the views (the bins' layout), once views 0 .. n-1 are set.
-static void finish_views(DViews& dv, int n) {
+static void finish_views(DViews& dv, int n, int n_pairs) {
     dv.n = n;
+    dv.n_pairs = n_pairs;
     dv.tsum[0] = 0;
     for (int v = 0; v < n; ++v) dv.tsum[v + 1] = dv.tsum[v] + dv.v[v].tiles_x * dv.v[v].tiles_y;
 }
@@ -544,7 +545,7 @@ extern "C" dr_status dr_render(dr_ctx* c, const float* theta, const dr_view* vie
     DViews dv;
     std::memset(&dv, 0, sizeof(dv));
     dv.v[0] = make_dview(*view, tile, 0);
-    finish_views(dv, 1);
+    finish_views(dv, 1, 1);
     int max_tiles = dv.tsum[1];
     s = ensure_raster(c, 1, 1, max_tiles);
     if (s) return s;
@@ -668,7 +669,8 @@ struct EstScratch {
     long long* qtot = nullptr;
     float* fpos = nullptr;
     int cap = 0;
-    long long per = 1;
+    long long per = 1;          // items per raster launch
+    long long group = 1;        // items per setup launch (a multiple of per, or all)
 };
 
 // Validated arguments of an estimate.
@@ -698,7 +700,7 @@ static dr_status estimate_check(dr_ctx* c, const float* theta, const dr_view* vi
         tgt_off += 3ll * views[v].width * views[v].height;
         pl.max_tiles = std::max(pl.max_tiles, pl.dv.v[v].tiles_x * pl.dv.v[v].tiles_y);
     }
-    finish_views(pl.dv, n_views);
+    finish_views(pl.dv, n_views, n_pairs);
     pl.items = (long long)n_pairs * n_views;
     return DR_OK;
 }
@@ -717,10 +719,26 @@ static long long pert_slots(const EstPlan& pl, long long per) {
     return 2 * (per >= pl.items ? pl.items / nv : (per + nv - 1) / nv + 1);
 }
 
+// Items per setup launch.  A launch that sets up one item leaves most of the
+// chip idle and puts its latency before every raster launch, so the setup of
+// several raster launches goes in one as long as their records, bins and spill
+// lists stay within SETUP_SCRATCH (20480 triangles at 512 px: 2.5 MB an item,
+// 8.6 us of setup each alone, 1.0 us in a launch of 100).
+static constexpr long long SETUP_SCRATCH = 256ll << 20;
+
+static long long setup_group(const dr_ctx* c, const EstPlan& pl, long long per) {
+    const long long item = 2 * (c->sc.n_tris * (long long)(sizeof(TriR) + sizeof(TriS) + sizeof(TriG)) +
+                                (long long)pl.max_tiles * (c->tune.bin_capacity + 1ll) * 4 + SPILL_CAP * 8ll);
+    const long long n = std::min<long long>(std::min<long long>(SETUP_SCRATCH / item, 32767), pl.items);
+    if (n >= pl.items) return pl.items;
+    return std::max(per, n / per * per);
+}
+
 // The context's own scratch, grown as needed.
 static dr_status estimate_scratch_ctx(dr_ctx* c, const EstPlan& pl, int32_t n_pairs, bool full, EstScratch& x) {
     x.per = items_per_launch(c, pl.items);
-    dr_status s = ensure_raster(c, 2 * x.per, pert_slots(pl, x.per), pl.max_tiles);
+    x.group = setup_group(c, pl, x.per);
+    dr_status s = ensure_raster(c, 2 * x.group, pert_slots(pl, x.group), pl.max_tiles);
     if (s) return s;
     s = ensure_signs(c, n_pairs);
     if (s) return s;
@@ -763,7 +781,7 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     };
     int tile = c->tune.tile_px;
     const int max_tiles = pl.max_tiles;
-    const long long items = pl.items, per = x.per;
+    const long long items = pl.items, per = x.per, group = x.group;
     DPert dp;
     dp.sg = x.sg;
     for (int b = 0; b <= DRD_MAX_TEX; ++b) dp.eps[b] = (b < 1 + c->sc.n_tex) ? eps[b] : 0.0f;
@@ -787,7 +805,7 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     sa.recR = x.recR;
     sa.recS = x.recS;
     sa.recG = x.recG;
-    sa.whole = per >= items;
+    sa.whole = group >= items;
     sa.counts = x.counts;
     sa.bins = x.bins;
     sa.spn = x.spn;
@@ -807,7 +825,7 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     ta.recR = x.recR;
     ta.recS = x.recS;
     ta.recG = x.recG;
-    ta.whole = per >= items;
+    ta.whole = group >= items;
     ta.counts = x.counts;
     ta.bins = x.bins;
     ta.spn = x.spn;
@@ -828,12 +846,16 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     dr_status s = tessellate_into(c, theta, dp, n_pairs, 2, 1.0f, -1.0f, x.fpos, timed, &sa.fpos);
     if (s) return s;
     if (full) HIPCHK(c, launch_zero64(c->stream, x.qtot, n_pairs));
-    for (long long i0 = 0; i0 < items; i0 += per) {
-        int n = (int)std::min(per, items - i0);
+    for (long long i0 = 0; i0 < items; i0 += group) {
+        const long long n = std::min(group, items - i0);
         sa.item0 = ta.item0 = (int)i0;
-        sa.n_items = ta.n_items = n;
+        sa.n_items = (int)n;
         HIPCHK(c, run(K_SETUP, [&] { return launch_setup(c->stream, sa); }));
-        HIPCHK(c, run(K_TILE, [&] { return launch_tile(c->stream, ta, tile, full ? 3 : 0); }));
+        for (long long j = 0; j < n; j += per) {
+            ta.first = (int)j;
+            ta.n_items = (int)std::min(per, n - j);
+            HIPCHK(c, run(K_TILE, [&] { return launch_tile(c->stream, ta, tile, full ? 3 : 0); }));
+        }
     }
     FoldArgs fa;
     std::memset(&fa, 0, sizeof(fa));
@@ -977,7 +999,7 @@ static unsigned long long static_layout(const dr_ctx* c, const EstPlan& pl, int3
     x->spill = (unsigned long long*)take(slots * (unsigned long long)SPILL_CAP * sizeof(unsigned long long));
     if (sc.n_ctrl > 0) x->fpos = (float*)take((unsigned long long)n_pairs * 2ull * (unsigned long long)sc.n_verts * 12ull);
     x->cap = (int)cap;
-    x->per = per;
+    x->per = x->group = per;
     return off;
 }
 
@@ -1037,7 +1059,7 @@ extern "C" dr_status dr_loss(dr_ctx* c, const float* theta, const dr_view* views
         tgt_off += 3ll * views[v].width * views[v].height;
         max_tiles = std::max(max_tiles, dv.v[v].tiles_x * dv.v[v].tiles_y);
     }
-    finish_views(dv, n_views);
+    finish_views(dv, n_views, 1);
     dr_status s = device_guard(c);
     if (s) return s;
     s = ensure_raster(c, n_views, 1, max_tiles);
@@ -1562,7 +1584,7 @@ extern "C" dr_status dr_batch_create(dr_batch** out, const dr_batch_scene* scene
         TileArgs& ta = b->one_tile;
         sa.sc = ta.sc = S.sc;
         for (size_t v = 0; v < hv.size(); ++v) sa.views.v[v] = hv[v];
-        finish_views(sa.views, (int)hv.size());
+        finish_views(sa.views, (int)hv.size(), n_pairs);
         ta.views = sa.views;
         sa.pert.sg = S.sg;
         std::memcpy(sa.pert.eps, S.eps, sizeof(S.eps));

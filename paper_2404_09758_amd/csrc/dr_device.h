@@ -61,7 +61,7 @@ struct DView {
 
 struct DViews {
     DView v[DRD_MAX_VIEWS];
-    int n;
+    int n, n_pairs;                      // of the call
     int tsum[DRD_MAX_VIEWS + 1];         // tiles of the views before v
 };
 

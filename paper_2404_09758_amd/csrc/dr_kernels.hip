@@ -868,7 +868,8 @@ int scene_shade(const DScene& sc) {
 hipError_t launch_tile(hipStream_t st, TileArgs a, int tile, int mode) {
     // the interleaved order needs the call's units in one grid dimension
     const long long units = (long long)(a.n_items / a.n_views) * a.views.tsum[a.n_views];
-    a.interleave = a.whole && units * 512 < (1ll << 32);
+    const bool all = a.whole && (long long)a.n_items == (long long)a.views.n_pairs * a.n_views;
+    a.interleave = all && units * 1024 < (1ll << 32);
     dim3 grid((unsigned)a.max_tiles, (unsigned)a.n_items);
     if (a.interleave) grid = dim3((unsigned)units);
     if (a.sc.layers > 0) {
@@ -938,7 +939,7 @@ hipError_t launch_batch_setup(hipStream_t st, const BatchArgs& b, long long blk0
 
 hipError_t launch_batch_tile(hipStream_t st, const BatchArgs& b, long long w0, long long n) {
     BatchArgs a = b;
-    const long long most = 1ll << 22;               // a grid dimension holds 2^32 threads
+    const long long most = 1ll << 21;               // a grid dimension holds 2^32 threads
     for (a.unit0 = w0; a.unit0 < w0 + n; a.unit0 += most) {
         const unsigned grid = (unsigned)(w0 + n - a.unit0 < most ? w0 + n - a.unit0 : most);
         hipError_t e = a.tile == 8 ? launch_batch_tile_t<8>(st, a, grid)

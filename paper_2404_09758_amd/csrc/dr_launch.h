@@ -61,8 +61,8 @@ struct TileArgs {
     DPert pert;
     const float* theta;
     int n_views;
-    int item0;
-    int n_items;
+    int item0;                       // first item that the setup laid out
+    int first, n_items;              // this launch's items of those
     int whole;
     int interleave;                  // grid of tile units in (view, tile, pair) order (launch_tile)
     int nsign;
