@@ -233,21 +233,19 @@ __device__ __forceinline__ Foot footprint(float u, float v, int W, int H) {
     float x0f = floorf(x), y0f = floorf(y);
     f.fx = x - x0f;
     f.fy = y - y0f;
-    int x0 = (int)x0f, y0 = (int)y0f;
-    // x0 mod W (non-negative); UVs within a period or two need no division
-    int xa;
-    if (x0 >= 0 && x0 < W) xa = x0;
-    else if (x0 >= W && x0 < 2 * W) xa = x0 - W;
-    else if (x0 < 0 && x0 >= -W) xa = x0 + W;
-    else {
-        xa = x0 % W;
-        if (xa < 0) xa += W;
+    const int x0 = (int)x0f, y0 = (int)y0f;
+    // x0 mod W (non-negative).  Of x0, x0 - W and x0 + W as unsigned numbers
+    // the least lies in [0, W) when x0 is within a period of it; UVs further
+    // out take the division.
+    unsigned xa = min((unsigned)x0, min((unsigned)x0 - (unsigned)W, (unsigned)x0 + (unsigned)W));
+    if (xa >= (unsigned)W) {
+        int m = x0 % W;
+        xa = (unsigned)(m < 0 ? m + W : m);
     }
-    f.xa = xa;
-    f.xb = (xa + 1 == W) ? 0 : xa + 1;
-    f.ya = y0 < 0 ? 0 : (y0 > H - 1 ? H - 1 : y0);
-    int y1 = y0 + 1;
-    f.yb = y1 < 0 ? 0 : (y1 > H - 1 ? H - 1 : y1);
+    f.xa = (int)xa;
+    f.xb = (f.xa + 1 == W) ? 0 : f.xa + 1;
+    f.ya = max(0, min(y0, H - 1));
+    f.yb = max(0, min(y0 + 1, H - 1));
     return f;
 }
 
@@ -264,6 +262,26 @@ __device__ __forceinline__ T gload(const T* p) {
 #else
     return *p;             // host pass: parsed, never run
 #endif
+}
+
+// A footprint: its first texel (row ya, column xa) and its last (yb, xb),
+// column in the low half, row in the high one (texture sides are at most 2^15,
+// so all ones matches no texel).  Nearest mode: both the nearest texel.
+struct FootBox {
+    unsigned a, b;
+};
+
+__device__ __forceinline__ FootBox foot_corners(const DScene& sc, const Foot& f) {
+    int xa = f.xa, xb = f.xb, ya = f.ya, yb = f.yb;
+    if (sc.tex_mode == 1) {
+        xa = xb = (f.fx >= 0.5f) ? f.xb : f.xa;
+        ya = yb = (f.fy >= 0.5f) ? f.yb : f.ya;
+    }
+    return {(unsigned)xa | ((unsigned)ya << 16), (unsigned)xb | ((unsigned)yb << 16)};
+}
+
+__device__ __forceinline__ FootBox foot_box(const DScene& sc, int c, float u, float v) {
+    return foot_corners(sc, footprint(u, v, sc.cls_w[c], sc.cls_h[c]));
 }
 
 // Signs of a footprint's four texels: sg is the class's first group byte.
@@ -402,14 +420,21 @@ __device__ __forceinline__ float sqrt_rn(float x) { return sqrt_fast_ok(x) ? sqr
 // 1.0f / y, correctly rounded
 __device__ __forceinline__ float rcp_rn(float y) { return rcp_fast_ok(y) ? rcp_rn_fast(y) : 1.0f / y; }
 
+// x / |x| (0 for 0): 1 / sqrt(l2) with each operation correctly rounded.  One
+// range test serves both short sequences: the root of an operand in
+// [2^-96, 2^126] lies in [2^-48, 2^63], within the reciprocal's range.
 __device__ __forceinline__ void nrm3(float* x) {
-    float l2 = (x[0] * x[0] + x[1] * x[1]) + x[2] * x[2];
-    if (l2 > 0.0f) {
-        float inv = rcp_rn(sqrt_rn(l2));                     // 1 / sqrt(l2), each correctly rounded
-        x[0] = x[0] * inv; x[1] = x[1] * inv; x[2] = x[2] * inv;
+    const float l2 = (x[0] * x[0] + x[1] * x[1]) + x[2] * x[2];
+    float inv;
+    if (sqrt_fast_ok(l2)) {
+        inv = rcp_rn_fast(sqrt_rn_fast(l2));
+    } else if (l2 > 0.0f) {
+        inv = 1.0f / sqrtf(l2);
     } else {
         x[0] = 0.0f; x[1] = 0.0f; x[2] = 0.0f;
+        return;
     }
+    x[0] = x[0] * inv; x[1] = x[1] * inv; x[2] = x[2] * inv;
 }
 
 __device__ __forceinline__ float dot3(const float* a, const float* b) {
@@ -501,6 +526,7 @@ __device__ __forceinline__ Attr frag_attr(const DScene& sc, const TriR& r, const
 // textures are compact (sample_texels); SHADE_ANY reads the shading from the
 // scene and takes textures of any size.  DEEP: the albedo has four channels.
 // G: the face's GGX record (read for GGX only).
+// fb: the footprint of texel class 0 (foot_box's value).
 #define SHADE_ANY 3
 
 template <int SHADE, bool DEEP>
@@ -508,7 +534,7 @@ __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, c
                                             const uint8_t* __restrict__ sg, const float* eps, unsigned flip,
                                             const TriR& r, const TriS& s, const TriG* __restrict__ G,
                                             const CornerUV& cu, int px, int py, float* rgb, float* uvo,
-                                            float& opacity) {
+                                            FootBox& fb, float& opacity) {
     constexpr bool COMPACT = SHADE != SHADE_ANY;
     const int shading = SHADE != SHADE_ANY ? SHADE : sc.shading;
     Attr a = frag_attr(sc, r, s, cu, px, py);
@@ -524,6 +550,7 @@ __device__ __forceinline__ void shade_pixel(const DScene& sc, const DView& vw, c
     FootSigns sig0 = {{0u, 0u}};
     if (sc.n_tex > 0) {
         foot0 = footprint(u, v, sc.cls_w[0], sc.cls_h[0]);
+        fb = foot_corners(sc, foot0);
         if (pert) sig0 = foot_signs(gsg + sc.cls_goff[0], sc.cls_w[0], flip, foot0);
         sample_tex<DEEP ? 4 : 3, COMPACT>(sc, th, pert && eps[1] != 0.0f, eps[1], 0, foot0, sig0, alb);
     }
@@ -627,8 +654,7 @@ __device__ __forceinline__ long long quantize(float delta, int& flag) {
 // downstream loss with respect to the pixel's colour and the difference is
 // <g, I+ - I->, the first-order change of that loss, so that the estimator
 // approximates the vector-Jacobian product of the render.
-__device__ __forceinline__ float pixel_delta(const float* p, const float* m, const float* t_, int img) {
-    const DRD_GLOBAL float* t = (const DRD_GLOBAL float*)t_;
+__device__ __forceinline__ float pixel_delta(const float* p, const float* m, const float* t, int img) {
     float t0 = t[0], t1 = t[1], t2 = t[2];
     if (img) {
         float d0 = p[0] - m[0], d1 = p[1] - m[1], d2 = p[2] - m[2];

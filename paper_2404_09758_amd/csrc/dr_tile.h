@@ -103,11 +103,11 @@ struct RasterShared {
 struct RasterJob {
     const TriR* rec;             // [NS, n_tris]
     int n_tris;
-    const unsigned* counts;      // of the tile; sign 1's tstride further
+    unsigned* counts;            // of the tile; sign 1's tstride further
     const unsigned* bins;        // of the tile; sign 1's tstride * cap further
     long long tstride;
     int cap;
-    const unsigned* spn;         // [NS, 2]
+    unsigned* spn;               // [NS, 2]
     const unsigned long long* spill;   // [NS, SPILL_CAP]
     int tile;
     int px0, py0, cx1, cy1;      // the tile's pixels that lie in the view
@@ -427,15 +427,15 @@ __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TIL
         }
         __syncthreads();
     }
-}
-
-// After the tile's raster: leave its bin (counter *count) empty for the next
-// use, and the last overflowing tile of the render empties the render's spill
-// list.
-__device__ __forceinline__ void release_bin(unsigned* count, unsigned cap, unsigned* spn) {
-    const unsigned c = *count;
-    *count = 0u;
-    if (c > cap && atomicSub(&spn[1], 1u) == 1u) spn[0] = 0u;
+    // leave the bins empty for the next use; the last overflowing tile of a
+    // render empties the render's spill list
+    if (tid == 0) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            J.counts[s * J.tstride] = 0u;
+            if (cnt[s] > cap && atomicSub(&J.spn[2 * s + 1], 1u) == 1u) J.spn[2 * s] = 0u;
+        }
+    }
 }
 
 // ------------------------------------------------ tile-local aggregation --
@@ -588,8 +588,6 @@ struct TileJob {
     const float* eps;                    // per block
     unsigned flip;                       // one-sign modes: sign 0 is the minus render (all ones) or the plus one
     RasterJob ras;                       // (its tile's pixels are set by the body)
-    unsigned* counts;                    // bin counter of the tile; sign 1's ras.tstride further
-    unsigned* spn;
     const TriS* recS;                    // [NS, n_tris]
     const TriG* recG;
     // estimate
@@ -622,23 +620,6 @@ __device__ __forceinline__ void both_sides(float x, float& p, float& m) {
     both_sides(__float_as_uint(x), a, b);
     p = __uint_as_float(a);
     m = __uint_as_float(b);
-}
-
-// A footprint: its first texel (row ya, column xa) and its last (yb, xb),
-// column in the low half, row in the high one (texture sides are at most 2^15,
-// so all ones matches no texel).  Nearest mode: both the nearest texel.
-struct FootBox {
-    unsigned a, b;
-};
-
-__device__ __forceinline__ FootBox foot_box(const DScene& sc, int c, float u, float v) {
-    const Foot f = footprint(u, v, sc.cls_w[c], sc.cls_h[c]);
-    int xa = f.xa, xb = f.xb, ya = f.ya, yb = f.yb;
-    if (sc.tex_mode == 1) {
-        xa = xb = (f.fx >= 0.5f) ? f.xb : f.xa;
-        ya = yb = (f.fy >= 0.5f) ? f.yb : f.ya;
-    }
-    return {(unsigned)xa | ((unsigned)ya << 16), (unsigned)xb | ((unsigned)yb << 16)};
 }
 
 // Texels of a footprint, as bits 2 row + column: those that repeat an earlier
@@ -807,12 +788,20 @@ __device__ __forceinline__ T block_sum(T* red, T v, int tid) {
     return red[0];
 }
 
+// A pixel's target colour (image form: the loss gradient at it).
+__device__ __forceinline__ void pixel_target(const TileJob& J, long long pix, float* t) {
+    struct Rgb { float c[3]; };
+    const Rgb v = gload((const Rgb*)(J.targets + 3 * pix));
+#pragma unroll
+    for (int c = 0; c < 3; ++c) t[c] = v.c[c];
+}
+
 // The loss difference's fixed-point code of a pixel from its two sides'
 // colours; `note`: this lane reports its saturation.
-__device__ __forceinline__ long long pixel_code(const TileJob& J, const float* P, const float* M, long long pix,
+__device__ __forceinline__ long long pixel_code(const TileJob& J, const float* P, const float* M, const float* target,
                                                 bool note) {
     int flag;
-    const long long q = quantize(pixel_delta(P, M, J.targets + 3 * pix, J.img), flag);
+    const long long q = quantize(pixel_delta(P, M, target, J.img), flag);
     if (flag && note) atomicAdd(&J.ras.stats[flag == 1 ? ST_SATURATIONS : ST_NONFINITE], 1ull);
     return q;
 }
@@ -855,7 +844,6 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
     for (int j = tid; j < NS * TILE * KS; j += TB) S.key[j] = ~0ull;
     raster_tile<TILE, false, NS, TB, C::NE>(R, S.u.ras, S.key, 1);
     __syncthreads();                             // (a tile without triangles has only cleared its keys)
-    if (tid < NS) release_bin(&J.counts[tid * R.tstride], (unsigned)R.cap, J.spn + 2 * tid);
     if constexpr (MODE == 0) groups_clear<C>(S.u.g, tid);
 
     GroupTable tb{};
@@ -866,14 +854,20 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
         const int x = px0 + lx, y = py0 + ly;
         const bool inpix = x < vw.W && y < vw.H;
         const int px = 256 * x + 128, py = 256 * y + 128;
+        const long long pix = (long long)y * vw.W + x;
+        // the target pixel's read is under way while the pixel is shaded
+        float tgt[3] = {0.0f, 0.0f, 0.0f};
+        if (MODE != 1 && inpix) pixel_target(J, pix, tgt);
         unsigned id[NS];
         float rgb[NS][3], uv[NS][2];
+        FootBox f[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const unsigned long long k = inpix ? S.key[(s * TILE + ly) * KS + lx] : ~0ull;
             id[s] = (k == ~0ull) ? DRD_BG : (unsigned)k;
             rgb[s][0] = 0.0f; rgb[s][1] = 0.0f; rgb[s][2] = 0.0f;
             uv[s][0] = 0.0f; uv[s][1] = 0.0f;
+            f[s] = {0xFFFFFFFFu, 0xFFFFFFFFu};
             if (id[s] != DRD_BG) {
                 const TriR* rec = R.rec + (long long)s * sc.n_tris;
                 const TriS* recS = J.recS + (long long)s * sc.n_tris;
@@ -884,14 +878,12 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
                 float alpha;
                 const unsigned flip = NS == 2 ? (s ? 0xFFFFFFFFu : 0u) : J.flip;
                 shade_pixel<SHADE, false>(sc, vw, J.theta, J.sg, J.eps, flip, r, sh, recG + id[s], cu, px, py, rgb[s],
-                                          uv[s], alpha);
+                                          uv[s], f[s], alpha);
             }
         }
-        const long long pix = (long long)y * vw.W + x;
         if constexpr (MODE == 2) {
             if (inpix) {
-                const float* tg = J.targets + 3 * pix;
-                float dr = rgb[0][0] - tg[0], dg = rgb[0][1] - tg[1], db = rgb[0][2] - tg[2];
+                float dr = rgb[0][0] - tgt[0], dg = rgb[0][1] - tgt[1], db = rgb[0][2] - tgt[2];
                 loss_acc += (double)((dr * dr + dg * dg) + db * db);
             }
         } else if constexpr (MODE == 1) {
@@ -910,17 +902,15 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
             // an empty contribution set (background in both renders) adds nothing
             const bool act = inpix && (id[0] != DRD_BG || id[NS - 1] != DRD_BG) && (MODE == 3 || J.any_act);
             long long q = 0;
-            if (act) q = pixel_code(J, rgb[0], rgb[NS - 1], pix, true);
+            if (act) q = pixel_code(J, rgb[0], rgb[NS - 1], tgt, true);
             if constexpr (MODE == 3) {
                 qsum += q;
             } else {
-                FootBox f[2] = {{0xFFFFFFFFu, 0xFFFFFFFFu}, {0xFFFFFFFFu, 0xFFFFFFFFu}};
                 unsigned lo = 0xFFFFFFFFu, hi = 0u;
-                if (sc.n_cls > 0 && J.act_cls[0] && act) {
+                if (act) {
 #pragma unroll
                     for (int s = 0; s < 2; ++s)
                         if (id[s] != DRD_BG) {
-                            f[s] = foot_box(sc, 0, uv[s][0], uv[s][1]);
                             lo = pk_min(lo, pk_min(f[s].a, f[s].b));
                             hi = pk_max(hi, pk_max(f[s].a, f[s].b));
                         }
@@ -1027,7 +1017,6 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
     raster_tile<TILE, true, NS, TB, C::NE>(R, S.u.ras, S.key, sc.layers);
     __syncthreads();
     const int L = sc.layers;
-    if (tid < NS) release_bin(&J.counts[tid * R.tstride], (unsigned)R.cap, J.spn + 2 * tid);
     if constexpr (MODE == 0) groups_clear<C>(S.u.g, tid);
 
     const int side = NS == 2 ? lane >> 5 : 0;
@@ -1037,6 +1026,8 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
     const bool inpix = x < vw.W && y < vw.H;
     const int px = 256 * x + 128, py = 256 * y + 128;
     const long long pix = (long long)y * vw.W + x;
+    float tgt[3] = {0.0f, 0.0f, 0.0f};
+    if (MODE != 1 && inpix) pixel_target(J, pix, tgt);
     unsigned long long* mine = &S.key[(side * NPIX + local) * LM];   // this side's fragments
     float* mine_v = &S.v[MODE == 0 ? (side * NPIX + local) * LM : 0];
     // Lists fill from the front, so a list is empty when its first layer is.
@@ -1058,7 +1049,8 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
             const CornerUV cu = load_cuv(sc, id);
             float c[3], al;
             const unsigned flip = NS == 2 ? (unsigned)-side : J.flip;
-            shade_pixel<SHADE, true>(sc, vw, J.theta, J.sg, J.eps, flip, r, sh, J.recG + ti, cu, px, py, c, uv, al);
+            FootBox fb;
+            shade_pixel<SHADE, true>(sc, vw, J.theta, J.sg, J.eps, flip, r, sh, J.recG + ti, cu, px, py, c, uv, fb, al);
             const float wt = T * al;
             rgb[0] = rgb[0] + wt * c[0];
             rgb[1] = rgb[1] + wt * c[1];
@@ -1092,8 +1084,7 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
     if constexpr (MODE == 2) {
         double loss_acc = 0.0;
         if (inpix) {
-            const float* tg = J.targets + 3 * pix;
-            float dr = rgb[0] - tg[0], dg = rgb[1] - tg[1], db = rgb[2] - tg[2];
+            float dr = rgb[0] - tgt[0], dg = rgb[1] - tgt[1], db = rgb[2] - tgt[2];
             loss_acc = (double)((dr * dr + dg * dg) + db * db);
         }
         loss_acc = block_sum<TB>(S.u.red, loss_acc, tid);
@@ -1108,7 +1099,7 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
         for (int c = 0; c < 3; ++c) both_sides(rgb[c], P[c], M[c]);
         const bool act = inpix && (anyP | anyM) != 0u && (MODE == 3 || J.any_act);
         long long q = 0;
-        if (act) q = pixel_code(J, P, M, pix, side == 0);
+        if (act) q = pixel_code(J, P, M, tgt, side == 0);
         if constexpr (MODE == 3) {
             q = block_sum<TB>(S.u.qred, side == 0 ? q : 0ll, tid);
             if (tid == 0 && q != 0) atomicAdd((unsigned long long*)J.qtot, (unsigned long long)q);
@@ -1230,11 +1221,11 @@ __device__ __forceinline__ TileJob single_job(const TileArgs& a, int li, int pai
     const long long base = bin_base(a.whole, a.views, a.n_views, NS, a.max_tiles, li, 0) + tile;
     J.ras.rec = a.recR + slot * sc.n_tris;
     J.ras.n_tris = sc.n_tris;
-    J.ras.counts = J.counts = a.counts + base;
+    J.ras.counts = a.counts + base;
     J.ras.bins = a.bins + base * a.cap;
     J.ras.tstride = a.whole ? vw.tiles_x * vw.tiles_y : a.max_tiles;
     J.ras.cap = a.cap;
-    J.ras.spn = J.spn = a.spn + 2 * slot;
+    J.ras.spn = a.spn + 2 * slot;
     J.ras.spill = a.spill + slot * SPILL_CAP;
     J.ras.tile = tile;
     J.ras.stats = a.stats;
@@ -1270,11 +1261,11 @@ __device__ __forceinline__ TileJob batch_job(const BatchArgs& b, int item, int t
     J.flip = 0u;
     J.ras.rec = b.recR + I.rec_off;
     J.ras.n_tris = sc.n_tris;
-    J.ras.counts = J.counts = b.counts + I.cnt_off + tile;
+    J.ras.counts = b.counts + I.cnt_off + tile;
     J.ras.bins = b.bins + I.bin_off + (long long)tile * I.cap;
     J.ras.tstride = vw.tiles_x * vw.tiles_y;
     J.ras.cap = I.cap;
-    J.ras.spn = J.spn = b.spn + 2 * I.sp_off;
+    J.ras.spn = b.spn + 2 * I.sp_off;
     J.ras.spill = b.spill + I.sp_off * SPILL_CAP;
     J.ras.tile = tile;
     J.ras.stats = b.stats;
