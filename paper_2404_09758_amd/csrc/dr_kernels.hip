@@ -562,6 +562,11 @@ __device__ __forceinline__ void fold_group(const DScene& sc, long long g, long l
     }
 }
 
+// The last kernel of an estimate tells the host the largest bin seen so far.
+__device__ __forceinline__ void tell_max_bin(const FoldArgs& a, long long g) {
+    if (g == 0 && a.seen) __hip_atomic_store(a.seen, a.stats[ST_MAX_BIN], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Full-image estimate: every parameter of an active block gets
 // s_i^(n) * T[n] for every pair n; every active group counts one
 // contribution per (pair, view).  T is zeroed by k_zero64 before the call.
@@ -569,6 +574,7 @@ __global__ void __launch_bounds__(256) k_broadcast(FoldArgs a) {
     long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const DScene& sc = a.sc;
     if (g >= sc.G) return;
+    tell_max_bin(a, g);
     bool active = false;
     for_params(sc, g, [&](long long, int b, int) { active = active || a.eps[b] != 0.0f; });
     if (!active) return;
@@ -599,6 +605,7 @@ __global__ void k_zero64(long long* p, int n) {
 __global__ void __launch_bounds__(256) k_fold(FoldArgs a) {
     long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= a.sc.G) return;
+    tell_max_bin(a, g);
     fold_group(a.sc, g, a.R, a.sg, a.n_pairs, a.eps, a.Q);
 }
 

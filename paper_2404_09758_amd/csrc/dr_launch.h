@@ -106,6 +106,9 @@ struct FoldArgs {
     const long long* qtot;       // [pairs]
     unsigned* K;
     int n_views;
+    // the largest bin so far, told to the host (pinned memory; null: not told)
+    const unsigned long long* stats;
+    unsigned long long* seen;
 };
 
 struct OptimConst {
