@@ -126,3 +126,81 @@ def test_raster_edges_bit_exact(tile, cap, layers):
     Q, K = ctx.estimate_grad(th, sc.views, torch.tensor(tg[0], device=DEV).reshape(-1), 11, 2, 2, sc.eps)
     assert np.array_equal(host(K).view(np.uint32), Ko)
     assert np.array_equal(host(Q), Qo)
+
+
+# Subdivision scatter: control lists shorter and longer than a row of 16 lanes
+# (a fan's hub raises the valence), pairs with one side background, tiles whose
+# every pixel is a pair of its own, and the three tile sizes' pair tables.
+def fan_scene(n, levels, res, seed=0):
+    """A closed double pyramid over an n-gon: two hub vertices of valence n."""
+    rng = np.random.default_rng(40 + seed)
+    ang = 2 * np.pi * np.arange(n) / n
+    pos = np.concatenate([np.stack([np.cos(ang), 0.25 * np.sin(3 * ang), np.sin(ang)], 1), [[0, 0.9, 0], [0, -0.9, 0]]])
+    tri = [(i, n, (i + 1) % n) for i in range(n)] + [((i + 1) % n, n + 1, i) for i in range(n)]
+    tri = np.array(tri, np.int32)
+    cuv = rng.uniform(0, 1, (len(tri), 3, 2)).astype(np.float32)
+    tex = [rng.uniform(0.05, 0.95, (40, 24, 3)).astype(np.float32)]
+    ttex = [rng.uniform(0.05, 0.95, (40, 24, 3)).astype(np.float32)]
+    pos = pos.astype(np.float32)
+    tpos = (pos + rng.normal(0, 0.03, pos.shape)).astype(np.float32)
+    eps = [0.03, 1.0 / 255.0]
+    return S.Scene("fan", tri, cuv, pos, tex, tpos, ttex, [S.look_at_view(res, res - 13, 20.0, 35.0)],
+                   shading=S.SHADING_LAMBERT, eps=eps, lr=list(eps), n_pairs=1, subdiv_levels=levels)
+
+
+@pytest.mark.parametrize("n,levels,res,tile", [(3, 1, 40, 8), (24, 1, 90, 16), (24, 2, 60, 32), (40, 2, 100, 16),
+                                               (40, 2, 33, 8)])
+def test_subdivision_scatter_bit_exact(n, levels, res, tile):
+    print(f"[kernels] subdivision n {n} levels {levels} res {res} tile {tile}", flush=True)
+    sc = fan_scene(n, levels, res)
+    o = oracle.Oracle(sc)
+    tg = [o.render(sc.flat_params(True), v)[0] for v in sc.views]
+    Qo, Ko, _, _ = o.estimate(sc.flat_params(), sc.views, tg, 3, 1, 2, sc.eps)
+    ctx = api.Context(sc, DEV, tuning=(tile, 256, 0))
+    Q, K = ctx.estimate_grad(torch.tensor(sc.flat_params(), device=DEV), sc.views,
+                             torch.tensor(tg[0], device=DEV).reshape(-1), 3, 1, 2, sc.eps)
+    assert np.array_equal(host(K).view(np.uint32), Ko)
+    assert np.array_equal(host(Q), Qo)
+    assert np.count_nonzero(Qo) > 0
+
+
+# Sign bytes: groups at and around a block's chunk (8192), texel classes of
+# their own, four-channel albedo; the texel box: rectangles at its limit, the
+# UV seam, clamped rows, a texture finer than the pixels (hashed instead).
+@pytest.mark.parametrize("tex_shapes,shading,layers,tile,freq", [
+    (((8192, 1, 3),), 1, 0, 16, 6), (((91, 90, 3),), 1, 0, 8, 6), (((1, 8193, 3),), 0, 0, 16, 6),
+    (((96, 128, 3), (64, 50, 3), (200, 3, 1)), 2, 0, 16, 5), (((128, 128, 3), (128, 128, 3), (32, 32, 1)), 2, 0, 32, 5),
+    (((33, 47, 4),), 1, 3, 16, 5), (((600, 700, 4),), 0, 2, 8, 4), (((1024, 900, 3),), 1, 0, 16, 8),
+    (((2, 2, 3),), 1, 0, 16, 6)])
+def test_signs_and_texel_box_bit_exact(tex_shapes, shading, layers, tile, freq):
+    print(f"[kernels] textures {tex_shapes} shading {shading} layers {layers} tile {tile}", flush=True)
+    sc = H.sphere_scene(freq, 0, res=(91, 75), shading=shading, tex_shapes=tex_shapes, seed=8, views=2)
+    sc.layers = layers
+    o = oracle.Oracle(sc)
+    tg = [o.render(sc.flat_params(True), v)[0] for v in sc.views]
+    Qo, Ko, _, _ = o.estimate(sc.flat_params(), sc.views, tg, 21, 4, 2, sc.eps)
+    ctx = api.Context(sc, DEV, tuning=(tile, 256, 0))
+    th = torch.tensor(sc.flat_params(), device=DEV)
+    dtg = torch.cat([torch.tensor(t, device=DEV).reshape(-1) for t in tg])
+    Q, K = ctx.estimate_grad(th, sc.views, dtg, 21, 4, 2, sc.eps)
+    assert np.array_equal(host(K).view(np.uint32), Ko)
+    assert np.array_equal(host(Q), Qo)
+
+
+# Plain launches share a setup of as many items as fit its scratch: 5 views x
+# 7 pairs in launches of 1, 2, 3 and 4 items, with bins large enough that the
+# items need several setups.
+@pytest.mark.parametrize("items,cap", [(1, 256), (2, 65536), (3, 16384), (4, 65536)])
+def test_plain_launches_share_setups_bit_exact(items, cap):
+    print(f"[kernels] items {items} cap {cap}", flush=True)
+    sc = H.sphere_scene(6, 0, res=(120, 104), shading=2, tex_shapes=((32, 32, 3), (32, 32, 3), (16, 16, 1)), seed=5,
+                        views=5)
+    o = oracle.Oracle(sc)
+    tg = [o.render(sc.flat_params(True), v)[0] for v in sc.views]
+    Qo, Ko, _, _ = o.estimate(sc.flat_params(), sc.views, tg, 2, 6, 7, sc.eps)
+    ctx = api.Context(sc, DEV, tuning=(16, cap, items))
+    th = torch.tensor(sc.flat_params(), device=DEV)
+    dtg = torch.cat([torch.tensor(t, device=DEV).reshape(-1) for t in tg])
+    Q, K = ctx.estimate_grad(th, sc.views, dtg, 2, 6, 7, sc.eps)
+    assert np.array_equal(host(K).view(np.uint32), Ko)
+    assert np.array_equal(host(Q), Qo)
