@@ -466,11 +466,11 @@ extern "C" dr_status dr_create(dr_ctx** out, const dr_scene* s, const dr_tuning*
 extern "C" dr_status dr_destroy(dr_ctx* c) {
     if (!c) return DR_E_INVALID;
     (void)hipStreamSynchronize(c->stream);
-    if (c->h_seen) (void)hipHostFree(c->h_seen);
     void* ptrs[] = {c->recR, c->recS, c->counts, c->bins, c->spn, c->spill, c->R, c->sg, c->stats, c->partials,
                     c->recG, c->qtot, c->tri_rowptr, c->tri_cols, c->fpos};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
+    if (c->h_seen) (void)hipHostFree(c->h_seen);
     c->timer.destroy();
     delete c;
     return DR_OK;

@@ -458,7 +458,15 @@ __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TIL
 // against the table alone: 1483 -> 1353 us.
 
 #define HASH_NONE 0xFFFFFFFFu    // no group
-#define HASH_PROBES 64
+// Slots looked at for a group before its sum goes straight to memory.  Tiles at
+// a texture's pole or seam hold nearly as many texels as slots; with 64 slots
+// looked at their adds ran along the full table, 27 us of a 47 us launch of
+// one 512 px item.  Whole steps with 64 / 6 / 4 / 3 / 2 slots: 512 px, 128
+// single-item launches 4886 / 3270 / 3256 / 3256 / 3225 us, four layers
+// 270 / 246 / 245 / 245 / 249, 10240-triangle soup (nearest texels, about 500
+// groups a tile) 1399 / 1388 / 1387 / 1452 / 1971, 1024 px GGX
+// 1337 / 1326 / 1323 / 1320 / 1319.
+#define HASH_PROBES 5
 
 // A slot packs the group's sum and count into one 64-bit word,
 // sum * 2^12 + count, so one LDS atomic adds both: a tile has at most 1024
