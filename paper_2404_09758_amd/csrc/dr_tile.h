@@ -55,8 +55,12 @@ struct TileCfg {
     static constexpr int LOG2T = TILE == 8 ? 8 : (TILE == 16 ? 10 : 11);
     static constexpr int LOG2B = TILE == 8 ? 7 : (TILE == 16 ? 9 : 10);
     static constexpr int BOX = TILE == 8 ? 320 : (TILE == 16 ? 1120 : 1536);
-    // triangles rasterised at a time
-    static constexpr int NE = TILE == 32 ? 128 : (TB < 192 ? TB : 192);
+    // triangles rasterised at a time: tiles at a silhouette hold 200 to 250, and
+    // end the launch when they take a second batch (192 against 256, whole
+    // steps: launches of one 512 px item 3265 / 3088 us, 12 uneven scenes
+    // 1195 / 1175, others even)
+    static constexpr int NEMAX = DEEP ? 192 : 256;
+    static constexpr int NE = TILE == 32 ? 128 : (TB < NEMAX ? TB : NEMAX);
 };
 
 // Keys per row of a tile: spare ones after its pixels for opaque tiles, since
@@ -93,8 +97,7 @@ struct RasterShared {
     // bit i: a triangle begins at slot i of the batch
     unsigned long long begin[NE * TILE * (TILE / 4) / 64];
     unsigned wtot[NW];           // slots and triangles staged by each wave
-    unsigned big[NE];            // large triangles of the batch (bit 31: sign)
-    unsigned nbig;               // their number
+    unsigned nbig;               // large triangles of the batch: tri[NE - 1 - i].t (bit 31: sign)
     unsigned nhit;
 };
 
@@ -345,7 +348,7 @@ __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TIL
             unsigned at = 0u;
             if (lane == 0) at = atomicAdd(&S.nbig, (unsigned)__popcll(lm));
             at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
-            if (large) S.big[at + lanes_below(lm)] = t | ((unsigned)s << 31);
+            if (large) S.tri[NE - 1 - (int)(at + lanes_below(lm))].t = t | ((unsigned)s << 31);
         }
         if (tid == 0) S.nhit = 0u;
         __syncthreads();
@@ -406,7 +409,7 @@ __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TIL
         // ---- its large triangles, 64 pixels of a box per wave and pass
         const unsigned nbig = S.nbig;
         for (unsigned i = 0; i < nbig; ++i) {
-            const unsigned ts = (unsigned)__builtin_amdgcn_readfirstlane((int)S.big[i]);
+            const unsigned ts = (unsigned)__builtin_amdgcn_readfirstlane((int)S.tri[NE - 1 - (int)i].t);
             const unsigned tt = ts & 0x7FFFFFFFu;
             const int sb = (int)(ts >> 31);
             const TriR b = gload(&J.rec[(long long)sb * J.n_tris + tt]);
