@@ -550,25 +550,40 @@ __device__ __forceinline__ void table_add_all(const GroupTable& tb, long long* _
 // with a slot per pixel (so every pair finds one) that takes the keys' place,
 // and then adds each distinct pair's sum to the union of its two lists once,
 // 16 lanes to a pair (before: a butterfly sum per distinct triangle of a wave,
-// and a merge of the two lists per pixel where they differed).
+// and a merge of the two lists per pixel where they differed).  Vertices before
+// texels: in a crowded table the texels' many groups would take the slots of the
+// few that every pixel adds to (the other order: 1487 -> 2306 us).
 struct PairSlot {
     unsigned long long key;              // + triangle + 1 (high half), - triangle + 1; 0: empty
     unsigned long long sum;              // packed sum and count
 };
 
+// Every lane of a wave calls; list: the slots in use, *n_list of them.
 template <int N>
-__device__ __forceinline__ void pair_add(PairSlot* slots, unsigned tp, unsigned tm, long long q) {
+__device__ __forceinline__ void pair_add(PairSlot* slots, unsigned short* list, unsigned* n_list, bool act,
+                                         unsigned tp, unsigned tm, long long q) {
     const unsigned long long k = ((unsigned long long)(tp + 1u) << 32) | (tm + 1u);
     unsigned h = ((tp * 0x9E3779B1u) ^ (tm * 0x85EBCA6Bu)) >> 16;
-    for (int probe = 0; probe < N; ++probe, ++h) {
-        PairSlot& p = slots[h & (N - 1)];
-        unsigned long long seen = __hip_atomic_load(&p.key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (seen == 0ull) seen = atomicCAS(&p.key, 0ull, k);
-        if (seen == 0ull || seen == k) {
-            atomicAdd(&p.sum, pack_sc(q, 1u));
-            return;
+    bool fresh = false;
+    if (act) {
+        for (int probe = 0; probe < N; ++probe, ++h) {
+            PairSlot& p = slots[h & (N - 1)];
+            unsigned long long seen = __hip_atomic_load(&p.key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (seen == 0ull) {
+                seen = atomicCAS(&p.key, 0ull, k);
+                fresh = seen == 0ull;
+            }
+            if (fresh || seen == k) {
+                atomicAdd(&p.sum, pack_sc(q, 1u));
+                break;
+            }
         }
     }
+    const unsigned long long m = __ballot(fresh);
+    unsigned base = 0;
+    if ((threadIdx.x & 63) == 0 && m) base = atomicAdd(n_list, (unsigned)__popcll(m));
+    base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+    if (fresh) list[base + lanes_below(m)] = (unsigned short)(h & (N - 1));
 }
 
 // Whether x is among the 16-lane row's values of y (each lane compares with the
@@ -584,25 +599,14 @@ __device__ __forceinline__ bool in_row(int x, int y) {
 
 // Adds the distinct pairs' sums to their control vertices, a row of 16 lanes
 // to a pair.  Both lists hold each control vertex once; an entry of the - side's
-// that the + side holds too is left to the + side.  list: LDS for N slot
-// numbers, n_list zero.
+// that the + side holds too is left to the + side.
 // Bound by the latency of the list reads.  Measured at 1024 px, 48000
 // tessellated triangles, GGX, 32 items (whole step): 1920 -> 1499 us.
-template <int N, int TB>
-__device__ __forceinline__ void pair_expand(const PairSlot* slots, unsigned short* list, unsigned* n_list,
+template <int TB>
+__device__ __forceinline__ void pair_expand(const PairSlot* slots, const unsigned short* list, int n,
                                             const GroupTable& tb, long long* __restrict__ Rp,
                                             unsigned* __restrict__ K, const DScene& sc, int tid) {
-    const int lane = tid & 63, l = tid & 15;
-    for (int j = tid; j < N; j += TB) {
-        const bool occ = slots[j].key != 0ull;
-        const unsigned long long m = __ballot(occ);
-        unsigned base = 0;
-        if (lane == 0 && m) base = atomicAdd(n_list, (unsigned)__popcll(m));
-        base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
-        if (occ) list[base + lanes_below(m)] = (unsigned short)j;
-    }
-    __syncthreads();
-    const int n = (int)*n_list;
+    const int l = tid & 15;
     for (int i0 = 0; i0 < n; i0 += TB / 16) {
         const int i = i0 + (tid >> 4);
         int a0 = 0, a1 = 0, b0 = 0, b1 = 0;
@@ -629,6 +633,43 @@ __device__ __forceinline__ void pair_expand(const PairSlot* slots, unsigned shor
             if (k0 > 0) ga = a0 + k0 + l < a1 ? gload(&sc.tri_cols[a0 + k0 + l]) : -1;
             if (ga >= 0) table_add(tb, Rp, K, (unsigned)ga, q, c);
         }
+    }
+}
+
+struct Tri3 { unsigned v[3]; };
+
+// A mesh's vertices go by pairs of triangles too where the launch fills the
+// chip (256 CUs of 2048 threads): few adds, and few lanes on one vertex's slot.
+// Where it doesn't, the two barriers and the list's chain of reads cost more
+// than each pixel's up to six adds.  Whole steps per pixel / by pairs: 1024 px
+// GGX, 131072 tiles, 1320 / 1301 us; 10240-triangle soup, 131072 tiles,
+// 1384 / 1323; 12 uneven scenes 1176 / 1149; launches of 1024 tiles
+// 3082 / 3206.
+template <int TB>
+__device__ __forceinline__ bool by_pair() {
+    return (long long)gridDim.x * gridDim.y > 256 * 2048 / TB;
+}
+
+// pair_expand for a mesh's own vertices, six lanes to a pair.
+template <int TB>
+__device__ __forceinline__ void pair_verts(const PairSlot* slots, const unsigned short* list, int n,
+                                           const GroupTable& tb, long long* __restrict__ Rp,
+                                           unsigned* __restrict__ K, const DScene& sc, int tid) {
+    for (int i = tid; i < 6 * n; i += TB) {
+        const int j = (int)(((unsigned)i * 10923u) >> 16), l = i - 6 * j;      // i / 6 (exact: i < 6144)
+        const PairSlot p = slots[list[j]];
+        const unsigned tp = (unsigned)(p.key >> 32), tm = (unsigned)p.key;       // plus 1
+        const unsigned t = l < 3 ? tp : tm;
+        if (t == 0u || (l >= 3 && tm == tp)) continue;
+        const unsigned g = gload(&sc.tri[3 * (long long)(t - 1u) + (l < 3 ? l : l - 3)]);
+        if (l >= 3 && tp != 0u) {
+            const Tri3 a = gload((const Tri3*)(sc.tri + 3 * (long long)(tp - 1u)));
+            if (g == a.v[0] || g == a.v[1] || g == a.v[2]) continue;
+        }
+        long long q;
+        unsigned c;
+        unpack_sc(p.sum, q, c);
+        table_add(tb, Rp, K, g, q, c);
     }
 }
 
@@ -977,19 +1018,19 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
                 static_assert(C::NPIX == TB, "the box is known when the pixel is scattered");
                 tb = groups_open<C>(S.u.g, boxable(J), lo, hi, tid);
                 // the + side's groups, and those of the - side that it does not hold
-                if (J.act_pos && sc.n_ctrl > 0) {
-                    static_assert(sizeof(S.key) >= C::NPIX * sizeof(PairSlot), "pair table");
+                if (J.act_pos && (sc.n_ctrl > 0 || by_pair<TB>())) {
+                    static_assert(sizeof(S.key) >= C::NPIX * (sizeof(PairSlot) + 2), "pair table and list");
                     PairSlot* slots = reinterpret_cast<PairSlot*>(S.key);
+                    unsigned short* pairs = reinterpret_cast<unsigned short*>(slots + C::NPIX);
                     slots[tid] = {0ull, 0ull};
                     if (tid == 0) S.n_pairs = 0u;
                     __syncthreads();
-                    if (act) pair_add<C::NPIX>(slots, id[0], id[1], q);
+                    pair_add<C::NPIX>(slots, pairs, &S.n_pairs, act, id[0], id[1], q);
                     __syncthreads();
-                    static_assert(sizeof(S.key) >= C::NPIX * (sizeof(PairSlot) + 2), "pair list");
-                    pair_expand<C::NPIX, TB>(slots, reinterpret_cast<unsigned short*>(slots + C::NPIX), &S.n_pairs, tb,
-                                             J.Rp, J.K, sc, tid);
+                    const int n = __builtin_amdgcn_readfirstlane((int)S.n_pairs);
+                    if (sc.n_ctrl > 0) pair_expand<TB>(slots, pairs, n, tb, J.Rp, J.K, sc, tid);
+                    else pair_verts<TB>(slots, pairs, n, tb, J.Rp, J.K, sc, tid);
                 } else if (J.act_pos && act) {
-                    struct Tri3 { unsigned v[3]; };
                     Tri3 a = {{HASH_NONE, HASH_NONE, HASH_NONE}}, b = a;
                     if (id[0] != DRD_BG) a = gload((const Tri3*)(sc.tri + 3 * (long long)id[0]));
                     if (id[1] != DRD_BG && id[1] != id[0]) b = gload((const Tri3*)(sc.tri + 3 * (long long)id[1]));

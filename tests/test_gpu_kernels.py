@@ -204,3 +204,26 @@ def test_plain_launches_share_setups_bit_exact(items, cap):
     Q, K = ctx.estimate_grad(th, sc.views, dtg, 2, 6, 7, sc.eps)
     assert np.array_equal(host(K).view(np.uint32), Ko)
     assert np.array_equal(host(Q), Qo)
+
+
+# Launches that fill the chip sum their pixels by pairs of triangles first: 9
+# items of 256 px hold more tiles than that takes at each tile size.  The soup's
+# triangles share no vertices, the sphere's share most.
+@pytest.mark.parametrize("mesh", ["sphere", "soup"])
+@pytest.mark.parametrize("tile", [8, 16, 32])
+def test_vertices_by_pairs_bit_exact(mesh, tile):
+    print(f"[kernels] by pairs {mesh} tile {tile}", flush=True)
+    if mesh == "soup":
+        sc, pairs = S.make_soup(700, res=256, seed=4, pairs=9), 9
+        tg = [sc.target_image]
+        o = oracle.Oracle(sc)
+    else:
+        sc, pairs = H.sphere_scene(12, 0, res=(256, 250), shading=1, tex_shapes=((64, 64, 3),), seed=4, views=3), 3
+        o = oracle.Oracle(sc)
+        tg = [o.render(sc.flat_params(True), v)[0] for v in sc.views]
+    Qo, Ko, _, _ = o.estimate(sc.flat_params(), sc.views, tg, 8, 2, pairs, sc.eps)
+    ctx = api.Context(sc, DEV, tuning=(tile, 256, 0))
+    dtg = torch.cat([torch.as_tensor(t, device=DEV).reshape(-1) for t in tg])
+    Q, K = ctx.estimate_grad(torch.tensor(sc.flat_params(), device=DEV), sc.views, dtg, 8, 2, pairs, sc.eps)
+    assert np.array_equal(host(K).view(np.uint32), Ko)
+    assert np.array_equal(host(Q), Qo)
