@@ -18,18 +18,18 @@ __device__ __forceinline__ int xcd_tile(int bid, int nb) {
 }
 
 // Rasterise triangle t over the tile: one lane per covered pixel.  Opaque
-// (DEEP false): key[pixel] keeps the least depth|id (64-bit atomic min).
-// Deep: key[pixel * DRD_MAX_LAYERS + l] keeps the L least keys in order,
+// (LM 0): key[pixel] keeps the least depth|id (64-bit atomic min).
+// Deep: key[pixel * LM + l] keeps the L <= LM least keys in order,
 // by an atomic-min cascade -- the key is offered to layer 0, and whichever
 // of the offered and the resident key is larger moves on to the next layer
 // (an empty slot ends the cascade).  Every layer thus ends with the least
 // key that reached it, i.e. the l-th least key of the pixel, whatever the
 // interleaving of the lanes and waves.
 // Offer depth|id key k to pixel li of the tile.
-template <bool DEEP>
+template <int LM>
 __device__ __forceinline__ void insert_key(unsigned long long* key, int li, unsigned long long k, int L) {
-    if constexpr (DEEP) {
-        unsigned long long* list = key + li * DRD_MAX_LAYERS;
+    if constexpr (LM > 0) {
+        unsigned long long* list = key + li * LM;
         for (int l = 0; l < L; ++l) {
             unsigned long long old = atomicMin(&list[l], k);
             if (old == ~0ull) break;
@@ -153,9 +153,10 @@ struct RasterJob {
 // have grown; 6 and 8 within 2 % of 4).
 #define RASTER_SLOT 4
 
-template <int TILE, bool DEEP, int NS, int TB, int NE>
+template <int TILE, int LM, int NS, int TB, int NE>
 __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TILE, NE, TB / 64>& S,
                                             unsigned long long* key, int L) {
+    constexpr bool DEEP = LM > 0;
     constexpr int SL = RASTER_SLOT, KS = KeyRow<TILE, DEEP>::N, NW = TB / 64;
     constexpr int MW = NE * TILE * (TILE / SL) / 64;     // words of begin[]
     constexpr int GATHER = NE / 64 < 3 ? NE / 64 : 3;    // a wave's hits of one look fit an empty list
@@ -397,7 +398,7 @@ __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TIL
                     if (in && min(e[0], min(e[1], e[2])) > 0) {
                         float z = (q.z0 + q.zx * xf) + zrow;
                         z = fmaxf(z, 0.0f);              // 0 for negative values and NaN
-                        insert_key<DEEP>(key, off + k, ((unsigned long long)__float_as_uint(z) << 32) | q.t, L);
+                        insert_key<LM>(key, off + k, ((unsigned long long)__float_as_uint(z) << 32) | q.t, L);
                     }
                     e[0] -= a[0];
                     e[1] -= a[1];
@@ -424,7 +425,7 @@ __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TIL
                 long long e0, e1, e2;
                 if (!inside(b, px, py, e0, e1, e2)) continue;
                 const float z = depth_at(b, px, py);
-                insert_key<DEEP>(key, (sb * TILE + y - J.py0) * KS + (x - J.px0),
+                insert_key<LM>(key, (sb * TILE + y - J.py0) * KS + (x - J.px0),
                                  ((unsigned long long)__float_as_uint(z) << 32) | tt, L);
             }
         }
@@ -673,9 +674,13 @@ __device__ __forceinline__ void pair_verts(const PairSlot* slots, const unsigned
     }
 }
 
-// Opaque tile kernels of 8- and 16-pixel tiles are asked for 8 resident
-// waves per SIMD (at most 64 VGPRs): 16-pixel tiles hold 20 KB of LDS in
-// blocks of eight waves.  Larger tiles are held to fewer waves by their LDS.
+// Tile kernels of 8- and 16-pixel tiles are asked for 8 resident waves per SIMD
+// (at most 64 VGPRs and 96 SGPRs): their blocks hold 20 KB of LDS per 4 waves
+// or less.  Unasked, the deep ones took 106 SGPRs and 7 waves (512 px, two
+// layers, 32 items 1124 -> 1087 us, four ragged layers 246 -> 227).  The GGX
+// render spills at this bound and is still faster (145.5 us for four 1024 px
+// views; 153.8 with 7 waves and no spill).  Larger tiles are held to fewer waves
+// by their LDS.
 #define TILE_MIN_WAVES 8
 
 // Everything the tile body needs, resolved by the kernel's prologue.
@@ -942,7 +947,7 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
         if ((gload(&R.counts[0]) | gload(&R.counts[R.tstride])) == 0u) return;
     }
     for (int j = tid; j < NS * TILE * KS; j += TB) S.key[j] = ~0ull;
-    raster_tile<TILE, false, NS, TB, C::NE>(R, S.u.ras, S.key, 1);
+    raster_tile<TILE, 0, NS, TB, C::NE>(R, S.u.ras, S.key, 1);
     __syncthreads();                             // (a tile without triangles has only cleared its keys)
     if constexpr (MODE == 0) groups_clear<C>(S.u.g, tid);
 
@@ -1086,11 +1091,11 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
 // texels, each group once per pixel.  Tiles are 8 or 16 pixels (one pixel
 // per lane).
 
-template <int TILE, int MODE>
+template <int TILE, int MODE, int LM>
 struct DeepShared {
     using C = TileCfg<TILE, MODE, true>;
-    unsigned long long key[C::NS * C::NPIX * DRD_MAX_LAYERS];
-    float v[MODE == 0 ? C::NS * C::NPIX * DRD_MAX_LAYERS : 1];      // the fragments' texture coordinate v
+    unsigned long long key[C::NS * C::NPIX * LM];
+    float v[MODE == 0 ? C::NS * C::NPIX * LM : 1];      // the fragments' texture coordinate v
     // the raster's stage, then (estimate) the group table, or the sums
     union {
         RasterShared<TILE, C::NE, C::NW> ras;
@@ -1100,11 +1105,10 @@ struct DeepShared {
     } u;
 };
 
-template <int TILE, int MODE, int SHADE>
-__device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE>& S) {
+template <int TILE, int MODE, int LM, int SHADE>
+__device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE, LM>& S) {
     using C = TileCfg<TILE, MODE, true>;
     constexpr int TB = C::TB, NS = C::NS, NPIX = C::NPIX;
-    constexpr int LM = DRD_MAX_LAYERS;
     const int tid = threadIdx.x, lane = tid & 63;
     const DScene& sc = *J.sc;
     const DView& vw = *J.vw;
@@ -1119,7 +1123,7 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
         if ((gload(&R.counts[0]) | gload(&R.counts[R.tstride])) == 0u) return;
     }
     for (int j = tid; j < NS * NPIX * LM; j += TB) S.key[j] = ~0ull;
-    raster_tile<TILE, true, NS, TB, C::NE>(R, S.u.ras, S.key, sc.layers);
+    raster_tile<TILE, LM, NS, TB, C::NE>(R, S.u.ras, S.key, sc.layers);
     __syncthreads();
     const int L = sc.layers;
     if constexpr (MODE == 0) groups_clear<C>(S.u.g, tid);
@@ -1402,10 +1406,11 @@ __device__ __forceinline__ TileJob batch_job(const BatchArgs& b, int item, int t
 // and target pixels of the tile.  Otherwise the grid is (tile, item).
 // Measured at 1024 px, 46080 triangles, GGX, 32 items: 1989 -> 1586 us
 // (specialised and interleaved; the interleaved general kernel 1640 us).
-template <int TILE, int MODE, bool DEEP, int SHADE>
-__global__ void __launch_bounds__((TileCfg<TILE, MODE, DEEP>::TB), (DEEP || TILE > 16) ? 1 : TILE_MIN_WAVES)
+template <int TILE, int MODE, int LM, int SHADE>
+__global__ void __launch_bounds__((TileCfg<TILE, MODE, (LM > 0)>::TB), TILE > 16 ? 1 : TILE_MIN_WAVES)
 k_tile(TileArgs a) {
-    using SH = std::conditional_t<DEEP, DeepShared<TILE, MODE>, TileShared<TILE, MODE>>;
+    constexpr bool DEEP = LM > 0;
+    using SH = std::conditional_t<DEEP, DeepShared<TILE, MODE, (DEEP ? LM : 1)>, TileShared<TILE, MODE>>;
     __shared__ SH S;
     int li, pair, view, tile;
     if (a.interleave) {
@@ -1426,7 +1431,7 @@ k_tile(TileArgs a) {
     }
     if (tile >= a.views.v[view].tiles_x * a.views.v[view].tiles_y) return;
     TileJob J = single_job<TileCfg<TILE, MODE, DEEP>::NS, MODE>(a, li, pair, view, tile);
-    if constexpr (DEEP) tile_body_deep<TILE, MODE, SHADE>(J, S);
+    if constexpr (DEEP) tile_body_deep<TILE, MODE, LM, SHADE>(J, S);
     else tile_body<TILE, MODE, SHADE>(J, S);
 }
 
@@ -1444,33 +1449,37 @@ k_tile_b(BatchArgs b) {
     tile_body<TILE, 0, SHADE>(J, S);
 }
 
-template <int TILE, bool DEEP, int SHADE>
+template <int TILE, int LM, int SHADE>
 static void launch_tile_mode(hipStream_t st, const TileArgs& a, int mode, dim3 grid) {
-    const dim3 one(TileCfg<TILE, 1, DEEP>::TB), two(TileCfg<TILE, 0, DEEP>::TB);      // threads of one- and two-sign tiles
-    if (mode == 0) hipLaunchKernelGGL((k_tile<TILE, 0, DEEP, SHADE>), grid, two, 0, st, a);
-    else if (mode == 1) hipLaunchKernelGGL((k_tile<TILE, 1, DEEP, SHADE>), grid, one, 0, st, a);
-    else if (mode == 2) hipLaunchKernelGGL((k_tile<TILE, 2, DEEP, SHADE>), grid, one, 0, st, a);
-    else hipLaunchKernelGGL((k_tile<TILE, 3, DEEP, SHADE>), grid, two, 0, st, a);
+    const dim3 one(TileCfg<TILE, 1, (LM > 0)>::TB), two(TileCfg<TILE, 0, (LM > 0)>::TB);      // threads of one- and two-sign tiles
+    if (mode == 0) hipLaunchKernelGGL((k_tile<TILE, 0, LM, SHADE>), grid, two, 0, st, a);
+    else if (mode == 1) hipLaunchKernelGGL((k_tile<TILE, 1, LM, SHADE>), grid, one, 0, st, a);
+    else if (mode == 2) hipLaunchKernelGGL((k_tile<TILE, 2, LM, SHADE>), grid, one, 0, st, a);
+    else hipLaunchKernelGGL((k_tile<TILE, 3, LM, SHADE>), grid, two, 0, st, a);
 }
 
-template <int TILE, bool DEEP>
+template <int TILE, int LM>
 static hipError_t launch_tile_shade(hipStream_t st, const TileArgs& a, int mode, dim3 grid) {
     const int shade = scene_shade(a.sc);
-    if (shade == 0) launch_tile_mode<TILE, DEEP, 0>(st, a, mode, grid);
-    else if (shade == 1) launch_tile_mode<TILE, DEEP, 1>(st, a, mode, grid);
-    else if (shade == 2) launch_tile_mode<TILE, DEEP, 2>(st, a, mode, grid);
-    else launch_tile_mode<TILE, DEEP, SHADE_ANY>(st, a, mode, grid);
+    if (shade == 0) launch_tile_mode<TILE, LM, 0>(st, a, mode, grid);
+    else if (shade == 1) launch_tile_mode<TILE, LM, 1>(st, a, mode, grid);
+    else if (shade == 2) launch_tile_mode<TILE, LM, 2>(st, a, mode, grid);
+    else launch_tile_mode<TILE, LM, SHADE_ANY>(st, a, mode, grid);
     return hipGetLastError();
 }
 
 template <int TILE>
 hipError_t launch_tile_t(hipStream_t st, const TileArgs& a, int mode, dim3 grid) {
-    return launch_tile_shade<TILE, false>(st, a, mode, grid);
+    return launch_tile_shade<TILE, 0>(st, a, mode, grid);
 }
 
+// Deep kernels for up to two layers and for up to four: half the keys and
+// coordinates in LDS and in the unrolled unions of the scatter (512 px, two
+// layers, 32 items 1144 -> 1124 us).
 template <int TILE>
 hipError_t launch_tile_deep_t(hipStream_t st, const TileArgs& a, int mode, dim3 grid) {
-    return launch_tile_shade<TILE, true>(st, a, mode, grid);
+    return a.sc.layers <= 2 ? launch_tile_shade<TILE, 2>(st, a, mode, grid)
+                            : launch_tile_shade<TILE, DRD_MAX_LAYERS>(st, a, mode, grid);
 }
 
 template <int TILE>

@@ -227,3 +227,24 @@ def test_vertices_by_pairs_bit_exact(mesh, tile):
     Q, K = ctx.estimate_grad(torch.tensor(sc.flat_params(), device=DEV), sc.views, dtg, 8, 2, pairs, sc.eps)
     assert np.array_equal(host(K).view(np.uint32), Ko)
     assert np.array_equal(host(Q), Qo)
+
+
+# The deep kernels for up to two and up to four layers, at each number of layers.
+@pytest.mark.parametrize("layers", [1, 2, 3, 4])
+@pytest.mark.parametrize("tile,shading", [(8, 0), (16, 1), (16, 0)])
+def test_layer_counts_bit_exact(layers, tile, shading):
+    print(f"[kernels] layers {layers} tile {tile} shading {shading}", flush=True)
+    sc = H.sphere_scene(9, 0, res=(83, 69), shading=shading, tex_shapes=((40, 56, 4),), seed=11, views=2)
+    sc.layers = layers
+    o = oracle.Oracle(sc)
+    tg = [o.render(sc.flat_params(True), v)[0] for v in sc.views]
+    Qo, Ko, _, _ = o.estimate(sc.flat_params(), sc.views, tg, 5, 3, 2, sc.eps)
+    ctx = api.Context(sc, DEV, tuning=(tile, 256, 0))
+    th = torch.tensor(sc.flat_params(), device=DEV)
+    for v, t in zip(sc.views, tg):
+        img = ctx.render(torch.tensor(sc.flat_params(True), device=DEV), v, ids=False, uv=False)[0]
+        assert np.array_equal(host(img).reshape(-1), np.asarray(t).reshape(-1))
+    dtg = torch.cat([torch.tensor(t, device=DEV).reshape(-1) for t in tg])
+    Q, K = ctx.estimate_grad(th, sc.views, dtg, 5, 3, 2, sc.eps)
+    assert np.array_equal(host(K).view(np.uint32), Ko)
+    assert np.array_equal(host(Q), Qo)
