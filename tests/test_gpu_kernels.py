@@ -248,3 +248,37 @@ def test_layer_counts_bit_exact(layers, tile, shading):
     Q, K = ctx.estimate_grad(th, sc.views, dtg, 5, 3, 2, sc.eps)
     assert np.array_equal(host(K).view(np.uint32), Ko)
     assert np.array_equal(host(Q), Qo)
+
+
+# Decode, step, fold and full-image sums work on a group's parameters as vectors
+# of 3, 1 or 4: buffers that start off a 16-byte boundary, groups without a
+# contribution, gradients past the type's range, and blocks with a zero eps.
+@pytest.mark.parametrize("shapes,shading,layers,zero", [
+    (((9, 7, 3), (9, 7, 3), (5, 3, 1)), 2, 0, 1), (((9, 7, 3), (9, 7, 3), (9, 7, 1)), 2, 0, -1),
+    (((11, 5, 4),), 1, 2, -1), (((11, 5, 3),), 0, 0, 0)])
+@pytest.mark.parametrize("kind,averaging", [(api.ADAM, api.AVG_COUNT), (api.SGD, 1 - api.AVG_COUNT)])
+def test_parameter_vectors_bit_exact(shapes, shading, layers, zero, kind, averaging):
+    sc = H.sphere_scene(3, 0, res=(24, 20), shading=shading, tex_shapes=shapes, seed=2, views=1)
+    sc.layers = layers
+    eps = list(sc.eps)
+    if zero >= 0:
+        eps[zero] = 0.0
+    eps[-1] = 1e-38 if zero != len(eps) - 1 else 0.0      # (an infinite gradient for large sums)
+    ctx, o = api.Context(sc, DEV), oracle.Oracle(sc)
+    rng = np.random.default_rng(9)
+    th, m, v = [rng.normal(size=ctx.d).astype(np.float32) for _ in range(3)]
+    v = np.abs(v)
+    Q = rng.integers(-2**45, 2**45, ctx.d) * rng.integers(0, 2, ctx.d)
+    K = (rng.integers(0, 9, ctx.G) * rng.integers(0, 2, ctx.G)).astype(np.uint32)
+
+    def off(a):                                           # the array one element into a buffer
+        return torch.cat([torch.zeros(1, dtype=torch.as_tensor(a).dtype), torch.as_tensor(a)]).to(DEV)[1:]
+
+    d_th, d_m, d_v, d_Q, d_K = off(th), off(m), off(v), off(Q), off(K.view(np.int32))
+    g = ctx.decode_grad(d_Q, d_K, eps, averaging=averaging, n_pairs=3)
+    assert np.array_equal(host(g), o.decode(Q, K, eps, averaging, 3), equal_nan=True)
+    ctx.step(d_th, d_m, d_v, 2, d_Q, d_K, eps, 3, kind=kind, averaging=averaging, lr=sc.lr)
+    o.step(th, m, v, 2, Q, K, eps, 3, kind=kind, averaging=averaging, lr=sc.lr)
+    for a, b in ((d_th, th), (d_m, m), (d_v, v)):
+        assert np.array_equal(host(a).view(np.uint32), b.view(np.uint32))
+    assert not host(d_Q).any() and not host(d_K).any()
