@@ -54,7 +54,7 @@ struct TileCfg {
     // the box's texels
     static constexpr int LOG2T = TILE == 8 ? 8 : (TILE == 16 ? 10 : 11);
     static constexpr int LOG2B = TILE == 8 ? 7 : (TILE == 16 ? 9 : 10);
-    static constexpr int BOX = TILE == 8 ? 320 : (TILE == 16 ? 1120 : 1536);
+    static constexpr int BOX = DEEP ? 0 : TILE == 8 ? 320 : (TILE == 16 ? 1120 : 1536);
     // triangles rasterised at a time: tiles at a silhouette hold 200 to 250, and
     // end the launch when they take a second batch (192 against 256, whole
     // steps: launches of one 512 px item 3265 / 3088 us, 12 uneven scenes
@@ -457,9 +457,9 @@ __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TIL
 // unrelated triangles) or of other classes, go to an open-addressing table
 // keyed by group.  Both are in one zeroed region; which part of it is table is
 // settled once the rectangle is known.
-// Bound by the latency of the table's dependent LDS operations and by
-// same-address conflicts.  Measured on the paper step (1024 px, GGX, 32 items)
-// against the table alone: 1483 -> 1353 us.
+// Bound by the latency of the table's dependent LDS operations, by same-address
+// conflicts and by the memory's rate of atomics (1024 px GGX, 32 items: 1330 us
+// a step, 1142 without the flush's atomics, before groups were hashed in runs).
 
 #define HASH_NONE 0xFFFFFFFFu    // no group
 // Slots looked at for a group before its sum goes straight to memory.  Tiles at
@@ -650,15 +650,15 @@ __device__ __forceinline__ void pair_expand(const PairSlot* slots, const unsigne
 
 struct Tri3 { unsigned v[3]; };
 
-// A mesh's vertices go by pairs of triangles too where the launch fills the
-// chip (256 CUs of 2048 threads): few adds, and few lanes on one vertex's slot.
-// Where it doesn't, the two barriers and the list's chain of reads cost more
-// than each pixel's up to six adds.  Whole steps per pixel / by pairs: 1024 px
-// GGX, 131072 tiles, 1320 / 1301 us; 10240-triangle soup, 131072 tiles,
-// 1384 / 1323; 12 uneven scenes 1176 / 1149; launches of 1024 tiles
-// 3082 / 3206.
+// Whether the launch fills the chip (256 CUs of 2048 threads).  If so, what
+// costs fewer operations wins; if not, the shorter chain of dependent ones.
+// A mesh's vertices go by pairs of triangles in full launches: few adds, and few
+// lanes on one vertex's slot, against two barriers and the list's chain of reads.
+// Whole steps per pixel / by pairs: 1024 px GGX, 131072 tiles, 1320 / 1301 us;
+// 10240-triangle soup, 131072 tiles, 1384 / 1323; 12 uneven scenes 1176 / 1149;
+// launches of 1024 tiles 3082 / 3206.
 template <int TB>
-__device__ __forceinline__ bool by_pair() {
+__device__ __forceinline__ bool full_launch() {
     return (long long)gridDim.x * gridDim.y > 256 * 2048 / TB;
 }
 
@@ -800,7 +800,11 @@ __device__ __forceinline__ void wave_corners(unsigned& lo, unsigned& hi) {
 
 // Whether a tile's class-0 texels may go to a box: only bilinear footprints,
 // four texels a side; the nearest-texel mode's single one costs the table less
-// than the rectangle (10240-triangle soup 1432 us, with boxes 1464 us).
+// than the rectangle (10240-triangle soup 1291 us, with boxes 1313).  Opaque
+// tiles only: whole steps without / with boxes, 1024 px GGX 1259 / 1232 us,
+// subdivision 1374 / 1340, 12 uneven scenes 1128 / 1114, two layers 676 / 687, four
+// 214 / 217.  (Launches of one 512 px item: 2981 / 3032 without the code, but a
+// choice by the launch's size there cost 3052, and the others 1 %.)
 __device__ __forceinline__ bool boxable(const TileJob& J) {
     return J.sc->n_cls > 0 && J.act_cls[0] && J.sc->tex_mode == 0;
 }
@@ -819,6 +823,7 @@ template <typename C>
 __device__ __forceinline__ GroupTable groups_open(GroupMem<C>& M, bool boxed, unsigned lo, unsigned hi, int tid) {
     GroupTable tb;
     tb.bw = tb.bh = tb.bx = tb.by = 0;
+    boxed = boxed && C::BOX > 0;
     if (boxed) {                                 // (uniform)
         wave_corners(lo, hi);
         if ((tid & 63) == 63) {
@@ -1034,7 +1039,7 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
                 static_assert(C::NPIX == TB, "the box is known when the pixel is scattered");
                 tb = groups_open<C>(S.u.g, boxable(J), lo, hi, tid);
                 // the + side's groups, and those of the - side that it does not hold
-                if (J.act_pos && (sc.n_ctrl > 0 || by_pair<TB>())) {
+                if (J.act_pos && (sc.n_ctrl > 0 || full_launch<TB>())) {
                     static_assert(sizeof(S.key) >= C::NPIX * (sizeof(PairSlot) + 2), "pair table and list");
                     PairSlot* slots = reinterpret_cast<PairSlot*>(S.key);
                     unsigned short* pairs = reinterpret_cast<unsigned short*>(slots + C::NPIX);
@@ -1225,20 +1230,7 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
             if (tid == 0 && q != 0) atomicAdd((unsigned long long*)J.qtot, (unsigned long long)q);
         } else {
             FootBox f[LM];
-            unsigned lo = 0xFFFFFFFFu, hi = 0u;
-            const bool tex0 = sc.n_cls > 0 && J.act_cls[0];
-            if (tex0) {
-#pragma unroll
-                for (int l = 0; l < LM; ++l) {
-                    f[l] = {0xFFFFFFFFu, 0xFFFFFFFFu};
-                    if (l < L && act && mine[l] != ~0ull) {
-                        f[l] = foot_box(sc, 0, __uint_as_float((unsigned)(mine[l] >> 32)), mine_v[l]);
-                        lo = pk_min(lo, pk_min(f[l].a, f[l].b));
-                        hi = pk_max(hi, pk_max(f[l].a, f[l].b));
-                    }
-                }
-            }
-            const GroupTable tb = groups_open<C>(S.u.g, boxable(J), lo, hi, tid);
+            const GroupTable tb = groups_open<C>(S.u.g, false, 0u, 0u, tid);
             // Each side adds its own fragments' groups, each by the first
             // fragment that holds it; the - side leaves out what the + side
             // holds.  Empty layers have all ones for a vertex or coordinate.
@@ -1288,11 +1280,9 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
                 unsigned skip[LM];
 #pragma unroll
                 for (int l = 0; l < LM; ++l) {
-                    if (c > 0) {
-                        f[l] = {0xFFFFFFFFu, 0xFFFFFFFFu};
-                        if (l < L && act && mine[l] != ~0ull)
-                            f[l] = foot_box(sc, c, __uint_as_float((unsigned)(mine[l] >> 32)), mine_v[l]);
-                    }
+                    f[l] = {0xFFFFFFFFu, 0xFFFFFFFFu};
+                    if (l < L && act && mine[l] != ~0ull)
+                        f[l] = foot_box(sc, c, __uint_as_float((unsigned)(mine[l] >> 32)), mine_v[l]);
                     skip[l] = f[l].a == 0xFFFFFFFFu ? 0xFu : foot_repeats(f[l]);
                 }
 #pragma unroll
@@ -1310,7 +1300,7 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
                 }
 #pragma unroll
                 for (int l = 0; l < LM; ++l)
-                    if (l < L && skip[l] != 0xFu) foot_add(tb, c == 0 && tb.bw > 0, J.Rp, J.K, sc, c, f[l], skip[l], q);
+                    if (l < L && skip[l] != 0xFu) foot_add(tb, false, J.Rp, J.K, sc, c, f[l], skip[l], q);
             }
             __syncthreads();
             // (the fragments are done with: the slot list takes their place)
