@@ -282,3 +282,43 @@ def test_parameter_vectors_bit_exact(shapes, shading, layers, zero, kind, averag
     for a, b in ((d_th, th), (d_m, m), (d_v, v)):
         assert np.array_equal(host(a).view(np.uint32), b.view(np.uint32))
     assert not host(d_Q).any() and not host(d_K).any()
+
+
+# Plain launches on several streams: calls that follow each other without a
+# synchronisation, from the default and from another stream, with buffers made
+# and dropped between them; and the same call recorded in a graph, which stays on
+# one stream, replayed with eager calls in between.
+@pytest.mark.parametrize("form", ["loss", "full"])
+@pytest.mark.parametrize("items,views,pairs", [(1, 5, 6), (1, 2, 3), (2, 4, 7)])
+def test_plain_launches_on_several_streams_bit_exact(form, items, views, pairs):
+    print(f"[kernels] streams {form} items {items} views {views} pairs {pairs}", flush=True)
+    sc = H.sphere_scene(8, 0, res=(400, 360), shading=1, tex_shapes=((48, 64, 3),), seed=6, views=views)
+    ctx = api.Context(sc, DEV, tuning=(16, 256, items))
+    one = api.Context(sc, DEV, tuning=(16, 256, 0))
+    th = torch.tensor(sc.flat_params(), device=DEV)
+    tg = torch.rand(sum(3 * v.width * v.height for v in sc.views), device=DEV)
+
+    def call(c, t):
+        return c.estimate_grad(th, sc.views, tg, 3, t, pairs, sc.eps, full_image=form == "full")
+
+    want = [tuple(host(a) for a in call(one, t)) for t in range(4)]
+    got = []
+    for t in range(4):
+        got.append(call(ctx, t))
+        torch.empty(1 << 20, device=DEV).fill_(float("nan"))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        for t in range(4):
+            got.append(call(ctx, t))
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    for k, g in enumerate(got):
+        assert all(np.array_equal(host(a), b) for a, b in zip(g, want[k % 4]))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        held = call(ctx, 2)
+    for t in range(3):
+        graph.replay()
+        assert all(np.array_equal(host(a), b) for a, b in zip(held, want[2]))
+        assert all(np.array_equal(host(a), b) for a, b in zip(call(ctx, t), want[t]))
