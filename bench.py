@@ -386,10 +386,9 @@ def main():
     tile_avg_ms = tm["tile_ms"] / max(tm["tile_launches"], 1)
     launches_per_step = tm["tile_launches"] / args.steps
     alg_bytes_launch = BYTES_PER_PIXEL_ESTIMATE * px_per_step / launches_per_step
-    # the graph-captured step is a one-scene batch, whose tile kernel takes the
-    # scene in its arguments; the host-driven modes (all items in one launch,
-    # or one launch per item) run the context's tile kernel
-    kernel = f"k_tile<{tile}>" if main_mode == "graph" else f"k_tile<{tile},0,false>"
+    # the tile kernel of an opaque scene, specialised for its shading; a one-scene
+    # batch and a context launch the same one
+    kernel = f"k_tile<{tile},0,0,{sc.shading}>"
     traffic = measured_traffic(kernel) if args.config == "paper" else None
     achieved = alg_bytes_launch / (tile_avg_ms * 1e-3) / 1e9
     out = {
@@ -578,7 +577,7 @@ def main_layers(args, torch, api, autotune, scenes, dev):
                "contributions_per_step": r["contributions_per_step"],
                "roofline": {"bound": "hbm", "achieved": alg / (tile_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
                             "unit": "GB/s", "frac": alg / (tile_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                            "kernel": f"k_tile<{tile},0,{'true' if layers else 'false'}>",
+                            "kernel": f"k_tile<{tile},0,{(0, 2, 2, 4, 4)[layers]},{sc.shading}>",
                             "kernel_avg_ms": tile_ms},
                "kernels_ms_per_step": {k[:-3]: tm[k] / args.steps for k in tm if k.endswith("_ms")}}
         if not args.no_cpu:

@@ -16,7 +16,10 @@
  *    GPU the context was created on.  Struct arguments are host memory and
  *    are copied before the call returns.
  *  - Calls are asynchronous on the context's HIP stream; results are ready
- *    once that stream is synchronised.  dr_stats synchronises it.
+ *    once that stream is synchronised.  dr_stats synchronises it.  (An
+ *    estimate of many raster launches spreads them over streams of the
+ *    context's own, which start after and end before what the caller's
+ *    stream holds before and after the call; not while it is captured.)
  *  - Errors are returned as dr_status codes (never aborts or exceptions);
  *    dr_last_error gives the message of the last failing call.  An invalid
  *    argument is detected on the host and nothing is launched.
@@ -258,13 +261,15 @@ dr_status dr_estimate_grad_image(dr_ctx* ctx, const float* theta, const dr_view*
  * allocate: code being captured into a HIP graph, tight serving loops, and
  * harnesses that forbid hipMalloc.  Same arguments, results (bit for bit)
  * and errors as dr_estimate_grad, except that:
- *  - all scratch (sign bits, triangle records, bins, per-pair group sums,
- *    tessellated positions) comes from one static device array of
- *    DR_NOALLOC_SCRATCH_BYTES, which every GPU the library is loaded on
- *    holds until the process ends;
- *  - a call whose scratch would exceed that size (after lowering the
- *    items per raster launch as far as one) returns DR_E_INVALID and
- *    launches nothing; dr_last_error states the bytes it needed;
+ *  - all scratch (signs, triangle records, bins, per-pair group sums,
+ *    tessellated positions) comes from one static device array, which every
+ *    GPU the library is loaded on holds until the process ends;
+ *  - a call whose scratch would exceed DR_NOALLOC_SCRATCH_BYTES (after
+ *    lowering the items per raster launch as far as one) returns
+ *    DR_E_INVALID and launches nothing; dr_last_error states the bytes it
+ *    needed.  (They are counted at 96 bytes a triangle record and a bit a
+ *    sign; the array is 11/8 of the limit and holds what the kernels lay
+ *    out for every call accepted by that count;)
  *  - the bin capacity is the context's current one (no adaptive raise:
  *    an overflowing bin is exact but slower), and no timing events are
  *    recorded;

@@ -17,15 +17,13 @@ __device__ __forceinline__ int xcd_tile(int bid, int nb) {
     return x * q + min(x, rem) + k;
 }
 
-// Rasterise triangle t over the tile: one lane per covered pixel.  Opaque
-// (LM 0): key[pixel] keeps the least depth|id (64-bit atomic min).
-// Deep: key[pixel * LM + l] keeps the L <= LM least keys in order,
-// by an atomic-min cascade -- the key is offered to layer 0, and whichever
-// of the offered and the resident key is larger moves on to the next layer
-// (an empty slot ends the cascade).  Every layer thus ends with the least
-// key that reached it, i.e. the l-th least key of the pixel, whatever the
-// interleaving of the lanes and waves.
-// Offer depth|id key k to pixel li of the tile.
+// Offer depth|id key k to pixel li of the tile.  Opaque (LM 0): key[pixel] keeps
+// the least (64-bit atomic min).  Deep: key[pixel * LM + l] keeps the L <= LM
+// least keys in order, by an atomic-min cascade -- the key is offered to layer
+// 0, and whichever of the offered and the resident key is larger moves on to
+// the next layer (an empty slot ends the cascade).  Every layer thus ends with
+// the least key that reached it, i.e. the l-th least key of the pixel, whatever
+// the interleaving of the lanes and waves.
 template <int LM>
 __device__ __forceinline__ void insert_key(unsigned long long* key, int li, unsigned long long k, int L) {
     if constexpr (LM > 0) {
@@ -42,8 +40,9 @@ __device__ __forceinline__ void insert_key(unsigned long long* key, int li, unsi
 
 // Work split of one tile.  Opaque: a thread takes a pixel and shades both its
 // signs, so the two chains of dependent reads overlap (the loss of a 32-pixel
-// tile: four pixels, which keeps the order of its sum).  Deep: a thread takes one side of a pixel, lanes l and l + 32 of a
-// wave holding the + and - side; half the layers per thread.
+// tile: four pixels, which keeps the order of its sum).  Deep: a thread takes
+// one side of a pixel, lanes l and l + 32 of a wave holding the + and - side;
+// half the layers per thread.
 template <int TILE, int MODE, bool DEEP>
 struct TileCfg {
     static constexpr int NS = (MODE == 0 || MODE == 3) ? 2 : 1;
@@ -1100,7 +1099,7 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
 //
 // Sec. 4.4 "Transparent geometry": the raster keeps, per pixel and sign,
 // the L nearest fragments in front-to-back order (a deep ID buffer in LDS,
-// built by the atomic-min cascade of raster_tri), the shading pass
+// built by the atomic-min cascade of insert_key), the shading pass
 // composites them over black, C = sum_l T_l alpha_l c_l with
 // T_{l+1} = T_l (1 - alpha_l), and the scatter credits the union over both
 // renders and all listed layers of the layers' vertices and footprint
@@ -1397,7 +1396,7 @@ __device__ __forceinline__ TileJob batch_job(const BatchArgs& b, int item, int t
 }
 
 // One (item, tile) of a single-scene launch: opaque or semi-transparent
-// body, specialised for the scene's shading (kernels of about 30 KB of code
+// body, specialised for the scene's shading (kernels of 30 to 40 KB of code
 // and 60 registers in place of one of 90 KB and 77: the instruction cache
 // holds 64 KB).
 //
