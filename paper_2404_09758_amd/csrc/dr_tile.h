@@ -43,22 +43,26 @@ __device__ __forceinline__ void insert_key(unsigned long long* key, int li, unsi
 // tile: four pixels, which keeps the order of its sum).  Deep: a thread takes
 // one side of a pixel, lanes l and l + 32 of a wave holding the + and - side;
 // half the layers per thread.
-template <int TILE, int MODE, bool DEEP>
+template <int TILE, int MODE, int LM>
 struct TileCfg {
+    static constexpr bool DEEP = LM > 0;
     static constexpr int NS = (MODE == 0 || MODE == 3) ? 2 : 1;
     static constexpr int NPIX = TILE * TILE;
     static constexpr int TB = DEEP ? NS * NPIX : (MODE == 2 && NPIX > 256 ? 256 : NPIX);
     static constexpr int NW = TB / 64;
     // the group table: slots without and with a texel box beside them, and
-    // the box's texels
-    static constexpr int LOG2T = TILE == 8 ? 8 : (TILE == 16 ? 10 : 11);
+    // the box's texels.  Up to two layers leave room for twice the slots at the
+    // same occupancy (512 px, two layers, 32 items: 674 -> 644 us); with four
+    // they would cost two of eight waves (900 x 800, three layers: 753 -> 854).
+    static constexpr int LOG2T = (TILE == 8 ? 8 : (TILE == 16 ? 10 : 11)) + (LM == 2 ? 1 : 0);
     static constexpr int LOG2B = TILE == 8 ? 7 : (TILE == 16 ? 9 : 10);
     static constexpr int BOX = DEEP ? 0 : TILE == 8 ? 320 : (TILE == 16 ? 1120 : 1536);
     // triangles rasterised at a time: tiles at a silhouette hold 200 to 250, and
     // end the launch when they take a second batch (192 against 256, whole
     // steps: launches of one 512 px item 3265 / 3088 us, 12 uneven scenes
-    // 1195 / 1175, others even)
-    static constexpr int NEMAX = DEEP ? 192 : 256;
+    // 1195 / 1175, two layers 644 / 638, others even); four layers' keys leave
+    // room for 192
+    static constexpr int NEMAX = LM == 4 ? 192 : 256;
     static constexpr int NE = TILE == 32 ? 128 : (TB < NEMAX ? TB : NEMAX);
 };
 
@@ -930,7 +934,7 @@ __device__ __forceinline__ long long pixel_code(const TileJob& J, const float* P
 // estimate (both signs, per-tile sum of the fixed-point differences).
 template <int TILE, int MODE>
 struct TileShared {
-    using C = TileCfg<TILE, MODE, false>;
+    using C = TileCfg<TILE, MODE, 0>;
     static constexpr int KS = KeyRow<TILE, false>::N;
     alignas(16) unsigned long long key[C::NS * TILE * KS];
     // the raster's stage, then (estimate) the group table, or the sums
@@ -945,7 +949,7 @@ struct TileShared {
 
 template <int TILE, int MODE, int SHADE>
 __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S) {
-    using C = TileCfg<TILE, MODE, false>;
+    using C = TileCfg<TILE, MODE, 0>;
     constexpr int TB = C::TB, NS = C::NS, KS = TileShared<TILE, MODE>::KS;
     const int tid = threadIdx.x;
     const DScene& sc = *J.sc;
@@ -1108,7 +1112,7 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
 
 template <int TILE, int MODE, int LM>
 struct DeepShared {
-    using C = TileCfg<TILE, MODE, true>;
+    using C = TileCfg<TILE, MODE, LM>;
     unsigned long long key[C::NS * C::NPIX * LM];
     float v[MODE == 0 ? C::NS * C::NPIX * LM : 1];      // the fragments' texture coordinate v
     // the raster's stage, then (estimate) the group table, or the sums
@@ -1122,7 +1126,7 @@ struct DeepShared {
 
 template <int TILE, int MODE, int LM, int SHADE>
 __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE, LM>& S) {
-    using C = TileCfg<TILE, MODE, true>;
+    using C = TileCfg<TILE, MODE, LM>;
     constexpr int TB = C::TB, NS = C::NS, NPIX = C::NPIX;
     const int tid = threadIdx.x, lane = tid & 63;
     const DScene& sc = *J.sc;
@@ -1407,7 +1411,7 @@ __device__ __forceinline__ TileJob batch_job(const BatchArgs& b, int item, int t
 // Measured at 1024 px, 46080 triangles, GGX, 32 items: 1989 -> 1586 us
 // (specialised and interleaved; the interleaved general kernel 1640 us).
 template <int TILE, int MODE, int LM, int SHADE>
-__global__ void __launch_bounds__((TileCfg<TILE, MODE, (LM > 0)>::TB), TILE > 16 ? 1 : TILE_MIN_WAVES)
+__global__ void __launch_bounds__((TileCfg<TILE, MODE, LM>::TB), TILE > 16 ? 1 : TILE_MIN_WAVES)
 k_tile(TileArgs a) {
     constexpr bool DEEP = LM > 0;
     using SH = std::conditional_t<DEEP, DeepShared<TILE, MODE, (DEEP ? LM : 1)>, TileShared<TILE, MODE>>;
@@ -1430,7 +1434,7 @@ k_tile(TileArgs a) {
         tile = xcd_tile(blockIdx.x, gridDim.x);
     }
     if (tile >= a.views.v[view].tiles_x * a.views.v[view].tiles_y) return;
-    TileJob J = single_job<TileCfg<TILE, MODE, DEEP>::NS, MODE>(a, li, pair, view, tile);
+    TileJob J = single_job<TileCfg<TILE, MODE, LM>::NS, MODE>(a, li, pair, view, tile);
     if constexpr (DEEP) tile_body_deep<TILE, MODE, LM, SHADE>(J, S);
     else tile_body<TILE, MODE, SHADE>(J, S);
 }
@@ -1439,7 +1443,7 @@ k_tile(TileArgs a) {
 // batch of several scenes: one workgroup per unit, units in the XCD-aware
 // order of xcd_tile(), items of the costliest scenes first.
 template <int TILE, int SHADE>
-__global__ void __launch_bounds__((TileCfg<TILE, 0, false>::TB), TILE > 16 ? 1 : TILE_MIN_WAVES)
+__global__ void __launch_bounds__((TileCfg<TILE, 0, 0>::TB), TILE > 16 ? 1 : TILE_MIN_WAVES)
 k_tile_b(BatchArgs b) {
     __shared__ TileShared<TILE, 0> S;
     const long long w = b.unit0 + xcd_tile(blockIdx.x, gridDim.x);
@@ -1451,7 +1455,7 @@ k_tile_b(BatchArgs b) {
 
 template <int TILE, int LM, int SHADE>
 static void launch_tile_mode(hipStream_t st, const TileArgs& a, int mode, dim3 grid) {
-    const dim3 one(TileCfg<TILE, 1, (LM > 0)>::TB), two(TileCfg<TILE, 0, (LM > 0)>::TB);      // threads of one- and two-sign tiles
+    const dim3 one(TileCfg<TILE, 1, LM>::TB), two(TileCfg<TILE, 0, LM>::TB);      // threads of one- and two-sign tiles
     if (mode == 0) hipLaunchKernelGGL((k_tile<TILE, 0, LM, SHADE>), grid, two, 0, st, a);
     else if (mode == 1) hipLaunchKernelGGL((k_tile<TILE, 1, LM, SHADE>), grid, one, 0, st, a);
     else if (mode == 2) hipLaunchKernelGGL((k_tile<TILE, 2, LM, SHADE>), grid, one, 0, st, a);
@@ -1484,7 +1488,7 @@ hipError_t launch_tile_deep_t(hipStream_t st, const TileArgs& a, int mode, dim3 
 
 template <int TILE>
 hipError_t launch_batch_tile_t(hipStream_t st, const BatchArgs& b, unsigned grid) {
-    const dim3 block(TileCfg<TILE, 0, false>::TB);
+    const dim3 block(TileCfg<TILE, 0, 0>::TB);
     if (b.shade == 0) hipLaunchKernelGGL((k_tile_b<TILE, 0>), dim3(grid), block, 0, st, b);
     else if (b.shade == 1) hipLaunchKernelGGL((k_tile_b<TILE, 1>), dim3(grid), block, 0, st, b);
     else if (b.shade == 2) hipLaunchKernelGGL((k_tile_b<TILE, 2>), dim3(grid), block, 0, st, b);
