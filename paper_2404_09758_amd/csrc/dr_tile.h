@@ -1453,13 +1453,17 @@ k_tile_b(BatchArgs b) {
     tile_body<TILE, 0, SHADE>(J, S);
 }
 
+template <int TILE, int MODE, int LM, int SHADE>
+static void launch_tile_kernel(hipStream_t st, const TileArgs& a, dim3 grid) {
+    hipLaunchKernelGGL((k_tile<TILE, MODE, LM, SHADE>), grid, dim3(TileCfg<TILE, MODE, LM>::TB), 0, st, a);
+}
+
 template <int TILE, int LM, int SHADE>
 static void launch_tile_mode(hipStream_t st, const TileArgs& a, int mode, dim3 grid) {
-    const dim3 one(TileCfg<TILE, 1, LM>::TB), two(TileCfg<TILE, 0, LM>::TB);      // threads of one- and two-sign tiles
-    if (mode == 0) hipLaunchKernelGGL((k_tile<TILE, 0, LM, SHADE>), grid, two, 0, st, a);
-    else if (mode == 1) hipLaunchKernelGGL((k_tile<TILE, 1, LM, SHADE>), grid, one, 0, st, a);
-    else if (mode == 2) hipLaunchKernelGGL((k_tile<TILE, 2, LM, SHADE>), grid, one, 0, st, a);
-    else hipLaunchKernelGGL((k_tile<TILE, 3, LM, SHADE>), grid, two, 0, st, a);
+    if (mode == 0) launch_tile_kernel<TILE, 0, LM, SHADE>(st, a, grid);
+    else if (mode == 1) launch_tile_kernel<TILE, 1, LM, SHADE>(st, a, grid);
+    else if (mode == 2) launch_tile_kernel<TILE, 2, LM, SHADE>(st, a, grid);
+    else launch_tile_kernel<TILE, 3, LM, SHADE>(st, a, grid);
 }
 
 template <int TILE, int LM>

@@ -322,3 +322,20 @@ def test_plain_launches_on_several_streams_bit_exact(form, items, views, pairs):
         graph.replay()
         assert all(np.array_equal(host(a), b) for a, b in zip(held, want[2]))
         assert all(np.array_equal(host(a), b) for a, b in zip(call(ctx, t), want[t]))
+
+
+# The loss's own launch shape: a 32-pixel tile is summed by 256 threads.
+@pytest.mark.parametrize("tile,layers", [(8, 0), (16, 0), (32, 0), (8, 2), (16, 3)])
+def test_loss_at_every_tile_size(tile, layers):
+    print(f"[kernels] loss tile {tile} layers {layers}", flush=True)
+    sc = H.sphere_scene(5, 0, res=(83, 69), shading=1, tex_shapes=((24, 20, 4 if layers else 3),), seed=3, views=2)
+    sc.layers = layers
+    o = oracle.Oracle(sc)
+    tg = [o.render(sc.flat_params(True), v)[0] for v in sc.views]
+    want = np.array([o.pixel_loss(sc.flat_params(), v, t).astype(np.float64).sum() for v, t in zip(sc.views, tg)])
+    ctx = api.Context(sc, DEV, tuning=(tile, 256, 0))
+    dtg = torch.cat([torch.tensor(t, device=DEV).reshape(-1) for t in tg])
+    got = host(ctx.loss(torch.tensor(sc.flat_params(), device=DEV), sc.views, dtg))
+    # the same terms in another order of summing: both sums within n u of the exact one
+    n = 83 * 69
+    assert np.all(np.abs(got - want) <= 2 * n * 2.0 ** -53 * np.abs(want))
