@@ -339,3 +339,56 @@ def test_loss_at_every_tile_size(tile, layers):
     # the same terms in another order of summing: both sums within n u of the exact one
     n = 83 * 69
     assert np.all(np.abs(got - want) <= 2 * n * 2.0 ** -53 * np.abs(want))
+
+
+# Every form of the tile kernel at every tile size and shading.
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("shading", [0, 1, 2])
+def test_forms_at_every_tile_size_bit_exact(tile, shading):
+    print(f"[kernels] forms tile {tile} shading {shading}", flush=True)
+    shapes = ((24, 20, 3), (24, 20, 3), (9, 11, 1))[: 3 if shading == 2 else 1]
+    sc = H.sphere_scene(5, 0, res=(83, 69), shading=shading, tex_shapes=shapes, seed=3, views=2)
+    o, ctx = oracle.Oracle(sc), api.Context(sc, DEV, tuning=(tile, 256, 0))
+    tg = []
+    for v in sc.views:
+        rgb, ids, uv = ctx.render(torch.tensor(sc.flat_params(True), device=DEV), v)
+        want = o.render(sc.flat_params(True), v)
+        tg.append(want[0])
+        for a, b in zip((rgb, ids, uv), want):
+            assert np.array_equal(host(a).reshape(-1).view(np.uint32), np.asarray(b).reshape(-1).view(np.uint32))
+    th = torch.tensor(sc.flat_params(), device=DEV)
+    dtg = torch.cat([torch.tensor(t, device=DEV).reshape(-1) for t in tg])
+    for kw in ({}, {"full_image": True}, {"image_grad": True}):
+        Qo, Ko, _, _ = o.estimate(sc.flat_params(), sc.views, tg, 5, 3, 2, sc.eps, **kw)
+        Q, K = ctx.estimate_grad(th, sc.views, dtg, 5, 3, 2, sc.eps, **kw)
+        assert np.array_equal(host(K).view(np.uint32), Ko), kw
+        assert np.array_equal(host(Q), Qo), kw
+
+
+# A batch of mixed shadings takes the general kernels, as does a texture of more
+# than 2^24 texels.
+@pytest.mark.parametrize("tile", [8, 16, 32])
+def test_batch_of_mixed_shadings_bit_exact(tile):
+    scs = [H.sphere_scene(5, 0, res=(60, 50), shading=s, seed=s, views=2,
+                          tex_shapes=((24, 20, 3), (24, 20, 3), (9, 11, 1))[: 3 if s == 2 else 1]) for s in (0, 1, 2)]
+    tg = [[oracle.Oracle(sc).render(sc.flat_params(True), v)[0] for v in sc.views] for sc in scs]
+    bt = batch.Batch(scs, 2, DEV, tile_px=tile, seed=9, first_step=1,
+                     targets=[[torch.tensor(t, device=DEV) for t in ts] for ts in tg])
+    bt.estimate()
+    for b, sc in enumerate(scs):
+        Qo, Ko, _, _ = oracle.Oracle(sc).estimate(sc.flat_params(), sc.views, tg[b], 9, 1, 2, sc.eps, scene_index=b)
+        assert np.array_equal(host(bt.K[b]).view(np.uint32), Ko), b
+        assert np.array_equal(host(bt.Q[b]), Qo), b
+
+
+@pytest.mark.parametrize("tile", [8, 16, 32])
+def test_texture_past_24_bit_offsets_bit_exact(tile):
+    print(f"[kernels] large texture tile {tile}", flush=True)
+    sc = H.sphere_scene(4, 0, res=(48, 40), shading=1, tex_shapes=((4100, 4099, 3),), seed=3, views=1)
+    o, ctx = oracle.Oracle(sc), api.Context(sc, DEV, tuning=(tile, 256, 0))
+    tg = [o.render(sc.flat_params(True), sc.views[0])[0]]
+    Qo, Ko, _, _ = o.estimate(sc.flat_params(), sc.views, tg, 5, 3, 1, sc.eps)
+    Q, K = ctx.estimate_grad(torch.tensor(sc.flat_params(), device=DEV), sc.views,
+                             torch.tensor(tg[0], device=DEV).reshape(-1), 5, 3, 1, sc.eps)
+    assert np.array_equal(host(K).view(np.uint32), Ko)
+    assert np.array_equal(host(Q), Qo)
