@@ -267,9 +267,9 @@ dr_status dr_estimate_grad_image(dr_ctx* ctx, const float* theta, const dr_view*
  *  - a call whose scratch would exceed DR_NOALLOC_SCRATCH_BYTES (after
  *    lowering the items per raster launch as far as one) returns
  *    DR_E_INVALID and launches nothing; dr_last_error states the bytes it
- *    needed.  (They are counted at 96 bytes a triangle record and a bit a
- *    sign; the array is 11/8 of the limit and holds what the kernels lay
- *    out for every call accepted by that count;)
+ *    needed.  (They are counted at 96 bytes a triangle and render and a bit
+ *    a sign; the array is 11/8 of the limit and holds what the kernels lay
+ *    out for every call accepted by that count);
  *  - the bin capacity is the context's current one (no adaptive raise:
  *    an overflowing bin is exact but slower), and no timing events are
  *    recorded;

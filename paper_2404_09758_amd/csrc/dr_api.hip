@@ -710,10 +710,12 @@ static long long items_per_launch(const dr_ctx* c, long long items) {
 }
 
 // (pair, sign) perturbations that a launch of `per` items touches: all of
-// the call's, or those of a run of items that may start within a pair.
+// the call's, or those of a run of items that may start within a pair: with
+// its first item the last of a pair's nv, the other per - 1 touch
+// ceil((per - 1) / nv) pairs more.  Never more pairs than items.
 static long long pert_slots(const EstPlan& pl, long long per) {
     const long long nv = pl.dv.n;
-    return 2 * (per >= pl.items ? pl.items / nv : (per + nv - 1) / nv + 1);
+    return 2 * (per >= pl.items ? pl.items / nv : (per + nv - 2) / nv + 1);
 }
 
 // Items per setup launch.  A launch that sets up one item leaves most of the
@@ -984,8 +986,11 @@ extern "C" dr_status dr_estimate_grad_image(dr_ctx* c, const float* theta, const
 // current) and kept in scratch_dev[].
 
 // A call is accepted by its accounted size (static_account), which the public
-// limit is stated in.  What the kernels lay out for it differs from that by a
-// third at most (64 to 128 B of records per triangle against 96 accounted).
+// limit is stated in.  What the kernels lay out for an accepted call is at most
+// 4/3 of that (records: 64 B a triangle and render, and for GGX 64 B a triangle
+// and perturbation, of which a launch has no more than renders, against 96;
+// signs and sums: 9 B a group and pair against 8 1/8 or more) and 64 B a pair
+// (padding of the sign bytes, at most 65535 pairs): 174.7 MiB of the array's 176.
 static constexpr unsigned long long SCRATCH_ARRAY_BYTES = DR_NOALLOC_SCRATCH_BYTES / 8 * 11;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_ARRAY_BYTES];
 

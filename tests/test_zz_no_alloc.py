@@ -134,3 +134,27 @@ def test_noalloc_refuses_scratch_beyond_the_array():
         out.append((host(Q), host(K)))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
     assert out[0][1].sum() > 0
+
+
+# GGX: the faces' frames, one per (pair, sign), are in the array too.  Launches
+# that start within a pair, and a mesh that fills most of the array at one item
+# per launch.
+@pytest.mark.parametrize("freq,res,items,views,pairs", [
+    (6, (96, 80), 0, 2, 3), (6, (96, 80), 1, 3, 2), (6, (96, 80), 2, 3, 3), (6, (96, 80), 3, 2, 4),
+    (158, (256, 256), 1, 2, 1), (158, (256, 256), 1, 1, 2)])
+def test_noalloc_ggx_equals_estimate(freq, res, items, views, pairs):
+    print(f"[noalloc] ggx freq {freq} items {items} views {views} pairs {pairs}", flush=True)
+    sc = H.sphere_scene(freq, 0, res=res, shading=S.SHADING_GGX, seed=4, views=views,
+                        tex_shapes=((64, 64, 3), (64, 64, 3), (32, 48, 1)))
+    ctx = api.Context(sc, DEV, tuning=(16, 256, items))
+    ctx.set_adaptive_bins(False)
+    theta = dev(sc.flat_params())
+    tg = dev(np.random.default_rng(3).random(sum(3 * v.width * v.height for v in sc.views), dtype=np.float32))
+    out = []
+    for noalloc in (False, True, True):          # the second finds what the first left in the array
+        Q, K = ctx.new_accumulators()
+        ctx.estimate_grad(theta, sc.views, tg, 9, 2, pairs, sc.eps, Q, K, noalloc=noalloc)
+        out.append((host(Q), host(K)))
+    for Q, K in out[1:]:
+        assert np.array_equal(out[0][0], Q) and np.array_equal(out[0][1], K)
+    assert out[0][1].sum() > 0
