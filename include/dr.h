@@ -19,7 +19,13 @@
  *    once that stream is synchronised.  dr_stats synchronises it.  (An
  *    estimate of many raster launches spreads them over streams of the
  *    context's own, which start after and end before what the caller's
- *    stream holds before and after the call; not while it is captured.)
+ *    stream holds before and after the call; not while it is captured, nor
+ *    while launches are timed.)
+ *  - dr_render, dr_loss and the estimates may be captured into a HIP graph
+ *    once a call of at least their size has run uncaptured (a capture cannot
+ *    allocate).  The context keeps the scratch of a captured call until
+ *    dr_destroy, so its graph stays valid when later calls or tunings need
+ *    other buffers; replays and calls on the context must not overlap.
  *  - Errors are returned as dr_status codes (never aborts or exceptions);
  *    dr_last_error gives the message of the last failing call.  An invalid
  *    argument is detected on the host and nothing is launched.
@@ -190,7 +196,9 @@ dr_status dr_subdivide(const int32_t* tri, const float* corner_uv, int32_t n_ver
  * spill list, exact but slower), a later dr_estimate_grad* call raises
  * the capacity to the next power of two above 1.5x that bin (at most 2^16),
  * reallocating the bins once.  The figure is read back asynchronously, so
- * the raise may come one call later.  Results never depend on it.
+ * the raise may come one call later.  A call that is captured into a graph
+ * neither raises the capacity nor, in its replays, reports a figure.  Results
+ * never depend on it.
  * dr_get_tuning reports the launch shape in force. */
 dr_status dr_set_adaptive_bins(dr_ctx* ctx, int32_t on);
 dr_status dr_get_tuning(const dr_ctx* ctx, dr_tuning* out);

@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -133,6 +134,13 @@ struct dr_ctx {
     hipStream_t side[SIDE_STREAMS] = {};
     hipEvent_t ev_fork = nullptr, ev_join[SIDE_STREAMS] = {};
     bool side_made = false;
+    // scratch that a captured call's graph uses: freed with the context only,
+    // also after the context has gone on to larger buffers (retired)
+    struct Held {
+        void* p;
+        bool retired;
+    };
+    std::vector<Held> held;
     Timer timer;
 };
 
@@ -161,12 +169,24 @@ static dr_status device_guard(dr_ctx* c) {
 
 // ------------------------------------------------------------ scratch --
 
+// Gives back a scratch buffer that the context replaces, unless a graph uses it.
+static dr_status release(dr_ctx* c, void* p) {
+    for (dr_ctx::Held& h : c->held)
+        if (h.p == p) {
+            h.retired = true;
+            return DR_OK;
+        }
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    HIPCHK(c, hipFree(p));
+    return DR_OK;
+}
+
 template <typename T>
 static dr_status grow(dr_ctx* c, T** p, long long* have, long long need, size_t elem, bool zero) {
     if (need <= *have) return DR_OK;
     if (*p) {
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        HIPCHK(c, hipFree(*p));
+        dr_status s = release(c, *p);
+        if (s) return s;
         *p = nullptr;
         *have = 0;
     }
@@ -203,6 +223,34 @@ static dr_status ensure_raster(dr_ctx* c, long long slots, long long g_slots, in
     if (s) return s;
     return grow(c, &c->bins, &c->bin_entries, slots * (long long)max_tiles * c->tune.bin_capacity,
                 sizeof(unsigned), false);
+}
+
+// Whether the call goes into a graph (active), is run (none), or the runtime
+// does not say (the legacy stream while another is captured: invalidated).
+static hipStreamCaptureStatus capture_status(dr_ctx* c) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return hipStreamCaptureStatusInvalidated;
+    }
+    return st;
+}
+
+// Keeps the scratch of a captured call, whose addresses its graph holds, for as
+// long as the context lives.
+static dr_status hold_scratch(dr_ctx* c) {
+    void* ptrs[] = {c->recR, c->recS, c->recG, c->counts, c->bins, c->spn,
+                    c->spill, c->R, c->sg, c->qtot, c->partials, c->fpos};
+    try {
+        for (void* p : ptrs) {
+            bool known = p == nullptr;
+            for (const dr_ctx::Held& h : c->held) known = known || h.p == p;
+            if (!known) c->held.push_back({p, false});
+        }
+    } catch (const std::bad_alloc&) {
+        return fail(c, DR_E_OOM, "out of host memory");
+    }
+    return DR_OK;
 }
 
 // ---------------------------------------------------------- validation --
@@ -477,6 +525,8 @@ extern "C" dr_status dr_destroy(dr_ctx* c) {
                     c->recG, c->qtot, c->tri_rowptr, c->tri_cols, c->fpos};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
+    for (const dr_ctx::Held& h : c->held)
+        if (h.retired) (void)hipFree(h.p);
     if (c->h_seen) (void)hipHostFree(c->h_seen);
     if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
     for (int i = 0; i < SIDE_STREAMS; ++i) {
@@ -500,8 +550,7 @@ extern "C" dr_status dr_set_tuning(dr_ctx* c, const dr_tuning* t) {
     if (s) return s;
     if (t->bin_capacity != c->tune.bin_capacity) {
         // the bin array is indexed with the capacity: reallocate on next use
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        if (c->bins) HIPCHK(c, hipFree(c->bins));
+        if (c->bins && (s = release(c, c->bins))) return s;
         c->bins = nullptr;
         c->bin_entries = 0;
     }
@@ -596,6 +645,7 @@ extern "C" dr_status dr_render(dr_ctx* c, const float* theta, const dr_view* vie
     sa.spill = c->spill;
     s = tessellate(c, theta, dp, 1, 1, sg, sg, &sa.fpos);
     if (s) return s;
+    if (capture_status(c) == hipStreamCaptureStatusActive && (s = hold_scratch(c))) return s;
     HIPCHK(c, c->timer.run(c->stream, K_SETUP, [&] { return launch_setup(c->stream, sa); }));
     TileArgs ta;
     std::memset(&ta, 0, sizeof(ta));
@@ -633,7 +683,9 @@ extern "C" dr_status dr_render(dr_ctx* c, const float* theta, const dr_view* vie
 // the estimate that saw it ends; until then the call goes on with the capacity
 // it has.  Results never depend on the capacity, only the speed does.  (Written
 // by the estimate's last kernel: a copy and an event of their own took 2.4 us
-// of device time and two host calls on every estimate.)
+// of device time and two host calls on every estimate.)  Not for a captured
+// call, which can neither allocate nor synchronise, and whose replays do not
+// write the figure either.
 static dr_status adapt_capacity(dr_ctx* c) {
     if (!c->adapt) return DR_OK;
     if (!c->h_seen) {
@@ -675,6 +727,7 @@ struct EstPlan {
     DViews dv;
     int max_tiles = 1;
     long long items = 0;
+    bool eager = false;         // not captured (estimate_common)
 };
 
 static dr_status estimate_check(dr_ctx* c, const float* theta, const dr_view* views, int32_t n_views,
@@ -768,17 +821,11 @@ static dr_status estimate_scratch_ctx(dr_ctx* c, const EstPlan& pl, int32_t n_pa
     return DR_OK;
 }
 
-// Whether an estimate's raster launches may go to the side streams too: not
-// while the context's stream is captured (a capture holds what the caller's
-// stream does, and makes no streams) and not while launches are timed.  Makes
-// the streams and events on first use.
+// Whether an uncaptured estimate's raster launches may go to the side streams
+// too: not while launches are timed.  (A capture holds what the caller's stream
+// does, and makes no streams.)  Makes the streams and events on first use.
 static bool side_streams(dr_ctx* c) {
     if (c->timer.on) return false;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return false;
-    }
     if (!c->side_made) {
         bool ok = c->ev_fork || hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) == hipSuccess;
         for (int i = 0; ok && i < SIDE_STREAMS; ++i)
@@ -833,8 +880,8 @@ static hipError_t raster_launches(dr_ctx* c, long long n, long long per, int max
 
 // Signs, (tessellation,) setup and tile launches, then the fold or the
 // full-image broadcast, on the scratch x.  timed: bracket the launches with
-// the context's timing events, spread the raster launches over the context's
-// streams, and keep the adaptive bin capacity's figure.
+// the context's timing events; if the call is not captured, spread the raster
+// launches over the context's streams and keep the adaptive bin capacity's figure.
 static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* theta, int32_t n_views,
                                  const float* targets, uint64_t seed, uint32_t step, int32_t n_pairs,
                                  const float* eps, int64_t* Q, uint32_t* K, bool full, bool image,
@@ -909,7 +956,7 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     dr_status s = tessellate_into(c, theta, dp, n_pairs, 2, 1.0f, -1.0f, x.fpos, timed, &sa.fpos);
     if (s) return s;
     if (full) HIPCHK(c, launch_zero64(c->stream, x.qtot, n_pairs));
-    const bool spread = timed && group >= 6 * per && side_streams(c);
+    const bool spread = timed && pl.eager && group >= 6 * per && side_streams(c);
     for (long long i0 = 0; i0 < items; i0 += group) {
         const long long n = std::min(group, items - i0);
         sa.item0 = ta.item0 = (int)i0;
@@ -932,7 +979,7 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     fa.qtot = x.qtot;
     fa.K = K;
     fa.n_views = n_views;
-    if (timed && c->adapt) {
+    if (pl.eager && c->adapt) {
         fa.stats = c->stats;
         fa.seen = c->h_seen;
     }
@@ -949,11 +996,13 @@ static dr_status estimate_common(dr_ctx* c, const float* theta, const dr_view* v
     if (s) return s;
     s = device_guard(c);
     if (s) return s;
-    s = adapt_capacity(c);
-    if (s) return s;
+    const hipStreamCaptureStatus capture = capture_status(c);
+    pl.eager = capture == hipStreamCaptureStatusNone;
+    if (pl.eager && (s = adapt_capacity(c))) return s;
     EstScratch x;
     s = estimate_scratch_ctx(c, pl, n_pairs, full, x);
     if (s) return s;
+    if (capture == hipStreamCaptureStatusActive && (s = hold_scratch(c))) return s;
     return estimate_launch(c, pl, theta, n_views, targets, seed, step, n_pairs, eps, Q, K, full, image, x, true);
 }
 
@@ -1161,6 +1210,7 @@ extern "C" dr_status dr_loss(dr_ctx* c, const float* theta, const dr_view* views
     sa.spill = c->spill;
     s = tessellate(c, theta, dp, 1, 1, 1.0f, 1.0f, &sa.fpos);
     if (s) return s;
+    if (capture_status(c) == hipStreamCaptureStatusActive && (s = hold_scratch(c))) return s;
     HIPCHK(c, c->timer.run(c->stream, K_SETUP, [&] { return launch_setup(c->stream, sa); }));
     TileArgs ta;
     std::memset(&ta, 0, sizeof(ta));

@@ -392,3 +392,41 @@ def test_texture_past_24_bit_offsets_bit_exact(tile):
                              torch.tensor(tg[0], device=DEV).reshape(-1), 5, 3, 1, sc.eps)
     assert np.array_equal(host(K).view(np.uint32), Ko)
     assert np.array_equal(host(Q), Qo)
+
+
+# A captured estimate whose bins overflow: replays between eager calls that raise
+# the capacity and need larger scratch go on using what the graph was made with.
+@pytest.mark.parametrize("form", ["loss", "full"])
+@pytest.mark.parametrize("items", [0, 1])
+def test_captured_estimate_outlives_new_scratch(form, items):
+    print(f"[kernels] capture {form} items {items}", flush=True)
+    sc = H.sphere_scene(8, 0, res=(150, 130), shading=2, tex_shapes=((32, 48, 3), (32, 48, 3), (16, 16, 1)), seed=6,
+                        views=2)
+    ctx = api.Context(sc, DEV, tuning=(16, 4, items))
+    ref = api.Context(sc, DEV, tuning=(16, 256, 0))
+    th = torch.tensor(sc.flat_params(), device=DEV)
+    tg = torch.rand(sum(3 * v.width * v.height for v in sc.views), device=DEV)
+
+    def call(c, t, pairs=3):
+        return c.estimate_grad(th, sc.views, tg, 3, t, pairs, sc.eps, full_image=form == "full")
+
+    def same(got, want):
+        return all(np.array_equal(host(a), b) for a, b in zip(got, want))
+
+    want = {(t, p): tuple(host(a) for a in call(ref, t, p)) for t in range(3) for p in (3, 40)}
+    assert same(call(ctx, 0), want[0, 3])
+    graphs = []
+    for t in (1, 2):                                     # at the first capacity and at the raised one
+        graph = torch.cuda.CUDAGraph()
+        capacity = ctx.get_tuning()[1]
+        with torch.cuda.graph(graph):
+            out = call(ctx, t)
+        assert ctx.get_tuning()[1] == capacity
+        graphs.append((graph, out, want[t, 3]))
+        for pairs in (3, 3, 40):
+            assert same(call(ctx, 0, pairs), want[0, pairs])
+            torch.empty(1 << 22, device=DEV).fill_(float("nan"))
+            for g, o, w in graphs:
+                g.replay()
+                assert same(o, w)
+    assert ctx.get_tuning()[1] > 4

@@ -132,6 +132,48 @@ def case_noalloc_pairs(fake):
     assert x.estimate([(16, 16)], 65535, "dr_estimate_grad_noalloc") == 0, x.error()
 
 
+def case_capture(fake, items):
+    """A captured estimate neither synchronises, allocates nor changes the bins,
+    and what its graph holds stays until the context goes."""
+    x = Host(fake, 3, 300, 2, GGX_TEX, (16, 1, items))
+    small, large = [(64, 48)] * 2, [(300, 200)] * 3
+    assert x.estimate(small, 3) == 0
+    x.fake.fake_pinned()[0] = 1000                          # a bin overflowed in that call
+    fake.fake_capture(1)
+    fake.fake_reset_launches()
+    assert x.estimate(small, 3) == 0, x.error()
+    assert fake.fake_streams() == 1
+    fake.fake_capture(0)
+    assert fake.fake_violations() == 0
+    assert x.capacity() == 1
+    graph = x.live()
+    assert x.estimate(small, 3) == 0
+    assert x.capacity() == 2048
+    assert graph <= x.live()
+    for pairs, views, name in ((9, large, "dr_estimate_grad"), (40, large, "dr_estimate_grad_full")):
+        assert x.estimate(views, pairs, name) == 0
+        assert graph <= x.live()
+    p, vw = C.c_void_p(0x1000), x.L.View()
+    vw.width = vw.height = 1500
+    assert x.lib.dr_render(x.h, p, C.byref(vw), None, p, p, p) == 0
+    assert x.lib.dr_loss(x.h, p, C.byref(vw), 1, p, p) == 0
+    n = None
+    for cap in (64, 32, 64, 16, 64):                        # buffers that no graph uses are given back
+        x.tuning(16, cap, items)
+        assert x.estimate(small, 3) == 0
+        assert graph <= x.live() and n in (None, len(x.live()))
+        n = len(x.live())
+    fake.fake_capture(1)
+    assert x.estimate(small, 3) == 0
+    fake.fake_capture(0)
+    graph |= x.live()
+    x.tuning(16, 512, items)
+    assert x.estimate(large, 50) == 0
+    assert graph <= x.live() and fake.fake_violations() == 0
+    assert x.lib.dr_destroy(x.h) == 0
+    assert fake.fake_used() == 0
+
+
 # --------------------------------------------------------------- tests
 
 @pytest.mark.parametrize("shading,items,n_views,pairs", [
@@ -143,6 +185,11 @@ def test_allocation_free_call_accepts_what_its_count_does(stand_in, shading, ite
 
 def test_allocation_free_call_of_many_pairs(stand_in):
     run_case(stand_in, "noalloc_pairs")
+
+
+@pytest.mark.parametrize("items", [0, 1, 2])
+def test_captured_call_keeps_its_scratch(stand_in, items):
+    run_case(stand_in, "capture", items)
 
 
 if __name__ == "__main__":
