@@ -102,7 +102,7 @@ struct dr_ctx {
     std::string err;
     TriR* recR = nullptr;
     TriS* recS = nullptr;
-    long long rec_slots = 0;
+    long long recR_slots = 0, recS_slots = 0;
     TriG* recG = nullptr;           // GGX scenes: [pairs * signs, n_tris]
     long long g_slots = 0;
     unsigned* counts = nullptr;
@@ -204,13 +204,10 @@ static dr_status grow(dr_ctx* c, T** p, long long* have, long long need, size_t 
 // Records and bins of `slots` (item, sign) renders of g_slots (pair, sign)
 // perturbations.
 static dr_status ensure_raster(dr_ctx* c, long long slots, long long g_slots, int max_tiles) {
-    long long have = c->rec_slots;
-    dr_status s = grow(c, &c->recR, &have, slots * c->sc.n_tris, sizeof(TriR), false);
+    dr_status s = grow(c, &c->recR, &c->recR_slots, slots * c->sc.n_tris, sizeof(TriR), false);
     if (s) return s;
-    have = c->rec_slots;
-    s = grow(c, &c->recS, &have, slots * c->sc.n_tris, sizeof(TriS), false);
+    s = grow(c, &c->recS, &c->recS_slots, slots * c->sc.n_tris, sizeof(TriS), false);
     if (s) return s;
-    if (slots * c->sc.n_tris > c->rec_slots) c->rec_slots = slots * c->sc.n_tris;
     if (c->sc.shading == DR_GGX) {
         s = grow(c, &c->recG, &c->g_slots, g_slots * c->sc.n_tris, sizeof(TriG), false);
         if (s) return s;

@@ -174,6 +174,23 @@ def case_capture(fake, items):
     assert fake.fake_used() == 0
 
 
+def case_failed_growth(fake):
+    """After a call that ran out of memory the next one has all its buffers."""
+    n, triangles = None, 30000
+    for room in (1, 2, 3, 4):                               # larger raster records, in units of one of their parts
+        x = Host(fake, 3, triangles, 2, GGX_TEX, (16, 16, 0))
+        assert x.estimate([(64, 48)], 1) == 0
+        n = n or len(x.live())
+        assert len(x.live()) == n
+        fake.fake_room(fake.fake_used() + room * 2 * 20 * triangles * 16)
+        assert x.estimate([(64, 48)], 20) == -2 and "hipMalloc" in x.error()
+        fake.fake_room(1 << 50)
+        assert x.estimate([(64, 48)], 1) == 0
+        assert len(x.live()) == n
+        assert x.lib.dr_destroy(x.h) == 0
+        assert fake.fake_used() == 0
+
+
 # --------------------------------------------------------------- tests
 
 @pytest.mark.parametrize("shading,items,n_views,pairs", [
@@ -190,6 +207,10 @@ def test_allocation_free_call_of_many_pairs(stand_in):
 @pytest.mark.parametrize("items", [0, 1, 2])
 def test_captured_call_keeps_its_scratch(stand_in, items):
     run_case(stand_in, "capture", items)
+
+
+def test_failed_growth_leaves_no_missing_buffer(stand_in):
+    run_case(stand_in, "failed_growth")
 
 
 if __name__ == "__main__":
