@@ -124,7 +124,10 @@ typedef struct {
  * overflowing tile reads after its bin; only when that list is full does
  * the tile test every triangle of the render.  items_per_launch is the number of
  * (pair, view) items one raster launch covers: 1 = one launch per item
- * ("plain"), 0 = every item of the call in one launch ("batched").
+ * ("plain"), 0 = every item of the call in one launch ("batched").  A
+ * context's scratch grows with it, and holds at least as many items as fit in
+ * 256 MiB of triangle records, bins and spill lists, whose setup goes in one
+ * launch (fewer where device memory is short, down to items_per_launch).
  * Results never depend on these values. */
 typedef struct {
     int32_t tile_px;

@@ -222,6 +222,25 @@ static dr_status ensure_raster(dr_ctx* c, long long slots, long long g_slots, in
                 sizeof(unsigned), false);
 }
 
+// Gives all of that back.
+static dr_status drop_raster(dr_ctx* c) {
+    auto drop = [&](auto& p, long long& have) {
+        dr_status s = p ? release(c, p) : DR_OK;
+        if (s) return s;
+        p = nullptr;
+        have = 0;
+        return DR_OK;
+    };
+    dr_status s = drop(c->recR, c->recR_slots);
+    if (!s) s = drop(c->recS, c->recS_slots);
+    if (!s) s = drop(c->recG, c->g_slots);
+    if (!s) s = drop(c->counts, c->tile_slots);
+    if (!s) s = drop(c->spn, c->spn_words);
+    if (!s) s = drop(c->spill, c->spill_entries);
+    if (!s) s = drop(c->bins, c->bin_entries);
+    return s;
+}
+
 // Whether the call goes into a graph (active), is run (none), or the runtime
 // does not say (the legacy stream while another is captured: invalidated).
 static hipStreamCaptureStatus capture_status(dr_ctx* c) {
@@ -783,26 +802,33 @@ static long long setup_group(const dr_ctx* c, const EstPlan& pl, long long per) 
     return std::max(per, n / per * per);
 }
 
-// The context's own scratch, grown as needed.
+// Signs, group sums (full: totals) and tessellated positions of the pairs.
+static dr_status ensure_pairs(dr_ctx* c, int32_t n_pairs, bool full) {
+    dr_status s = ensure_signs(c, n_pairs);
+    if (s) return s;
+    if (full) s = grow(c, &c->qtot, &c->qtot_pairs, n_pairs, sizeof(long long), false);
+    else s = grow(c, &c->R, &c->R_pairs, n_pairs, (size_t)c->sc.G * sizeof(long long), true);
+    if (s || c->sc.n_ctrl == 0) return s;
+    return grow(c, &c->fpos, &c->fpos_slots, (long long)n_pairs * 2, (size_t)c->sc.n_verts * 3 * sizeof(float), false);
+}
+
+// The context's own scratch, grown as needed.  Where the memory for the group
+// is not there, the setup takes fewer items at a time, down to a raster launch's;
+// the buffers of larger groups are given back first.
 static dr_status estimate_scratch_ctx(dr_ctx* c, const EstPlan& pl, int32_t n_pairs, bool full, EstScratch& x) {
     x.per = items_per_launch(c, pl.items);
     x.group = setup_group(c, pl, x.per);
-    dr_status s = ensure_raster(c, 2 * x.group, pert_slots(pl, x.group), pl.max_tiles);
-    if (s) return s;
-    s = ensure_signs(c, n_pairs);
-    if (s) return s;
-    if (full) {
-        s = grow(c, &c->qtot, &c->qtot_pairs, n_pairs, sizeof(long long), false);
-        if (s) return s;
-    } else {
-        s = grow(c, &c->R, &c->R_pairs, n_pairs, (size_t)c->sc.G * sizeof(long long), true);
-        if (s) return s;
+    auto ensure = [&] {
+        dr_status s = ensure_pairs(c, n_pairs, full);
+        return s ? s : ensure_raster(c, 2 * x.group, pert_slots(pl, x.group), pl.max_tiles);
+    };
+    dr_status s = ensure();
+    for (bool first = true; s == DR_E_OOM && pl.eager && (first || x.group > x.per); first = false) {
+        if ((s = drop_raster(c))) return s;
+        x.group = std::max(x.per, x.group / 2 / x.per * x.per);
+        s = ensure();
     }
-    if (c->sc.n_ctrl > 0) {
-        s = grow(c, &c->fpos, &c->fpos_slots, (long long)n_pairs * 2, (size_t)c->sc.n_verts * 3 * sizeof(float),
-                 false);
-        if (s) return s;
-    }
+    if (s) return s;
     x.sg = c->sg;
     x.recR = c->recR;
     x.recS = c->recS;

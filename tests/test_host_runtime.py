@@ -191,6 +191,47 @@ def case_failed_growth(fake):
         assert fake.fake_used() == 0
 
 
+def case_short_of_memory(fake, items, full):
+    """A call that fits the card with the records of one raster launch runs."""
+    name = "dr_estimate_grad_full" if full else "dr_estimate_grad"
+    triangles, cap, views, pairs, tiles = 20000, 256, [(512, 512)] * 2, 30, 32 * 32
+    x = Host(fake, 3, triangles, 2, GGX_TEX, (16, cap, items))
+    fixed = fake.fake_used()
+    assert x.estimate(views, pairs, name) == 0
+    most = fake.fake_used()
+    fake.fake_reset_launches()
+    assert x.estimate(views, pairs, name) == 0
+    launches = fake.fake_launches()
+    x.lib.dr_destroy(x.h)
+    sums = pairs * (8 if full else 8 * x.G) + pairs * ((x.G + 64) // 64 * 64)
+    pairs_touched = items if items <= 1 else (items + 2 - 2) // 2 + 1
+    least = fixed + sums + 2 * items * (triangles * 64 + tiles * (cap + 1) * 4 + 8 + 8192 * 8) + 2 * pairs_touched * triangles * 64
+    assert least < most
+    for room in (most - 1, (least + most) // 2, least + (most - least) // 7, least):
+        x = Host(fake, 3, triangles, 2, GGX_TEX, (16, cap, items))
+        fake.fake_room(room)
+        for _ in range(2):
+            fake.fake_reset_launches()
+            assert x.estimate(views, pairs, name) == 0, (room, x.error())
+            assert fake.fake_launches() > launches           # (more setups)
+        assert fake.fake_used() <= room
+        # a context that already holds a large group gives it up for more pairs
+        fake.fake_room(1 << 50)
+        assert x.estimate(views, pairs, name) == 0
+        more = least + pairs * (8 if full else 8 * x.G) + pairs * ((x.G + 64) // 64 * 64)
+        fake.fake_room(max(more, fake.fake_used()))
+        assert x.estimate(views, 2 * pairs, name) == 0, x.error()
+        fake.fake_room(1 << 50)
+        assert x.lib.dr_destroy(x.h) == 0 and fake.fake_used() == 0
+    x = Host(fake, 3, triangles, 2, GGX_TEX, (16, cap, items))
+    fake.fake_room(least - 1)
+    assert x.estimate(views, pairs, name) == -2
+    fake.fake_room(1 << 50)
+    fake.fake_reset_launches()
+    assert x.estimate(views, pairs, name) == 0
+    assert fake.fake_launches() == launches
+
+
 # --------------------------------------------------------------- tests
 
 @pytest.mark.parametrize("shading,items,n_views,pairs", [
@@ -211,6 +252,12 @@ def test_captured_call_keeps_its_scratch(stand_in, items):
 
 def test_failed_growth_leaves_no_missing_buffer(stand_in):
     run_case(stand_in, "failed_growth")
+
+
+@pytest.mark.parametrize("full", [0, 1])
+@pytest.mark.parametrize("items", [1, 3, 6])
+def test_call_runs_where_memory_is_short(stand_in, items, full):
+    run_case(stand_in, "short_of_memory", items, full)
 
 
 if __name__ == "__main__":
