@@ -100,6 +100,7 @@ def parse():
 
 
 def run_mode(ctx, sc, th, m, v, tg, eps, steps, warmup, tuning, api, torch):
+    """Steps driven by the host through a context, as a program runs them."""
     ctx.set_tuning(*tuning)
     Q, K = ctx.new_accumulators()
     n_pairs = sc.n_pairs
@@ -114,12 +115,10 @@ def run_mode(ctx, sc, th, m, v, tg, eps, steps, warmup, tuning, api, torch):
     for _ in range(warmup):
         one_step()
     torch.cuda.synchronize()
-    ctx.timing_read(reset=True)
-    ctx.timing_enable(True)
+    snap = [a.clone() for a in (th, m, v)]
     start = torch.cuda.Event(enable_timing=True)
     stop = torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
-    gate(torch)
     w0 = time.perf_counter()
     start.record()
     for _ in range(steps):
@@ -127,9 +126,21 @@ def run_mode(ctx, sc, th, m, v, tg, eps, steps, warmup, tuning, api, torch):
     stop.record()
     torch.cuda.synchronize()
     wall = time.perf_counter() - w0
+    ev_ms = start.elapsed_time(stop)
+    # per-kernel durations: the same steps again with launch timing, which keeps
+    # an estimate's launches on one stream
+    for dst, src in zip((th, m, v), snap):
+        dst.copy_(src)
+    t -= steps
+    torch.cuda.synchronize()
+    ctx.timing_read(reset=True)
+    ctx.timing_enable(True)
+    gate(torch)
+    for _ in range(steps):
+        one_step()
+    torch.cuda.synchronize()
     ctx.timing_enable(False)
     tm = ctx.timing_read(reset=True)
-    ev_ms = start.elapsed_time(stop)
     # one extra estimate to count contributions (sum of K) of a step
     Q2, K2 = ctx.new_accumulators()
     ctx.estimate_grad(th, sc.views, tg, sc.seed, t + 1, n_pairs, eps, Q=Q2, K=K2)
