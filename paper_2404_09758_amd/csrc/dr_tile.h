@@ -1238,7 +1238,6 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
             // fragment that holds it; the - side leaves out what the + side
             // holds.  Empty layers have all ones for a vertex or coordinate.
             if (J.act_pos) {
-                struct Tri3 { unsigned v[3]; };
                 Tri3 g[LM];
 #pragma unroll
                 for (int l = 0; l < LM; ++l) {
@@ -1306,8 +1305,9 @@ __device__ __forceinline__ void tile_body_deep(TileJob& J, DeepShared<TILE, MODE
                     if (l < L && skip[l] != 0xFu) foot_add(tb, false, J.Rp, J.K, sc, c, f[l], skip[l], q);
             }
             __syncthreads();
-            // (the fragments are done with: the slot list takes their place)
-                groups_flush<C>(tb, reinterpret_cast<unsigned short*>(S.key), &S.u.g.n_list, J.Rp, J.K, sc, tid);
+            // the fragments are done with: the list of occupied slots takes their place
+            static_assert(sizeof(S.key) >= (2u << C::LOG2T), "slot list");
+            groups_flush<C>(tb, reinterpret_cast<unsigned short*>(S.key), &S.u.g.n_list, J.Rp, J.K, sc, tid);
         }
     }
 }
