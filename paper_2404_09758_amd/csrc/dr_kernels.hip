@@ -694,24 +694,26 @@ __device__ __forceinline__ void step_group(const DScene& sc, long long g, const 
     for_vectors(sc, g, [&](auto size, long long i, int b, int) {
         constexpr int C = decltype(size)::value;
         const float e = eps[b];
-        // a decode reads no sums where there is no gradient (7.4 M parameters, 1024 px
-        // GGX maps: none of the groups counted 14.1 -> 10.3 us, a tenth of them 15.7 ->
-        // 13.1, all of them 16.4 either way)
-        Vec<long long, C> q{};
-        if (!decode_only || (e != 0.0f && D != 0.0)) q = vload<C>(Q + i);
+        if (decode_only) {
+            // no sums are read where there is no gradient (7.4 M parameters, 1024 px
+            // GGX maps: none of the groups counted 14.1 -> 10.3 us, a tenth of them
+            // 15.7 -> 13.1, all of them 16.4 either way)
+            Vec<float, C> go{};
+            if (e != 0.0f && D != 0.0) {
+                const Vec<long long, C> q = vload<C>(Q + i);
+#pragma unroll
+                for (int ch = 0; ch < C; ++ch) go.c[ch] = decoded(q.c[ch], e, D);
+            }
+            vstore<C>(grad + i, go);
+            return;
+        }
+        const Vec<long long, C> q = vload<C>(Q + i);
         float gi[C];
         bool some = false;
 #pragma unroll
         for (int ch = 0; ch < C; ++ch) {
             gi[ch] = decoded(q.c[ch], e, D);
             some = some || q.c[ch] != 0;
-        }
-        if (decode_only) {
-            Vec<float, C> go;
-#pragma unroll
-            for (int ch = 0; ch < C; ++ch) go.c[ch] = gi[ch];
-            vstore<C>(grad + i, go);
-            return;
         }
         if (some) vstore<C>(Q + i, Vec<long long, C>{});
         if (e == 0.0f) return;
