@@ -40,15 +40,16 @@ __device__ __forceinline__ void insert_key(unsigned long long* key, int li, unsi
 
 // Work split of one tile.  Opaque: a thread takes a pixel and shades both its
 // signs, so the two chains of dependent reads overlap (the loss of a 32-pixel
-// tile: four pixels, which keeps the order of its sum).  Deep: a thread takes
+// tile: four pixels, which keeps the order of its sum; MODE 3 of one: four,
+// where there are blocks enough, see launch_tile_mode).  Deep: a thread takes
 // one side of a pixel, lanes l and l + 32 of a wave holding the + and - side;
 // half the layers per thread.
 template <int TILE, int MODE, int LM>
 struct TileCfg {
     static constexpr bool DEEP = LM > 0;
-    static constexpr int NS = (MODE == 0 || MODE == 3) ? 2 : 1;
+    static constexpr int NS = (MODE == 0 || MODE >= 3) ? 2 : 1;
     static constexpr int NPIX = TILE * TILE;
-    static constexpr int TB = DEEP ? NS * NPIX : (MODE == 2 && NPIX > 256 ? 256 : NPIX);
+    static constexpr int TB = DEEP ? NS * NPIX : ((MODE == 2 || MODE == 3) && NPIX > 256 ? 256 : NPIX);
     static constexpr int NW = TB / 64;
     // the group table: slots without and with a texel box beside them, and
     // the box's texels.  Up to two layers leave room for twice the slots at the
@@ -500,6 +501,11 @@ struct GroupMem {
     unsigned n_list;                     // occupied slots (flush)
 };
 
+// Modes that do not scatter, where the table's room would cost them blocks: at
+// 32 pixels (8- and 16-pixel tiles have 7 and 8 waves per SIMD with it; full-image
+// calls are 0 to 2 % slower without).
+struct NoGroups {};
+
 // The region as the tile uses it: 2^logt slots of sums and of keys (group + 1;
 // 0: empty), then the box (bw = 0: none).
 struct GroupTable {
@@ -931,7 +937,8 @@ __device__ __forceinline__ long long pixel_code(const TileJob& J, const float* P
 
 // MODE: 0 estimate (both signs, scatter), 1 render (write rgb/id/uv),
 // 2 loss (per-tile sum of the per-pixel L2 error f_{w,h}), 3 full-image
-// estimate (both signs, per-tile sum of the fixed-point differences).
+// estimate (both signs, per-tile sum of the fixed-point differences); 4 is 3
+// with a thread per pixel of a 32-pixel tile.
 template <int TILE, int MODE>
 struct TileShared {
     using C = TileCfg<TILE, MODE, 0>;
@@ -940,7 +947,7 @@ struct TileShared {
     // the raster's stage, then (estimate) the group table, or the sums
     union {
         RasterShared<TILE, C::NE, C::NW> ras;
-        GroupMem<C> g;
+        std::conditional_t<MODE == 0 || TILE <= 16, GroupMem<C>, NoGroups> g;
         double red[C::TB];
         long long qred[C::TB];
     } u;
@@ -1024,10 +1031,10 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
             }
         } else {
             // an empty contribution set (background in both renders) adds nothing
-            const bool act = inpix && (id[0] != DRD_BG || id[NS - 1] != DRD_BG) && (MODE == 3 || J.any_act);
+            const bool act = inpix && (id[0] != DRD_BG || id[NS - 1] != DRD_BG) && (MODE >= 3 || J.any_act);
             long long q = 0;
             if (act) q = pixel_code(J, rgb[0], rgb[NS - 1], tgt, true);
-            if constexpr (MODE == 3) {
+            if constexpr (MODE >= 3) {
                 qsum += q;
             } else {
                 unsigned lo = 0xFFFFFFFFu, hi = 0u;
@@ -1087,7 +1094,7 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
         loss_acc = block_sum<TB>(S.u.red, loss_acc, tid);
         if (tid == 0) *J.partial = loss_acc;
     }
-    if constexpr (MODE == 3) {
+    if constexpr (MODE >= 3) {
         qsum = block_sum<TB>(S.u.qred, qsum, tid);
         if (tid == 0 && qsum != 0) atomicAdd((unsigned long long*)J.qtot, (unsigned long long)qsum);
     }
@@ -1355,7 +1362,7 @@ __device__ __forceinline__ TileJob single_job(const TileArgs& a, int li, int pai
     J.out_id = a.out_id;
     J.out_uv = a.out_uv;
     J.partial = a.partials ? a.partials + (long long)li * a.max_tiles + tile : nullptr;
-    J.qtot = (MODE == 3) ? a.qtot + pair : nullptr;
+    J.qtot = (MODE >= 3) ? a.qtot + pair : nullptr;
     return J;
 }
 
@@ -1458,8 +1465,18 @@ static void launch_tile_kernel(hipStream_t st, const TileArgs& a, dim3 grid) {
     hipLaunchKernelGGL((k_tile<TILE, MODE, LM, SHADE>), grid, dim3(TileCfg<TILE, MODE, LM>::TB), 0, st, a);
 }
 
+// A full-image estimate of 32-pixel tiles takes 256 threads of four pixels each,
+// since more, smaller blocks hide one another's chains, but a thread per pixel
+// while all blocks of 1024 threads are in flight at once (two a CU).  Whole calls
+// with 1024 / 256 threads (Lambert, two views): 128 blocks 144 / 168 us, 256 blocks
+// 47 / 57, 352 blocks 52 / 62, 484 blocks 59 / 55, 1444 blocks 90 / 61, 2048 blocks
+// 183 / 113, 32768 blocks 1163 / 549.  (With the group table's room, which this form
+// does not use, 737 for the last.)
 template <int TILE, int LM, int SHADE>
 static void launch_tile_mode(hipStream_t st, const TileArgs& a, int mode, dim3 grid) {
+    if constexpr (TILE == 32) {
+        if (mode == 3 && (long long)grid.x * grid.y <= 512) return launch_tile_kernel<TILE, 4, LM, SHADE>(st, a, grid);
+    }
     if (mode == 0) launch_tile_kernel<TILE, 0, LM, SHADE>(st, a, grid);
     else if (mode == 1) launch_tile_kernel<TILE, 1, LM, SHADE>(st, a, grid);
     else if (mode == 2) launch_tile_kernel<TILE, 2, LM, SHADE>(st, a, grid);

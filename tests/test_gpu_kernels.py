@@ -430,3 +430,21 @@ def test_captured_estimate_outlives_new_scratch(form, items):
                 g.replay()
                 assert same(o, w)
     assert ctx.get_tuning()[1] > 4
+
+
+# Full-image sums of 32-pixel tiles: a thread per pixel up to 512 blocks, four
+# pixels a thread above; views that end within a tile.
+@pytest.mark.parametrize("res,pairs", [((512, 512), 2), ((513, 512), 2), ((505, 250), 4), ((505, 250), 5), ((40, 30), 1)])
+def test_full_image_of_large_tiles_bit_exact(res, pairs):
+    print(f"[kernels] full image {res} pairs {pairs}", flush=True)
+    sc = H.sphere_scene(7, 0, res=res, shading=2, tex_shapes=((40, 56, 3), (40, 56, 3), (9, 11, 1)), seed=12, views=1)
+    o = oracle.Oracle(sc)
+    tg = [o.render(sc.flat_params(True), sc.views[0])[0]]
+    Qo, Ko, _, _ = o.estimate(sc.flat_params(), sc.views, tg, 5, 3, pairs, sc.eps, full_image=True)
+    th = torch.tensor(sc.flat_params(), device=DEV)
+    dtg = torch.tensor(tg[0], device=DEV).reshape(-1)
+    for items in (0, 1):
+        Q, K = api.Context(sc, DEV, tuning=(32, 256, items)).estimate_grad(th, sc.views, dtg, 5, 3, pairs, sc.eps,
+                                                                           full_image=True)
+        assert np.array_equal(host(K).view(np.uint32), Ko)
+        assert np.array_equal(host(Q), Qo)
