@@ -448,3 +448,29 @@ def test_full_image_of_large_tiles_bit_exact(res, pairs):
                                                                            full_image=True)
         assert np.array_equal(host(K).view(np.uint32), Ko)
         assert np.array_equal(host(Q), Qo)
+
+
+# Bins whose render's spill list is full look through the whole render: looks that
+# are all hits (neighbouring triangles in one tile), batches that end when one
+# finds no room, the remainder of a render; and spill lists that just hold.
+@pytest.mark.parametrize("tile,layers", [(8, 0), (16, 0), (32, 0), (8, 2), (16, 4)])
+@pytest.mark.parametrize("freq,res,scans", [(24, (70, 61), True), (31, (40, 33), True), (13, (40, 33), False)])
+def test_overflowing_bins_bit_exact(freq, res, scans, tile, layers):
+    print(f"[kernels] overflow freq {freq} res {res} tile {tile} layers {layers}", flush=True)
+    sc = H.sphere_scene(freq, 0, res=res, shading=1, tex_shapes=((24, 20, 4 if layers else 3),), seed=3, views=1)
+    sc.layers = layers
+    o, v = oracle.Oracle(sc), sc.views[0]
+    ctx = api.Context(sc, DEV, tuning=(tile, 4, 0))
+    ctx.set_adaptive_bins(False)
+    rgb, ids, uv = ctx.render(torch.tensor(sc.flat_params(True), device=DEV), v)
+    ro, io, uo = o.render(sc.flat_params(True), v)
+    assert np.array_equal(host(ids).view(np.uint32), io)
+    assert np.array_equal(host(rgb), ro) and np.array_equal(host(uv), uo)
+    Qo, Ko, _, _ = o.estimate(sc.flat_params(), sc.views, [ro], 5, 3, 2, sc.eps)
+    for _ in range(2):                                   # the second finds bins and lists as the first left them
+        Q, K = ctx.estimate_grad(torch.tensor(sc.flat_params(), device=DEV), sc.views,
+                                 torch.tensor(ro, device=DEV).reshape(-1), 5, 3, 2, sc.eps)
+        assert np.array_equal(host(K).view(np.uint32), Ko)
+        assert np.array_equal(host(Q), Qo)
+    st = ctx.stats()
+    assert st["tile_overflows"] > 0 and (st["full_scans"] > 0) == scans
