@@ -62,9 +62,12 @@ struct TileCfg {
     // end the launch when they take a second batch (192 against 256, whole
     // steps: launches of one 512 px item 3265 / 3088 us, 12 uneven scenes
     // 1195 / 1175, two layers 644 / 638, others even); four layers' keys leave
-    // room for 192
-    static constexpr int NEMAX = LM == 4 ? 192 : 256;
-    static constexpr int NE = TILE == 32 ? 128 : (TB < NEMAX ? TB : NEMAX);
+    // room for 192.  32-pixel tiles hold four times as many, and wait for each
+    // batch (128 against 256, one render of 11520 triangles at 64 px 72 / 46 us,
+    // four pairs of them 243 / 180); MODE 3 of them is held to fewer blocks by the
+    // larger stage (1024 px, two views x 16 pairs 546 / 614)
+    static constexpr int NEMAX = LM == 4 ? 192 : (TILE == 32 && MODE == 3 ? 128 : 256);
+    static constexpr int NE = TB < NEMAX ? TB : NEMAX;
 };
 
 // Keys per row of a tile: spare ones after its pixels for opaque tiles, since
@@ -83,12 +86,16 @@ struct __align__(16) PTri {
     int c[3];            // edge k at the box's corner pixel, plus 1 on a top-left edge
     unsigned t;
     int d[3];            // dX_k (low half), dY_k (high half)
-    unsigned pk;         // box width - 1, key index of the corner pixel, first slot (PK_*)
+    unsigned pk;         // box width - 1, key index of the corner pixel, first slot (PackBits)
     float z0, zx, zy;    // depth plane
     int dz;              // corner pixel centre minus vertex 0, in subpixels: x low, y high
 };
-#define PK_KEY 5                 // bits 0..4: box width - 1
-#define PK_SLOT 17               // bits 5..16: key index; from 17: the triangle's first slot
+// PTri::pk, from bit 0: box width - 1, for 32-pixel tiles in whole slots (their
+// batch has up to 2^16 slots); 12 bits of key index; the triangle's first slot.
+template <int TILE>
+struct PackBits {
+    static constexpr int DROP = TILE == 32 ? 2 : 0, KEY = 5 - DROP, SLOT = KEY + 12;
+};
 
 static_assert(sizeof(PTri) == 48, "PTri layout");
 
@@ -170,7 +177,9 @@ __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TIL
     constexpr int SL = RASTER_SLOT, KS = KeyRow<TILE, DEEP>::N, NW = TB / 64;
     constexpr int MW = NE * TILE * (TILE / SL) / 64;     // words of begin[]
     constexpr int GATHER = NE / 64 < 3 ? NE / 64 : 3;    // a wave's hits of one look fit an empty list
-    static_assert(SL == 4 && NS * TILE * KS <= (1 << (PK_SLOT - PK_KEY)), "PTri::pk key index");
+    constexpr int PK_KEY = PackBits<TILE>::KEY, PK_SLOT = PackBits<TILE>::SLOT, PK_DROP = PackBits<TILE>::DROP;
+    static_assert(SL == 4 && (1 << PK_DROP) <= SL && !(DEEP && PK_DROP), "PTri::pk box width");
+    static_assert(NS * TILE * KS <= (1 << (PK_SLOT - PK_KEY)), "PTri::pk key index");
     static_assert(64 * MW <= (1 << (32 - PK_SLOT)), "PTri::pk first slot");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned cap = (unsigned)J.cap;
@@ -353,7 +362,7 @@ __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TIL
             q.dz = ((cx - r.X[0]) & 0xFFFF) | ((cy - r.Y[0]) << 16);
             q.z0 = r.z0; q.zx = r.zx; q.zy = r.zy;
             q.t = t;
-            q.pk = (unsigned)(bw - 1) | ((unsigned)((s * TILE + y0 - J.py0) * KS + (x0 - J.px0)) << PK_KEY) |
+            q.pk = ((unsigned)(bw - 1) >> PK_DROP) | ((unsigned)((s * TILE + y0 - J.py0) * KS + (x0 - J.px0)) << PK_KEY) |
                    (pex << PK_SLOT);
             S.tri[ex & 511u] = q;
             atomicOr(reinterpret_cast<unsigned*>(S.begin) + (pex >> 5), 1u << (pex & 31u));
@@ -387,7 +396,7 @@ __device__ __forceinline__ void raster_tile(const RasterJob& J, RasterShared<TIL
             if (sl < N) {
                 const PTri q = S.tri[rr];
                 const int idx = sl - (int)(q.pk >> PK_SLOT);
-                const unsigned w4 = q.pk & 0x1Cu;        // 4 (slots per row - 1)
+                const unsigned w4 = (q.pk << PK_DROP) & 0x1Cu;       // 4 (slots per row - 1)
                 int dy;                                  // idx / slots per row
                 if constexpr (TILE <= 16) {
                     // idx < 64, at most 4 slots: idx * ceil(128 / slots) >> 7
