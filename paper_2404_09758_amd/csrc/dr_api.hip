@@ -877,8 +877,9 @@ static bool side_streams(dr_ctx* c) {
 //   8 launches of one 512 px item                   214 /  158 /  162 /  174
 //   8 launches of one 64 px item                    133 /  138 /  153 /  167
 //   4 launches of one 512 px item                   122 /  116 /  129 /  144
-// A stream costs two waits and two records, so few or short launches take one
-// more or none.
+// A stream costs two waits and two records, so few launches take one more or
+// none.  (From 12 launches on the rule goes by their number alone, and four streams
+// are not the best for very short ones: 16 launches of 16 tiles.)
 template <typename F>
 static hipError_t raster_launches(dr_ctx* c, long long n, long long per, int max_tiles, bool spread, F launch) {
     const long long launches = (n + per - 1) / per;

@@ -139,11 +139,9 @@ __global__ void __launch_bounds__(256) k_group_signs(DScene sc, unsigned long lo
 
 // ---------------------------------------------------------------- setup --
 
-// Triangle t of one (item, sign): perturbed vertices, projection, snap,
-// setup record, and its entries in the bins of the tiles it may cover.
+// The perturbed world positions of triangle t's corners (original order).
 // fpos: the perturbed tessellated vertex positions of this (pair, sign) of a
 // subdivision surface, or null (positions are the perturbed parameters).
-// The perturbed world positions of triangle t's corners (original order).
 __device__ __forceinline__ void tri_positions(const DScene& sc, const float* __restrict__ theta,
                                               const uint8_t* __restrict__ sg, float e0, float sgn, int t,
                                               const float* __restrict__ fpos, float* p) {

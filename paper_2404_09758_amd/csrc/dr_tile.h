@@ -714,12 +714,16 @@ __device__ __forceinline__ void pair_verts(const PairSlot* slots, const unsigned
 }
 
 // Tile kernels of 8- and 16-pixel tiles are asked for 8 resident waves per SIMD
-// (at most 64 VGPRs and 96 SGPRs): their blocks hold 20 KB of LDS per 4 waves
-// or less.  Unasked, the deep ones took 106 SGPRs and 7 waves (512 px, two
-// layers, 32 items 1124 -> 1087 us, four ragged layers 246 -> 227).  The GGX
-// render spills at this bound and is still faster (145.5 us for four 1024 px
-// views; 153.8 with 7 waves and no spill).  Larger tiles are held to fewer waves
-// by their LDS.
+// (at most 64 VGPRs and 96 SGPRs) and get them where their LDS allows it, 20 KB
+// per 4 waves: 16-pixel estimates, opaque 20.3 KB and deep 18.5, opaque renders of
+// both sizes, 8-pixel estimates of two layers.  More LDS leaves 7 waves to opaque
+// 8-pixel estimates (22.7 KB) and 16-pixel renders of four layers (20.5), 6 to
+// 8-pixel estimates of four (25.1), 5 to renders of two (28.8, of which they use
+// the raster's part); the compiler bounds those kernels' registers accordingly.
+// Unasked, the deep estimates took 106 SGPRs and 7 waves (512 px, two layers, 32
+// items 1124 -> 1087 us, four ragged layers 246 -> 227).  The GGX render spills at
+// this bound and is still faster (145.5 us for four 1024 px views; 153.8 with 7
+// waves and no spill).  32-pixel tiles are held to 4 to 8 waves by LDS and threads.
 #define TILE_MIN_WAVES 8
 
 // Everything the tile body needs, resolved by the kernel's prologue.
@@ -1133,8 +1137,8 @@ __device__ __forceinline__ void tile_body(TileJob& J, TileShared<TILE, MODE>& S)
 // composites them over black, C = sum_l T_l alpha_l c_l with
 // T_{l+1} = T_l (1 - alpha_l), and the scatter credits the union over both
 // renders and all listed layers of the layers' vertices and footprint
-// texels, each group once per pixel.  Tiles are 8 or 16 pixels (one pixel
-// per lane).
+// texels, each group once per pixel.  Tiles are 8 or 16 pixels (a lane per
+// pixel and side).
 
 template <int TILE, int MODE, int LM>
 struct DeepShared {
