@@ -222,8 +222,8 @@ static dr_status ensure_raster(dr_ctx* c, long long slots, long long g_slots, in
                 sizeof(unsigned), false);
 }
 
-// Gives all of that back.
-static dr_status drop_raster(dr_ctx* c) {
+// Gives back the scratch of estimates.
+static dr_status drop_scratch(dr_ctx* c) {
     auto drop = [&](auto& p, long long& have) {
         dr_status s = p ? release(c, p) : DR_OK;
         if (s) return s;
@@ -238,6 +238,10 @@ static dr_status drop_raster(dr_ctx* c) {
     if (!s) s = drop(c->spn, c->spn_words);
     if (!s) s = drop(c->spill, c->spill_entries);
     if (!s) s = drop(c->bins, c->bin_entries);
+    if (!s) s = drop(c->sg, c->sg_bytes);
+    if (!s) s = drop(c->R, c->R_pairs);
+    if (!s) s = drop(c->qtot, c->qtot_pairs);
+    if (!s) s = drop(c->fpos, c->fpos_slots);
     return s;
 }
 
@@ -746,6 +750,11 @@ struct EstPlan {
     bool eager = false;         // not captured (estimate_common)
 };
 
+static void plan_pairs(EstPlan& pl, int32_t n_views, int32_t n_pairs) {
+    finish_views(pl.dv, n_views, n_pairs);
+    pl.items = (long long)n_pairs * n_views;
+}
+
 static dr_status estimate_check(dr_ctx* c, const float* theta, const dr_view* views, int32_t n_views,
                                 const float* targets, int32_t n_pairs, const float* eps, int64_t* Q, uint32_t* K,
                                 EstPlan& pl) {
@@ -766,8 +775,7 @@ static dr_status estimate_check(dr_ctx* c, const float* theta, const dr_view* vi
         tgt_off += 3ll * views[v].width * views[v].height;
         pl.max_tiles = std::max(pl.max_tiles, pl.dv.v[v].tiles_x * pl.dv.v[v].tiles_y);
     }
-    finish_views(pl.dv, n_views, n_pairs);
-    pl.items = (long long)n_pairs * n_views;
+    plan_pairs(pl, n_views, n_pairs);
     return DR_OK;
 }
 
@@ -814,7 +822,7 @@ static dr_status ensure_pairs(dr_ctx* c, int32_t n_pairs, bool full) {
 
 // The context's own scratch, grown as needed.  Where the memory for the group
 // is not there, the setup takes fewer items at a time, down to a raster launch's;
-// the buffers of larger groups are given back first.
+// larger buffers of earlier calls and attempts are given back first.
 static dr_status estimate_scratch_ctx(dr_ctx* c, const EstPlan& pl, int32_t n_pairs, bool full, EstScratch& x) {
     x.per = items_per_launch(c, pl.items);
     x.group = setup_group(c, pl, x.per);
@@ -824,7 +832,7 @@ static dr_status estimate_scratch_ctx(dr_ctx* c, const EstPlan& pl, int32_t n_pa
     };
     dr_status s = ensure();
     for (bool first = true; s == DR_E_OOM && pl.eager && (first || x.group > x.per); first = false) {
-        if ((s = drop_raster(c))) return s;
+        if ((s = drop_scratch(c))) return s;
         x.group = std::max(x.per, x.group / 2 / x.per * x.per);
         s = ensure();
     }
@@ -902,13 +910,13 @@ static hipError_t raster_launches(dr_ctx* c, long long n, long long per, int max
     return e;
 }
 
-// Signs, (tessellation,) setup and tile launches, then the fold or the
-// full-image broadcast, on the scratch x.  timed: bracket the launches with
+// Signs, (tessellation,) setup and tile launches of pairs pair0 .. pair0 + n_pairs
+// - 1, then the fold or the full-image broadcast, on the scratch x.  timed: bracket the launches with
 // the context's timing events; if the call is not captured, spread the raster
 // launches over the context's streams and keep the adaptive bin capacity's figure.
 static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* theta, int32_t n_views,
-                                 const float* targets, uint64_t seed, uint32_t step, int32_t n_pairs,
-                                 const float* eps, int64_t* Q, uint32_t* K, bool full, bool image,
+                                 const float* targets, uint64_t seed, uint32_t step, int32_t pair0,
+                                 int32_t n_pairs, const float* eps, int64_t* Q, uint32_t* K, bool full, bool image,
                                  const EstScratch& x, bool timed) {
     auto run = [&](int kind, auto launch) -> hipError_t {
         return timed ? c->timer.run(c->stream, kind, launch) : launch();
@@ -920,7 +928,7 @@ static dr_status estimate_launch(dr_ctx* c, const EstPlan& pl, const float* thet
     dp.sg = x.sg;
     for (int b = 0; b <= DRD_MAX_TEX; ++b) dp.eps[b] = (b < 1 + c->sc.n_tex) ? eps[b] : 0.0f;
     HIPCHK(c, run(K_SIGNS, [&] {
-        return launch_group_signs(c->stream, c->sc, seed, step, 0u, c->scene_index, n_pairs, x.sg);
+        return launch_group_signs(c->stream, c->sc, seed, step, (unsigned)pair0, c->scene_index, n_pairs, x.sg);
     }));
 
     SetupArgs sa;
@@ -1023,11 +1031,22 @@ static dr_status estimate_common(dr_ctx* c, const float* theta, const dr_view* v
     const hipStreamCaptureStatus capture = capture_status(c);
     pl.eager = capture == hipStreamCaptureStatusNone;
     if (pl.eager && (s = adapt_capacity(c))) return s;
-    EstScratch x;
-    s = estimate_scratch_ctx(c, pl, n_pairs, full, x);
-    if (s) return s;
-    if (capture == hipStreamCaptureStatusActive && (s = hold_scratch(c))) return s;
-    return estimate_launch(c, pl, theta, n_views, targets, seed, step, n_pairs, eps, Q, K, full, image, x, true);
+    // All pairs at once; where the signs and sums of so many do not fit, as many as
+    // do (a launch's pairs share nothing but the integer sums they add to).
+    for (int32_t p0 = 0, np = n_pairs; p0 < n_pairs; p0 += np) {
+        np = std::min(np, n_pairs - p0);
+        EstScratch x;
+        for (;; np = (np + 1) / 2) {
+            plan_pairs(pl, n_views, np);
+            s = estimate_scratch_ctx(c, pl, np, full, x);
+            if (s != DR_E_OOM || !pl.eager || np == 1) break;
+        }
+        if (s) return s;
+        if (capture == hipStreamCaptureStatusActive && (s = hold_scratch(c))) return s;
+        s = estimate_launch(c, pl, theta, n_views, targets, seed, step, p0, np, eps, Q, K, full, image, x, true);
+        if (s) return s;
+    }
+    return DR_OK;
 }
 
 extern "C" dr_status dr_estimate_grad(dr_ctx* c, const float* theta, const dr_view* views, int32_t n_views,
@@ -1178,7 +1197,7 @@ extern "C" dr_status dr_estimate_grad_noalloc(dr_ctx* c, const float* theta, con
     // the array keeps the last call's contents: clear the bin counters and
     // the group sums (a fill kernel, so the call can be captured in a graph)
     HIPCHK(c, launch_zero64(c->stream, (long long*)base, (int)(zero_bytes / 8ull)));
-    return estimate_launch(c, pl, theta, n_views, targets, seed, step, n_pairs, eps, Q, K, false, false, x, false);
+    return estimate_launch(c, pl, theta, n_views, targets, seed, step, 0, n_pairs, eps, Q, K, false, false, x, false);
 }
 
 

@@ -177,13 +177,16 @@ def case_capture(fake, items):
 def case_failed_growth(fake):
     """After a call that ran out of memory the next one has all its buffers."""
     n, triangles = None, 30000
-    for room in (1, 2, 3, 4):                               # larger raster records, in units of one of their parts
+    for room in (1, 3, 5, 7):                               # of 16 views' records, in units of their smaller half
         x = Host(fake, 3, triangles, 2, GGX_TEX, (16, 16, 0))
         assert x.estimate([(64, 48)], 1) == 0
         n = n or len(x.live())
         assert len(x.live()) == n
-        fake.fake_room(fake.fake_used() + room * 2 * 20 * triangles * 16)
-        assert x.estimate([(64, 48)], 20) == -2 and "hipMalloc" in x.error()
+        views, p = (x.L.View * 16)(), C.c_void_p(0x1000)
+        for v in views:
+            v.width, v.height = 64, 48
+        fake.fake_room(fake.fake_used() + room * 8 * triangles * 16)
+        assert x.lib.dr_loss(x.h, p, views, 16, p, p) == -2 and "hipMalloc" in x.error()
         fake.fake_room(1 << 50)
         assert x.estimate([(64, 48)], 1) == 0
         assert len(x.live()) == n
@@ -192,7 +195,8 @@ def case_failed_growth(fake):
 
 
 def case_short_of_memory(fake, items, full):
-    """A call that fits the card with the records of one raster launch runs."""
+    """A call runs where there is room for one raster launch's records, and where
+    there is not room for all its pairs' signs and sums."""
     name = "dr_estimate_grad_full" if full else "dr_estimate_grad"
     triangles, cap, views, pairs, tiles = 20000, 256, [(512, 512)] * 2, 30, 32 * 32
     x = Host(fake, 3, triangles, 2, GGX_TEX, (16, cap, items))
@@ -203,11 +207,18 @@ def case_short_of_memory(fake, items, full):
     assert x.estimate(views, pairs, name) == 0
     launches = fake.fake_launches()
     x.lib.dr_destroy(x.h)
-    sums = pairs * (8 if full else 8 * x.G) + pairs * ((x.G + 64) // 64 * 64)
-    pairs_touched = items if items <= 1 else (items + 2 - 2) // 2 + 1
-    least = fixed + sums + 2 * items * (triangles * 64 + tiles * (cap + 1) * 4 + 8 + 8192 * 8) + 2 * pairs_touched * triangles * 64
-    assert least < most
-    for room in (most - 1, (least + most) // 2, least + (most - least) // 7, least):
+
+    def least(n):
+        """Scratch of n pairs with one raster launch's records."""
+        per = min(items, 2 * n)
+        touched = n if per == 2 * n else per // 2 + 1
+        sums = n * (8 if full else 8 * x.G) + n * ((x.G + 64) // 64 * 64)
+        return (fixed + sums + 2 * per * (triangles * 64 + tiles * (cap + 1) * 4 + 8 + 8192 * 8)
+                + 2 * touched * triangles * 64)
+
+    all_pairs = least(pairs)
+    assert least(1) < all_pairs < most
+    for room in (most - 1, (all_pairs + most) // 2, all_pairs, all_pairs - 1, (least(1) + all_pairs) // 2, least(1)):
         x = Host(fake, 3, triangles, 2, GGX_TEX, (16, cap, items))
         fake.fake_room(room)
         for _ in range(2):
@@ -218,16 +229,15 @@ def case_short_of_memory(fake, items, full):
         # a context that already holds a large group gives it up for more pairs
         fake.fake_room(1 << 50)
         assert x.estimate(views, pairs, name) == 0
-        more = least + pairs * (8 if full else 8 * x.G) + pairs * ((x.G + 64) // 64 * 64)
-        fake.fake_room(max(more, fake.fake_used()))
+        fake.fake_room(fake.fake_used())
         assert x.estimate(views, 2 * pairs, name) == 0, x.error()
         fake.fake_room(1 << 50)
         assert x.lib.dr_destroy(x.h) == 0 and fake.fake_used() == 0
     x = Host(fake, 3, triangles, 2, GGX_TEX, (16, cap, items))
-    fake.fake_room(least - 1)
-    assert x.estimate(views, pairs, name) == -2
-    fake.fake_room(1 << 50)
+    fake.fake_room(least(1) - 1)
     fake.fake_reset_launches()
+    assert x.estimate(views, pairs, name) == -2 and fake.fake_launches() == 0
+    fake.fake_room(1 << 50)
     assert x.estimate(views, pairs, name) == 0
     assert fake.fake_launches() == launches
 
