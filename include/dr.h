@@ -127,7 +127,8 @@ typedef struct {
  * ("plain"), 0 = every item of the call in one launch ("batched").  A
  * context's scratch grows with it, and holds at least as many items as fit in
  * 256 MiB of triangle records, bins and spill lists, whose setup goes in one
- * launch (fewer where device memory is short, down to items_per_launch).
+ * launch (fewer where device memory is short, down to items_per_launch, and
+ * then fewer pairs at a time).
  * Results never depend on these values. */
 typedef struct {
     int32_t tile_px;
