@@ -125,11 +125,11 @@ typedef struct {
  * the tile test every triangle of the render.  items_per_launch is the number of
  * (pair, view) items one raster launch covers: 1 = one launch per item
  * ("plain"), 0 = every item of the call in one launch ("batched").  A
- * context's scratch grows with it, and holds at least as many items as fit in
- * 256 MiB of triangle records, bins and spill lists, whose setup goes in one
- * launch (fewer where device memory is short, down to items_per_launch, and
- * then fewer pairs at a time).
- * Results never depend on these values. */
+ * context's scratch holds the triangle records, bins and spill lists of one
+ * raster launch's items, or of as many of the call's as fit in 256 MiB if
+ * that is more (their setup goes in one launch); where device memory is
+ * short, of fewer, down to one raster launch's, and then of fewer pairs at
+ * a time.  Results never depend on these values. */
 typedef struct {
     int32_t tile_px;
     int32_t bin_capacity;
